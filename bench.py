@@ -344,13 +344,12 @@ def main():
     # executed: what the kernel multiplies, i.e. also the scores a backward kernel computes a second time.
     alg_flops_per_step = {"joint_scores_fwd": 2.0 * R * HV, "joint_scores_bwd": 0.0,
                           "joint_scores_fwd_keep": 2.0 * R * HV,
-                          "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV, "joint_bwd_fused": 2.0 * R * HV,
+                          "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV,
                           "fwd_f32": 2.0 * R * HV, "bwd_f32": 4.0 * R * HV}
-    exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=6.0 * R * HV,
-                               joint_bwd_fused=(2.0 if args.keep_scores else 4.0) * R * HV)
+    exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=6.0 * R * HV)
     if bwd_share < 1.0:
         # tiles of negligible posterior are left out: both counts cover only the rows the kernels worked on
-        for name in ("joint_bwd_fused", "gemm_dw_db"):
+        for name in ("joint_scores_bwd", "gemm_dz", "gemm_dw_db"):
             alg_flops_per_step[name] *= bwd_share
             exec_flops_per_step[name] *= bwd_share
     kernels = {}

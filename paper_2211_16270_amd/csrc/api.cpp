@@ -99,10 +99,10 @@ namespace {
 
 // Optional per-kernel timing with HIP events on the caller's stream (off by default).
 enum KernelClass { KC_PREPARE = 0, KC_FWD_SCORES, KC_LATTICE, KC_BWD_SCORES, KC_GEMM_DZ, KC_GEMM_DW,
-                   KC_BWD_FUSED, KC_FWD_F32, KC_BWD_F32, KC_DW_REDUCE, KC_PROJ, KC_FWD_KEEP, KC_KEPT_TO_DH,
+                   KC_FWD_F32, KC_BWD_F32, KC_DW_REDUCE, KC_PROJ, KC_FWD_KEEP, KC_KEPT_TO_DH,
                    KC_GRADS_TO_BF16, KC_SELECT, KC_COUNT };
 const char* const kKernelNames[KC_COUNT] = {"prepare", "joint_scores_fwd", "lattice",
-                                            "joint_scores_bwd", "gemm_dz", "gemm_dw_db", "joint_bwd_fused",
+                                            "joint_scores_bwd", "gemm_dz", "gemm_dw_db",
                                             "fwd_f32", "bwd_f32", "dw_reduce", "projections",
                                             "joint_scores_fwd_keep", "kept_scores_to_dh", "input_grads_to_bf16",
                                             "select_tiles"};
@@ -326,7 +326,11 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         pa.B = desc->B;
         pa.W = W_out;
         pa.Wp = bf16 ? wv.wpack : nullptr;
-        pa.Wq = (plan.fused && grads) ? wv.wq : nullptr;
+        pa.Wq = (bf16 && grads) ? wv.wq : nullptr;
+        if (bf16) {
+            pa.zero_ptr[4] = (float*)(w + plan.off_arrived);
+            pa.zero_n[4] = SCORE_SPLIT_MAX_WG;
+        }
         pa.H = desc->H;
         pa.V = desc->V;
         RNNT_HIP(timed(KC_PREPARE, stream, [&] { return launch_prepare(pa, stream); }));
@@ -356,12 +360,13 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         const LatticeState ls = group_state(gi);
         if (keep)
             RNNT_HIP(timed(KC_FWD_KEEP, stream, [&] {
-                return launch_fwd_keep_bf16(pr, wv.wpack, wv.st, ls, g.s0, g.s1, g.tile0, g.tile1, wv.dH, wv.Z,
-                                            wv.kept_max, stream);
+                return launch_fwd_keep_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, wv.Z, wv.kept_max, stream);
             }));
         else if (bf16)
             RNNT_HIP(timed(KC_FWD_SCORES, stream, [&] {
-                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.s0, g.s1, g.tile0, g.tile1, stream);
+                // (the chunk buffers are free until the group's backward pass: scratch)
+                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, plan.chunk_bytes,
+                                       (int*)(w + plan.off_arrived), stream);
             }));
         else if (plan.f32_gemm)
             for (long long r0 = 0; r0 < g.rows; r0 += plan.chunk_rows)
@@ -415,38 +420,18 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
                 const ActiveTiles at{skip ? (const int*)(w + plan.off_tile_esum) : nullptr,
                                      skip ? (const int*)(w + plan.off_n_active) + gi : nullptr, g.tile0,
                                      c.tile0 - g.tile0, keep ? c.tile0 : -1};
-                if (keep && plan.fused) {
-                    // the group's scores are in the chunk buffers already: the fused kernel turns them into dh
-                    // on their way into the dz GEMM and writes dh back for the dW GEMM
-                    RNNT_HIP(timed(KC_BWD_FUSED, stream, [&] {
-                        return launch_bwd_fused_kept_bf16(pr, wv.wq, wv.st, ls, g.s0, g.s1, c.tile0, c.tile1, wv.dH,
-                                                          wv.kept_max, d_enc, d_pred, at, stream);
-                    }));
-                } else if (keep) {
-                    // ... or, for joint sizes the fused kernel does not cover, one pass turns them into dh
+                // dh: from the group's kept scores (in place, in the chunk buffers), or from the scores computed again
+                if (keep)
                     RNNT_HIP(timed(KC_KEPT_TO_DH, stream, [&] {
-                        return launch_kept_to_dh_bf16(pr, wv.st, ls, g.s0, g.s1, c.tile0, c.tile1, wv.dH,
-                                                      wv.kept_max, at, stream);
+                        return launch_kept_to_dh_bf16(pr, wv.st, ls, c.tile0, c.tile1, wv.dH, wv.kept_max, at, stream);
                     }));
-                    RNNT_HIP(timed(KC_GEMM_DZ, stream, [&] {
-                        return launch_gemm_dz_bf16(pr, wv.st, g.s0, g.s1, c.tile0, c.tile1, wv.dH, d_enc, d_pred,
-                                                   at, stream);
-                    }));
-                } else if (plan.fused) {
-                    RNNT_HIP(timed(KC_BWD_FUSED, stream, [&] {
-                        return launch_bwd_fused_bf16(pr, wv.wpack, wv.wq, wv.st, ls, g.s0, g.s1, c.tile0, c.tile1,
-                                                     wv.dH, wv.Z, d_enc, d_pred, at, stream);
-                    }));
-                } else {
+                else
                     RNNT_HIP(timed(KC_BWD_SCORES, stream, [&] {
-                        return launch_bwd_scores_bf16(pr, wv.wpack, wv.st, ls, g.s0, g.s1, c.tile0, c.tile1, wv.dH,
-                                                      wv.Z, at, stream);
+                        return launch_bwd_scores_bf16(pr, wv.wpack, wv.st, ls, c.tile0, c.tile1, wv.dH, wv.Z, at, stream);
                     }));
-                    RNNT_HIP(timed(KC_GEMM_DZ, stream, [&] {
-                        return launch_gemm_dz_bf16(pr, wv.st, g.s0, g.s1, c.tile0, c.tile1, wv.dH, d_enc, d_pred,
-                                                   at, stream);
-                    }));
-                }
+                RNNT_HIP(timed(KC_GEMM_DZ, stream, [&] {
+                    return launch_gemm_dz_bf16(pr, wv.wq, wv.st, c.tile0, c.tile1, wv.dH, d_enc, d_pred, at, stream);
+                }));
                 RNNT_HIP(timed(KC_GEMM_DW, stream, [&] {
                     return launch_gemm_dw_bf16(desc->H, desc->V, rows, plan.dw_splits, dw_first, wv.Z, wv.dH,
                                                wv.dw_slots, db_out, at, stream);

@@ -47,13 +47,13 @@ struct GradOut {
     float* db;
 };
 
-// Set-up of one call in a single launch: clears up to four float regions (null or empty ones are
+// Set-up of one call in a single launch: clears up to five float regions (null or empty ones are
 // skipped), writes tile_sample[tile] = s for every tile of every sample (one lookup instead of a
 // search per workgroup; skipped if tile_sample is null) and the fragment-major copies of W_out [H,V]
 // (bf16): Wp for the A operand of the score GEMM, Wq for the dz GEMM (each skipped if null).
 struct PrepArgs {
-    float* zero_ptr[4];
-    size_t zero_n[4];
+    float* zero_ptr[5];
+    size_t zero_n[5];
     const int* tile_off;     // [B+1], device
     int* tile_sample;        // [tiles], device
     int B;
@@ -116,27 +116,42 @@ struct ActiveTiles {
 constexpr ActiveTiles EVERY_TILE{nullptr, nullptr, 0, 0, -1};
 
 // ---- bf16 MFMA path -------------------------------------------------------------------------
-// joint tile in LDS -> scores on MFMA -> online log-softmax -> lse, lpb, lpy   (tiles [tile0,tile1))
-hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st,
-                           const LatticeState& ls, int s0, int s1, int tile0, int tile1,
-                           hipStream_t stream);
-// joint tile -> scores recomputed -> dh (bf16) into the chunk buffers dH [rows,V], Z [rows,H]
-hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st,
-                                  const LatticeState& ls, int s0, int s1, int tile0, int tile1,
-                                  void* dH, void* Z, const ActiveTiles& at, hipStream_t stream);
-// The forward launch that also keeps the joint tiles (Z [rows,H]) and the scores (kept [rows,V]: fp16
-// differences to the running maxima kept_max [tiles][V/64][64]) of tiles [tile0,tile1), and the launch that
-// turns the kept scores into dh (bf16, in place) once alpha and beta are known.
-hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st,
-                                const LatticeState& ls, int s0, int s1, int tile0, int tile1, void* kept,
-                                void* Z, float* kept_max, hipStream_t stream);
-hipError_t launch_kept_to_dh_bf16(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0,
-                                  int s1, int tile0, int tile1, void* kept, const float* kept_max,
-                                  const ActiveTiles& at, hipStream_t stream);
+// How many workgroups share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
+// its share of the blocks and `fixed` blocks' time for its start and end.
+inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
+    int best = 1;
+    long long best_cost = 0;
+    for (int vs = 1; vs <= 4; vs *= 2) {
+        const long long cost = ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
+        if (vs == 1 || cost * 10 < best_cost * 9) {
+            best = vs;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+
+// Wpack: W_out^T in fragments [V/32][H/16], Wq: W_out in fragments [V/16][H/32] (launch_prepare).
+// scores on MFMA -> online log-softmax -> lse, lpb, lpy   (tiles [tile0,tile1)).  part: scratch for partial statistics where
+// a small launch splits the vocabulary over workgroups; arrived: SCORE_SPLIT_MAX_WG counters, zero before the first launch (every
+// launch leaves them zero)
+constexpr int SCORE_SPLIT_MAX_WG = 512;
+hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                           int tile1, void* part, size_t part_bytes, int* arrived, hipStream_t stream);
+// scores recomputed -> dh and z (bf16) into the chunk buffers   (H > 512)
+hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                                  int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream);
+// The forward launch that also keeps the joint rows (Z) and the scores (kept, in the dH buffer: fp16 differences to the running
+// maxima kept_max [tiles][V/64][64]) of tiles [tile0,tile1), and the launch that turns the kept scores into dh (bf16, in
+// place) once alpha and beta are known.
+hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                                int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream);
+hipError_t launch_kept_to_dh_bf16(const Problem& pr, const SampleTable& st, const LatticeState& ls, int tile0, int tile1,
+                                  void* kept, const float* kept_max, const ActiveTiles& at, hipStream_t stream);
 // dz = dH W^T, times the tanh derivative, reduced over the tile's u resp. t, added to d_enc, d_pred
-hipError_t launch_gemm_dz_bf16(const Problem& pr, const SampleTable& st, int s0, int s1, int tile0,
-                               int tile1, const void* dH, float* d_enc, float* d_pred, const ActiveTiles& at,
-                               hipStream_t stream);
+hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
+                               float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream);
 // Shape of a sample's lattice tiles (64 rows each): 8 frames x 8 label positions, or 16 x 4 where that covers the
 // sample's T x (U + 1) lattice with at least 3 % fewer tiles (the padding rows of partly filled tiles cost as
 // much as real ones; a 16 x 4 tile adds to 20 rows of d_enc / d_pred instead of 16, which costs about 2 %).
@@ -150,21 +165,10 @@ __host__ __device__ inline long long sample_tiles(int T, int U) {
     const int uw = tile_label_width(T, U), th = 64 / uw;
     return (long long)((T + th - 1) / th) * ((U + uw) / uw);
 }
-// Row pitch (elements) of the two bf16 chunk buffers Z [rows, H] and dH [rows, V]: one 128-byte line more
-// than the row, so that rows whose length is a power of two do not all start in the same memory channel.
+// Elements a row takes in the two bf16 chunk buffers Z [rows, H] and dH [rows, V] (a block of 32 rows is 4 KiB longer than its
+// data; layout: device_common.h)
 __host__ __device__ inline int chunk_pitch(int n) { return n + 64; }
 
-// fused backward: scores recomputed, dh, dz = dh W^T, tanh derivative, reductions into d_enc / d_pred;
-// writes dH [rows,V] and Z [rows,H] (bf16, row-major) for the dW GEMM.  Wq is the second
-// fragment-major copy of W_out.
-hipError_t launch_bwd_fused_bf16(const Problem& pr, const void* Wpack, const void* Wq, const SampleTable& st,
-                                 const LatticeState& ls, int s0, int s1, int tile0, int tile1, void* dH,
-                                 void* Z, float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream);
-// The same for scores the forward pass has kept (launch_fwd_keep_bf16): `kept` holds them and leaves as dH; Z is
-// not touched.
-hipError_t launch_bwd_fused_kept_bf16(const Problem& pr, const void* Wq, const SampleTable& st, const LatticeState& ls,
-                                      int s0, int s1, int tile0, int tile1, void* kept, const float* kept_max,
-                                      float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream);
 // Split-K GEMM Z^T dH over one chunk's rows: every (split, tile) workgroup adds its 256x256 partial
 // product to its own slot (`first` != 0: overwrites it), db += column sums of dH.  `splits` and the
 // slot buffer size follow dw_split_count / dw_slot_bytes (plan.h).

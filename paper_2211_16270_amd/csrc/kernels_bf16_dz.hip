@@ -1,18 +1,19 @@
-// Unfused backward, second half (Alg. 1 lines 10, 11) for hidden sizes the fused kernel does not cover:
-//   dz = dH W_out^T   (dH [rows,V] from the chunk buffer, W_out [H,V]: both with the contraction index,
-//                      the vocabulary, contiguous),
+// dz GEMM of the bf16 backward pass (Alg. 1 lines 10, 11):
+//   dz = dH W_out^T   (dH [rows,V] from the chunk buffer, contraction over the vocabulary),
 //   dx = dz (1 - z^2),  d_enc[t] += sum_u dx,  d_pred[u] += sum_t dx  per lattice tile (64 rows: 8 frames x 8 labels or 16 x 4).
 //
 // 256x256 output tile (4 lattice tiles x 256 hidden) per workgroup; 256 threads = 4 waves in 2 x 2, one per
 // SIMD, each 128 x 128 = 4 x 4 accumulator tiles (256 accumulator registers), so that one k16-step is 8
-// LDS fragment reads for 16 MFMAs.  Stages of 64 vocabulary entries (whole 128-byte lines of the operand
-// rows) travel global -> LDS asynchronously (global_load_lds) into two stage buffers.  A stage holds the
-// operand rows as 128-byte LDS rows; the 16-byte segment s of row r lies at position s ^ ((r/2)%8), which
-// makes the 16-byte fragment reads of 16 consecutive rows hit all 64 banks.  Fragments are read one
-// k16-step ahead of their MFMAs, also across the stage hand-over.  The epilogue recomputes
-// z = tanh(enc + pred) in fp32 from input rows staged in LDS.
-#include <type_traits>
-
+// LDS fragment reads for 16 MFMAs.  Where only 128 hidden columns are left (H not a multiple of 256) the waves stand 4 x 1, each 64 x 128.
+// Both operands lie in memory as MFMA fragments of 1 KiB (dH: device_common.h; W_out: the packed copy
+// [V/16][H/32]), so stages of 32 vocabulary entries (16 fragments of each) travel global -> LDS
+// asynchronously in whole cache lines, five stages deep, and are read back without bank conflicts.  Fragments are read one
+// k16-step ahead of their MFMAs, also across the stage hand-over.
+//
+// The epilogue costs as much as 16 stages of the loop: 1 - z^2 = 4 r (1 - r) with r = 1 / (1 + e^{2 enc} e^{2 pred}), one reciprocal per
+// element from per-row exponentials; the input rows they come from are loaded before the main loop.  Everything after the product
+// is linear in dz, so the vocabulary may be split over workgroups (gridDim.y): a launch that leaves the chip partly idle, or its last
+// round partly filled, does that.
 #include "device_common.h"
 
 namespace rnnt {
@@ -20,30 +21,271 @@ namespace rnnt {
 namespace {
 
 constexpr int ZT = 256;       // tile edge
-constexpr int ZK = 64;        // vocabulary entries per stage: one 128-byte line of every operand row
-constexpr int ZST = 2;        // stages
-constexpr unsigned Z_OPER = (unsigned)ZT * ZK * 2u;     // bytes of one operand of a stage
+constexpr int ZK = 32;        // vocabulary entries per stage
+constexpr int ZST = 5;        // stages
+constexpr unsigned Z_OPER = 16u * 1024u;     // bytes of one operand of a stage
 constexpr unsigned Z_STAGE = 2u * Z_OPER;
-constexpr int Z_EP = 264;     // pitch (bf16 elements) of the epilogue's enc / pred rows in LDS
+constexpr int Z_EP = 264;     // pitch (floats) of the epilogue's rows in LDS
+constexpr int Z_ROWS = 20;    // input rows of a lattice tile: 8 + 8 or 16 + 4
 
 struct DzArgs {
-    const bf16_t* dH;
-    const bf16_t* W;
+    const unsigned char* dH;
+    const unsigned char* Wq;
     Problem pr;
     SampleTable st;
-    int s0, s1, tile0, tile1;
+    int tile0, tile1;
     float* d_enc;
     float* d_pred;
-    int m_tiles, n_tiles;
-    long long rows;           // rows of the dH chunk buffer that were written (a multiple of 64)
+    int n_tiles;              // hidden tiles, the half one included
     ActiveTiles at;           // which tiles the chunk's 64-row slots hold (see kernels.h)
 };
 
-__global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
-    extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A [256][64], B [256][64] } bf16
+// HALF: the last hidden tile, 128 columns
+template <bool HALF>
+__device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem, int bx, int n0, int n_slots) {
+    constexpr int MT = HALF ? 2 : 4;                  // 32-row blocks per wave
+    constexpr int DMAS = HALF ? 6 : 8;                // copies per wave and stage
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = HALF ? wv : wv >> 1, wn = HALF ? 0 : wv & 1;
+    const int H = g.pr.H, V = g.pr.V;
+    const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dz_smem;
+
+    // global -> LDS: a stage is, per operand, blocks of 32 rows (lattice rows / hidden columns) x 2 fragments of 16 entries.
+    // LDS order: A [entry half][8 row blocks], B [entry half][8 hidden blocks].  Wave w moves the row blocks of lattice tile w and hidden
+    // blocks 2 w, 2 w + 1 (HALF: w).  Everything but the lane's 16 bytes is wave-uniform.  Slots past the list's end read the last
+    // listed tile again; their products are never stored.
+    const size_t DB = chunk_block_bytes(V);   // bytes of a block of 32 rows of dH
+    const unsigned lane_b = (unsigned)lane * 16u;
+    const bool present = bx * 4 + wv < n_slots;
+    const int entry = present ? bx * 4 + wv : n_slots - 1;
+    const int tile = __builtin_amdgcn_readfirstlane(g.at.active ? g.at.active[g.at.group_tile0 + g.at.cbase + entry] : g.tile0 + entry);
+    // (kept scores: wherever the forward pass has put the listed tile)
+    const int slot = (g.at.active && g.at.slot_tile0 >= 0) ? tile - g.at.slot_tile0 : entry;
+    const int nsteps = V / ZK / (int)gridDim.y, step0 = (int)blockIdx.y * nsteps;
+    const unsigned char* As = g.dH + (size_t)(2 * slot) * DB + (size_t)step0 * 2048;
+    const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
+    const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(n0 / 32 + (HALF ? wv : 2 * wv)) * 1024;
+    // DMA j of stage gstep into LDS buffer buf
+    auto issue_one = [&](int gstep, unsigned buf, auto j_tag) {
+        constexpr int j = decltype(j_tag)::value;
+        const unsigned sb = smem_base + buf * Z_STAGE;
+        if constexpr (j < 4) {
+            constexpr int rb = j & 1, eh = j >> 1;    // row block of the tile, entry half
+            lds_dma16_s(As + rb * DB + (size_t)gstep * 2048 + eh * 1024, lane_b, sb + (unsigned)(eh * 8 + 2 * wv + rb) * 1024u);
+        } else if constexpr (HALF) {
+            constexpr int eh = j - 4;
+            lds_dma16_s(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + wv) * 1024u);
+        } else {
+            constexpr int hbk = j & 1, eh = (j - 4) >> 1;
+            lds_dma16_imm<hbk * 1024>(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + 2 * wv) * 1024u);
+        }
+    };
+    const int last = nsteps - 1;
+#pragma unroll
+    for (int s4 = 0; s4 < ZST - 1; ++s4)
+        static_for<0, DMAS>([&](auto j) { issue_one(s4 < last ? s4 : last, (unsigned)s4, j); });
+
+    // the epilogue's input rows, this wave's lattice tile: lane = 8 columns of rows (lane / 32) + 2 i (zero outside the sample)
+    const TilePos tp = locate_tile(g.st, 0, 0, tile);
+    constexpr int NC = HALF ? 16 : 32, RPS = 64 / NC, NR = Z_ROWS / RPS;      // 8-column pieces per row, rows per step, steps
+    bf16x8 in[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int r = lane / NC + RPS * i, c = lane % NC, th = 64 >> tp.us, u = tp.u0 + r - th;
+        const bool is_enc = r < th, ok = is_enc ? tp.t0 + r < tp.T : (r - th < tp.uw && u <= tp.U);
+        const bf16_t* src = is_enc ? reinterpret_cast<const bf16_t*>(g.pr.enc) + ((size_t)tp.s * g.pr.T_max + tp.t0 + r) * H
+                                   : reinterpret_cast<const bf16_t*>(g.pr.pred) + ((size_t)tp.s * (g.pr.U_max + 1) + u) * H;
+        in[i] = bf16x8{};
+        if (ok) in[i] = *reinterpret_cast<const bf16x8*>(src + n0 + c * 8);
+    }
+
+    // fragment of a row block, k16-step kk (= entry half): dH lies with its rows permuted (frag_granule), W_out in lane order
+    const unsigned a_off[2] = {frag_granule(lane, 0), frag_granule(lane, 1)};
+    f32x16 acc[MT][4];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
+    bf16x8 fa[2][MT], fb[2][4];
+    auto frag_a = [&](unsigned buf, int kk, int mt) {
+        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + kk * 8192 + (wm * MT + mt) * 1024 + a_off[kk]);
+    };
+    auto frag_b = [&](unsigned buf, int kk, int nt) {
+        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + Z_OPER + kk * 8192 + (wn * 4 + nt) * 1024 + lane_b);
+    };
+    // The MFMAs of one k16-step (register set `set`).  Behind each of the first ones, one fragment of the following k16-step is
+    // read into the other set; behind the others of the second step goes one DMA of a later stage each.  An MFMA keeps the matrix pipe
+    // busy for 32 clocks but the issue port only briefly: with one wave per SIMD nothing else would hide these instructions.
+    auto multiply = [&](auto set_tag, unsigned next_buf, auto next_kk_tag, int dma_g, unsigned dma_buf) {
+        constexpr int set = decltype(set_tag)::value, next_kk = decltype(next_kk_tag)::value;
+        static_for<0, 4 * MT>([&](auto idx_tag) {
+            constexpr int idx = decltype(idx_tag)::value, mt = idx >> 2, nt = idx & 3;
+            acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
+            if constexpr (idx < MT) fa[set ^ 1][idx] = frag_a(next_buf, next_kk, idx);
+            else if constexpr (idx < MT + 4) fb[set ^ 1][idx - MT] = frag_b(next_buf, next_kk, idx - MT);
+            if constexpr (set == 1 && idx >= 4 * MT - DMAS)
+                issue_one(dma_g, dma_buf, std::integral_constant<int, idx - (4 * MT - DMAS)>{});
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // Four stages in flight before the first one is consumed.  The hand-over to the next stage (wait for this wave's copies, then for
+    // everyone's) sits in the middle of a stage.  Beyond the last stage the pipeline re-loads the last one into buffers nobody reads
+    // any more, which keeps the loop free of branches and the number of copies in flight constant.  The waits for LDS reads are placed
+    // by hand (as the builtin the compiler's own counter tracking understands) before the reads of the following step are issued: the
+    // counter completes in order, so a wait placed after them would wait for them too.
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * DMAS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < MT; ++i) fa[0][i] = frag_a(0, 0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fb[0][i] = frag_b(0, 0, i);
+    unsigned buf = 0, refill = ZST - 1;               // of stage it, of stage it + 4
+    for (int it = 0; it < nsteps; ++it) {
+        const unsigned next = buf + 1 == ZST ? 0 : buf + 1;
+        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(I0{}, buf, I1{}, 0, 0u);
+        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
+        // stage it+1 landed (it+2 and it+3 stay in flight); every wave is past stage it-1, whose buffer takes stage it+4
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DMAS) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(I1{}, next, I0{}, it + 4 < last ? it + 4 : last, refill);
+        refill = buf;
+        buf = next;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy may land any more: the stages become the epilogue's scratch
+    __syncthreads();
+
+    // ---- epilogue.  Per lattice tile Z_ROWS rows of e^{2x}: the tile's frames, behind them its label positions; where an input lies beyond
+    // +-40 (the product of two exponentials could overflow, or cancel as inf * 0) the tile's rows are the inputs themselves.
+    float* ex = reinterpret_cast<float*>(dz_smem);                // [4 tiles][Z_ROWS][Z_EP]
+    struct TileInfo {
+        int s, T, U, t0, u0, us, by_sum;
+    };
+    TileInfo* info = reinterpret_cast<TileInfo*>(dz_smem + 4 * Z_ROWS * Z_EP * sizeof(float));
+    {
+        constexpr float K2 = 2.0f * LOG2E_F;
+        float big = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) big = fmaxf(big, fabsf((float)in[i][k]));
+        const bool by_sum = __any(!(big <= 115.0f / K2));
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            float* dst = ex + (wv * Z_ROWS + lane / NC + RPS * i) * Z_EP + (lane % NC) * 8;
+            f32x4 lo, hi;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                lo[k] = (float)in[i][k];
+                hi[k] = (float)in[i][4 + k];
+                if (!by_sum) {
+                    lo[k] = __builtin_amdgcn_exp2f(lo[k] * K2);
+                    hi[k] = __builtin_amdgcn_exp2f(hi[k] * K2);
+                }
+            }
+            *reinterpret_cast<f32x4*>(dst) = lo;
+            *reinterpret_cast<f32x4*>(dst + 4) = hi;
+        }
+        if (lane == 0) info[wv] = TileInfo{present ? tp.s : -1, tp.T, tp.U, tp.t0, tp.u0, tp.us, by_sum};
+    }
+    __syncthreads();
+    // Accumulator register 4j+i of row block 2*lt + m2 is row r = 32 m2 + 8j + 4 hb + i of lattice tile lt, hidden column l32: in an 8 x 8
+    // tile frame 4 m2 + j, label 4 hb + i; in a 16 x 4 tile frame 8 m2 + 2j + hb, label i.  One copy of the loop nest per shape.
+    auto tile_epilogue = [&](auto lt_tag) {
+        constexpr int lt = decltype(lt_tag)::value;
+        const int t4 = HALF ? wv : wm * 2 + lt;
+        const TileInfo ti = info[t4];
+        const int s = __builtin_amdgcn_readfirstlane(ti.s), us = __builtin_amdgcn_readfirstlane(ti.us);
+        const bool by_sum = __builtin_amdgcn_readfirstlane(ti.by_sum) != 0;
+        if (s < 0) return;
+        float* d_enc = g.d_enc + (size_t)s * g.pr.T_max * H;
+        float* d_prd = g.d_pred + (size_t)s * (g.pr.U_max + 1) * H;
+        const float* er = ex + (t4 * Z_ROWS) * Z_EP;
+        auto reduce = [&](auto wide_tag, auto sum_tag) {
+            constexpr bool WIDE = decltype(wide_tag)::value, SUM = decltype(sum_tag)::value;
+            constexpr int TH = WIDE ? 8 : 16;
+            const int ulb = WIDE ? 4 * hb : 0;              // first of this lane's four label positions
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int hc = wn * 128 + nt * 32 + l32, h = n0 + hc;        // column inside the tile, hidden column
+                float qv[4], pu[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qv[i] = er[(TH + ulb + i) * Z_EP + hc];
+#pragma unroll
+                for (int m2 = 0; m2 < 2; ++m2) {
+                    float se[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float ev = er[(WIDE ? 4 * m2 + j : 8 * m2 + 2 * j + hb) * Z_EP + hc];
+                        se[j] = 0.0f;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float w;                        // (1 - z^2) / 4
+                            if (SUM) {
+                                const float z = fast_tanh(ev + qv[i]);
+                                w = fmaf(-0.25f * z, z, 0.25f);
+                            } else {
+                                const float r = __builtin_amdgcn_rcpf(fmaf(ev, qv[i], 1.0f));
+                                w = fmaf(-r, r, r);
+                            }
+                            const float dx = acc[2 * lt + m2][nt][4 * j + i] * w;
+                            se[j] += dx;
+                            pu[i] += dx;
+                        }
+                    }
+                    if (WIDE) {
+#pragma unroll
+                        for (int j = 0; j < 4; j += 2) {    // a frame's eight labels lie in both lane halves; each half adds one frame
+                            const float s0 = both_halves_sum(se[j]), s1 = both_halves_sum(se[j + 1]);
+                            const int t = ti.t0 + 4 * m2 + j + hb;
+                            if (t < ti.T) atomicAdd(&d_enc[(size_t)t * H + h], 4.0f * (hb ? s1 : s0));
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const int t = ti.t0 + 8 * m2 + 2 * j + hb;
+                            if (t < ti.T) atomicAdd(&d_enc[(size_t)t * H + h], 4.0f * se[j]);
+                        }
+                    }
+                }
+                if (WIDE) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int u = ti.u0 + 4 * hb + i;
+                        if (u <= ti.U) atomicAdd(&d_prd[(size_t)u * H + h], 4.0f * pu[i]);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2) {        // a label's sixteen frames lie in both lane halves; each half adds one label
+                        const float s0 = both_halves_sum(pu[i]), s1 = both_halves_sum(pu[i + 1]);
+                        const int u = ti.u0 + i + hb;
+                        if (u <= ti.U) atomicAdd(&d_prd[(size_t)u * H + h], 4.0f * (hb ? s1 : s0));
+                    }
+                }
+            }
+        };
+        if (us == 3) {
+            if (by_sum) reduce(std::true_type{}, std::true_type{});
+            else reduce(std::true_type{}, std::false_type{});
+        } else {
+            if (by_sum) reduce(std::false_type{}, std::true_type{});
+            else reduce(std::false_type{}, std::false_type{});
+        }
+    };
+    tile_epilogue(std::integral_constant<int, 0>{});
+    if constexpr (!HALF) tile_epilogue(std::integral_constant<int, 1>{});
+}
+
+__global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
+    extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A, B: 16 fragments each }
     // XCD-aware order (ids that agree modulo 8 share an L2): the hidden tiles of one row tile are
     // neighbours on one XCD, so the rows of dH are fetched from HBM once.
     const int L = blockIdx.x, xcd = L & 7, q = L >> 3;
@@ -54,250 +296,20 @@ __global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
         const int left = *g.at.n_active - g.at.cbase;
         n_slots = left < n_slots ? left : n_slots;
     }
-    if (bx * 4 >= n_slots) return;          // also covers bx >= m_tiles (uniform per workgroup)
-    const int H = g.pr.H, V = g.pr.V;
-    const long long m0 = (long long)bx * ZT;
+    if (bx * 4 >= n_slots) return;          // (uniform per workgroup)
     const int n0 = by * ZT;
-    const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dz_smem;
-
-    // global -> LDS: one DMA instruction moves 8 operand rows of 128 bytes (whole cache lines: with
-    // 64-byte pieces every line would be fetched into L1 twice, by two stages).  Wave w moves row groups
-    // w, w+4, ..., w+28 of both operands.  Lane l serves row l/8 of the group and LDS segment l%8, which
-    // holds global segment (l%8) ^ ((row/2)%8); row groups are 32 rows apart, so a lane's byte offset
-    // within its group is the same for all of them, and
-    // everything else is wave-uniform: issuing a DMA costs no vector instruction.  Rows of dH past the
-    // written ones lie inside the chunk buffer (its size is a multiple of the tile edge) and hidden rows
-    // past H (H is a multiple of 128: the upper half of the last tile) re-read the lower half; their
-    // products are never stored.
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    const long long DL = chunk_pitch(V);      // row pitch of the dH chunk buffer
-    const int lseg = ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) * 8;
-    const unsigned lane_offA = (unsigned)(((long long)(lane >> 3) * DL + lseg) * 2);
-    const unsigned lane_offB = (unsigned)(((long long)(lane >> 3) * V + lseg) * 2);
-    // the workgroup's four 64-row slots of the dH buffer: consecutive, or (kept scores) wherever the forward pass
-    // has put the listed tiles; entries past the list's end read the last listed tile again
-    const char* As[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        long long row = m0 + 64 * k;
-        if (g.at.active && g.at.slot_tile0 >= 0) {
-            const int e = bx * 4 + k < n_slots ? bx * 4 + k : n_slots - 1;
-            row = (long long)(g.at.active[g.at.group_tile0 + g.at.cbase + e] - g.at.slot_tile0) * 64;
-        }
-        As[k] = reinterpret_cast<const char*>(g.dH) + (row + 8 * wv) * DL * 2;
-    }
-    const char* Bs = reinterpret_cast<const char*>(g.W) + (long long)(n0 + 8 * wv) * V * 2;
-    const bool half_tile = (n0 + 128 >= H);
-    const unsigned dst0 = smem_base + (unsigned)(8 * wv) * 128u;
-    // DMA j (0..15) of the stage that takes vocabulary entries [gstep*ZK, +ZK) into LDS buffer buf
-    auto issue_one = [&](int gstep, unsigned buf, int j) {
-        const int i = j >> 1;
-        const unsigned sb = dst0 + buf * Z_STAGE + (unsigned)(32 * i) * 128u;
-        if (j & 1) {
-            const int ib = (half_tile && i >= 4) ? i - 4 : i;
-            lds_dma16_s(Bs + ((long long)(32 * ib) * V + (long long)gstep * ZK) * 2, lane_offB, sb + Z_OPER);
-        } else {
-            lds_dma16_s(As[i >> 1] + ((long long)(32 * (i & 1)) * DL + (long long)gstep * ZK) * 2, lane_offA, sb);
-        }
-    };
-    // fragment of 32 rows, k16-step kk of a stage: lane holds row l32, segment 2*kk + hb at position
-    // (2*kk + hb) ^ ((row/2)%8): sixteen consecutive rows then cover all 64 banks
-    const int xr = (l32 >> 1) & 7;
-    unsigned frag_off[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) frag_off[kk] = (unsigned)l32 * 128u + (unsigned)(((2 * kk + hb) ^ xr) << 4);
-
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
-
-    const int nsteps = V / ZK;
-    bf16x8 fa[2][4], fb[2][4];
-    auto read_frags = [&](int set, int stage, int kk) {
-        const unsigned char* st = dz_smem + (size_t)(stage & (ZST - 1)) * Z_STAGE + frag_off[kk];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            fa[set][mt] = *reinterpret_cast<const bf16x8*>(st + (wm * 128 + mt * 32) * 128);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            fb[set][nt] = *reinterpret_cast<const bf16x8*>(st + Z_OPER + (wn * 128 + nt * 32) * 128);
-    };
-    // The 16 MFMAs of one k16-step (register set `set`).  Behind each of the first eight, one fragment of the
-    // following k16-step is read into the other set; behind each of the last eight go two DMAs of a later
-    // stage (DMA = true).  An MFMA keeps the matrix pipe busy for 32 clocks but the issue port only briefly:
-    // with one wave per SIMD nothing else would hide these instructions.
-    auto multiply = [&](int set, int next_stage, int next_kk, bool DMA, int dma_g, unsigned dma_buf) {
-        const unsigned char* st = dz_smem + (size_t)(next_stage & (ZST - 1)) * Z_STAGE + frag_off[next_kk];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
-                const int idx = mt * 4 + nt;
-                if (idx < 4) {
-                    fa[set ^ 1][idx] = *reinterpret_cast<const bf16x8*>(st + (wm * 128 + idx * 32) * 128);
-                } else if (idx < 8) {
-                    fb[set ^ 1][idx - 4] = *reinterpret_cast<const bf16x8*>(st + Z_OPER + (wn * 128 + (idx - 4) * 32) * 128);
-                } else if (DMA) {
-                    issue_one(dma_g, dma_buf, 2 * (idx - 8));
-                    issue_one(dma_g, dma_buf, 2 * (idx - 8) + 1);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-    };
-    // Two stage buffers.  Fragments are read one k16-step ahead of their MFMAs.  Before the last k16-step of
-    // a stage every wave has issued and completed all its reads of that stage: there the next stage is
-    // waited for (own copies, then everyone's) and the stage after it is sent into the buffer just left.
-    // Beyond the last stage the pipeline re-loads the last one into a buffer nobody reads any more, which
-    // keeps the loop free of branches.  The waits for LDS reads are placed by hand (as the builtin the
-    // compiler's own counter tracking understands) before the reads of the following step are issued: the
-    // counter completes in order, so a wait placed after them would wait for them too.
-    const int last = nsteps - 1;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) issue_one(0, 0u, j);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) issue_one(last < 1 ? last : 1, 1u, j);
-    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    __syncthreads();
-    read_frags(0, 0, 0);
-    for (int it = 0; it < nsteps; ++it) {
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0, it, 1, false, 0, 0u);
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1, it, 2, false, 0, 0u);
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0, it, 3, false, 0, 0u);
-        // all reads of stage `it` are complete, stage it+1 has landed: its buffer takes stage it+2
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1, it + 1, 0, true, it + 2 < last ? it + 2 : last, (unsigned)(it & (ZST - 1)));
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no copy may land after the workgroup has ended
-
-    // ---- epilogue: dx = dz (1 - z^2) with z = tanh(enc + pred) recomputed in fp32, summed over the label
-    // positions / frames of each lattice tile.  The input rows of the workgroup's four lattice tiles (8 + 8 or
-    // 16 + 4 of them; this tile's 256 hidden columns) go through LDS, which the main loop no longer needs:
-    // per tile 20 row slots, the tile's frames first, its label positions behind them.
-    __shared__ TilePos tpos[4];      // where the workgroup's four lattice tiles lie (s < 0: past the last tile)
-    if (tid < 4) {
-        const int slot = bx * 4 + tid;
-        TilePos t{};
-        t.s = -1;
-        if (slot < n_slots)
-            t = locate_tile(g.st, g.s0, g.s1,
-                            g.at.active ? g.at.active[g.at.group_tile0 + g.at.cbase + slot] : g.tile0 + slot);
-        tpos[tid] = t;
-    }
-    __syncthreads();
-    bf16_t* eq = reinterpret_cast<bf16_t*>(dz_smem);              // [4 tiles][20 rows][Z_EP]
-    {
-        // 4 tiles x 20 rows x 32 chunks of 8 columns = 2560 chunks, 10 per thread
-#pragma unroll
-        for (int i = 0; i < 10; ++i) {
-            const int e = tid + 256 * i;
-            const int c = e & 31, r = (e >> 5) % 20, t4 = e / (32 * 20);
-            const TilePos tp = tpos[t4];
-            bf16x8 v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (bf16_t)0.0f;
-            if (tp.s >= 0 && n0 + c * 8 < H) {
-                const int th = 64 >> tp.us;
-                if (r < th) {
-                    if (tp.t0 + r < tp.T)
-                        v = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(g.pr.enc) +
-                                                             ((size_t)tp.s * g.pr.T_max + tp.t0 + r) * H + n0 + c * 8);
-                } else if (r - th < tp.uw && tp.u0 + r - th <= tp.U) {
-                    v = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(g.pr.pred) +
-                                                         ((size_t)tp.s * (g.pr.U_max + 1) + tp.u0 + r - th) * H + n0 + c * 8);
-                }
-            }
-            *reinterpret_cast<bf16x8*>(eq + (t4 * 20 + r) * Z_EP + c * 8) = v;
-        }
-    }
-    __syncthreads();
-    // Rows wm*128 + 64*lt .. +63 are one lattice tile; accumulator register 4j+i of row block mt = 2*lt + m2 is
-    // tile row r = 32 m2 + 8j + 4 hb + i, hidden column l32: in an 8 x 8 tile frame 4 m2 + j, label 4 hb + i; in a
-    // 16 x 4 tile frame 8 m2 + 2j + hb, label i.  One copy of the loop nest per shape.
-    // (the two lattice tiles of a wave as two instantiations: every accumulator index is a constant)
-    auto tile_epilogue = [&](auto lt_tag) {
-        constexpr int lt = decltype(lt_tag)::value;
-        const int t4 = wm * 2 + lt;
-        const TilePos tp = tpos[t4];
-        if (tp.s < 0) return;
-        const int b = tp.s;
-        float* d_enc = g.d_enc + (size_t)b * g.pr.T_max * H;
-        float* d_prd = g.d_pred + (size_t)b * (g.pr.U_max + 1) * H;
-        const bf16_t* er = eq + (t4 * 20) * Z_EP;
-        auto reduce = [&](auto wide_tag) {
-            constexpr bool WIDE = decltype(wide_tag)::value;
-            constexpr int TH = WIDE ? 8 : 16;
-            const int ulb = WIDE ? 4 * hb : 0;              // first of this lane's four label positions
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int hc = wn * 128 + nt * 32 + l32;        // column inside the tile
-                const int h = n0 + hc;
-                if (h >= H) continue;
-                float qv[4], pu[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) qv[i] = (float)er[(TH + ulb + i) * Z_EP + hc];
-#pragma unroll
-                for (int m2 = 0; m2 < 2; ++m2)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int tl = WIDE ? 4 * m2 + j : 8 * m2 + 2 * j + hb;
-                        const bool tv = (tp.t0 + tl < tp.T);
-                        const float ev = (float)er[tl * Z_EP + hc];
-                        float se = 0.0f;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const bool ok = tv && (tp.u0 + ulb + i <= tp.U);
-                            const float z = fast_tanh(ev + qv[i]);
-                            const float dx = ok ? acc[2 * lt + m2][nt][4 * j + i] * (1.0f - z * z) : 0.0f;
-                            se += dx;
-                            pu[i] += dx;
-                        }
-                        if (WIDE) {
-                            se += __shfl_xor(se, 32, 64);       // a frame's eight labels lie in both lane halves
-                            if (tv && hb == (j & 1)) atomicAdd(&d_enc[(size_t)(tp.t0 + tl) * H + h], se);
-                        } else if (tv) {
-                            atomicAdd(&d_enc[(size_t)(tp.t0 + tl) * H + h], se);
-                        }
-                    }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (WIDE) {
-                        if (tp.u0 + 4 * hb + i <= tp.U) atomicAdd(&d_prd[(size_t)(tp.u0 + 4 * hb + i) * H + h], pu[i]);
-                    } else {
-                        const float both = pu[i] + __shfl_xor(pu[i], 32, 64);   // a label's sixteen frames do
-                        if (hb == (i & 1) && tp.u0 + i <= tp.U) atomicAdd(&d_prd[(size_t)(tp.u0 + i) * H + h], both);
-                    }
-                }
-            }
-        };
-        if (tp.uw == 8) reduce(std::true_type{});
-        else reduce(std::false_type{});
-    };
-    tile_epilogue(std::integral_constant<int, 0>{});
-    tile_epilogue(std::integral_constant<int, 1>{});
+    if (n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots);
+    else dz_tile<false>(g, dz_smem, bx, n0, n_slots);
 }
 
 }  // namespace
 
-hipError_t launch_gemm_dz_bf16(const Problem& pr, const SampleTable& st, int s0, int s1, int tile0, int tile1,
-                               const void* dH, float* d_enc, float* d_pred, const ActiveTiles& at,
-                               hipStream_t stream) {
+hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
+                               float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream) {
     const int n = tile1 - tile0;
     if (n <= 0) return hipSuccess;
-    if (pr.V % ZK != 0) return hipErrorInvalidValue;
-    DzArgs g{(const bf16_t*)dH, (const bf16_t*)pr.W, pr, st, s0, s1, tile0, tile1, d_enc, d_pred,
-             (n + 3) / 4, (pr.H + ZT - 1) / ZT, (long long)n * 64, at};
+    if (pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
+    const DzArgs g{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, (pr.H + ZT - 1) / ZT, at};
     const size_t smem = (size_t)ZST * Z_STAGE;
     static bool configured = false;
     if (!configured) {
@@ -306,8 +318,10 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const SampleTable& st, int s0,
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const int m8 = (g.m_tiles + 7) / 8 * 8;
-    k_gemm_dz256<<<dim3((unsigned)(m8 * g.n_tiles)), dim3(256), smem, stream>>>(g);
+    const int m_tiles = (n + 3) / 4, m8 = (m_tiles + 7) / 8 * 8;
+    // (a half hidden tile counts half; about 16 stages' time for start and epilogue)
+    const int vs = vocabulary_split((m_tiles * pr.H + ZT - 1) / ZT, 256, pr.V / ZK, 16);
+    k_gemm_dz256<<<dim3((unsigned)(m8 * g.n_tiles), (unsigned)vs), dim3(256), smem, stream>>>(g);
     return hipGetLastError();
 }
 

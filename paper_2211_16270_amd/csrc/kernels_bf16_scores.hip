@@ -1,0 +1,563 @@
+// bf16 score kernels (gfx950): joint rows in registers, W_out^T streamed through LDS, one pass over the vocabulary.
+//   z = tanh(enc_t + pred_u)                       (Eq. 4)
+//   h = z W_out + b_out on MFMA, fp32 accumulation   (Eq. 6)
+// and, per mode,
+//   MODE 0  running log-softmax statistics                                        (f^W_1)
+//   MODE 1  dh = gamma softmax - posteriors as bf16, and z, into the chunk buffers (f^W_4, backward)
+//   MODE 2  MODE 0, and z and the scores themselves kept for the backward pass, as fp16 differences t = h - m to a running
+//           maximum m (t <= 0, so an entry's error exp(t) |t| 2^-11 in the softmax is at most 2^-11 / e whatever the size of
+//           the scores; m is the row's largest score so far, one float per row and 64 entries)
+//
+// A workgroup is 4 waves; a wave owns 32 RB rows (RB = 1: half a lattice tile, 2: a whole one) and keeps their joint
+// activations in registers for the whole pass (H/16 fragments of 4 registers per 32 rows: 128 registers at H = 512).
+// The scores are computed transposed (A = 32 vocabulary entries of W_out^T, B = 32 rows), so a lane owns one row (with its
+// partner lane in the other half) and the softmax reductions over the vocabulary stay in registers.
+//
+// What bounds it: the power limit.  On random bf16 values a loop of MFMAs alone runs at 1.8 PFLOP/s, with one 1 KiB
+// fragment read from LDS per MFMA at 1.6, with two vector and one exponential instruction per MFMA besides at 1.45.  A design in
+// which every compute unit pulls a fragment from the L2 for every two MFMAs (64-row tiles, joint tile in LDS) reached 1.0-1.1;
+// here the 128 or 256 rows of a workgroup share every fragment: W_out^T goes L2 -> LDS once per workgroup (asynchronous
+// copies, a ring of stages).  The row statistics of the previous block are computed in the shadow of the current
+// block's MFMAs (an MFMA holds the matrix pipe for 32 clocks and the issue port for 4; up to about 4 vector or 2
+// transcendental instructions behind each one cost nothing), so one wave per SIMD is enough where the joint rows leave
+// no registers for a second one.  Measured (forward kernel): H = 512, V = 8192, 4 M nodes 53.6 ms (61.4 before), H = 640, V = 4096 7.8 ms
+// (9.5), H = 512, V = 1024, 106 M nodes 98.7 ms (111.8).
+#include "device_common.h"
+
+namespace rnnt {
+
+namespace {
+
+struct ScoreArgs {
+    Problem pr;
+    SampleTable st;
+    LatticeState ls;
+    const bf16_t* Wp;
+    int tile0, tile1;
+    unsigned char* dH;     // MODE 1, 2: chunk buffers (device_common.h)
+    unsigned char* Z;
+    float* kept_max;       // MODE 2: [tiles][V/64][64 rows]
+    ActiveTiles at;        // MODE 1
+    f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0): [4 segments][rows of the launch] {max, sum, blank, label score}
+    int* arrived;          // and one counter per workgroup column, zero between launches
+};
+
+constexpr int SC_VB = 32;          // vocabulary entries per block
+constexpr int SC_RING = 8;         // W_out fragments a wave holds ahead of its MFMAs
+constexpr int SC_SEG = 4;          // statistics are formed per quarter of the vocabulary and folded in order, so that a
+                                   // result does not depend on how many workgroups share the vocabulary
+constexpr int SC_AGPR_FRAGS = 64;  // joint fragments kept in the 256 accumulation registers; the rest in vector registers
+
+// LDS ring: stages of SF fragments (1 KiB each), a whole or half block of W_out^T, so many of them that a stage's copies are sent
+// at least one whole stage ahead of their use, inside the 160 KiB of a compute unit (half of it where two workgroups share one).
+constexpr int stage_frags(int KK, int WPS) { return KK <= 16 || (WPS == 1 && KK <= 32) ? KK : KK / 2; }
+constexpr int score_stages(int KK, int WPS) {
+    const int room = (WPS == 2 ? 76 : 152) / stage_frags(KK, WPS);
+    return room < 6 ? room : 6;
+}
+constexpr size_t score_smem_bytes(int KK, int WPS) {
+    return (size_t)score_stages(KK, WPS) * (stage_frags(KK, WPS) * 1024 + 256) + 256;
+}
+
+template <int MODE, int KK, int RB, int WPS>
+__global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NST = score_stages(KK, WPS), SF = stage_frags(KK, WPS), SPB = KK / SF;
+    constexpr unsigned SB = SF * 1024;
+    constexpr int PER = SF / 4;                       // fragments a wave copies per stage
+    constexpr int RG = SC_RING;
+    constexpr int TW = 2 * RB;                        // lattice tiles per workgroup
+    constexpr int NACC = MODE == 2 ? 4 : 2;           // score blocks alive: running, previous (MODE 2: two more until their pair is stored)
+    static_assert(KK % RG == 0 && KK % SF == 0 && SF % 4 == 0 && SF >= RG && NST >= 4, "ring geometry");
+    static_assert((NST - 1) * SB >= 4 * JR_SCRATCH, "the build scratch lies in the later stages");
+    const int H = KK * 16, V = a.pr.V;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the workgroup's tiles (uniform)
+    int n_tiles = a.tile1 - a.tile0;
+    if (MODE == 1 && a.at.active) {
+        const int left = *a.at.n_active - a.at.cbase;
+        n_tiles = left < n_tiles ? left : n_tiles;
+    }
+    if ((int)blockIdx.x * TW >= n_tiles) return;
+    const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    float* bias_lds = reinterpret_cast<float*>(smem + NST * SB);          // [NST][64], 32 values and their repetition
+    float* esum_lds = bias_lds + NST * 64;                               // [4], and the arrival order [1]
+    // this workgroup's part of the vocabulary: blocks [vb0, vb0 + nvb)
+    const int nvb = V / SC_VB / (int)gridDim.y, vb0 = (int)blockIdx.y * nvb;
+    const char* wpb = reinterpret_cast<const char*>(a.Wp) + (size_t)vb0 * (KK * 1024) + wave * (PER * 1024);
+    const float* bias_g = a.pr.b_out + vb0 * SC_VB;
+    const unsigned lane_b = (unsigned)lane * 16u;
+    // stage content q (fragments [q SF, q SF + SF) of W_out^T) -> ring slot: PER copies of 1 KiB by this wave, and the
+    // 32 biases of its block (by every wave, the same values).  Four copies share one base pair (their immediate offset
+    // moves both addresses).
+    const int nq = nvb * SPB;
+    auto issue_one = [&](int q, int slot, auto i_tag) {
+        constexpr int i = decltype(i_tag)::value;
+        q = q < nq ? q : nq - 1;                      // (past the end: a slot nobody reads any more)
+        if constexpr (i < PER)
+            lds_dma16_imm<(i & 3) * 1024>(wpb + (size_t)q * SB + (i >> 2) * 4096, lane_b,
+                                          smem_base + (unsigned)slot * SB + (unsigned)(wave * PER * 1024 + (i >> 2) * 4096));
+        else
+            lds_dma4_s(bias_g + (q / SPB) * SC_VB, (unsigned)l32 * 4u, smem_base + NST * SB + (unsigned)slot * 256u);
+    };
+    auto issue = [&](int q, int slot) { static_for<0, PER + 1>([&](auto i) { issue_one(q, slot, i); }); };
+    issue(0, 0);
+
+    const int ti = (int)blockIdx.x * TW + (RB == 2 ? wave : wave >> 1);
+    const bool present = ti < n_tiles;
+    const int tslot = __builtin_amdgcn_readfirstlane(present ? ti : n_tiles - 1);     // the tile's 64-row slot in the chunk buffers
+    const int tile = __builtin_amdgcn_readfirstlane(
+        (MODE == 1 && a.at.active) ? a.at.active[a.at.group_tile0 + a.at.cbase + tslot] : a.tile0 + tslot);
+    const TilePos tp = locate_tile(a.st, 0, 0, tile);
+    const int b = tp.s;
+    // rows of this wave in its tile: 32 (half0 + rb) + l32
+    const int half0 = RB == 2 ? 0 : wave & 1;
+    const bf16_t* enc = reinterpret_cast<const bf16_t*>(a.pr.enc) + (size_t)b * a.pr.T_max * H;
+    const bf16_t* prd = reinterpret_cast<const bf16_t*>(a.pr.pred) + (size_t)b * (a.pr.U_max + 1) * H;
+    JointInputs<KK> in[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) in[rb].load(enc, prd, H, tp, half0 + rb, lane);
+    int lab[RB];
+    float gexp[RB], vB[RB], vY[RB];                   // MODE 1: exponent offset of the row, its final values at blank and label
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int r = 32 * (half0 + rb) + l32, t = tp.t0 + (r >> tp.us), u = tp.u0 + (r & (tp.uw - 1));
+        lab[rb] = (t < tp.T && u < tp.U) ? a.pr.labels[(size_t)b * a.pr.U_max + u] : -1;
+        if (MODE == 1) {
+            gexp[rb] = RNNT_NEG_INF;
+            vB[rb] = vY[rb] = 0.0f;
+            if (t < tp.T && u <= tp.U) {
+                const long long idx = (a.st.row_off[b] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+                const RowDh rd = row_score_gradient(a.ls, idx, t, u, tp.T, tp.U, b, lab[rb], a.pr.blank);
+                gexp[rb] = rd.g;
+                vB[rb] = rd.at_blank;
+                vY[rb] = rd.at_label;
+            }
+        }
+    }
+    u32x4 z[RB][KK];
+    unsigned char* dh_out[RB];
+    static_for<0, RB>([&](auto rb_tag) {
+        constexpr int rb = decltype(rb_tag)::value;
+        const size_t block = (size_t)tslot * 2 + half0 + rb;
+        unsigned char* zout = nullptr;
+        if (MODE != 0 && present && blockIdx.y == 0) zout = a.Z + block * chunk_block_bytes(H);
+        if (MODE != 0) dh_out[rb] = a.dH + block * chunk_block_bytes(V) + (size_t)vb0 * 2048;
+        build_joint_rows<KK, rb * KK, SC_AGPR_FRAGS>(z[rb], in[rb], reinterpret_cast<float*>(smem + SB) + wave * (JR_SCRATCH / 4), enc,
+                                                     prd, H, tp, half0 + rb, lane, zout);
+    });
+
+    // every wave has left the build scratch: the remaining stages may be filled
+    __syncthreads();
+#pragma unroll
+    for (int q = 1; q < NST; ++q) issue(q, q);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * (PER + 1)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    float m_run[RB], s_run[RB], m_tot[RB], s_tot[RB], cap_b[RB], cap_y[RB], m_pair[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        m_run[rb] = m_tot[rb] = cap_b[rb] = cap_y[rb] = RNNT_NEG_INF;
+        s_run[rb] = s_tot[rb] = m_pair[rb] = 0.0f;
+    }
+    const u32x4* frag0 = reinterpret_cast<const u32x4*>(smem) + lane;
+    const float* bias0 = bias_lds + 4 * hb;
+    u32x4 wf[RG];
+#pragma unroll
+    for (int i = 0; i < RG; ++i) wf[i] = frag0[i * 64];
+    f32x4 bn[4];                                      // bias of the next block
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bn[j] = *reinterpret_cast<const f32x4*>(bias0 + 8 * j);
+
+    // Work on a finished block, cut into KK - 1 pieces (one behind each MFMA step of the next block).
+    // MODE 0, 2: first the block's maximum, then the rescaled running sum.
+    float tmax[RB] = {}, mn2[RB] = {}, sum0[RB] = {}, sum1[RB] = {};
+    auto stats = [&](const f32x16& p, int rb, int k) {
+        constexpr int NM = KK >= 32 ? 8 : 2;          // pieces that take the maximum, 16 / NM values each
+        constexpr int NE = KK >= 32 ? 16 : KK - NM - 2;  // pieces that take the exponentials
+        constexpr int PE = (16 + NE - 1) / NE;
+        if (k < NM) {
+            if (k == 0) tmax[rb] = p[0];
+#pragma unroll
+            for (int i = 0; i < 16 / NM; i += 2)
+                tmax[rb] = fmaxf(fmaxf(tmax[rb], p[k * (16 / NM) + i]), p[k * (16 / NM) + i + 1]);
+        } else if (k == NM) {
+            const float mn = fmaxf(m_run[rb], both_halves_max(tmax[rb]));
+            mn2[rb] = mn * LOG2E_F;
+            s_run[rb] *= __builtin_amdgcn_exp2f((m_run[rb] - mn) * LOG2E_F);
+            m_run[rb] = mn;
+            sum0[rb] = sum1[rb] = 0.0f;
+        } else if (k - NM - 1 < NE) {
+#pragma unroll
+            for (int q = 0; q < PE; ++q) {
+                const int i = (k - NM - 1) * PE + q;
+                if (i < 16) {
+                    const float e = __builtin_amdgcn_exp2f(fmaf(p[i], LOG2E_F, -mn2[rb]));
+                    if (i & 1) sum1[rb] += e; else sum0[rb] += e;
+                }
+            }
+        }
+        // (finishes each piece where it stands: the compiler would sink the arithmetic to the end of the block)
+        asm volatile("" : "+v"(tmax[rb]), "+v"(sum0[rb]), "+v"(sum1[rb]));
+    };
+    auto rare = [&](int rb, int vb, auto&& at_hit) {
+        const int vbase = (vb0 + vb) * SC_VB;
+        int relb = a.pr.blank - vbase, rely = lab[rb] - vbase;
+        if (__any((unsigned)rely < 32u) || (unsigned)relb < 32u) {
+            // rarely taken: keep it a branch, and its comparisons inside
+            relb -= 4 * hb;
+            rely -= 4 * hb;
+            asm volatile("" : "+v"(relb), "+v"(rely)::"memory");
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int vloc = 8 * (i >> 2) + (i & 3);
+                at_hit(i, vloc == relb, vloc == rely);
+            }
+        }
+    };
+    auto capture = [&](const f32x16 (&p)[RB], int vb) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            rare(rb, vb, [&](int i, bool blank, bool label) {
+                if (blank) cap_b[rb] = p[rb][i];
+                if (label) cap_y[rb] = p[rb][i];
+            });
+    };
+    // a segment of the vocabulary is complete: fold it in, or leave it to the workgroup that arrives last
+    auto fold = [&](int rb, float M, float S) {
+        const float mn = fmaxf(m_tot[rb], M);
+        s_tot[rb] = s_tot[rb] * __builtin_amdgcn_exp2f((m_tot[rb] - mn) * LOG2E_F) + S * __builtin_amdgcn_exp2f((M - mn) * LOG2E_F);
+        m_tot[rb] = mn;
+    };
+    const int segs = SC_SEG / (int)gridDim.y, seg_blocks = nvb / segs;
+    const size_t part_rows = (size_t)gridDim.x * TW * 64, part_row = (size_t)ti * 64 + 32 * half0 + l32;
+    auto segment_end = [&](int seg) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const float S = both_halves_sum(s_run[rb]);
+            if (gridDim.y == 1) {
+                fold(rb, m_run[rb], S);
+            } else {
+                const float cb = both_halves_max(cap_b[rb]), cy = both_halves_max(cap_y[rb]);
+                if (hb == 0) {
+                    float* q = reinterpret_cast<float*>(a.part + (size_t)((int)blockIdx.y * segs + seg) * part_rows + part_row + 32 * rb);
+                    __hip_atomic_store(q, m_run[rb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(q + 1, S, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(q + 2, cb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(q + 3, cy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            m_run[rb] = RNNT_NEG_INF;
+            s_run[rb] = 0.0f;
+        }
+    };
+    // MODE 1: the block's scores become its score gradients, in place, then two bf16 fragments per 32 rows
+    auto dh_piece = [&](f32x16& p, int rb, int vb, auto k_tag) {
+        constexpr int k = decltype(k_tag)::value;     // 1 .. KK - 1
+        constexpr int PE = KK >= 24 ? 1 : (16 + KK - 5) / (KK - 4), NE = (16 + PE - 1) / PE;
+        if constexpr (k <= NE) {
+#pragma unroll
+            for (int q = 0; q < PE; ++q) {
+                const int i = (k - 1) * PE + q;
+                if (i < 16) {
+                    float d = __builtin_amdgcn_exp2f(fmaf(p[i], LOG2E_F, gexp[rb]));
+                    asm volatile("" : "+v"(d));
+                    p[i] = d;
+                }
+            }
+        } else if constexpr (k == NE + 1) {
+            rare(rb, vb, [&](int i, bool blank, bool label) {
+                if (blank) p[i] = vB[rb];
+                if (label) p[i] = vY[rb];
+            });
+        } else if constexpr (k == NE + 2 || k == NE + 3) {
+            constexpr int h = k - NE - 2;
+            const u32x4 f = fragment_from_scores(p, h);
+            if (present)
+                __builtin_nontemporal_store(f, reinterpret_cast<u32x4*>(dh_out[rb] + (size_t)vb * 2048 + h * 1024 +
+                                                                        frag_granule(lane, h)));
+        }
+    };
+    // MODE 2: a pair of blocks (64 entries) leaves as fp16 differences to the running maximum after the pair
+    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+    auto keep_piece = [&](const f32x16& p, int rb, int vb, int h) {
+        f16x8 t;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = (_Float16)(p[8 * h + i] - m_pair[rb]);
+        if (present)
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, t),
+                                        reinterpret_cast<u32x4*>(dh_out[rb] + (size_t)vb * 2048 + h * 1024 + lane_b));
+    };
+    auto keep_max = [&](int rb, int vb) {
+        if (present && hb == 0)
+            a.kept_max[((size_t)tslot * (V / 64) + (vb >> 1)) * 64 + 32 * (half0 + rb) + l32] = m_pair[rb];
+    };
+
+    // One block: KK steps of RB MFMAs; behind them the LDS read of the fragment RG steps ahead, a piece of work on the
+    // previous block and, every third step, a copy into a slot that has been left.  RG steps before the end of a stage
+    // its last fragment read is on its way; there the next stage is waited for (own copies, then everyone's; the stores of MODE 1 and 2
+    // count in the same order, so the wait may cover a few of them).  Every wave has then consumed its fragments of the stage before,
+    // whose slot may be refilled (refilling the slot just read would need a wait for the reads just sent).
+    int q = 0, slot = 0;                              // stage being read (content, ring slot)
+    const u32x4* fs = frag0;                          // its fragments
+    f32x16 acc[NACC][RB];
+    // CUR: accumulator set of block vb; the previous block's is (CUR + NACC - 1) % NACC
+    auto block = [&](auto cur_tag, int vb, bool with_prev, bool with_pair) {
+        constexpr int CUR = decltype(cur_tag)::value, PREV = (CUR + NACC - 1) % NACC;
+        f32x16 (&cur)[RB] = acc[CUR];
+        f32x16 (&prev)[RB] = acc[PREV];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cur[rb][4 * j + i] = bn[j][i];
+        static_for<0, KK>([&](auto k_tag) {
+            constexpr int k = decltype(k_tag)::value, kk = k % SF;
+            if constexpr (kk == SF - RG) {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 3) * (PER + 1)) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                ++q;
+                slot = slot + 1 == NST ? 0 : slot + 1;
+                fs = frag0 + slot * (SB / 16);
+            }
+            if constexpr (k == 0) MFMA_AFTER_VALU();
+            static_for<0, RB>([&](auto rb_tag) {
+                constexpr int rb = decltype(rb_tag)::value;
+                mfma_zb<(rb * KK + k < SC_AGPR_FRAGS)>(cur[rb], wf[k % RG], z[rb][k]);
+            });
+            wf[k % RG] = fs[((kk + RG) % SF) * 64];
+            if constexpr (k >= KK - 4)
+                bn[k - (KK - 4)] = *reinterpret_cast<const f32x4*>(bias0 + slot * 64 + 8 * (k - (KK - 4)));
+            // refill of the slot before the one left last (q counts the stage being read): content q - 2 + NST, spread over the SF
+            // steps up to the next hand-over
+            constexpr int p = (kk + RG) % SF;
+            if constexpr (p % 3 == 0 && p / 3 <= PER) {
+                if (with_prev || k >= 2 * SF - RG)
+                    issue_one(q - 2 + NST, slot < 2 ? slot + NST - 2 : slot - 2, std::integral_constant<int, p / 3>{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (with_prev) {
+                if constexpr (MODE != 1) {
+                    if constexpr (k == 1) capture(prev, vb - 1);
+                    if constexpr (k >= 1) {
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb) stats(prev[rb], rb, k - 1);
+                    }
+                    if constexpr (k == KK - 1) {
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb) {
+                            s_run[rb] += sum0[rb] + sum1[rb];
+                            if (MODE == 2) m_pair[rb] = m_run[rb];
+                        }
+                        if (vb % seg_blocks == 0) segment_end(vb / seg_blocks - 1);
+                    }
+                    if constexpr (MODE == 2 && CUR % 2 == 1) {
+                        // the pair (vb - 3, vb - 2): its running maximum was complete when block vb - 1 ended
+                        constexpr int S0 = KK >= 32 ? KK / 8 : 1;
+                        if constexpr (k >= 1 && (k - 1) % S0 == 0 && (k - 1) / S0 < 4) {
+                            constexpr int e = (k - 1) / S0;
+                            if (with_pair) {
+#pragma unroll
+                                for (int rb = 0; rb < RB; ++rb) {
+                                    keep_piece(acc[(CUR + 1 + e / 2) % NACC][rb], rb, vb - 3 + e / 2, e % 2);
+                                    if (e == 0) keep_max(rb, vb - 3);
+                                }
+                            }
+                        }
+                    }
+                } else if constexpr (k >= 1) {
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) dh_piece(prev[rb], rb, vb - 1, k_tag);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
+    typedef std::integral_constant<int, 3> I3;
+    block(I0{}, 0, false, false);
+    if constexpr (MODE != 2) {
+        for (int vb = 1; vb + 1 < nvb; vb += 2) {
+            block(I1{}, vb, true, false);
+            block(I0{}, vb + 1, true, false);
+        }
+        block(I1{}, nvb - 1, true, false);            // nvb is a multiple of 2 (MODE 2: of 4)
+    } else {
+        block(I1{}, 1, true, false);
+        for (int vb = 2; vb + 2 < nvb; vb += 4) {
+            block(I2{}, vb, true, false);
+            block(I3{}, vb + 1, true, true);
+            block(I0{}, vb + 2, true, false);
+            block(I1{}, vb + 3, true, true);
+        }
+        block(I2{}, nvb - 2, true, false);
+        block(I3{}, nvb - 1, true, true);
+    }
+    auto tail = [&](auto set_tag) {
+        constexpr int S = decltype(set_tag)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) mfma_result_ready(acc[S][rb]);
+        if constexpr (MODE == 1) {
+            static_for<1, KK>([&](auto k_tag) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) dh_piece(acc[S][rb], rb, nvb - 1, k_tag);
+            });
+        } else {
+            capture(acc[S], nvb - 1);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+                for (int k = 0; k < KK - 1; ++k) stats(acc[S][rb], rb, k);
+                s_run[rb] += sum0[rb] + sum1[rb];
+                if (MODE == 2) {
+                    m_pair[rb] = m_run[rb];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) keep_piece(acc[S - 1 + e / 2][rb], rb, nvb - 2 + e / 2, e % 2);
+                    keep_max(rb, nvb - 2);
+                }
+            }
+            segment_end(segs - 1);
+        }
+    };
+    tail(std::integral_constant<int, NACC - 1>{});
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy may land after the workgroup has ended
+    if constexpr (MODE == 1) return;
+
+    if (gridDim.y > 1) {
+        // the workgroup of this column that arrives last folds the segments of all of them, in order
+        int* order = reinterpret_cast<int*>(esum_lds + 4);
+        // (the segments leave as agent-scope stores, complete at the vmcnt(0) above, and are read by agent-scope loads: no cache
+        // has to be written back or invalidated between them)
+        __syncthreads();
+        if (tid == 0) {
+            const int n = __hip_atomic_fetch_add(a.arrived + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *order = n;
+            if (n == (int)gridDim.y - 1)              // ready for the next launch
+                __hip_atomic_store(a.arrived + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (*order != (int)gridDim.y - 1) return;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+            for (int seg = 0; seg < SC_SEG; ++seg) {
+                const float* p = reinterpret_cast<const float*>(a.part + (size_t)seg * part_rows + part_row + 32 * rb);
+                const float M = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const float S = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                cap_b[rb] = fmaxf(cap_b[rb], __hip_atomic_load(p + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                cap_y[rb] = fmaxf(cap_y[rb], __hip_atomic_load(p + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                fold(rb, M, S);
+            }
+        }
+    }
+    float esum = 0.0f;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int r = 32 * (half0 + rb) + l32, t = tp.t0 + (r >> tp.us), u = tp.u0 + (r & (tp.uw - 1));
+        const float cb = both_halves_max(cap_b[rb]), cy = both_halves_max(cap_y[rb]);
+        const float lse = m_tot[rb] + __logf(s_tot[rb]);
+        if (present && t < tp.T && u <= tp.U && hb == 0) {
+            const long long idx = (a.st.row_off[b] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+            a.ls.lse[idx] = lse;
+            a.ls.lpb[idx] = cb - lse;
+            a.ls.lpy[idx] = (lab[rb] >= 0) ? cy - lse : 0.0f;
+            // this node's share of the sum the lattice kernels take their per-sample offset from
+            esum += (u < tp.U) ? fmaxf(cb, cy) - lse : cb - lse;
+        }
+    }
+    esum = wave_sum(esum);
+    if constexpr (RB == 2) {
+        if (lane == 0 && present) a.ls.tile_esum[tile] = esum;
+    } else {
+        if (lane == 0) esum_lds[wave] = esum;
+        __syncthreads();
+        if (lane == 0 && (wave & 1) == 0 && present) a.ls.tile_esum[tile] = esum + esum_lds[wave + 1];
+    }
+}
+
+template <int MODE, int KK, int RB, int WPS>
+hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
+    constexpr int TW = 2 * RB;
+    const int n = (a.tile1 - a.tile0 + TW - 1) / TW;
+    constexpr size_t smem = score_smem_bytes(KK, WPS);
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scores<MODE, KK, RB, WPS>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    int vs = 1;
+    if (MODE == 1) {
+        vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
+    } else if (MODE == 0 && n <= SCORE_SPLIT_MAX_WG) {
+        vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
+        if ((size_t)SC_SEG * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
+    }
+    k_scores<MODE, KK, RB, WPS><<<dim3((unsigned)n, (unsigned)vs), dim3(256), smem, stream>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Joint sizes up to 512: two workgroups per compute unit (one's joint rows are built beside the other's MFMAs); 640: whole
+// tiles per wave (half the LDS reads per MFMA); above: 32 rows per wave fill the registers.
+hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                           int tile1, void* part, size_t part_bytes, int* arrived, hipStream_t stream) {
+    if (tile1 <= tile0) return hipSuccess;
+    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, nullptr, nullptr, nullptr, EVERY_TILE, (f32x4*)part, arrived};
+    switch (pr.H) {
+        case 128: return launch_scores_t<0, 8, 1, 2>(a, part_bytes, stream);
+        case 256: return launch_scores_t<0, 16, 1, 2>(a, part_bytes, stream);
+        case 384: return launch_scores_t<0, 24, 1, 2>(a, part_bytes, stream);
+        case 512: return launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
+        case 640: return launch_scores_t<0, 40, 2, 1>(a, part_bytes, stream);
+        case 768: return launch_scores_t<0, 48, 1, 1>(a, part_bytes, stream);
+        case 896: return launch_scores_t<0, 56, 1, 1>(a, part_bytes, stream);
+        case 1024: return launch_scores_t<0, 64, 1, 1>(a, part_bytes, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                                  int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream) {
+    if (tile1 <= tile0) return hipSuccess;
+    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)dH, (unsigned char*)Z, nullptr, at, nullptr, nullptr};
+    switch (pr.H) {
+        case 128: return launch_scores_t<1, 8, 1, 2>(a, 0, stream);
+        case 256: return launch_scores_t<1, 16, 1, 2>(a, 0, stream);
+        case 384: return launch_scores_t<1, 24, 1, 2>(a, 0, stream);
+        case 512: return launch_scores_t<1, 32, 1, 2>(a, 0, stream);
+        case 640: return launch_scores_t<1, 40, 2, 1>(a, 0, stream);
+        case 768: return launch_scores_t<1, 48, 1, 1>(a, 0, stream);
+        case 896: return launch_scores_t<1, 56, 1, 1>(a, 0, stream);
+        case 1024: return launch_scores_t<1, 64, 1, 1>(a, 0, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
+                                int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream) {
+    if (tile1 <= tile0) return hipSuccess;
+    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)kept, (unsigned char*)Z, kept_max, EVERY_TILE,
+                      nullptr, nullptr};
+    switch (pr.H) {
+        case 128: return launch_scores_t<2, 8, 1, 1>(a, 0, stream);
+        case 256: return launch_scores_t<2, 16, 1, 1>(a, 0, stream);
+        case 384: return launch_scores_t<2, 24, 1, 1>(a, 0, stream);
+        case 512: return launch_scores_t<2, 32, 1, 1>(a, 0, stream);
+        case 640: return launch_scores_t<2, 40, 1, 1>(a, 0, stream);
+        case 768: return launch_scores_t<2, 48, 1, 1>(a, 0, stream);
+        case 896: return launch_scores_t<2, 56, 1, 1>(a, 0, stream);
+        case 1024: return launch_scores_t<2, 64, 1, 1>(a, 0, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace rnnt

@@ -5,7 +5,7 @@
 // of gamma).  On long utterances gamma is far below the resolution of the sums the gradients are
 // accumulated in for most of the lattice: the alignments that carry the probability pass through a narrow
 // band.  A tile whose 64 nodes all have gamma < 2^-k contributes less than 2^-k per gradient entry and node
-// and is left out; with k = 135 (the default where the fused backward kernel runs) everything such a tile would
+// and is left out; with k = 135 (the default of the bf16 paths) everything such a tile would
 // feed into the backward GEMMs is exactly zero as a bfloat16 value.  k_tile_flags marks the tiles that stay,
 // k_compact_tiles lists them in their original order (so that every sum that is formed in a fixed order still is).
 #include "device_common.h"

@@ -68,7 +68,8 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     // (the lattice pass has consumed them by then): only the per-group counts need room of their own
     p.off_n_active = take(p.skip_log2 ? B * 4 : 0);
     p.off_wpack = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
-    p.off_wq = take(p.fused ? (size_t)d.H * d.V * 2 : 0);
+    p.off_wq = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
+    p.off_arrived = take(p.bf16 ? (size_t)SCORE_SPLIT_MAX_WG * 4 : 0);
     p.dw_splits = p.bf16 ? dw_split_count(d.H, d.V) : 0;
     p.off_dwslots = take(p.bf16 ? dw_slot_bytes(d.H, d.V) : 0);
     size_t lat0 = o;
@@ -83,8 +84,7 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     p.lattice_bytes = o - lat0;
     size_t ch0 = o;
     if (p.bf16) {
-        // the dz GEMM reads dH in tiles of 256 rows: the buffer ends on such a boundary
-        p.off_dh = take(align_up((size_t)chunk_rows, 256) * chunk_pitch(d.V) * 2);
+        p.off_dh = take((size_t)chunk_rows * chunk_pitch(d.V) * 2);
         p.off_z = take((size_t)chunk_rows * chunk_pitch(d.H) * 2);
         p.off_kept_max = take(p.keep ? (size_t)chunk_rows * (d.V / 64) * 4 : 0);
     } else if (p.f32_gemm) {
@@ -115,7 +115,6 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
     const long long lat_row_bytes = 20LL * p.lat_buffers;    // workspace bytes per lattice node a group may hold
     p.bf16 = (d.dtype == RNNT_BF16);
     p.keep = p.bf16 && d.keep_scores;
-    p.fused = p.bf16 && fused_backward_shape(d.H, d.V);
     p.stage = p.bf16 && d.input_grads_bf16;
     // 0: on the bf16 paths, tiles whose score gradients are all zero as bf16 values are left out
     // (ZERO_IN_BF16_LOG2); -1: no tile is ever left out
@@ -244,7 +243,7 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
         p.groups.push_back(g);
     }
     // backward chunks of at most chunk_rows rows: a group that fits one chunk is one chunk; a larger one is cut
-    // into chunks of whole rounds of 256 tiles where the chunk buffers hold at least four rounds (the last chunk
+    // into chunks of a whole number of 256 tiles where the chunk buffers hold at least four times that (the last chunk
     // takes the rest), else into equal parts of an even number of tiles
     if (p.bf16 && !p.keep) {
         const long long cap_tiles = chunk_rows / TILE_ROWS;
@@ -254,9 +253,9 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
             long long nch = (n + cap_tiles - 1) / cap_tiles;
             long long per = (n + nch - 1) / nch;
             per = std::min(cap_tiles, (per + 1) / 2 * 2);
-            // the backward kernels run one workgroup per tile (fused kernel, dz GEMM: one per compute unit of the 256;
-            // score kernel: one or two): chunks of whole rounds of 256 tiles leave no partly filled last round
-            // (B=64, T<=500, U<=100, H=1024, V=4096: 5 rounds instead of 5.3 per chunk, both kernels -12 %)
+            // chunks of whole rounds of 256 tiles leave no partly filled last round in the dz GEMM (H > 512; B=64, T<=500, U<=100, H=1024,
+            // V=4096: 5 rounds instead of 5.3 per chunk, -12 %); the kernels that cover two or four tiles per workgroup split the vocabulary
+            // where that fills their rounds better (vocabulary_split)
             if (cap_tiles >= 1024 && n > cap_tiles) per = cap_tiles / 256 * 256;
             for (long long t = g.tile0; t < g.tile1; t += per) {
                 Chunk c{gi, (int)t, (int)std::min<long long>(g.tile1, t + per)};

@@ -36,7 +36,6 @@ struct Chunk {
 struct Plan {
     int B = 0;
     bool bf16 = false;
-    bool fused = false;                 // bf16 only: backward runs in the fused kernel
     bool f32_gemm = false;              // fp32 only: H, V multiples of 4 from 64 on, the steps run as fp32 MFMA GEMMs over chunks
     bool keep = false;                  // bf16 only: forward keeps the scores, one backward chunk per group
     bool stage = false;                 // bf16 only: d_enc, d_pred leave as bf16; fp32 sums of one group in the workspace
@@ -56,6 +55,7 @@ struct Plan {
     size_t off_n_active = 0;           // skip_log2 > 0: per group the number of tiles that stay (their list lies in the
                                        // tile_esum array, over the entries of the same tiles)
     size_t off_wpack = 0, off_wq = 0;
+    size_t off_arrived = 0;             // bf16: counters of the forward launches that split the vocabulary
     size_t off_lse = 0, off_lpb = 0, off_lpy = 0, off_alpha = 0, off_beta = 0;
     size_t off_dh = 0, off_z = 0, off_kept_max = 0;
     size_t off_dz32 = 0;                // fp32 GEMM form: dZ [chunk_rows, H]; off_dh, off_z hold S and Z as fp32
@@ -70,9 +70,6 @@ struct Plan {
 // magnitude below 2^-134 (half the smallest bfloat16 denormal) rounds to zero as bf16: with gamma < 2^-135 at every
 // node of a tile, every operand the tile would feed into the backward GEMMs is exactly zero.
 constexpr int ZERO_IN_BF16_LOG2 = 135;
-
-// Shapes the fused backward kernel covers (its dz accumulators must fit the register file).
-inline bool fused_backward_shape(int H, int V) { return H % 128 == 0 && H <= 640 && V % 256 == 0; }
 
 // Shapes the fp32 GEMM form covers: rows of 16-byte pieces, and wide enough for 128 x 128 tiles to pay.
 inline bool f32_gemm_shape(int H, int V) { return H % 4 == 0 && V % 4 == 0 && H >= 64 && V >= 64; }
