@@ -158,18 +158,16 @@ __device__ __forceinline__ bf16x8 lds_read_tr_frag(const unsigned char* lo_p, co
     return __builtin_bit_cast(bf16x8, v);
 }
 
-template <bool BY_TILE>
-__global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
-    extern __shared__ __align__(16) unsigned char dw_smem[];   // [WST] x { A [WK][256], B [WK][256] } bf16
+// HALF: the last hidden tile of 128 columns; the waves stand 2 (hidden) x 2 as for a whole tile, each 64 x 128
+template <bool BY_TILE, bool HALF>
+__device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem, int split, int tile) {
+    constexpr int MT = HALF ? 2 : 4;                  // 32-column blocks of the hidden side per wave
+    constexpr int AF = HALF ? 2 : 4;                  // fragments of Z a wave copies per stage
+    constexpr int DMAS = AF + 4;                      // copies per wave and stage
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
-    // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  All output tiles of
-    // one K split read the same rows of Z and dH, so they are mapped to the same XCD (ids that
-    // agree modulo 8) and adjacent in its dispatch order: the rows then come from HBM once.
     const int ntile = g.mt * g.nt;
-    const int L = blockIdx.x, xcd = L & 7, q = L >> 3;
-    const int tile = q % ntile, split = xcd + 8 * (q / ntile);
     const int bm = tile % g.mt, bn = tile / g.mt;
     const long long m0 = (long long)bm * WT, n0 = (long long)bn * WT;
     long long K = g.K, k_per_split = g.k_per_split;
@@ -189,15 +187,14 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
     constexpr unsigned OPER_BYTES = (unsigned)WK * WT * 2u;
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dw_smem;
 
-    // global -> LDS: one DMA instruction moves one fragment; wave w moves fragments 4 w .. 4 w + 3 of both operands.  Everything but
+    // global -> LDS: one DMA instruction moves one fragment; wave w moves fragments 4 w .. 4 w + 3 of dH
+    // and AF w .. of Z.  Everything but
     // the lane's 16 bytes is wave-uniform and lives in scalar registers, so issuing a DMA costs no vector instruction.
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const size_t ZB = chunk_block_bytes(g.H), DB = chunk_block_bytes(g.V);   // bytes of a block of 32 rows
-    // fragments beyond H (H not a multiple of 256: the upper half of the last tile) re-read the lower half: never stored
-    const int a_frag = (m0 + 128 >= g.H) ? (4 * wv) & 7 : 4 * wv;
-    const unsigned char* Zs = g.Z + (size_t)(ks / WK) * ZB + (size_t)(m0 / 16 + a_frag) * 1024;
+    const unsigned char* Zs = g.Z + (size_t)(ks / WK) * ZB + (size_t)(m0 / 16 + AF * wv) * 1024;
     const unsigned char* Ds = g.dH + (size_t)(ks / WK) * DB + (size_t)(n0 / 16 + 4 * wv) * 1024;
-    const unsigned dst0 = smem_base + (unsigned)(4 * wv) * 1024u;
+    const unsigned dst_a = smem_base + (unsigned)(AF * wv) * 1024u, dst_b = smem_base + OPER_BYTES + (unsigned)(4 * wv) * 1024u;
     const unsigned lane_b = (unsigned)lane * 16u;
     // Block of 32 rows of stage gstep of the split, relative to the split's first; `entry` is the list entry of the stage's slot
     // (BY_TILE only).
@@ -210,12 +207,11 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
         if (!BY_TILE) return gstep;
         return ((long long)(entry - g.at.slot_tile0) << 1) + (((ks + gstep * WK) >> 5) & 1) - ks / WK;
     };
-    // DMA j (0..7) of the stage whose rows are block blk, into LDS buffer buf
+    // DMA j (0 .. DMAS - 1) of the stage whose rows are block blk, into LDS buffer buf
     auto issue_one = [&](long long blk, unsigned buf, auto j_tag) {
-        constexpr int j = decltype(j_tag)::value, i = j >> 1;
-        const unsigned sb = dst0 + buf * STAGE_BYTES;
-        if (j & 1) lds_dma16_imm<i * 1024>(Ds + blk * (long long)DB, lane_b, sb + OPER_BYTES);
-        else lds_dma16_imm<i * 1024>(Zs + blk * (long long)ZB, lane_b, sb);
+        constexpr int j = decltype(j_tag)::value;
+        if constexpr (j < 4) lds_dma16_imm<j * 1024>(Ds + blk * (long long)DB, lane_b, dst_b + buf * STAGE_BYTES);
+        else lds_dma16_imm<(j - 4) * 1024>(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
     };
     // fragment addresses: lane = 16 g + 4 j + c supplies row 8*(g/2) + j, columns 16*(g%2) + 4c .. +3 of a 32-column tile: granule
     // (row, c/2) of fragment 2 * tile + g % 2, at position 32 (c/2) + (row ^ 4 (2 (g % 2) + c/2))
@@ -224,12 +220,12 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
     const unsigned fbase = (unsigned)((fg & 1) * 1024 + (fc >> 1) * 512 + (fc & 1) * 8);
     const unsigned f_lo = fbase + (unsigned)(((8 * (fg >> 1)) ^ fswz) + fj) * 16u;
     const unsigned f_hi = fbase + (unsigned)(((8 * (fg >> 1) + 4) ^ fswz) + fj) * 16u;
-    const unsigned a_lo = f_lo + (unsigned)wm * 8192u, a_hi = f_hi + (unsigned)wm * 8192u;
+    const unsigned a_lo = f_lo + (unsigned)(wm * MT) * 2048u, a_hi = f_hi + (unsigned)(wm * MT) * 2048u;
     const unsigned b_lo = f_lo + OPER_BYTES + (unsigned)wn * 8192u, b_hi = f_hi + OPER_BYTES + (unsigned)wn * 8192u;
 
-    f32x16 acc[4][4];
+    f32x16 acc[MT][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
     float dbs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -238,28 +234,30 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
     const long long nsteps = ke > ks ? (ke - ks) / WK : 0;   // a split beyond the chunk still writes its slot
     if (nsteps == 0 && !g.first) return;                     // ... unless the slot already holds a sum: nothing to add
     static_assert(WK == 32, "the loop below is written for two k16-steps per stage");
-    bf16x8 fa[2][4], fb[2][4];
+    bf16x8 fa[2][MT], fb[2][4];
     auto read_frags = [&](int set, unsigned buf, int kk) {
         const unsigned char* st = dw_smem + buf * STAGE_BYTES + kk * 256;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) fa[set][mt] = lds_read_tr_frag(st + a_lo + mt * 2048, st + a_hi + mt * 2048);
+        for (int mt = 0; mt < MT; ++mt) fa[set][mt] = lds_read_tr_frag(st + a_lo + mt * 2048, st + a_hi + mt * 2048);
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) fb[set][nt] = lds_read_tr_frag(st + b_lo + nt * 2048, st + b_hi + nt * 2048);
     };
-    // The 16 MFMAs of one k16-step (register set `set`); behind each of the first eight, one fragment of the
+    // The 4 MT MFMAs of one k16-step (register set `set`); behind each of the first MT + 4, one fragment of the
     // following k16-step is read into the other set.  An MFMA keeps the matrix pipe busy for 32 clocks but
-    // the issue port only briefly: the reads go out in its shadow, and the last of them is 8 MFMAs old when
+    // the issue port only briefly: the reads go out in its shadow, and the last of them is 8 MFMAs (HALF: 2) old when
     // the step ends.
-    // Behind each of the last eight goes one DMA of a later stage (dma_g >= 0).
+    // Behind each of the last DMAS of a stage's second step goes one DMA of a later stage.
     auto multiply = [&](auto set_tag, unsigned next_buf, int next_kk, long long dma_block, unsigned dma_buf) {
         constexpr int set = decltype(set_tag)::value;
         const unsigned char* st = dw_smem + next_buf * STAGE_BYTES + next_kk * 256;
-        static_for<0, 16>([&](auto idx_tag) {
+        static_for<0, 4 * MT>([&](auto idx_tag) {
             constexpr int idx = decltype(idx_tag)::value, mt = idx >> 2, nt = idx & 3;
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
-            if constexpr (idx < 4) fa[set ^ 1][idx] = lds_read_tr_frag(st + a_lo + idx * 2048, st + a_hi + idx * 2048);
-            else if constexpr (idx < 8) fb[set ^ 1][idx - 4] = lds_read_tr_frag(st + b_lo + (idx - 4) * 2048, st + b_hi + (idx - 4) * 2048);
-            else if constexpr (set == 1) issue_one(dma_block, dma_buf, std::integral_constant<int, idx - 8>{});
+            if constexpr (idx < MT) fa[set ^ 1][idx] = lds_read_tr_frag(st + a_lo + idx * 2048, st + a_hi + idx * 2048);
+            else if constexpr (idx < MT + 4)
+                fb[set ^ 1][idx - MT] = lds_read_tr_frag(st + b_lo + (idx - MT) * 2048, st + b_hi + (idx - MT) * 2048);
+            if constexpr (set == 1 && idx >= 4 * MT - DMAS)
+                issue_one(dma_block, dma_buf, std::integral_constant<int, idx - (4 * MT - DMAS)>{});
             __builtin_amdgcn_sched_barrier(0);
         });
         if (do_db) {
@@ -272,7 +270,7 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
                 }
         }
     };
-    // Four stages in flight before the first one is consumed (8 DMA instructions per wave and stage).
+    // Four stages in flight before the first one is consumed (DMAS copies per wave and stage).
     // One wave per SIMD: nothing else hides an LDS read or the issue of a DMA, so both are spread over the
     // MFMAs (see multiply).  The hand-over to the next stage (wait for this wave's copies, then for
     // everyone's) sits in the middle of a stage.  Beyond the last stage the pipeline keeps re-loading the
@@ -284,10 +282,10 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
         for (int s4 = 0; s4 < WST - 1; ++s4) {
             const long long gs = s4 < last ? s4 : last;
             const long long blk = stage_block(gs, stage_entry(gs));
-            static_for<0, 8>([&](auto j) { issue_one(blk, (unsigned)s4, j); });
+            static_for<0, DMAS>([&](auto j) { issue_one(blk, (unsigned)s4, j); });
         }
         int entry_ahead = stage_entry(4 < last ? 4 : last);
-        asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * DMAS) : "memory");
         __syncthreads();
         read_frags(0, 0, 0);
         unsigned buf = 0, refill = WST - 1;             // of stage it, of stage it + 4
@@ -301,7 +299,7 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
             __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);     // set 1 landed
             // stage it+1 landed (it+2 and it+3 stay in flight); every wave is past stage it-1, whose buffer
             // takes stage it+4
-            asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DMAS) : "memory");
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
             multiply(std::integral_constant<int, 1>{}, next, 0, dma_block, refill);
@@ -316,7 +314,7 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
         f32x4* slot = reinterpret_cast<f32x4*>(g.slots) +
                       (((size_t)split * ntile + tile) * 4 + wave) * (size_t)(4 * 4 * 4 * 64) + lane;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -337,12 +335,33 @@ __global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
     }
 }
 
+// Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.  An XCD takes a contiguous range of the (split, tile)
+// pairs, so the output tiles that read the same rows of Z and dH run side by side on one XCD (or on neighbours) and the rows
+// come from HBM once or little more.  Whole tiles go first, the half ones (H not a multiple of 256) fill the gaps of the last round.
+template <bool BY_TILE>
+__global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
+    extern __shared__ __align__(16) unsigned char dw_smem[];   // [WST] x { A [WK][256], B [WK][256] } bf16
+    const int fm = g.H / WT, full = fm * g.nt, half = (g.mt - fm) * g.nt;     // whole and half tiles of a split
+    const int L = blockIdx.x, xcd = L & 7, q = L >> 3;
+    const int nf = g.splits * full, nh = g.splits * half, f8 = (nf + 7) >> 3, h8 = (nh + 7) >> 3;
+    if (q < f8) {
+        const int w = xcd * f8 + q;
+        if (w >= nf) return;
+        const int t = w % full;
+        dw_tile<BY_TILE, false>(g, dw_smem, w / full, t / fm * g.mt + t % fm);
+    } else {
+        const int w = xcd * h8 + (q - f8);
+        if (w >= nh) return;
+        dw_tile<BY_TILE, true>(g, dw_smem, w / half, w % half * g.mt + fm);
+    }
+}
+
 hipError_t launch_gemm_dw_bf16(int H, int V, long long rows, int splits, int first, const void* Z, const void* dH,
                                float* slots, float* db, const ActiveTiles& at, hipStream_t stream) {
-    if (rows <= 0 || splits <= 0 || (splits & 7) != 0 || rows % WK != 0) return hipErrorInvalidValue;
+    if (rows <= 0 || splits <= 0 || rows % WK != 0) return hipErrorInvalidValue;
     const long long mt = (H + WT - 1) / WT, nt = V / WT;
     DwArgs g{(const unsigned char*)Z, (const unsigned char*)dH, rows, 0, slots, db, first, H, V, (int)mt, (int)nt, splits, at};
-    // split s runs on XCD s % 8; a split past the end of a short chunk only touches its slot
+    // a split past the end of a short chunk only touches its slot
     long long per = (rows + splits - 1) / splits;
     g.k_per_split = (per + WK - 1) / WK * WK;
     const size_t smem = (size_t)WST * 2 * WK * WT * 2;
@@ -356,7 +375,8 @@ hipError_t launch_gemm_dw_bf16(int H, int V, long long rows, int splits, int fir
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const dim3 grid((unsigned)(mt * nt * splits));
+    const long long nf = H / WT * nt * splits, nh = mt * nt * splits - nf;
+    const dim3 grid((unsigned)(8 * ((nf + 7) / 8 + (nh + 7) / 8)));
     if (at.active && at.slot_tile0 >= 0) k_gemm_dw256<true><<<grid, dim3(256), smem, stream>>>(g);
     else k_gemm_dw256<false><<<grid, dim3(256), smem, stream>>>(g);
     return hipGetLastError();
@@ -368,18 +388,18 @@ __global__ __launch_bounds__(256) void k_dw_reduce(const f32x4* __restrict__ slo
                                                    int mt_tiles, int ntile, int splits, int accumulate) {
     const int tile = blockIdx.y;
     const int e = blockIdx.x * 256 + threadIdx.x;          // 0 .. 16383
+    const int bm = tile % mt_tiles, bn = tile / mt_tiles;
+    const int wave = e >> 12, mt = (e >> 10) & 3, nt = (e >> 8) & 3, j = (e >> 6) & 3, lane = e & 63;
+    const int wm_cols = bm * WT + 128 >= H ? 64 : 128;     // hidden columns of a wave: half tile, whole tile
+    if (mt * 32 >= wm_cols) return;
     f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int s = 0; s < splits; ++s) sum += slots[((size_t)s * ntile + tile) * 16384 + e];
-    const int wave = e >> 12, mt = (e >> 10) & 3, nt = (e >> 8) & 3, j = (e >> 6) & 3, lane = e & 63;
-    const int bm = tile % mt_tiles, bn = tile / mt_tiles;
-    const int m = bm * WT + (wave >> 1) * 128 + mt * 32 + 8 * j + 4 * (lane >> 5);
+    const int m = bm * WT + (wave >> 1) * wm_cols + mt * 32 + 8 * j + 4 * (lane >> 5);
     const int n = bn * WT + (wave & 1) * 128 + nt * 32 + (lane & 31);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if (m + i < H) {
-            float* q = dW + (size_t)(m + i) * V + n;
-            *q = accumulate ? *q + sum[i] : sum[i];
-        }
+        float* q = dW + (size_t)(m + i) * V + n;
+        *q = accumulate ? *q + sum[i] : sum[i];
     }
 }
 

@@ -70,7 +70,7 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     p.off_wpack = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
     p.off_wq = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
     p.off_arrived = take(p.bf16 ? (size_t)SCORE_SPLIT_MAX_WG * 4 : 0);
-    p.dw_splits = p.bf16 ? dw_split_count(d.H, d.V) : 0;
+    p.dw_splits = p.bf16 ? dw_split_choice(d.H, d.V, chunk_rows) : 0;
     p.off_dwslots = take(p.bf16 ? dw_slot_bytes(d.H, d.V) : 0);
     size_t lat0 = o;
     // lat_buffers = 2: consecutive groups alternate between two halves of each array, so that one group's
@@ -253,7 +253,7 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
             long long nch = (n + cap_tiles - 1) / cap_tiles;
             long long per = (n + nch - 1) / nch;
             per = std::min(cap_tiles, (per + 1) / 2 * 2);
-            // chunks of whole rounds of 256 tiles leave no partly filled last round in the dz GEMM (H > 512; B=64, T<=500, U<=100, H=1024,
+            // chunks of whole rounds of 256 tiles leave no partly filled last round in the dz GEMM (B=64, T<=500, U<=100, H=1024,
             // V=4096: 5 rounds instead of 5.3 per chunk, -12 %); the kernels that cover two or four tiles per workgroup split the vocabulary
             // where that fills their rounds better (vocabulary_split)
             if (cap_tiles >= 1024 && n > cap_tiles) per = cap_tiles / 256 * 256;

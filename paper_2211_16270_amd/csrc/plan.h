@@ -61,7 +61,7 @@ struct Plan {
     size_t off_dz32 = 0;                // fp32 GEMM form: dZ [chunk_rows, H]; off_dh, off_z hold S and Z as fp32
     size_t off_stage_enc = 0, off_stage_pred = 0;   // fp32 [stage_samples, T_max, H], [stage_samples, U_max+1, H]
     size_t off_dwslots = 0;             // bf16: per-workgroup partial sums of the dW GEMM
-    int dw_splits = 0;                  // bf16: K splits of the dW GEMM (a multiple of 8)
+    int dw_splits = 0;                  // bf16: K splits of the dW GEMM (dw_split_choice)
     size_t lattice_bytes = 0, chunk_bytes = 0, total_bytes = 0;
     size_t min_bytes = 0;               // smallest workable workspace
 };
@@ -74,9 +74,8 @@ constexpr int ZERO_IN_BF16_LOG2 = 135;
 // Shapes the fp32 GEMM form covers: rows of 16-byte pieces, and wide enough for 128 x 128 tiles to pay.
 inline bool f32_gemm_shape(int H, int V) { return H % 4 == 0 && V % 4 == 0 && H >= 64 && V >= 64; }
 
-// dW GEMM geometry: 256x256 output tiles, and as many K splits (a multiple of 8, one set per XCD) as
-// give about one workgroup per compute unit.  Every (split, tile) workgroup owns a 256 KiB slot of
-// partial sums in the workspace.
+// dW GEMM geometry: 256x256 output tiles (the last hidden one of 128 where H is not a multiple of 256).  Every (split, tile) workgroup
+// owns a 256 KiB slot of partial sums in the workspace, which holds dw_split_count splits; a call uses dw_split_choice of them.
 constexpr int DW_TILE = 256;
 inline int dw_tiles(int H, int V) { return ((H + DW_TILE - 1) / DW_TILE) * (V / DW_TILE); }
 inline int dw_split_count(int H, int V) {
@@ -85,6 +84,30 @@ inline int dw_split_count(int H, int V) {
 }
 inline size_t dw_slot_bytes(int H, int V) {
     return (size_t)dw_tiles(H, V) * dw_split_count(H, V) * DW_TILE * DW_TILE * 4;
+}
+
+// K splits for chunks of `rows` rows: the least of (longest chain of workgroups on one of the 32 compute units of an XCD) x (stages of 32
+// rows, and about 8 for start and end) + the slots' traffic, in units of a stage of a whole tile (about 0.5 us; a slot written
+// once and read once costs a fifth of that when the whole chip moves them).  Half tiles cost half and run two to a gap.
+// Against a multiple of 8 for every shape: H = 1024, V = 4096, 8800 rows 402 -> 394 us a call (4 splits, not 8), H = 640, V = 4096 60.1 -> 58.0 ms
+// (6 splits with the half tiles, not 8 with whole ones; both relative to the same start).
+inline int dw_split_choice(int H, int V, long long rows) {
+    const int fm = H / DW_TILE, hm = (H + DW_TILE - 1) / DW_TILE - fm, nt = V / DW_TILE;
+    const double stages = (double)rows / 32.0;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= dw_split_count(H, V); ++s) {
+        const int f8 = (s * fm * nt + 7) / 8, h8 = (s * hm * nt + 7) / 8;
+        const int gaps = f8 % 32 ? 2 * (32 - f8 % 32) : 0;
+        const int rest = h8 > gaps ? (h8 - gaps + 31) / 32 : 0;
+        const double rounds = (f8 + 31) / 32 + 0.5 * rest;
+        const double cost = rounds * (stages / s + 8.0) + 0.2 * s * nt * (fm + 0.5 * hm);
+        if (s == 1 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 // Argument checks shared by every entry point (no pointers to data arrays here).
