@@ -84,11 +84,11 @@ hipError_t launch_bwd_f32(const Problem& pr, const SampleTable& st, const Lattic
 
 // fp32 MFMA GEMM form of the same two steps for H, V multiples of 4, over lattice nodes [r0, r0 + n) of the
 // group (node index relative to the group's first).  S [rows, V], Z and dZ [rows, H] are chunk buffers of
-// n rounded up to a multiple of 128 rows.
+// n rounded up to a multiple of 128 rows.  have_scores: S and Z already hold what launch_fwd_f32_gemm left for these nodes.
 hipError_t launch_fwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0, int s1,
                                long long r0, long long n, float* S, float* Z, hipStream_t stream);
 hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, const GradOut& go,
-                               int s0, int s1, long long r0, long long n, float* S, float* Z, float* dZ,
+                               int s0, int s1, long long r0, long long n, bool have_scores, float* S, float* Z, float* dZ,
                                hipStream_t stream);
 
 // ---- lattice (alpha, beta, loss) ------------------------------------------------------------
@@ -139,7 +139,7 @@ inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
 constexpr int SCORE_SPLIT_MAX_WG = 512;
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                            int tile1, void* part, size_t part_bytes, int* arrived, hipStream_t stream);
-// scores recomputed -> dh and z (bf16) into the chunk buffers   (H > 512)
+// scores recomputed -> dh and z (bf16) into the chunk buffers
 hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                                   int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream);
 // The forward launch that also keeps the joint rows (Z) and the scores (kept, in the dH buffer: fp16 differences to the running

@@ -464,17 +464,20 @@ hipError_t launch_fwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
 }
 
 hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, const GradOut& go,
-                               int s0, int s1, long long r0, long long n, float* S, float* Z, float* dZ,
+                               int s0, int s1, long long r0, long long n, bool have_scores, float* S, float* Z, float* dZ,
                                hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     const long long np = (n + FT - 1) / FT * FT;
     const int H = pr.H, V = pr.V;
     const float* W = (const float*)pr.W;
-    k_rows_z_f32<<<dim3((unsigned)np), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, Z);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = joint_gemm_f32<false, true>(Z, H, W, V, S, V, pr.b_out, 0, np, V, H, 1, stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (!have_scores) {
+        k_rows_z_f32<<<dim3((unsigned)np), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, Z);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = joint_gemm_f32<false, true>(Z, H, W, V, S, V, pr.b_out, 0, np, V, H, 1, stream);
+        if (e != hipSuccess) return e;
+    }
     k_rows_dh_f32<<<dim3((unsigned)(np / 4)), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, np, S);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -88,7 +88,7 @@ def test_c4_subbatch_all_outputs_default_and_small_workspace():
 
 
 def test_c3_subbatch_all_outputs_default_small_workspace_and_kept_scores():
-    # H = 640 (the widest joint the fused backward kernel takes), V = 4096: 8 samples incl. fewest / most nodes
+    # H = 640 (a joint size with half a hidden tile), V = 4096: 8 samples incl. fewest / most nodes
     wl = synth.WORKLOADS["C3"]
     ids = _ids_spanning(wl, 8)
     batch = synth.make_batch(wl, sample_ids=ids)
@@ -254,6 +254,28 @@ def test_lattice_sweeps_on_a_second_stream_against_the_checker(name, n, frac):
     plan.close()
 
 
+@pytest.mark.parametrize("extra", [0, 1 << 20, 64 << 20])
+def test_f32_scores_left_by_the_forward_pass_on_one_and_two_streams(extra):
+    # fp32 GEMM form: the first backward chunk of a group takes the scores of the last forward chunk out of the chunk buffers.  Groups of
+    # several chunks, of one, and a second stream, where the next group's forward pass overwrites them first
+    import torch
+    wl = synth.custom_workload("left32", B=6, T_max=45, U_max=12, H=128, V=260, dtype="f32", index=143,
+                               t_rule="uniform", t_lo=20, u_rule="uniform", u_lo=3)
+    batch = synth.make_batch(wl)
+    ref = run_oracle(batch)
+    desc = Bd.make_desc(batch.B, wl.T_max, wl.U_max, wl.H, wl.V, 0, Bd.RNNT_F32)
+    nmin = Bd.rnnt_joint_loss_workspace_bytes(desc, batch.T_len, batch.U_len, 1)
+    for two in (False, True):
+        plan = Bd.PlanHandle(desc, batch.T_len, batch.U_len, budget_bytes=nmin + extra, overlap_lattice=two)
+        _say("fp32 scores left", extra, two, plan.describe())
+        got, ws = _run_planned(batch, plan)
+        assert_parity(got, ref, "f32", "one stream")
+        if two:
+            got, _ = _run_planned(batch, plan, lattice_stream=torch.cuda.Stream(), workspace=ws)
+            assert_parity(got, ref, "f32", "two streams")
+        plan.close()
+
+
 @pytest.mark.parametrize("name,n,k", [("C2", 32, 30), ("C4", 12, 30), ("C4", 12, 20), ("C3", 8, 30)])
 def test_backward_pass_without_the_tiles_of_negligible_posterior(name, n, k):
     # skip_below_log2 = k: lattice tiles whose nodes all have a posterior below 2^-k stay out of the backward pass.
@@ -312,7 +334,7 @@ def test_default_leaves_out_only_tiles_whose_score_gradients_are_zero_in_bf16(na
     # operands their score gradients are exactly zero, so against the pass over every tile (-1) only the order of the
     # floating-point additions differs: loss identical, gradients equal to a few units of fp32 rounding of the sums
     if name == "P1024":
-        # the paper's own shape (joint size 1024, 4096 word pieces, 500 x 100): the unfused backward kernels
+        # the paper's own shape (joint size 1024, 4096 word pieces, 500 x 100)
         wl = synth.custom_workload("P4", B=4, T_max=500, U_max=100, H=1024, V=4096, dtype="bf16", index=5,
                                    t_rule="uniform", t_lo=454, u_rule="uniform", u_lo=54)
         ids = list(range(n))
@@ -336,8 +358,7 @@ def test_default_leaves_out_only_tiles_whose_score_gradients_are_zero_in_bf16(na
 @pytest.mark.parametrize("name,n", [("C4", 12), ("C3", 8), ("P1024", 4)])
 def test_kept_scores_with_the_tile_selection(name, n):
     # keep_scores = 1: the forward pass has written every tile's scores and joint rows into the chunk buffers before
-    # the list exists, so the backward kernels and the dW_out GEMM pick the listed tiles' rows where they lie (fused
-    # kernel for H <= 640, conversion pass + dz GEMM above).  Default against the checker and against the pass over
+    # the list exists, so the backward kernels and the dW_out GEMM pick the listed tiles' rows where they lie.  Default against the checker and against the pass over
     # every tile (loss identical, gradients equal to rounding of the sums); k = 30 against the checker; a small
     # workspace (several groups) the same.
     if name == "P1024":
