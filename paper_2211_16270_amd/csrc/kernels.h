@@ -118,11 +118,14 @@ constexpr ActiveTiles EVERY_TILE{nullptr, nullptr, 0, 0, -1};
 // ---- bf16 MFMA path -------------------------------------------------------------------------
 // How many workgroups share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
 // its share of the blocks and `fixed` blocks' time for its start and end.
+inline long long split_cost(int workgroups, int vs, int slots, int nvb, int fixed) {
+    return ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
+}
 inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
     int best = 1;
     long long best_cost = 0;
     for (int vs = 1; vs <= 4; vs *= 2) {
-        const long long cost = ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
+        const long long cost = split_cost(workgroups, vs, slots, nvb, fixed);
         if (vs == 1 || cost * 10 < best_cost * 9) {
             best = vs;
             best_cost = cost;

@@ -37,6 +37,7 @@ struct DzArgs {
     float* d_enc;
     float* d_pred;
     int n_tiles;              // hidden tiles, the half one included
+    int edge;                 // their width: 256, or 128 (half tiles only)
     ActiveTiles at;           // which tiles the chunk's 64-row slots hold (see kernels.h)
 };
 
@@ -297,8 +298,8 @@ __global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
         n_slots = left < n_slots ? left : n_slots;
     }
     if (bx * 4 >= n_slots) return;          // (uniform per workgroup)
-    const int n0 = by * ZT;
-    if (n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots);
+    const int n0 = by * g.edge;
+    if (g.edge < ZT || n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots);
     else dz_tile<false>(g, dz_smem, bx, n0, n_slots);
 }
 
@@ -309,7 +310,17 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTa
     const int n = tile1 - tile0;
     if (n <= 0) return hipSuccess;
     if (pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
-    const DzArgs g{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, (pr.H + ZT - 1) / ZT, at};
+    const int m_tiles = (n + 3) / 4, m8 = (m_tiles + 7) / 8 * 8, stages = pr.V / ZK;
+    // Whole tiles (the half one counts half), or, in a launch of one round, half tiles alone where they fill the chip better: twice the
+    // workgroups of about half the cost each, so that a small launch need not split the vocabulary, which runs the epilogue and its atomics
+    // once per part (one utterance of 250 x 50, H = 512, V = 1024: a call 0.903 -> 0.941 of the speed of the same reference build).  Past one
+    // round the half tiles' poorer ratio of LDS reads to MFMAs shows (288 of them, H = 1024, V = 4096, against 144 whole ones: 394 -> 407 us a
+    // call).  About 16 stages' time for start and epilogue.
+    const int whole = (m_tiles * pr.H + ZT - 1) / ZT, halves = m_tiles * (pr.H / 128);
+    const int vs_w = vocabulary_split(whole, 256, stages, 16), vs_h = vocabulary_split(halves, 256, stages, 16);
+    const long long cost_w = 2 * split_cost(whole, vs_w, 256, stages, 16), cost_h = split_cost(halves, vs_h, 256, stages, 16);
+    const int edge = halves <= 256 && cost_h * 10 < cost_w * 9 ? 128 : ZT, vs = edge == ZT ? vs_w : vs_h;
+    const DzArgs g{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, (pr.H + edge - 1) / edge, edge, at};
     const size_t smem = (size_t)ZST * Z_STAGE;
     static bool configured = false;
     if (!configured) {
@@ -318,9 +329,6 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTa
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const int m_tiles = (n + 3) / 4, m8 = (m_tiles + 7) / 8 * 8;
-    // (a half hidden tile counts half; about 16 stages' time for start and epilogue)
-    const int vs = vocabulary_split((m_tiles * pr.H + ZT - 1) / ZT, 256, pr.V / ZK, 16);
     k_gemm_dz256<<<dim3((unsigned)(m8 * g.n_tiles), (unsigned)vs), dim3(256), smem, stream>>>(g);
     return hipGetLastError();
 }
