@@ -313,7 +313,7 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTa
     const int m_tiles = (n + 3) / 4, m8 = (m_tiles + 7) / 8 * 8, stages = pr.V / ZK;
     // Whole tiles (the half one counts half), or, in a launch of one round, half tiles alone where they fill the chip better: twice the
     // workgroups of about half the cost each, so that a small launch need not split the vocabulary, which runs the epilogue and its atomics
-    // once per part (one utterance of 250 x 50, H = 512, V = 1024: a call 0.903 -> 0.941 of the speed of the same reference build).  Past one
+    // once per part (one utterance of 250 x 50, H = 512, V = 1024: a call 175.7 -> 165 us).  Past one
     // round the half tiles' poorer ratio of LDS reads to MFMAs shows (288 of them, H = 1024, V = 4096, against 144 whole ones: 394 -> 407 us a
     // call).  About 16 stages' time for start and epilogue.
     const int whole = (m_tiles * pr.H + ZT - 1) / ZT, halves = m_tiles * (pr.H / 128);
