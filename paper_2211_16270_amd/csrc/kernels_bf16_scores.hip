@@ -6,7 +6,7 @@
 //   MODE 1  dh = gamma softmax - posteriors as bf16, and z, into the chunk buffers (f^W_4, backward)
 //   MODE 2  MODE 0, and z and the scores themselves kept for the backward pass, as fp16 differences t = h - m to a running
 //           maximum m (t <= 0, so an entry's error exp(t) |t| 2^-11 in the softmax is at most 2^-11 / e whatever the size of
-//           the scores; m is the row's largest score so far, one float per row and 64 entries)
+//           the scores; m is the row's largest score so far in its quarter of the vocabulary, one float per row and 64 entries)
 //
 // A workgroup is 4 waves; a wave owns 32 RB rows (RB = 1: half a lattice tile, 2: a whole one) and keeps their joint
 // activations in registers for the whole pass (H/16 fragments of 4 registers per 32 rows: 128 registers at H = 512).
@@ -46,6 +46,11 @@ constexpr int SC_VB = 32;          // vocabulary entries per block
 constexpr int SC_RING = 8;         // W_out fragments a wave holds ahead of its MFMAs
 constexpr int SC_SEG = 4;          // statistics are formed per quarter of the vocabulary and folded in order, so that a
                                    // result does not depend on how many workgroups share the vocabulary
+// Smallest running maximum, finite: entries that are masked out (bias -inf, or finite and below anything a network gives) then have the
+// exponential 0, and blocks or quarters of nothing else the sum 0, instead of -inf - -inf or the rounding error of -1e30 log2 e in the
+// exponent.  At this size that error is at most 2^6, and 2^64 times as many entries as there may be is still finite in fp32: maxima
+// just above the floor lose to any other quarter's without an infinity.
+constexpr float SC_MAX_FLOOR = -1073741824.0f;
 constexpr int SC_AGPR_FRAGS = 64;  // joint fragments kept in the 256 accumulation registers; the rest in vector registers
 
 // LDS ring: stages of SF fragments (1 KiB each), a whole or half block of W_out^T, so many of them that a stage's copies are sent
@@ -159,7 +164,8 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     float m_run[RB], s_run[RB], m_tot[RB], s_tot[RB], cap_b[RB], cap_y[RB], m_pair[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        m_run[rb] = m_tot[rb] = cap_b[rb] = cap_y[rb] = RNNT_NEG_INF;
+        m_run[rb] = m_tot[rb] = SC_MAX_FLOOR;
+        cap_b[rb] = cap_y[rb] = RNNT_NEG_INF;
         s_run[rb] = s_tot[rb] = m_pair[rb] = 0.0f;
     }
     const u32x4* frag0 = reinterpret_cast<const u32x4*>(smem) + lane;
@@ -249,7 +255,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
                     __hip_atomic_store(q + 3, cy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
-            m_run[rb] = RNNT_NEG_INF;
+            m_run[rb] = SC_MAX_FLOOR;
             s_run[rb] = 0.0f;
         }
     };

@@ -766,3 +766,41 @@ def test_random_small_shapes_against_the_checker(seed):
     ref = run_oracle(batch, blank=blank)
     assert_parity(got, ref, wl.dtype, f"random shape {seed}")
     assert_padding_zero(got, batch)
+
+
+@pytest.mark.parametrize("mask", [-np.inf, float(np.finfo(np.float32).min), -1e30, -1e4])
+@pytest.mark.parametrize("H,V", [(128, 1024), (512, 512), (640, 512), (1024, 512)])
+def test_bf16_masked_vocabulary_entries(H, V, mask):
+    # bias of entries that may never be emitted: a whole quarter of the vocabulary, the first block of every quarter, everything but
+    # blank and labels.  One sample (the vocabulary is split over workgroups) and many copies of it (it is not); losses alone, the
+    # default and kept scores
+    import torch
+    blank, n = 40, 400
+    wl = synth.custom_workload("masked", B=1, T_max=21, U_max=6, H=H, V=V, dtype="bf16", index=144, blank=blank)
+    batch = synth.make_batch(wl)
+    batch.labels[:] = 41 + 7 * np.arange(wl.U_max)
+    entry = np.arange(V)
+    for what, masked in (("last quarter", entry >= V - V // 4), ("head of every quarter", entry % (V // 4) < 32),
+                         ("all but blank and labels", (entry != blank) & ~np.isin(entry, batch.labels))):
+        batch.b_out[:] = np.where(masked, np.float32(mask), np.linspace(-0.2, 0.2, V, dtype=np.float32))
+        _say("masked", H, V, mask, what)
+        ref = run_oracle(batch)
+        many = synth.Batch(synth.custom_workload("masked", B=n, T_max=21, U_max=6, H=H, V=V, dtype="bf16", index=144, blank=blank),
+                           np.repeat(batch.sample_ids, n), np.repeat(batch.enc, n, 0), np.repeat(batch.pred, n, 0), batch.W_out,
+                           batch.b_out, np.repeat(batch.labels, n, 0), np.repeat(batch.T_len, n), np.repeat(batch.U_len, n))
+        for keep in (0, 1):
+            got = run_gpu(batch, keep_scores=keep)
+            assert_parity(got, ref, "bf16", f"{what} keep={keep}")
+            assert np.all(got["db_out"][masked] == 0.0) and np.all(got["dW_out"][:, masked] == 0.0)
+            all_ = run_gpu(many, keep_scores=keep, sample_weight=np.full(n, 1.0 / n, dtype=np.float32))
+            np.testing.assert_array_equal(all_["loss"], np.repeat(all_["loss"][:1], n))
+            assert_parity({k: all_[k][:1] if k in ("loss", "d_enc", "d_pred") else all_[k] for k in ("loss",) + GRADS},
+                          {k: ref[k] / n if k in ("d_enc", "d_pred") else ref[k] for k in ("loss",) + GRADS}, "bf16",
+                          f"{what} keep={keep}, {n} samples")
+        for x in (batch, many):
+            dev, loss = Bd.to_device(x), torch.empty(x.B, dtype=torch.float32, device="cuda")
+            desc = Bd.make_desc(x.B, wl.T_max, wl.U_max, H, V, blank, Bd.RNNT_BF16)
+            ws = Bd.Workspace(Bd.rnnt_joint_loss_workspace_bytes(desc, x.T_len, x.U_len))
+            assert Bd.rnnt_joint_loss_fwd(desc, dev["enc"], dev["pred"], dev["W_out"], dev["b_out"], dev["labels"], x.T_len, x.U_len,
+                                          loss, ws.buf) == 0
+            assert rel_loss_err(loss.cpu().numpy().astype(np.float64), np.repeat(ref["loss"], x.B)) <= TOL["bf16"]["loss"]
