@@ -133,15 +133,13 @@ __device__ __forceinline__ RowDh row_score_gradient(const LatticeState& ls, long
     return r;
 }
 
-// Asynchronous global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane l's 16 bytes land
-// at LDS byte address lds_base + 16*l (lds_base wave-uniform, passed in M0).  Completion is tracked by
-// the wave's vmcnt counter; the compiler does not see these loads, so the waits are explicit below.
-__device__ __forceinline__ void lds_dma16(const void* gptr, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base) : "memory", "m0");
-}
-// The same with a wave-uniform 64-bit base (scalar registers) plus a 32-bit byte offset per lane.
+// Asynchronous global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane l's 16 bytes, at sbase + voff (a wave-uniform
+// 64-bit base and a 32-bit byte offset per lane), land at LDS byte address lds_base + 16*l (lds_base wave-uniform, passed
+// in M0).  Completion is tracked by the wave's vmcnt counter; the compiler does not see these loads, so the waits are explicit below.
+// A load that takes its LDS address from M0 may not follow the scalar write of M0 directly: one wait state in between, which the
+// compiler does not add inside assembler text.  Here and in the other copies the s_nop is that wait state.
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
                  : "memory", "m0");
 }
 
@@ -172,12 +170,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // The same copy as lds_dma16_s with an immediate offset, which moves both addresses: OFF bytes from sbase and from lds_base.
 template <int OFF>
 __device__ __forceinline__ void lds_dma16_imm(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(voff), "s"(sbase), "s"(lds_base),
+                 "n"(OFF)
                  : "memory", "m0");
 }
 // 4 bytes per lane: word at sbase + voff of lane l -> lds_base + 4 l (64 words; lanes with equal voff write equal words)
 __device__ __forceinline__ void lds_dma4_s(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
                  : "memory", "m0");
 }
 

@@ -282,7 +282,8 @@ __device__ __forceinline__ void pin(float& a, float& b) {
 // byte address lds_base + 4*l (lds_base wave-uniform, passed in M0).  The compiler does not see
 // these loads; the sweep waits for them explicitly (vmcnt) before the first step that reads them.
 __device__ __forceinline__ void lds_dma4(const void* gptr, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" ::"v"(gptr), "s"(lds_base) : "memory", "m0");
+    // (the s_nop: one wait state between the write of M0 and the load that uses it)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gptr), "s"(lds_base) : "memory", "m0");
 }
 
 // Steps 1 .. nsteps-1 of a sweep.  Step k with (k+1) % LW_RB == 0 is the last one before the sweep enters the
