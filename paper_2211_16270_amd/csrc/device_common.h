@@ -203,8 +203,8 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // because the compiler copies operands that live in AGPRs to vector registers first (four moves per MFMA: the power
 // and the issue slots of this kernel).  The compiler places no wait states for it, so the code around it keeps the
 // required distances itself: a vector instruction that writes an operand stands at least two instructions ahead
-// (MFMA_AFTER_VALU), and the result is not read before the whole depth of the matrix pipe has passed (mfma_result_ready, or at least
-// two further MFMAs in between).
+// (mfma_after_valu), and the result is not read before the whole depth of the matrix pipe has passed (mfma_result_ready, or at least
+// two further MFMAs in between).  Both waits name the accumulators, so that no move of them can be placed behind the wait.
 template <bool AGPR>
 __device__ __forceinline__ void mfma_zb(f32x16& acc, const u32x4& w, const u32x4& z) {
     if constexpr (AGPR) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "a"(z));
@@ -224,7 +224,8 @@ __device__ __forceinline__ u32x4 fragment_from_scores(const f32x16& d, int p) {
     swap_halves(x[1], x[3]);
     return u32x4{x[0], x[1], x[2], x[3]};
 }
-#define MFMA_AFTER_VALU() asm volatile("s_nop 3" ::: "memory")
+__device__ __forceinline__ void mfma_after_valu(f32x16 (&acc)[1]) { asm volatile("s_nop 3" : "+v"(acc[0])::"memory"); }
+__device__ __forceinline__ void mfma_after_valu(f32x16 (&acc)[2]) { asm volatile("s_nop 3" : "+v"(acc[0]), "+v"(acc[1])::"memory"); }
 __device__ __forceinline__ void mfma_result_ready(f32x16& acc) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc)); }
 
 // The joint rows of one wave as MFMA B fragments: z[kk] of lane (l32, hb) holds row l32, columns 16 kk + 8 hb .. +7.

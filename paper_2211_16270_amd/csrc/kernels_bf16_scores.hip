@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
                 slot = slot + 1 == NST ? 0 : slot + 1;
                 fs = frag0 + slot * (SB / 16);
             }
-            if constexpr (k == 0) MFMA_AFTER_VALU();
+            if constexpr (k == 0) mfma_after_valu(cur);
             static_for<0, RB>([&](auto rb_tag) {
                 constexpr int rb = decltype(rb_tag)::value;
                 mfma_zb<(rb * KK + k < SC_AGPR_FRAGS)>(cur[rb], wf[k % RG], z[rb][k]);
