@@ -328,8 +328,8 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         pa.Wp = bf16 ? wv.wpack : nullptr;
         pa.Wq = (bf16 && grads) ? wv.wq : nullptr;
         if (bf16) {
-            pa.zero_ptr[4] = (float*)(w + plan.off_arrived);
-            pa.zero_n[4] = SCORE_SPLIT_MAX_WG;
+            pa.zero_ptr[4] = wv.ls.tile_esum;         // counters of the forward launch until it stores the sums
+            pa.zero_n[4] = (size_t)plan.tiles_total;
         }
         pa.H = desc->H;
         pa.V = desc->V;
@@ -371,8 +371,7 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         else if (bf16)
             RNNT_HIP(timed(KC_FWD_SCORES, stream, [&] {
                 // (the chunk buffers are free until the group's backward pass: scratch)
-                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, plan.chunk_bytes,
-                                       (int*)(w + plan.off_arrived), stream);
+                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, plan.chunk_bytes, stream);
             }));
         else if (plan.f32_gemm)
             for (long long r0 = 0; r0 < g.rows; r0 += plan.chunk_rows)

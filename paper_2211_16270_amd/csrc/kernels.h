@@ -137,11 +137,10 @@ inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
 
 // Wpack: W_out^T in fragments [V/32][H/16], Wq: W_out in fragments [V/16][H/32] (launch_prepare).
 // scores on MFMA -> online log-softmax -> lse, lpb, lpy   (tiles [tile0,tile1)).  part: scratch for partial statistics where
-// a small launch splits the vocabulary over workgroups; arrived: SCORE_SPLIT_MAX_WG counters, zero before the first launch (every
-// launch leaves them zero)
-constexpr int SCORE_SPLIT_MAX_WG = 512;
+// a small launch splits the vocabulary over workgroups; these count their arrivals in the emission sums of the tiles, which are
+// zero before the launch (launch_prepare)
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
-                           int tile1, void* part, size_t part_bytes, int* arrived, hipStream_t stream);
+                           int tile1, void* part, size_t part_bytes, hipStream_t stream);
 // scores recomputed -> dh and z (bf16) into the chunk buffers
 hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                                   int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream);
@@ -174,7 +173,7 @@ __host__ __device__ inline int chunk_pitch(int n) { return n + 64; }
 
 // Split-K GEMM Z^T dH over one chunk's rows: every (split, tile) workgroup adds its 256x256 partial
 // product to its own slot (`first` != 0: overwrites it), db += column sums of dH.  `splits` and the
-// slot buffer size follow dw_split_count / dw_slot_bytes (plan.h).
+// slot buffer size follow dw_split_choice / dw_slot_bytes (plan.h).
 // With at.active set the chunk holds only min(rows, 64 * (*at.n_active - at.cbase)) rows (read on the device).
 hipError_t launch_gemm_dw_bf16(int H, int V, long long rows, int splits, int first, const void* Z,
                                const void* dH, float* slots, float* db, const ActiveTiles& at, hipStream_t stream);

@@ -39,7 +39,6 @@ struct ScoreArgs {
     float* kept_max;       // MODE 2: [tiles][V/64][64 rows]
     ActiveTiles at;        // MODE 1
     f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0): [4 segments][rows of the launch] {max, sum, blank, label score}
-    int* arrived;          // and one counter per workgroup column, zero between launches
 };
 
 constexpr int SC_VB = 32;          // vocabulary entries per block
@@ -51,6 +50,7 @@ constexpr int SC_SEG = 4;          // statistics are formed per quarter of the v
 // exponent.  At this size that error is at most 2^6, and 2^64 times as many entries as there may be is still finite in fp32: maxima
 // just above the floor lose to any other quarter's without an infinity.
 constexpr float SC_MAX_FLOOR = -1073741824.0f;
+constexpr int SC_SPLIT_MAX_WG = 512;  // launches of more workgroups fill the chip without sharing the vocabulary (forward)
 constexpr int SC_AGPR_FRAGS = 64;  // joint fragments kept in the 256 accumulation registers; the rest in vector registers
 
 // LDS ring: stages of SF fragments (1 KiB each), a whole or half block of W_out^T, so many of them that a stage's copies are sent
@@ -442,10 +442,9 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
         // has to be written back or invalidated between them)
         __syncthreads();
         if (tid == 0) {
-            const int n = __hip_atomic_fetch_add(a.arrived + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *order = n;
-            if (n == (int)gridDim.y - 1)              // ready for the next launch
-                __hip_atomic_store(a.arrived + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // (the counter: the emission sum of the column's first tile, zero until the last one stores it below)
+            int* arrived = reinterpret_cast<int*>(a.ls.tile_esum) + a.tile0 + blockIdx.x * TW;
+            *order = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
         if (*order != (int)gridDim.y - 1) return;
@@ -502,7 +501,7 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
     int vs = 1;
     if (MODE == 1) {
         vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
-    } else if (MODE == 0 && n <= SCORE_SPLIT_MAX_WG) {
+    } else if (MODE == 0 && n <= SC_SPLIT_MAX_WG) {
         vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
         if ((size_t)SC_SEG * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
     }
@@ -515,9 +514,9 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
 // Joint sizes up to 512: two workgroups per compute unit (one's joint rows are built beside the other's MFMAs); 640: whole
 // tiles per wave (half the LDS reads per MFMA); above: 32 rows per wave fill the registers.
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
-                           int tile1, void* part, size_t part_bytes, int* arrived, hipStream_t stream) {
+                           int tile1, void* part, size_t part_bytes, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
-    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, nullptr, nullptr, nullptr, EVERY_TILE, (f32x4*)part, arrived};
+    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, nullptr, nullptr, nullptr, EVERY_TILE, (f32x4*)part};
     switch (pr.H) {
         case 128: return launch_scores_t<0, 8, 1, 2>(a, part_bytes, stream);
         case 256: return launch_scores_t<0, 16, 1, 2>(a, part_bytes, stream);
@@ -534,7 +533,7 @@ hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTab
 hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                                   int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
-    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)dH, (unsigned char*)Z, nullptr, at, nullptr, nullptr};
+    const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)dH, (unsigned char*)Z, nullptr, at, nullptr};
     switch (pr.H) {
         case 128: return launch_scores_t<1, 8, 1, 2>(a, 0, stream);
         case 256: return launch_scores_t<1, 16, 1, 2>(a, 0, stream);
@@ -552,7 +551,7 @@ hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const Samp
                                 int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
     const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)kept, (unsigned char*)Z, kept_max, EVERY_TILE,
-                      nullptr, nullptr};
+                      nullptr};
     switch (pr.H) {
         case 128: return launch_scores_t<2, 8, 1, 1>(a, 0, stream);
         case 256: return launch_scores_t<2, 16, 1, 1>(a, 0, stream);

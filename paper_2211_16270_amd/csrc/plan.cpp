@@ -69,7 +69,6 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     p.off_n_active = take(p.skip_log2 ? B * 4 : 0);
     p.off_wpack = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
     p.off_wq = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
-    p.off_arrived = take(p.bf16 ? (size_t)SCORE_SPLIT_MAX_WG * 4 : 0);
     p.dw_splits = p.bf16 ? dw_split_choice(d.H, d.V, chunk_rows) : 0;
     p.off_dwslots = take(p.bf16 ? dw_slot_bytes(d.H, d.V) : 0);
     size_t lat0 = o;

@@ -55,7 +55,6 @@ struct Plan {
     size_t off_n_active = 0;           // skip_log2 > 0: per group the number of tiles that stay (their list lies in the
                                        // tile_esum array, over the entries of the same tiles)
     size_t off_wpack = 0, off_wq = 0;
-    size_t off_arrived = 0;             // bf16: counters of the forward launches that split the vocabulary
     size_t off_lse = 0, off_lpb = 0, off_lpy = 0, off_alpha = 0, off_beta = 0;
     size_t off_dh = 0, off_z = 0, off_kept_max = 0;
     size_t off_dz32 = 0;                // fp32 GEMM form: dZ [chunk_rows, H]; off_dh, off_z hold S and Z as fp32
@@ -75,7 +74,9 @@ constexpr int ZERO_IN_BF16_LOG2 = 135;
 inline bool f32_gemm_shape(int H, int V) { return H % 4 == 0 && V % 4 == 0 && H >= 64 && V >= 64; }
 
 // dW GEMM geometry: 256x256 output tiles (the last hidden one of 128 where H is not a multiple of 256).  Every (split, tile) workgroup
-// owns a 256 KiB slot of partial sums in the workspace, which holds dw_split_count splits; a call uses dw_split_choice of them.
+// owns a 256 KiB slot of partial sums in the workspace.  The slots have room for dw_split_count splits less, for H > 640, a packed
+// copy of W_out: the room of the copy for the dz GEMM, which so takes nothing from what a workspace of a given size can hold.  A call
+// uses dw_split_choice of at most dw_splits_max.
 constexpr int DW_TILE = 256;
 inline int dw_tiles(int H, int V) { return ((H + DW_TILE - 1) / DW_TILE) * (V / DW_TILE); }
 inline int dw_split_count(int H, int V) {
@@ -83,7 +84,10 @@ inline int dw_split_count(int H, int V) {
     return ((256 + t - 1) / t + 7) / 8 * 8;
 }
 inline size_t dw_slot_bytes(int H, int V) {
-    return (size_t)dw_tiles(H, V) * dw_split_count(H, V) * DW_TILE * DW_TILE * 4;
+    return (size_t)dw_tiles(H, V) * dw_split_count(H, V) * DW_TILE * DW_TILE * 4 - (H > 640 ? (size_t)H * V * 2 : 0);
+}
+inline int dw_splits_max(int H, int V) {
+    return (int)(dw_slot_bytes(H, V) / ((size_t)dw_tiles(H, V) * DW_TILE * DW_TILE * 4));
 }
 
 // K splits for chunks of `rows` rows: the least of (longest chain of workgroups on one of the 32 compute units of an XCD) x (stages of 32
@@ -96,7 +100,7 @@ inline int dw_split_choice(int H, int V, long long rows) {
     const double stages = (double)rows / 32.0;
     int best = 1;
     double best_cost = 0.0;
-    for (int s = 1; s <= dw_split_count(H, V); ++s) {
+    for (int s = 1; s <= dw_splits_max(H, V); ++s) {
         const int f8 = (s * fm * nt + 7) / 8, h8 = (s * hm * nt + 7) / 8;
         const int gaps = f8 % 32 ? 2 * (32 - f8 % 32) : 0;
         const int rest = h8 > gaps ? (h8 - gaps + 31) / 32 : 0;

@@ -394,3 +394,44 @@ def test_plan_handle_holds_the_schedule_of_the_plan_query():
         Bd.PlanHandle(desc, T + 1000, U)
     assert Bd.lib().rnnt_plan_workspace_bytes(None) == 0
     Bd.lib().rnnt_plan_destroy(None)
+
+
+def _smallest_workspace_promised(T, U, H, V, keep, g16, T_max, U_max):
+    """What the smallest bf16 workspace may take: the tables, one packed copy of W_out and up to H = 640 a second one, slots of the
+    dW GEMM for about one 256 x 256 tile per compute unit in whole eighths, the largest sample's lattice state, one chunk."""
+    al = lambda n, a=256: -(-n // a) * a
+    B, tiles = len(T), _tiles(T, U)
+    rows = (T.astype(np.int64) * (U + 1)).max()
+    chunk = al(int(tiles.max()) * 64, 128) if keep else 128
+    dw = -(-H // 256) * (V // 256)
+    splits = al(-(-256 // dw), 8)
+    n = 6 * al(4 * B) + al(4 * (B + 1)) + al(8 * (B + 1)) + 2 * al(4 * int(tiles.sum())) + (2 if H <= 640 else 1) * al(2 * H * V)
+    n += dw * splits * (1 << 18) + 5 * al(4 * int(rows)) + al(al(chunk) * 2 * (V + 64)) + al(chunk * 2 * (H + 64))
+    n += al(chunk * (V // 64) * 4) if keep else 0
+    return n + (al(4 * T_max * H) + al(4 * (U_max + 1) * H) if g16 else 0)
+
+
+@pytest.mark.parametrize("H", [128, 256, 512, 640, 768, 896, 1024])
+@pytest.mark.parametrize("V", [256, 1024, 4096, 8192])
+def test_smallest_workspace_keeps_its_bound(H, V):
+    g = np.random.default_rng(H + V)
+    for T_max, U_max, B in ((1, 0, 1), (40, 9, 3), (700, 120, 1), (3000, 300, 2)):
+        T, U = g.integers(1, T_max + 1, B).astype(np.int32), g.integers(0, U_max + 1, B).astype(np.int32)
+        for keep, g16 in ((0, 0), (1, 0), (0, 1)):
+            desc = Bd.make_desc(B, T_max, U_max, H, V, 0, Bd.RNNT_BF16, keep_scores=keep, input_grads_bf16=g16)
+            need = Bd.rnnt_joint_loss_workspace_bytes(desc, T, U, 1)
+            assert need <= _smallest_workspace_promised(T, U, H, V, keep, g16, T_max, U_max), (T_max, U_max, keep, g16)
+            st, info, _ = Bd.rnnt_joint_loss_plan(desc, T, U, need)
+            assert st == 0 and info["workspace_bytes"] <= need
+
+
+def test_long_samples_that_just_fit_the_static_workspace():
+    # 128 MiB, the largest sample for which the bound above holds: 20 bytes per lattice node beside tables, weights and slots
+    for H, V in ((768, 256), (896, 512), (1024, 1024), (1024, 256)):
+        U = 1000
+        fits = lambda t: _smallest_workspace_promised(np.array([t]), np.array([U]), H, V, 0, 0, t, U) <= 128 << 20
+        T = max(t for t in range(1000, 5000) if fits(t))
+        assert not fits(T + 1)
+        desc = Bd.make_desc(1, T, U, H, V, 0, Bd.RNNT_BF16)
+        st, _, _ = Bd.rnnt_joint_loss_plan(desc, np.array([T], np.int32), np.array([U], np.int32), 128 << 20)
+        assert st == 0, (H, V, T)
