@@ -547,15 +547,18 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
     return hipErrorInvalidValue;
 }
 
+// Kept scores: two workgroups per compute unit up to 384 (the stores of one stand beside the other's MFMAs; against
+// one, 64 samples of 500 x 100, V = 1024: H = 256 4.85 -> 4.21 ms a call, H = 384 6.71 -> 6.09 ms; 16 samples, H = 256, V = 4096
+// 4.88 -> 4.32 ms).  At 512 the two further score blocks that wait for their pair leave no registers for a second one (13 would spill).
 hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                                 int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
     const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)kept, (unsigned char*)Z, kept_max, EVERY_TILE,
                       nullptr};
     switch (pr.H) {
-        case 128: return launch_scores_t<2, 8, 1, 1>(a, 0, stream);
-        case 256: return launch_scores_t<2, 16, 1, 1>(a, 0, stream);
-        case 384: return launch_scores_t<2, 24, 1, 1>(a, 0, stream);
+        case 128: return launch_scores_t<2, 8, 1, 2>(a, 0, stream);
+        case 256: return launch_scores_t<2, 16, 1, 2>(a, 0, stream);
+        case 384: return launch_scores_t<2, 24, 1, 2>(a, 0, stream);
         case 512: return launch_scores_t<2, 32, 1, 1>(a, 0, stream);
         case 640: return launch_scores_t<2, 40, 1, 1>(a, 0, stream);
         case 768: return launch_scores_t<2, 48, 1, 1>(a, 0, stream);
