@@ -366,7 +366,9 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         const LatticeState ls = group_state(gi);
         if (keep)
             RNNT_HIP(timed(KC_FWD_KEEP, stream, [&] {
-                return launch_fwd_keep_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, wv.Z, wv.kept_max, stream);
+                // (the chunk buffers hold the scores; the slots of the dW GEMM are free until the first backward pass)
+                return launch_fwd_keep_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, wv.Z, wv.kept_max, wv.dw_slots,
+                                            gi == 0 ? dw_slot_bytes(desc->H, desc->V) : 0, stream);
             }));
         else if (bf16)
             RNNT_HIP(timed(KC_FWD_SCORES, stream, [&] {

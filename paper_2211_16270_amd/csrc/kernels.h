@@ -146,9 +146,9 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
                                   int tile1, void* dH, void* Z, const ActiveTiles& at, hipStream_t stream);
 // The forward launch that also keeps the joint rows (Z) and the scores (kept, in the dH buffer: fp16 differences to the running
 // maxima kept_max [tiles][V/64][64]) of tiles [tile0,tile1), and the launch that turns the kept scores into dh (bf16, in
-// place) once alpha and beta are known.
+// place) once alpha and beta are known.  part: as for launch_fwd_bf16, of part_bytes (0: never split).
 hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
-                                int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream);
+                                int tile1, void* kept, void* Z, float* kept_max, void* part, size_t part_bytes, hipStream_t stream);
 hipError_t launch_kept_to_dh_bf16(const Problem& pr, const SampleTable& st, const LatticeState& ls, int tile0, int tile1,
                                   void* kept, const float* kept_max, const ActiveTiles& at, hipStream_t stream);
 // dz = dH W^T, times the tanh derivative, reduced over the tile's u resp. t, added to d_enc, d_pred

@@ -38,7 +38,7 @@ struct ScoreArgs {
     unsigned char* Z;
     float* kept_max;       // MODE 2: [tiles][V/64][64 rows]
     ActiveTiles at;        // MODE 1
-    f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0): [4 segments][rows of the launch] {max, sum, blank, label score}
+    f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0, 2): [4 segments][rows of the launch] {max, sum, blank, label score}
 };
 
 constexpr int SC_VB = 32;          // vocabulary entries per block
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     };
     auto keep_max = [&](int rb, int vb) {
         if (present && hb == 0)
-            a.kept_max[((size_t)tslot * (V / 64) + (vb >> 1)) * 64 + 32 * (half0 + rb) + l32] = m_pair[rb];
+            a.kept_max[((size_t)tslot * (V / 64) + ((vb0 + vb) >> 1)) * 64 + 32 * (half0 + rb) + l32] = m_pair[rb];
     };
 
     // One block: KK steps of RB MFMAs; behind them the LDS read of the fragment RG steps ahead, a piece of work on the
@@ -501,8 +501,9 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
     int vs = 1;
     if (MODE == 1) {
         vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
-    } else if (MODE == 0 && n <= SC_SPLIT_MAX_WG) {
+    } else if (n <= SC_SPLIT_MAX_WG) {
         vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
+        while (MODE == 2 && a.pr.V / SC_VB / vs % 4 != 0) vs /= 2;      // (kept scores leave in pairs of blocks, two pairs at a time)
         if ((size_t)SC_SEG * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
     }
     k_scores<MODE, KK, RB, WPS><<<dim3((unsigned)n, (unsigned)vs), dim3(256), smem, stream>>>(a);
@@ -550,20 +551,22 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
 // Kept scores: two workgroups per compute unit up to 384 (the stores of one stand beside the other's MFMAs; against
 // one, 64 samples of 500 x 100, V = 1024: H = 256 4.85 -> 4.21 ms a call, H = 384 6.71 -> 6.09 ms; 16 samples, H = 256, V = 4096
 // 4.88 -> 4.32 ms).  At 512 the two further score blocks that wait for their pair leave no registers for a second one (13 would spill).
+// A small launch splits the vocabulary as the forward kernel without kept scores does (one sample of 250 x 50, V = 1024: H = 256 144 -> 135 us a
+// call, H = 384 160 -> 150, H = 640 188 -> 173, H = 1024 213 -> 194).
 hipError_t launch_fwd_keep_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
-                                int tile1, void* kept, void* Z, float* kept_max, hipStream_t stream) {
+                                int tile1, void* kept, void* Z, float* kept_max, void* part, size_t part_bytes, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
     const ScoreArgs a{pr, st, ls, (const bf16_t*)Wpack, tile0, tile1, (unsigned char*)kept, (unsigned char*)Z, kept_max, EVERY_TILE,
-                      nullptr};
+                      (f32x4*)part};
     switch (pr.H) {
-        case 128: return launch_scores_t<2, 8, 1, 2>(a, 0, stream);
-        case 256: return launch_scores_t<2, 16, 1, 2>(a, 0, stream);
-        case 384: return launch_scores_t<2, 24, 1, 2>(a, 0, stream);
-        case 512: return launch_scores_t<2, 32, 1, 1>(a, 0, stream);
-        case 640: return launch_scores_t<2, 40, 1, 1>(a, 0, stream);
-        case 768: return launch_scores_t<2, 48, 1, 1>(a, 0, stream);
-        case 896: return launch_scores_t<2, 56, 1, 1>(a, 0, stream);
-        case 1024: return launch_scores_t<2, 64, 1, 1>(a, 0, stream);
+        case 128: return launch_scores_t<2, 8, 1, 2>(a, part_bytes, stream);
+        case 256: return launch_scores_t<2, 16, 1, 2>(a, part_bytes, stream);
+        case 384: return launch_scores_t<2, 24, 1, 2>(a, part_bytes, stream);
+        case 512: return launch_scores_t<2, 32, 1, 1>(a, part_bytes, stream);
+        case 640: return launch_scores_t<2, 40, 1, 1>(a, part_bytes, stream);
+        case 768: return launch_scores_t<2, 48, 1, 1>(a, part_bytes, stream);
+        case 896: return launch_scores_t<2, 56, 1, 1>(a, part_bytes, stream);
+        case 1024: return launch_scores_t<2, 64, 1, 1>(a, part_bytes, stream);
     }
     return hipErrorInvalidValue;
 }

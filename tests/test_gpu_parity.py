@@ -428,6 +428,32 @@ def test_bf16_kept_scores_match_the_checker_and_the_default_path(H, V):
     np.testing.assert_array_equal(small["loss"], got["loss"])
 
 
+@pytest.mark.parametrize("H,V", [(128, 256), (256, 512), (384, 1024), (512, 768), (640, 2048), (1024, 512)])
+def test_bf16_kept_scores_do_not_depend_on_how_the_vocabulary_is_shared(H, V):
+    # alone: the vocabulary is split over workgroups (V = 256, 768: two, kept scores leave by four blocks); with many copies of it: not;
+    # one sample per group: the first group's launch is split, the others' are not.  The same loss bits and the same kept scores
+    wl = synth.custom_workload("ksplit", B=1, T_max=21, U_max=9, H=H, V=V, dtype="bf16", index=146)
+    one = synth.make_batch(wl)
+    n = 640
+    many = synth.Batch(synth.custom_workload("ksplit", B=n, T_max=21, U_max=9, H=H, V=V, dtype="bf16", index=146),
+                       np.repeat(one.sample_ids, n), np.repeat(one.enc, n, 0), np.repeat(one.pred, n, 0), one.W_out, one.b_out,
+                       np.repeat(one.labels, n, 0), np.repeat(one.T_len, n), np.repeat(one.U_len, n))
+    _say("kept scores, vocabulary split", H, V)
+    alone, ref = run_gpu(one, keep_scores=1), run_oracle(one)
+    assert_parity(alone, ref, "bf16", f"H={H} V={V}")
+    all_ = run_gpu(many, keep_scores=1, sample_weight=np.full(n, 1.0 / n, dtype=np.float32))
+    np.testing.assert_array_equal(all_["loss"], np.repeat(alone["loss"], n))
+    three = synth.Batch(synth.custom_workload("ksplit", B=3, T_max=21, U_max=9, H=H, V=V, dtype="bf16", index=146),
+                        many.sample_ids[:3], many.enc[:3], many.pred[:3], one.W_out, one.b_out, many.labels[:3], many.T_len[:3],
+                        many.U_len[:3])
+    nmin = Bd.rnnt_joint_loss_workspace_bytes(Bd.make_desc(3, 21, 9, H, V, 0, Bd.RNNT_BF16, keep_scores=1), three.T_len, three.U_len, 1)
+    groups = run_gpu(three, budget_bytes=nmin, keep_scores=1)
+    np.testing.assert_array_equal(groups["loss"], np.repeat(alone["loss"], 3))
+    for b in range(3):
+        assert_parity({"loss": groups["loss"][:1], "d_enc": groups["d_enc"][b:b + 1], "d_pred": groups["d_pred"][b:b + 1],
+                       "dW_out": groups["dW_out"] / 3, "db_out": groups["db_out"] / 3}, ref, "bf16", f"group {b}")
+
+
 def test_bf16_kept_scores_with_large_scores_and_weights():
     # scores of several tens: what is kept is the difference to a running maximum, so the size of the
     # scores does not enter the error; weights scale the posteriors in the pass that makes dh
