@@ -510,10 +510,21 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Joint size 640, half tiles per wave (RB = 1) instead of whole ones: twice the workgroups of half the cost each.  A whole tile's workgroup reads half
+// as much from LDS per MFMA, but a small launch of them has to split the vocabulary to fill the chip, and then every part builds the
+// joint rows again, which costs as much as 8 blocks.  A call with V = 1024: one sample of 250 x 50 176 -> 147 us, two of 120 x 24 148 -> 116,
+// eight 195 -> 179, 32 619 -> 567; sixteen, where the rule leaves the whole tiles, 361 -> 362; V = 4096: one sample 319 -> 269 us.
+bool half_tiles_pay(int tiles, int V) {
+    const int nvb = V / SC_VB, n2 = (tiles + 3) / 4, n1 = (tiles + 1) / 2;
+    const long long c2 = 2 * split_cost(n2, vocabulary_split(n2, 256, nvb), 256, nvb, 8);
+    const long long c1 = split_cost(n1, vocabulary_split(n1, 256, nvb), 256, nvb, 8);
+    return c1 * 10 < c2 * 9;
+}
+
 }  // namespace
 
 // Joint sizes up to 512: two workgroups per compute unit (one's joint rows are built beside the other's MFMAs); 640: whole
-// tiles per wave (half the LDS reads per MFMA); above: 32 rows per wave fill the registers.
+// tiles per wave (half the LDS reads per MFMA) where they fill the chip; above: 32 rows per wave fill the registers.
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                            int tile1, void* part, size_t part_bytes, hipStream_t stream) {
     if (tile1 <= tile0) return hipSuccess;
@@ -523,7 +534,9 @@ hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTab
         case 256: return launch_scores_t<0, 16, 1, 2>(a, part_bytes, stream);
         case 384: return launch_scores_t<0, 24, 1, 2>(a, part_bytes, stream);
         case 512: return launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
-        case 640: return launch_scores_t<0, 40, 2, 1>(a, part_bytes, stream);
+        case 640:
+            return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<0, 40, 1, 1>(a, part_bytes, stream)
+                                                       : launch_scores_t<0, 40, 2, 1>(a, part_bytes, stream);
         case 768: return launch_scores_t<0, 48, 1, 1>(a, part_bytes, stream);
         case 896: return launch_scores_t<0, 56, 1, 1>(a, part_bytes, stream);
         case 1024: return launch_scores_t<0, 64, 1, 1>(a, part_bytes, stream);
@@ -540,7 +553,9 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
         case 256: return launch_scores_t<1, 16, 1, 2>(a, 0, stream);
         case 384: return launch_scores_t<1, 24, 1, 2>(a, 0, stream);
         case 512: return launch_scores_t<1, 32, 1, 2>(a, 0, stream);
-        case 640: return launch_scores_t<1, 40, 2, 1>(a, 0, stream);
+        case 640:
+            return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<1, 40, 1, 1>(a, 0, stream)
+                                                       : launch_scores_t<1, 40, 2, 1>(a, 0, stream);
         case 768: return launch_scores_t<1, 48, 1, 1>(a, 0, stream);
         case 896: return launch_scores_t<1, 56, 1, 1>(a, 0, stream);
         case 1024: return launch_scores_t<1, 64, 1, 1>(a, 0, stream);
