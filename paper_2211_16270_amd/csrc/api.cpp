@@ -100,12 +100,12 @@ namespace {
 // Optional per-kernel timing with HIP events on the caller's stream (off by default).
 enum KernelClass { KC_PREPARE = 0, KC_FWD_SCORES, KC_LATTICE, KC_BWD_SCORES, KC_GEMM_DZ, KC_GEMM_DW,
                    KC_FWD_F32, KC_BWD_F32, KC_DW_REDUCE, KC_PROJ, KC_FWD_KEEP, KC_KEPT_TO_DH,
-                   KC_GRADS_TO_BF16, KC_SELECT, KC_COUNT };
+                   KC_GRADS_TO_BF16, KC_SELECT, KC_GEMM_DZ_DW, KC_COUNT };
 const char* const kKernelNames[KC_COUNT] = {"prepare", "joint_scores_fwd", "lattice",
                                             "joint_scores_bwd", "gemm_dz", "gemm_dw_db",
                                             "fwd_f32", "bwd_f32", "dw_reduce", "projections",
                                             "joint_scores_fwd_keep", "kept_scores_to_dh", "input_grads_to_bf16",
-                                            "select_tiles"};
+                                            "select_tiles", "gemm_dz_dw_db"};
 struct Profiler {
     bool enabled = false;
     struct Rec { int cls; hipEvent_t e0, e1; };
@@ -442,13 +442,20 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
                     RNNT_HIP(timed(KC_BWD_SCORES, stream, [&] {
                         return launch_bwd_scores_bf16(pr, wv.wpack, wv.st, ls, c.tile0, c.tile1, wv.dH, wv.Z, at, stream);
                     }));
-                RNNT_HIP(timed(KC_GEMM_DZ, stream, [&] {
-                    return launch_gemm_dz_bf16(pr, wv.wq, wv.st, c.tile0, c.tile1, wv.dH, d_enc, d_pred, at, stream);
-                }));
-                RNNT_HIP(timed(KC_GEMM_DW, stream, [&] {
-                    return launch_gemm_dw_bf16(desc->H, desc->V, rows, plan.dw_splits, dw_first, wv.Z, wv.dH,
-                                               wv.dw_slots, db_out, at, stream);
-                }));
+                if (plan.one_grid)
+                    RNNT_HIP(timed(KC_GEMM_DZ_DW, stream, [&] {
+                        return launch_gemm_dz_dw_bf16(pr, wv.wq, wv.st, c.tile0, c.tile1, wv.Z, wv.dH, d_enc, d_pred, plan.dw_splits,
+                                                      dw_first, wv.dw_slots, db_out, at, stream);
+                    }));
+                else {
+                    RNNT_HIP(timed(KC_GEMM_DZ, stream, [&] {
+                        return launch_gemm_dz_bf16(pr, wv.wq, wv.st, c.tile0, c.tile1, wv.dH, d_enc, d_pred, at, stream);
+                    }));
+                    RNNT_HIP(timed(KC_GEMM_DW, stream, [&] {
+                        return launch_gemm_dw_bf16(desc->H, desc->V, rows, plan.dw_splits, dw_first, wv.Z, wv.dH,
+                                                   wv.dw_slots, db_out, at, stream);
+                    }));
+                }
                 dw_first = 0;
             } else if (plan.f32_gemm) {
                 RNNT_HIP(timed(KC_BWD_F32, stream, [&] {

@@ -116,25 +116,6 @@ struct ActiveTiles {
 constexpr ActiveTiles EVERY_TILE{nullptr, nullptr, 0, 0, -1};
 
 // ---- bf16 MFMA path -------------------------------------------------------------------------
-// How many workgroups share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
-// its share of the blocks and `fixed` blocks' time for its start and end.
-inline long long split_cost(int workgroups, int vs, int slots, int nvb, int fixed) {
-    return ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
-}
-inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
-    int best = 1;
-    long long best_cost = 0;
-    for (int vs = 1; vs <= 4; vs *= 2) {
-        const long long cost = split_cost(workgroups, vs, slots, nvb, fixed);
-        if (vs == 1 || cost * 10 < best_cost * 9) {
-            best = vs;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
-
 // Wpack: W_out^T in fragments [V/32][H/16], Wq: W_out in fragments [V/16][H/32] (launch_prepare).
 // scores on MFMA -> online log-softmax -> lse, lpb, lpy   (tiles [tile0,tile1)).  part: scratch for partial statistics where
 // a small launch splits the vocabulary over workgroups; these count their arrivals in the emission sums of the tiles, which are
@@ -154,6 +135,10 @@ hipError_t launch_kept_to_dh_bf16(const Problem& pr, const SampleTable& st, cons
 // dz = dH W^T, times the tanh derivative, reduced over the tile's u resp. t, added to d_enc, d_pred
 hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
                                float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream);
+// launch_gemm_dz_bf16 and launch_gemm_dw_bf16 in one launch, for plans whose one_grid is set
+hipError_t launch_gemm_dz_dw_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* Z,
+                                  const void* dH, float* d_enc, float* d_pred, int splits, int first, float* slots, float* db,
+                                  const ActiveTiles& at, hipStream_t stream);
 // Shape of a sample's lattice tiles (64 rows each): 8 frames x 8 label positions, or 16 x 4 where that covers the
 // sample's T x (U + 1) lattice with at least 3 % fewer tiles (the padding rows of partly filled tiles cost as
 // much as real ones; a 16 x 4 tile adds to 20 rows of d_enc / d_pred instead of 16, which costs about 2 %).

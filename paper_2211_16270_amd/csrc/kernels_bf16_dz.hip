@@ -15,6 +15,8 @@
 // is linear in dz, so the vocabulary may be split over workgroups (gridDim.y): a launch that leaves the chip partly idle, or its last
 // round partly filled, does that.
 #include "device_common.h"
+#include "gemm_dw_tile.h"
+#include "plan.h"
 
 namespace rnnt {
 
@@ -38,12 +40,14 @@ struct DzArgs {
     float* d_pred;
     int n_tiles;              // hidden tiles, the half one included
     int edge;                 // their width: 256, or 128 (half tiles only)
+    int v_splits;             // parts of the vocabulary
+    int per_part;             // workgroups per part, a multiple of 8
     ActiveTiles at;           // which tiles the chunk's 64-row slots hold (see kernels.h)
 };
 
-// HALF: the last hidden tile, 128 columns
+// HALF: the last hidden tile, 128 columns; vs: part of the vocabulary
 template <bool HALF>
-__device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem, int bx, int n0, int n_slots) {
+__device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem, int bx, int n0, int n_slots, int vs) {
     constexpr int MT = HALF ? 2 : 4;                  // 32-row blocks per wave
     constexpr int DMAS = HALF ? 6 : 8;                // copies per wave and stage
     const int tid = threadIdx.x;
@@ -64,7 +68,7 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const int tile = __builtin_amdgcn_readfirstlane(g.at.active ? g.at.active[g.at.group_tile0 + g.at.cbase + entry] : g.tile0 + entry);
     // (kept scores: wherever the forward pass has put the listed tile)
     const int slot = (g.at.active && g.at.slot_tile0 >= 0) ? tile - g.at.slot_tile0 : entry;
-    const int nsteps = V / ZK / (int)gridDim.y, step0 = (int)blockIdx.y * nsteps;
+    const int nsteps = V / ZK / g.v_splits, step0 = vs * nsteps;
     const unsigned char* As = g.dH + (size_t)(2 * slot) * DB + (size_t)step0 * 2048;
     const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
     const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(n0 / 32 + (HALF ? wv : 2 * wv)) * 1024;
@@ -285,11 +289,13 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     if constexpr (!HALF) tile_epilogue(std::integral_constant<int, 1>{});
 }
 
-__global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
-    extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A, B: 16 fragments each }
+// L: workgroup of the v_splits * per_part
+__device__ __forceinline__ void dz_workgroup(const DzArgs& g, unsigned char* dz_smem, int L) {
     // XCD-aware order (ids that agree modulo 8 share an L2): the hidden tiles of one row tile are
     // neighbours on one XCD, so the rows of dH are fetched from HBM once.
-    const int L = blockIdx.x, xcd = L & 7, q = L >> 3;
+    const int vs = L / g.per_part;
+    L -= vs * g.per_part;
+    const int xcd = L & 7, q = L >> 3;
     const int by = q % g.n_tiles, bx = xcd + 8 * (q / g.n_tiles);
     // slots of the chunk that hold a tile: all of the launch's, or what is left of the group's list
     int n_slots = g.tile1 - g.tile0;
@@ -299,8 +305,30 @@ __global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
     }
     if (bx * 4 >= n_slots) return;          // (uniform per workgroup)
     const int n0 = by * g.edge;
-    if (g.edge < ZT || n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots);
-    else dz_tile<false>(g, dz_smem, bx, n0, n_slots);
+    if (g.edge < ZT || n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots, vs);
+    else dz_tile<false>(g, dz_smem, bx, n0, n_slots, vs);
+}
+
+__global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
+    extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A, B: 16 fragments each }
+    dz_workgroup(g, dz_smem, blockIdx.x);
+}
+
+// Both GEMMs of a chunk: dW's workgroups, then dz's (they share nothing but what they read: dH).  The rule and what it gives: plan.h.
+template <bool BY_TILE>
+__global__ __launch_bounds__(256) void k_gemm_dz_dw(DzArgs z, DwArgs w, int nw) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if ((int)blockIdx.x < nw) dw_workgroup<BY_TILE>(w, smem, blockIdx.x);
+    else dz_workgroup(z, smem, blockIdx.x - nw);
+}
+
+constexpr size_t DZ_SMEM = (size_t)ZST * Z_STAGE;
+
+DzArgs dz_args(const DzForm& f, const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
+               float* d_enc, float* d_pred, const ActiveTiles& at) {
+    const int m_tiles = (tile1 - tile0 + 3) / 4, n_tiles = (pr.H + f.edge - 1) / f.edge;
+    return DzArgs{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, n_tiles, f.edge, f.vs,
+                  (m_tiles + 7) / 8 * 8 * n_tiles, at};
 }
 
 }  // namespace
@@ -310,26 +338,40 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTa
     const int n = tile1 - tile0;
     if (n <= 0) return hipSuccess;
     if (pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
-    const int m_tiles = (n + 3) / 4, m8 = (m_tiles + 7) / 8 * 8, stages = pr.V / ZK;
-    // Whole tiles (the half one counts half), or, in a launch of one round, half tiles alone where they fill the chip better: twice the
-    // workgroups of about half the cost each, so that a small launch need not split the vocabulary, which runs the epilogue and its atomics
-    // once per part (one utterance of 250 x 50, H = 512, V = 1024: a call 175.7 -> 165 us).  Past one
-    // round the half tiles' poorer ratio of LDS reads to MFMAs shows (288 of them, H = 1024, V = 4096, against 144 whole ones: 394 -> 407 us a
-    // call).  About 16 stages' time for start and epilogue.
-    const int whole = (m_tiles * pr.H + ZT - 1) / ZT, halves = m_tiles * (pr.H / 128);
-    const int vs_w = vocabulary_split(whole, 256, stages, 16), vs_h = vocabulary_split(halves, 256, stages, 16);
-    const long long cost_w = 2 * split_cost(whole, vs_w, 256, stages, 16), cost_h = split_cost(halves, vs_h, 256, stages, 16);
-    const int edge = halves <= 256 && cost_h * 10 < cost_w * 9 ? 128 : ZT, vs = edge == ZT ? vs_w : vs_h;
-    const DzArgs g{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, (pr.H + edge - 1) / edge, edge, at};
-    const size_t smem = (size_t)ZST * Z_STAGE;
+    const DzArgs g = dz_args(dz_alone(pr.H, pr.V, n), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at);
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz256),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)DZ_SMEM);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    k_gemm_dz256<<<dim3((unsigned)(m8 * g.n_tiles), (unsigned)vs), dim3(256), smem, stream>>>(g);
+    k_gemm_dz256<<<dim3((unsigned)(g.v_splits * g.per_part)), dim3(256), DZ_SMEM, stream>>>(g);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_dz_dw_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* Z,
+                                  const void* dH, float* d_enc, float* d_pred, int splits, int first, float* slots, float* db,
+                                  const ActiveTiles& at, hipStream_t stream) {
+    const long long rows = (long long)(tile1 - tile0) * JT_ROWS;
+    if (rows <= 0 || splits <= 0 || pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
+    const DzArgs z = dz_args(dz_one_grid(pr.H, pr.V, tile1 - tile0, splits), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at);
+    const DwArgs w = dw_args(pr.H, pr.V, rows, splits, first, Z, dH, slots, db, at);
+    constexpr size_t smem = DZ_SMEM > DW_SMEM ? DZ_SMEM : DW_SMEM;
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz_dw<false>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz_dw<true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    const int nw = dw_grid(pr.H, pr.V, splits);
+    const dim3 grid((unsigned)(nw + z.v_splits * z.per_part));
+    if (at.active && at.slot_tile0 >= 0) k_gemm_dz_dw<true><<<grid, dim3(256), smem, stream>>>(z, w, nw);
+    else k_gemm_dz_dw<false><<<grid, dim3(256), smem, stream>>>(z, w, nw);
     return hipGetLastError();
 }
 

@@ -23,6 +23,7 @@
 // no registers for a second one.  Measured (forward kernel): H = 512, V = 8192, 4 M nodes 53.6 ms (61.4 before), H = 640, V = 4096 7.8 ms
 // (9.5), H = 512, V = 1024, 106 M nodes 98.7 ms (111.8).
 #include "device_common.h"
+#include "plan.h"
 
 namespace rnnt {
 

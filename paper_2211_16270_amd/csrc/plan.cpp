@@ -69,7 +69,6 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     p.off_n_active = take(p.skip_log2 ? B * 4 : 0);
     p.off_wpack = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
     p.off_wq = take(p.bf16 ? (size_t)d.H * d.V * 2 : 0);
-    p.dw_splits = p.bf16 ? dw_split_choice(d.H, d.V, chunk_rows) : 0;
     p.off_dwslots = take(p.bf16 ? dw_slot_bytes(d.H, d.V) : 0);
     size_t lat0 = o;
     // lat_buffers = 2: consecutive groups alternate between two halves of each array, so that one group's
@@ -275,6 +274,10 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
     } else {
         for (int gi = 0; gi < (int)p.groups.size(); ++gi)
             p.chunks.push_back(Chunk{gi, p.groups[gi].tile0, p.groups[gi].tile1});
+    }
+    if (p.bf16) {
+        p.one_grid = p.chunks.size() == 1 && one_grid_shape(d.H, d.V, p.tiles_total);
+        p.dw_splits = p.one_grid ? dw_split_one_grid(d.H, d.V, p.tiles_total) : dw_split_choice(d.H, d.V, chunk_rows);
     }
 }
 

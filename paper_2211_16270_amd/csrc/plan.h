@@ -8,6 +8,8 @@
 // its per-node state (5 floats per lattice node) fits the workspace.  The backward pass walks a
 // group in *chunks* of tiles whose bf16 score-gradient buffers fit the rest of the workspace.
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -60,7 +62,8 @@ struct Plan {
     size_t off_dz32 = 0;                // fp32 GEMM form: dZ [chunk_rows, H]; off_dh, off_z hold S and Z as fp32
     size_t off_stage_enc = 0, off_stage_pred = 0;   // fp32 [stage_samples, T_max, H], [stage_samples, U_max+1, H]
     size_t off_dwslots = 0;             // bf16: per-workgroup partial sums of the dW GEMM
-    int dw_splits = 0;                  // bf16: K splits of the dW GEMM (dw_split_choice)
+    bool one_grid = false;              // bf16: the dz and dW GEMMs run as one grid (one_grid_shape)
+    int dw_splits = 0;                  // bf16: K splits of the dW GEMM (dw_split_choice, dw_split_one_grid)
     size_t lattice_bytes = 0, chunk_bytes = 0, total_bytes = 0;
     size_t min_bytes = 0;               // smallest workable workspace
 };
@@ -76,7 +79,7 @@ inline bool f32_gemm_shape(int H, int V) { return H % 4 == 0 && V % 4 == 0 && H 
 // dW GEMM geometry: 256x256 output tiles (the last hidden one of 128 where H is not a multiple of 256).  Every (split, tile) workgroup
 // owns a 256 KiB slot of partial sums in the workspace.  The slots have room for dw_split_count splits less, for H > 640, a packed
 // copy of W_out: the room of the copy for the dz GEMM, which so takes nothing from what a workspace of a given size can hold.  A call
-// uses dw_split_choice of at most dw_splits_max.
+// uses at most dw_splits_max of them.
 constexpr int DW_TILE = 256;
 inline int dw_tiles(int H, int V) { return ((H + DW_TILE - 1) / DW_TILE) * (V / DW_TILE); }
 inline int dw_split_count(int H, int V) {
@@ -88,6 +91,24 @@ inline size_t dw_slot_bytes(int H, int V) {
 }
 inline int dw_splits_max(int H, int V) {
     return (int)(dw_slot_bytes(H, V) / ((size_t)dw_tiles(H, V) * DW_TILE * DW_TILE * 4));
+}
+
+// How many workgroups share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
+// its share of the blocks and `fixed` blocks' time for its start and end.
+inline long long split_cost(int workgroups, int vs, int slots, int nvb, int fixed) {
+    return ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
+}
+inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
+    int best = 1;
+    long long best_cost = 0;
+    for (int vs = 1; vs <= 4; vs *= 2) {
+        const long long cost = split_cost(workgroups, vs, slots, nvb, fixed);
+        if (vs == 1 || cost * 10 < best_cost * 9) {
+            best = vs;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 // K splits for chunks of `rows` rows: the least of (longest chain of workgroups on one of the 32 compute units of an XCD) x (stages of 32
@@ -106,6 +127,85 @@ inline int dw_split_choice(int H, int V, long long rows) {
         const int rest = h8 > gaps ? (h8 - gaps + 31) / 32 : 0;
         const double rounds = (f8 + 31) / 32 + 0.5 * rest;
         const double cost = rounds * (stages / s + 8.0) + 0.2 * s * nt * (fm + 0.5 * hm);
+        if (s == 1 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// dz GEMM of a chunk of lattice tiles: 4 of them x `edge` hidden columns (256; 128 for the rest, or for all) and one of vs parts of the
+// vocabulary per workgroup.  Alone on the chip: whole tiles (the half one counts half), or, in a launch of one round, half tiles alone where they
+// fill the chip better: twice the workgroups of about half the cost each, so that a small launch need not split the vocabulary, which runs the
+// epilogue and its atomics once per part (one utterance of 250 x 50, H = 512, V = 1024: a call 175.7 -> 165 us).  Past one
+// round the half tiles' poorer ratio of LDS reads to MFMAs shows (288 of them, H = 1024, V = 4096, against 144 whole ones: 394 -> 407 us a
+// call).  About 16 stages' time for start and epilogue.
+struct DzForm {
+    int edge, vs;
+};
+inline DzForm dz_alone(int H, int V, long long tiles) {
+    const int m_tiles = (int)((tiles + 3) / 4), stages = V / 32;
+    const int whole = (m_tiles * H + 255) / 256, halves = m_tiles * (H / 128);
+    const int vs_w = vocabulary_split(whole, 256, stages, 16), vs_h = vocabulary_split(halves, 256, stages, 16);
+    const long long cost_w = 2 * split_cost(whole, vs_w, 256, stages, 16), cost_h = split_cost(halves, vs_h, 256, stages, 16);
+    return halves <= 256 && cost_h * 10 < cost_w * 9 ? DzForm{128, vs_h} : DzForm{256, vs_w};
+}
+
+// The two GEMMs of a call whose backward pass is one chunk run as one grid, dW's workgroups first: there neither fills the chip to the end,
+// and what one leaves idle the other takes (two launches -> one grid, V = 1024, a call: H = 512 one utterance of 20 x 4 80 -> 71 us, of 250 x 50 172 -> 157, of 500 x 100 445 -> 411, 32 samples 1042 -> 1010;
+// H = 256 one of 250 x 50 134 -> 120).  Their forms are those whose last
+// workgroup ends first when each is taken by the first of the 256 compute units that is free (a workgroup fills one).  Costs in stages of a
+// whole dz tile (32 entries, about 0.45 us): dz 16 for start and epilogue, a half tile 0.6 of a whole one (the 144 against 288 above); dW 8
+// for start and end and 1.15 per 32 rows; its slots, written once and read once by the whole chip, a fifth of a stage each.
+// Not in larger calls (one of H = 512, V = 8192 lost 1 %, one of 64 samples of 500 x 100 with kept scores, H = 640, 1.5 %; others gained 0 to
+// 4 %): there the ends matter less than that all workgroups of a chunk read the same rows at a time.
+constexpr long long ONE_GRID_MAX = 4096;      // workgroups
+inline long long dz_workgroups(int H, int V, long long tiles, DzForm f) { return (tiles + 3) / 4 * ((H + f.edge - 1) / f.edge) * f.vs; }
+// (whole hidden tiles and a half one: their mean, with dz's half at 0.9.  With 0.6 the rule takes whole ones at H = 384 where half tiles alone are
+// better, one sample of 400 x 80 313 against 304 us; with 1.0 the reverse at H = 640, 32 samples 1421 against 1386.)
+inline double tile_mean(int H, double half) { return (H / 256 + (H % 256 ? half : 0.0)) / ((H + 255) / 256); }
+inline double dz_cost(int H, int V, DzForm f) { return (16.0 + V / 32 / f.vs) * (f.edge == 128 || H == 128 ? 0.6 : tile_mean(H, 0.9)); }
+inline double dw_cost(int H, long long tiles, int splits) { return (1.15 * tiles * (TILE_ROWS / 32) / splits + 8.0) * tile_mean(H, 0.6); }
+inline bool one_grid_shape(int H, int V, long long tiles) {
+    return dz_workgroups(H, V, tiles, DzForm{256, 1}) + (long long)dw_tiles(H, V) * dw_split_choice(H, V, tiles * TILE_ROWS) <= ONE_GRID_MAX;
+}
+// When the last of n workgroups of cost c ends that follow nw of cost cw.
+inline double one_grid_end(long long nw, double cw, long long n, double c) {
+    const long long full = nw / 256, r = nw % 256;
+    const double ta = full * cw, tb = r ? ta + cw : ta;      // 256 - r units are free from ta on, r from tb on
+    for (double k = std::max(1.0, std::floor((n * c + r * cw) / (256.0 * c)) - 1.0);; k += 1.0) {
+        // in order of time: a unit of the first kind ends its k-th workgroup, then one of the second kind its (in_b + 1)-th
+        const double at_a = ta + k * c, in_b = std::floor(std::max(0.0, at_a - tb) / c), at_b = tb + (in_b + 1.0) * c;
+        if ((256 - r) * (long long)k + r * (long long)in_b >= n) return std::max(at_a, tb);
+        if (at_b < at_a + c && (256 - r) * (long long)k + r * (long long)(in_b + 1.0) >= n) return at_b;
+    }
+}
+inline double dz_dw_end(int H, int V, long long tiles, int splits, DzForm f) {
+    return one_grid_end((long long)dw_tiles(H, V) * splits, dw_cost(H, tiles, splits), dz_workgroups(H, V, tiles, f), dz_cost(H, V, f));
+}
+// (a split of the vocabulary repeats epilogue and atomics: only where it saves a tenth)
+inline DzForm dz_one_grid(int H, int V, long long tiles, int splits) {
+    DzForm best{256, 1};
+    double best_end = dz_dw_end(H, V, tiles, splits, best);
+    for (int vs = 1; vs <= 4; vs *= 2)
+        for (int edge = 256; edge >= 128; edge -= 128) {
+            const DzForm f{edge, vs};
+            if (vs > 1 && dz_workgroups(H, V, tiles, f) > 1024) continue;
+            const double end = dz_dw_end(H, V, tiles, splits, f);
+            if (end < (vs > best.vs ? 0.9 : 1.0) * best_end) {
+                best = f;
+                best_end = end;
+            }
+        }
+    return best;
+}
+inline int dw_split_one_grid(int H, int V, long long tiles) {
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1, most = dw_splits_max(H, V); s <= most; s += s < 4 ? 1 : s / 4) {
+        const double slots = 0.2 * s * (V / DW_TILE) * (H / DW_TILE + (H % DW_TILE ? 0.5 : 0.0));
+        const double cost = dz_dw_end(H, V, tiles, s, dz_one_grid(H, V, tiles, s)) + slots;
         if (s == 1 || cost < best_cost) {
             best = s;
             best_cost = cost;

@@ -830,3 +830,22 @@ def test_bf16_masked_vocabulary_entries(H, V, mask):
             assert Bd.rnnt_joint_loss_fwd(desc, dev["enc"], dev["pred"], dev["W_out"], dev["b_out"], dev["labels"], x.T_len, x.U_len,
                                           loss, ws.buf) == 0
             assert rel_loss_err(loss.cpu().numpy().astype(np.float64), np.repeat(ref["loss"], x.B)) <= TOL["bf16"]["loss"]
+
+
+@pytest.mark.parametrize("H,V,keep", [(128, 256, 0), (128, 1024, 1), (256, 512, 0), (384, 1024, 0), (384, 256, 1), (512, 256, 0),
+                                      (512, 1024, 1), (640, 512, 0), (768, 256, 1), (896, 512, 0), (1024, 256, 0), (1024, 1024, 1)])
+def test_bf16_both_backward_gemms_in_one_grid(H, V, keep):
+    # a call of one chunk: dz and dW as one grid, with whole and half tiles, the vocabulary in 1, 2 or 4 parts and few or many splits by
+    # size; in the smallest workspace the same call runs them as two launches per chunk
+    for B, T, U in ((1, 9, 3), (2, 40, 9), (3, 100, 23), (4, 200, 31))[:4 if H * V <= 1 << 18 else 3]:
+        wl = synth.custom_workload("onegrid", B=B, T_max=T, U_max=U, H=H, V=V, dtype="bf16", index=147, t_rule="uniform", t_lo=T // 2,
+                                   u_rule="uniform", u_lo=U // 2)
+        batch = synth.make_batch(wl)
+        _say("one grid", H, V, keep, B, T, U)
+        ref, got = run_oracle(batch), run_gpu(batch, keep_scores=keep)
+        assert_parity(got, ref, "bf16", f"{B} x {T} x {U}")
+        assert_padding_zero(got, batch)
+        nmin = Bd.rnnt_joint_loss_workspace_bytes(got["desc"], batch.T_len, batch.U_len, 1)
+        two = run_gpu(batch, keep_scores=keep, budget_bytes=nmin)
+        assert_parity(two, ref, "bf16", f"{B} x {T} x {U}, smallest workspace")
+        np.testing.assert_array_equal(two["loss"], got["loss"])

@@ -435,3 +435,40 @@ def test_long_samples_that_just_fit_the_static_workspace():
         desc = Bd.make_desc(1, T, U, H, V, 0, Bd.RNNT_BF16)
         st, _, _ = Bd.rnnt_joint_loss_plan(desc, np.array([T], np.int32), np.array([U], np.int32), 128 << 20)
         assert st == 0, (H, V, T)
+
+
+def test_end_of_one_grid_of_two_kinds_of_workgroups_against_a_schedule(tmp_path):
+    # the closed form that chooses the splits of the two backward GEMMs, against placing every workgroup on the first free unit
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "end.cpp"
+    src.write_text('#include "%s"\n' % os.path.join(ROOT, "paper_2211_16270_amd", "csrc", "plan.h") + """
+#include <cstdio>
+#include <functional>
+#include <queue>
+#include <random>
+int main() {
+    std::mt19937 g(7);
+    int bad = 0;
+    for (int i = 0; i < 4000; ++i) {
+        const long long nw = 1 + g() % 700, n = 1 + g() % 1500;
+        const double cw = 1 + g() % 60 + 0.25 * (g() % 4), c = 1 + g() % 60 + 0.5 * (g() % 2);
+        std::priority_queue<double, std::vector<double>, std::greater<double>> unit;
+        for (int u = 0; u < 256; ++u) unit.push(0.0);
+        double end = 0.0;
+        for (long long j = 0; j < nw + n; ++j) {
+            const double t = unit.top() + (j < nw ? cw : c);
+            unit.pop();
+            unit.push(t);
+            end = std::max(end, t);
+        }
+        if (std::abs(end - rnnt::one_grid_end(nw, cw, n, c)) > 1e-6) ++bad;
+    }
+    std::printf("%d\\n", bad);
+}
+""")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-o", str(tmp_path / "end"), str(src)], check=True)
+    assert subprocess.run([str(tmp_path / "end")], check=True, capture_output=True, text=True).stdout.strip() == "0"
