@@ -15,7 +15,7 @@ backward kernel computes a second time count as executed work only) divided by i
 measured with HIP events recorded on the call's stream in a second pass over the same K steps (the events
 are kept out of the pass that yields `value`); `exec_flops_per_launch` / `frac_exec` count what the kernel
 really multiplies.  `roofline.traffic` is read from the committed rocprofv3 counter summary of this workload
-under profiles/ (it is not measured in this run).  `cpu_baseline` is the float64 checker timed on the host
+under profiles/ (it is not measured in this run; the summaries are taken again when a kernel's traffic changes).  `cpu_baseline` is the float64 checker timed on the host
 cores on a few samples of the same workload.
 """
 import argparse
@@ -344,12 +344,12 @@ def main():
     # executed: what the kernel multiplies, i.e. also the scores a backward kernel computes a second time.
     alg_flops_per_step = {"joint_scores_fwd": 2.0 * R * HV, "joint_scores_bwd": 0.0,
                           "joint_scores_fwd_keep": 2.0 * R * HV,
-                          "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV,
+                          "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV, "gemm_dz_dw_db": 4.0 * R * HV,
                           "fwd_f32": 2.0 * R * HV, "bwd_f32": 4.0 * R * HV}
     exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=6.0 * R * HV)
     if bwd_share < 1.0:
         # tiles of negligible posterior are left out: both counts cover only the rows the kernels worked on
-        for name in ("joint_scores_bwd", "gemm_dz", "gemm_dw_db"):
+        for name in ("joint_scores_bwd", "gemm_dz", "gemm_dw_db", "gemm_dz_dw_db"):
             alg_flops_per_step[name] *= bwd_share
             exec_flops_per_step[name] *= bwd_share
     kernels = {}

@@ -37,10 +37,8 @@ struct TilePos {
     int s, T, U, t0, u0, uw, us;
 };
 
-__device__ __forceinline__ TilePos locate_tile(const SampleTable& st, int s0, int s1, int tile) {
+__device__ __forceinline__ TilePos locate_tile(const SampleTable& st, int tile) {
     TilePos p;
-    (void)s0;
-    (void)s1;
     p.s = st.tile_sample[tile];
     p.T = st.T[p.s];
     p.U = st.U[p.s];
@@ -60,16 +58,12 @@ __device__ __forceinline__ float fast_tanh(float x) {
     return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-// Eight joint activations z = tanh(e + q), rounded to bf16; keep = 0 gives zeros, keep = ~0u the values
-// (branch-free: a branch per element would cost more than the arithmetic).
-__device__ __forceinline__ bf16x8 joint_tanh8(bf16x8 e, bf16x8 q, unsigned keep) {
-    typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+// Eight joint activations z = tanh(e + q), rounded to bf16.
+__device__ __forceinline__ bf16x8 joint_tanh8(bf16x8 e, bf16x8 q) {
     bf16x8 z;
 #pragma unroll
     for (int j = 0; j < 8; ++j) z[j] = (bf16_t)fast_tanh((float)e[j] + (float)q[j]);
-    u32x4_t w = __builtin_bit_cast(u32x4_t, z);
-    w &= keep;
-    return __builtin_bit_cast(bf16x8, w);
+    return z;
 }
 
 // ln(e^a + e^b); either may be -inf.
@@ -280,7 +274,7 @@ __device__ __forceinline__ void build_joint_rows(u32x4 (&z)[KK], const JointInpu
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
             z[kk] = __builtin_bit_cast(u32x4, joint_tanh8(*reinterpret_cast<const bf16x8*>(er + kk * 16),
-                                                          *reinterpret_cast<const bf16x8*>(qr + kk * 16), ~0u));
+                                                          *reinterpret_cast<const bf16x8*>(qr + kk * 16)));
             if (FIRST + kk < AGPR_FRAGS) asm volatile("" : "+a"(z[kk]));
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -12,10 +12,9 @@ constexpr int JT_ROWS = 64;       // rows of a lattice tile
 // dW += Z^T dH and db += column sums of dH (Alg. 1 line 8) as one split-K GEMM with 256x256 tiles.
 // 256 threads = 4 waves in 2 (hidden) x 2 (vocabulary), one per SIMD; each wave owns 128 x 128 = 4 x 4
 // accumulator tiles (256 accumulator registers), so that a k16-step reads 8 fragments from LDS for 16
-// MFMAs and every byte of a stage feeds 128 flops.  Both operands are row-major with the contraction index (the
-// chunk's rows) as the slow one:
-// Z [rows,H], dH [rows,V], in 1 KiB fragments of 32 rows x 16 columns (device_common.h), so the 256 columns of a tile are 16 KiB
-// in one piece.  Stages of 32 rows travel global -> LDS asynchronously (global_load_lds, no registers), five stages deep, and lie
+// MFMAs and every byte of a stage feeds 128 flops.  Both operands, Z [rows,H] and dH [rows,V], lie in 1 KiB fragments of
+// 32 rows x 16 columns (device_common.h), eight columns of a row together, so the 256 columns of a tile are 16 KiB in one piece, and the
+// contraction index (the chunk's rows) is the slow one inside a fragment.  Stages of 32 rows travel global -> LDS asynchronously (global_load_lds, no registers), five stages deep, and lie
 // in LDS as in memory; MFMA fragments, which need 8 consecutive rows of one column per lane,
 // come from the transposing LDS read (ds_read_b64_tr_b16): within 16 lanes, lane 4j+c supplies 4
 // columns of row j and lane i receives rows 0..3 of column i.  The fragments' row order puts the 16 rows a 32-lane read touches

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void k_kept_to_dh(KeptArgs a) {
         tile = a.at.active[a.at.group_tile0 + ci];
     }
     const int slot = tile - a.tile0;
-    const TilePos tp = locate_tile(a.st, 0, 0, tile);
+    const TilePos tp = locate_tile(a.st, tile);
     const int r = 32 * half + l32, t = tp.t0 + (r >> tp.us), u = tp.u0 + (r & (tp.uw - 1)), b = tp.s;
     const int lab = (t < tp.T && u < tp.U) ? a.pr.labels[(size_t)b * a.pr.U_max + u] : -1;
     float g = RNNT_NEG_INF, vB = 0.0f, vY = 0.0f;

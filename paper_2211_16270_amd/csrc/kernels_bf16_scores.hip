@@ -13,10 +13,12 @@
 // The scores are computed transposed (A = 32 vocabulary entries of W_out^T, B = 32 rows), so a lane owns one row (with its
 // partner lane in the other half) and the softmax reductions over the vocabulary stay in registers.
 //
-// What bounds it: the power limit.  On random bf16 values a loop of MFMAs alone runs at 1.8 PFLOP/s, with one 1 KiB
-// fragment read from LDS per MFMA at 1.6, with two vector and one exponential instruction per MFMA besides at 1.45.  A design in
-// which every compute unit pulls a fragment from the L2 for every two MFMAs (64-row tiles, joint tile in LDS) reached 1.0-1.1;
-// here the 128 or 256 rows of a workgroup share every fragment: W_out^T goes L2 -> LDS once per workgroup (asynchronous
+// What bounds it: the power limit in the forward pass.  On random bf16 values a loop of MFMAs alone runs at 1.8 PFLOP/s, with one 1 KiB
+// fragment read from LDS per MFMA at 1.6, with two vector and one exponential instruction per MFMA besides at 1.45; at H = 512, V = 1024,
+// 106 M nodes the forward kernel runs at 1.55 GHz with the matrix pipes busy 64 % of the time (1.1 PFLOP/s).  The backward form (MODE 1) keeps
+// 2.0 GHz with the pipes busy 45 % (0.9 PFLOP/s) and waits more (41 % of the wave cycles against 32): it stores 2 bytes per score beside.
+// A design in which every compute unit pulls a fragment from the L2 for every two MFMAs (64-row tiles, joint tile in LDS) reached
+// 1.0-1.1; here the 128 or 256 rows of a workgroup share every fragment: W_out^T goes L2 -> LDS once per workgroup (asynchronous
 // copies, a ring of stages).  The row statistics of the previous block are computed in the shadow of the current
 // block's MFMAs (an MFMA holds the matrix pipe for 32 clocks and the issue port for 4; up to about 4 vector or 2
 // transcendental instructions behind each one cost nothing), so one wave per SIMD is enough where the joint rows leave
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     const int tslot = __builtin_amdgcn_readfirstlane(present ? ti : n_tiles - 1);     // the tile's 64-row slot in the chunk buffers
     const int tile = __builtin_amdgcn_readfirstlane(
         (MODE == 1 && a.at.active) ? a.at.active[a.at.group_tile0 + a.at.cbase + tslot] : a.tile0 + tslot);
-    const TilePos tp = locate_tile(a.st, 0, 0, tile);
+    const TilePos tp = locate_tile(a.st, tile);
     const int b = tp.s;
     // rows of this wave in its tile: 32 (half0 + rb) + l32
     const int half0 = RB == 2 ? 0 : wave & 1;

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void k_tile_flags(SelectArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tile = a.tile0 + (int)blockIdx.x * 4 + wave;
     if (tile >= a.tile1) return;
-    const TilePos tp = locate_tile(a.st, a.s0, a.s1, tile);
+    const TilePos tp = locate_tile(a.st, tile);
     const int t = tp.t0 + (lane >> tp.us), u = tp.u0 + (lane & (tp.uw - 1));
     float lg = RNNT_NEG_INF;
     if (t < tp.T && u <= tp.U) {

@@ -45,11 +45,6 @@ rnnt_status check_lengths(const rnnt_desc* d, const int32_t* T_len, const int32_
 
 namespace {
 
-struct Sizes {
-    size_t fixed;          // tables + packed W
-    size_t chunk_row_bytes;
-};
-
 // Fills every offset for the given capacities and returns the total size.
 size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_rows, long long stage_samples) {
     const size_t B = (size_t)d.B;
@@ -251,9 +246,10 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
             long long nch = (n + cap_tiles - 1) / cap_tiles;
             long long per = (n + nch - 1) / nch;
             per = std::min(cap_tiles, (per + 1) / 2 * 2);
-            // chunks of whole rounds of 256 tiles leave no partly filled last round in the dz GEMM (B=64, T<=500, U<=100, H=1024,
-            // V=4096: 5 rounds instead of 5.3 per chunk, -12 %); the kernels that cover two or four tiles per workgroup split the vocabulary
-            // where that fills their rounds better (vocabulary_split)
+            // chunks of whole multiples of 256 tiles: the dz GEMM takes 4 tiles x 256 hidden columns per workgroup, so 256 tiles are
+            // one round of the chip at H = 1024, and half a one at H = 512 (B=64, T<=500, U<=100, H=1024, V=4096: 5 rounds instead of
+            // 5.3 per chunk, -12 %, measured when dz took a tile per workgroup); the other kernels take two or four tiles
+            // per workgroup and split the vocabulary where that fills their rounds better (vocabulary_split)
             if (cap_tiles >= 1024 && n > cap_tiles) per = cap_tiles / 256 * 256;
             for (long long t = g.tile0; t < g.tile1; t += per) {
                 Chunk c{gi, (int)t, (int)std::min<long long>(g.tile1, t + per)};

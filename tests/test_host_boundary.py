@@ -472,3 +472,14 @@ int main() {
 """)
     subprocess.run([gxx, "-O1", "-std=c++17", "-o", str(tmp_path / "end"), str(src)], check=True)
     assert subprocess.run([str(tmp_path / "end")], check=True, capture_output=True, text=True).stdout.strip() == "0"
+
+
+def test_counter_summaries_name_kernels_the_library_has():
+    # bench.py looks bytes per launch up by kernel name: a summary may not outlive the kernels it was taken with
+    import glob
+    have = {Bd.rnnt_profile_kernel_name(i) for i in range(Bd.rnnt_profile_kernel_count())}
+    files = glob.glob(os.path.join(ROOT, "profiles", "hbm_traffic_*.txt"))
+    assert files
+    for f in files:
+        names = {line.split()[0] for line in open(f) if line.strip() and not line.startswith("#")}
+        assert names and names <= have, (os.path.basename(f), names - have)
