@@ -168,6 +168,13 @@ __device__ __forceinline__ void lds_dma16_imm(const void* sbase, unsigned voff, 
                  "n"(OFF)
                  : "memory", "m0");
 }
+// Two of them, OFF and OFF + 1024, for one write of M0.
+template <int OFF>
+__device__ __forceinline__ void lds_dma16_pair(const void* sbase, unsigned voff, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:%4" ::"v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF), "n"(OFF + 1024)
+                 : "memory", "m0");
+}
 // 4 bytes per lane: word at sbase + voff of lane l -> lds_base + 4 l (64 words; lanes with equal voff write equal words)
 __device__ __forceinline__ void lds_dma4_s(const void* sbase, unsigned voff, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)

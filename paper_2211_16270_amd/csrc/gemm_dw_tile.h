@@ -103,11 +103,11 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
         if (!BY_TILE) return gstep;
         return ((long long)(entry - g.at.slot_tile0) << 1) + (((ks + gstep * WK) >> 5) & 1) - ks / WK;
     };
-    // DMA j (0 .. DMAS - 1) of the stage whose rows are block blk, into LDS buffer buf
-    auto issue_one = [&](long long blk, unsigned buf, auto j_tag) {
+    // Copies 2 j, 2 j + 1 of the stage whose rows are block blk, into LDS buffer buf (in pairs: M0 and its wait state once)
+    auto issue_pair = [&](long long blk, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
-        if constexpr (j < 4) lds_dma16_imm<j * 1024>(Ds + blk * (long long)DB, lane_b, dst_b + buf * STAGE_BYTES);
-        else lds_dma16_imm<(j - 4) * 1024>(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
+        if constexpr (j < 2) lds_dma16_pair<j * 2048>(Ds + blk * (long long)DB, lane_b, dst_b + buf * STAGE_BYTES);
+        else lds_dma16_pair<(j - 2) * 2048>(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
     };
     // fragment addresses: lane = 16 g + 4 j + c supplies row 8*(g/2) + j, columns 16*(g%2) + 4c .. +3 of a 32-column tile: granule
     // (row, c/2) of fragment 2 * tile + g % 2, at position 32 (c/2) + (row ^ 4 (2 (g % 2) + c/2))
@@ -142,7 +142,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
     // following k16-step is read into the other set.  An MFMA keeps the matrix pipe busy for 32 clocks but
     // the issue port only briefly: the reads go out in its shadow, and the last of them is 8 MFMAs (HALF: 2) old when
     // the step ends.
-    // Behind each of the last DMAS of a stage's second step goes one DMA of a later stage.
+    // Behind every second of the last DMAS of a stage's second step go two copies of a later stage.
     auto multiply = [&](auto set_tag, unsigned next_buf, int next_kk, long long dma_block, unsigned dma_buf) {
         constexpr int set = decltype(set_tag)::value;
         const unsigned char* st = dw_smem + next_buf * STAGE_BYTES + next_kk * 256;
@@ -152,8 +152,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
             if constexpr (idx < MT) fa[set ^ 1][idx] = lds_read_tr_frag(st + a_lo + idx * 2048, st + a_hi + idx * 2048);
             else if constexpr (idx < MT + 4)
                 fb[set ^ 1][idx - MT] = lds_read_tr_frag(st + b_lo + (idx - MT) * 2048, st + b_hi + (idx - MT) * 2048);
-            if constexpr (set == 1 && idx >= 4 * MT - DMAS)
-                issue_one(dma_block, dma_buf, std::integral_constant<int, idx - (4 * MT - DMAS)>{});
+            if constexpr (set == 1 && idx >= 4 * MT - DMAS && (idx - (4 * MT - DMAS)) % 2 == 0)
+                issue_pair(dma_block, dma_buf, std::integral_constant<int, (idx - (4 * MT - DMAS)) / 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
         if (do_db) {
@@ -178,7 +178,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
         for (int s4 = 0; s4 < WST - 1; ++s4) {
             const long long gs = s4 < last ? s4 : last;
             const long long blk = stage_block(gs, stage_entry(gs));
-            static_for<0, DMAS>([&](auto j) { issue_one(blk, (unsigned)s4, j); });
+            static_for<0, DMAS / 2>([&](auto j) { issue_pair(blk, (unsigned)s4, j); });
         }
         int entry_ahead = stage_entry(4 < last ? 4 : last);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * DMAS) : "memory");

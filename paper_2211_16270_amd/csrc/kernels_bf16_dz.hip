@@ -59,7 +59,7 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dz_smem;
 
     // global -> LDS: a stage is, per operand, blocks of 32 rows (lattice rows / hidden columns) x 2 fragments of 16 entries.
-    // LDS order: A [entry half][8 row blocks], B [entry half][8 hidden blocks].  Wave w moves the row blocks of lattice tile w and hidden
+    // LDS order: A [8 row blocks][entry half], B [entry half][8 hidden blocks].  Wave w moves the row blocks of lattice tile w and hidden
     // blocks 2 w, 2 w + 1 (HALF: w).  Everything but the lane's 16 bytes is wave-uniform.  Slots past the list's end read the last
     // listed tile again; their products are never stored.
     const size_t DB = chunk_block_bytes(V);   // bytes of a block of 32 rows of dH
@@ -73,25 +73,25 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const unsigned char* As = g.dH + (size_t)(2 * slot) * DB + (size_t)step0 * 2048;
     const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
     const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(n0 / 32 + (HALF ? wv : 2 * wv)) * 1024;
-    // DMA j of stage gstep into LDS buffer buf
-    auto issue_one = [&](int gstep, unsigned buf, auto j_tag) {
+    // The copies of stage gstep into LDS buffer buf: both entry halves of row block j (0, 1), then of entry half j - 2 (2, 3) the hidden blocks.
+    // (In pairs: M0 and its wait state once.)
+    auto issue = [&](int gstep, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
         const unsigned sb = smem_base + buf * Z_STAGE;
-        if constexpr (j < 4) {
-            constexpr int rb = j & 1, eh = j >> 1;    // row block of the tile, entry half
-            lds_dma16_s(As + rb * DB + (size_t)gstep * 2048 + eh * 1024, lane_b, sb + (unsigned)(eh * 8 + 2 * wv + rb) * 1024u);
+        if constexpr (j < 2) {
+            lds_dma16_pair<0>(As + j * DB + (size_t)gstep * 2048, lane_b, sb + (unsigned)(2 * wv + j) * 2048u);
         } else if constexpr (HALF) {
-            constexpr int eh = j - 4;
+            constexpr int eh = j - 2;
             lds_dma16_s(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + wv) * 1024u);
         } else {
-            constexpr int hbk = j & 1, eh = (j - 4) >> 1;
-            lds_dma16_imm<hbk * 1024>(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + 2 * wv) * 1024u);
+            constexpr int eh = j - 2;
+            lds_dma16_pair<0>(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + 2 * wv) * 1024u);
         }
     };
     const int last = nsteps - 1;
 #pragma unroll
     for (int s4 = 0; s4 < ZST - 1; ++s4)
-        static_for<0, DMAS>([&](auto j) { issue_one(s4 < last ? s4 : last, (unsigned)s4, j); });
+        static_for<0, 4>([&](auto j) { issue(s4 < last ? s4 : last, (unsigned)s4, j); });
 
     // the epilogue's input rows, this wave's lattice tile: lane = 8 columns of rows (lane / 32) + 2 i (zero outside the sample)
     const TilePos tp = locate_tile(g.st, tile);
@@ -116,13 +116,13 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
     bf16x8 fa[2][MT], fb[2][4];
     auto frag_a = [&](unsigned buf, int kk, int mt) {
-        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + kk * 8192 + (wm * MT + mt) * 1024 + a_off[kk]);
+        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + (wm * MT + mt) * 2048 + kk * 1024 + a_off[kk]);
     };
     auto frag_b = [&](unsigned buf, int kk, int nt) {
         return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + Z_OPER + kk * 8192 + (wn * 4 + nt) * 1024 + lane_b);
     };
     // The MFMAs of one k16-step (register set `set`).  Behind each of the first ones, one fragment of the following k16-step is
-    // read into the other set; behind the others of the second step goes one DMA of a later stage each.  An MFMA keeps the matrix pipe
+    // read into the other set; behind every second of the others of the second step go the copies of a later stage.  An MFMA keeps the matrix pipe
     // busy for 32 clocks but the issue port only briefly: with one wave per SIMD nothing else would hide these instructions.
     auto multiply = [&](auto set_tag, unsigned next_buf, auto next_kk_tag, int dma_g, unsigned dma_buf) {
         constexpr int set = decltype(set_tag)::value, next_kk = decltype(next_kk_tag)::value;
@@ -131,8 +131,8 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
             if constexpr (idx < MT) fa[set ^ 1][idx] = frag_a(next_buf, next_kk, idx);
             else if constexpr (idx < MT + 4) fb[set ^ 1][idx - MT] = frag_b(next_buf, next_kk, idx - MT);
-            if constexpr (set == 1 && idx >= 4 * MT - DMAS)
-                issue_one(dma_g, dma_buf, std::integral_constant<int, idx - (4 * MT - DMAS)>{});
+            if constexpr (set == 1 && idx >= 4 * MT - 8 && idx % 2 == 0)
+                issue(dma_g, dma_buf, std::integral_constant<int, (idx - (4 * MT - 8)) / 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };

@@ -77,6 +77,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     constexpr int TW = 2 * RB;                        // lattice tiles per workgroup
     constexpr int NACC = MODE == 2 ? 4 : 2;           // score blocks alive: running, previous (MODE 2: two more until their pair is stored)
     static_assert(KK % RG == 0 && KK % SF == 0 && SF % 4 == 0 && SF >= RG && NST >= 4, "ring geometry");
+    static_assert(6 * ((PER + 1) / 2 - 1) < SF, "a stage's copies go out before the next hand-over");
     static_assert((NST - 1) * SB >= 4 * JR_SCRATCH, "the build scratch lies in the later stages");
     const int H = KK * 16, V = a.pr.V;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
@@ -98,18 +99,24 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     const unsigned lane_b = (unsigned)lane * 16u;
     // stage content q (fragments [q SF, q SF + SF) of W_out^T) -> ring slot: PER copies of 1 KiB by this wave, and the
     // 32 biases of its block (by every wave, the same values).  Four copies share one base pair (their immediate offset
-    // moves both addresses).
+    // moves both addresses).  They go out in pairs: next to the MFMAs of one wave per SIMD every issue slot counts, and a pair pays for
+    // M0 and its wait state once (against single copies in this kernel and the two GEMMs: kept scores at H = 1024, V = 4096 11.47 -> 11.39 ms a call, H = 512, V = 8192
+    // 22.27 -> 22.11).
     const int nq = nvb * SPB;
+    constexpr int NI = (PER + 1) / 2;                 // pairs (or a last single one) per stage; issue NI: the biases
     auto issue_one = [&](int q, int slot, auto i_tag) {
         constexpr int i = decltype(i_tag)::value;
         q = q < nq ? q : nq - 1;                      // (past the end: a slot nobody reads any more)
-        if constexpr (i < PER)
-            lds_dma16_imm<(i & 3) * 1024>(wpb + (size_t)q * SB + (i >> 2) * 4096, lane_b,
-                                          smem_base + (unsigned)slot * SB + (unsigned)(wave * PER * 1024 + (i >> 2) * 4096));
-        else
+        if constexpr (i < NI) {
+            constexpr int c = 2 * i;
+            const void* src = wpb + (size_t)q * SB + (c >> 2) * 4096;
+            const unsigned dst = smem_base + (unsigned)slot * SB + (unsigned)(wave * PER * 1024 + (c >> 2) * 4096);
+            if constexpr (c + 1 < PER) lds_dma16_pair<(c & 3) * 1024>(src, lane_b, dst);
+            else lds_dma16_imm<(c & 3) * 1024>(src, lane_b, dst);
+        } else
             lds_dma4_s(bias_g + (q / SPB) * SC_VB, (unsigned)l32 * 4u, smem_base + NST * SB + (unsigned)slot * 256u);
     };
-    auto issue = [&](int q, int slot) { static_for<0, PER + 1>([&](auto i) { issue_one(q, slot, i); }); };
+    auto issue = [&](int q, int slot) { static_for<0, NI + 1>([&](auto i) { issue_one(q, slot, i); }); };
     issue(0, 0);
 
     const int ti = (int)blockIdx.x * TW + (RB == 2 ? wave : wave >> 1);
@@ -305,7 +312,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     };
 
     // One block: KK steps of RB MFMAs; behind them the LDS read of the fragment RG steps ahead, a piece of work on the
-    // previous block and, every third step, a copy into a slot that has been left.  RG steps before the end of a stage
+    // previous block and, every sixth step, a pair of copies into a slot that has been left.  RG steps before the end of a stage
     // its last fragment read is on its way; there the next stage is waited for (own copies, then everyone's; the stores of MODE 1 and 2
     // count in the same order, so the wait may cover a few of them).  Every wave has then consumed its fragments of the stage before,
     // whose slot may be refilled (refilling the slot just read would need a wait for the reads just sent).
@@ -344,9 +351,9 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
             // refill of the slot before the one left last (q counts the stage being read): content q - 2 + NST, spread over the SF
             // steps up to the next hand-over
             constexpr int p = (kk + RG) % SF;
-            if constexpr (p % 3 == 0 && p / 3 <= PER) {
+            if constexpr ((p % 6 == 0 && p / 6 < NI) || p == 3) {
                 if (with_prev || k >= 2 * SF - RG)
-                    issue_one(q - 2 + NST, slot < 2 ? slot + NST - 2 : slot - 2, std::integral_constant<int, p / 3>{});
+                    issue_one(q - 2 + NST, slot < 2 ? slot + NST - 2 : slot - 2, std::integral_constant<int, p == 3 ? NI : p / 6>{});
             }
             __builtin_amdgcn_sched_barrier(0);
             if (with_prev) {

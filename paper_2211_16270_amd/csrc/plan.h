@@ -153,11 +153,12 @@ inline DzForm dz_alone(int H, int V, long long tiles) {
 }
 
 // The two GEMMs of a call whose backward pass is one chunk run as one grid, dW's workgroups first: there neither fills the chip to the end,
-// and what one leaves idle the other takes (two launches -> one grid, V = 1024, a call: H = 512 one utterance of 20 x 4 80 -> 71 us, of 250 x 50 172 -> 157, of 500 x 100 445 -> 411, 32 samples 1042 -> 1010;
-// H = 256 one of 250 x 50 134 -> 120).  Their forms are those whose last
-// workgroup ends first when each is taken by the first of the 256 compute units that is free (a workgroup fills one).  Costs in stages of a
-// whole dz tile (32 entries, about 0.45 us): dz 16 for start and epilogue, a half tile 0.6 of a whole one (the 144 against 288 above); dW 8
-// for start and end and 1.15 per 32 rows; its slots, written once and read once by the whole chip, a fifth of a stage each.
+// and what one leaves idle the other takes.  Two launches -> one grid, V = 1024, a call: H = 512 one utterance of 20 x 4 80 -> 71 us, of 250 x 50
+// 172 -> 157, of 500 x 100 445 -> 411, 32 samples 1042 -> 1010; H = 256 one of 250 x 50 134 -> 120.
+// Their forms are those whose last workgroup ends first when each is taken by the first of the 256 compute units that is free (a
+// workgroup fills one).  Costs in stages of a whole dz tile (32 entries, about 0.45 us): dz 16 for start and epilogue, a half tile 0.6 of a
+// whole one (the 144 against 288 above); dW 8 for start and end and 1.15 per 32 rows; its slots, written once and read once by the whole
+// chip, a fifth of a stage each.
 // Not in larger calls (one of H = 512, V = 8192 lost 1 %, one of 64 samples of 500 x 100 with kept scores, H = 640, 1.5 %; others gained 0 to
 // 4 %): there the ends matter less than that all workgroups of a chunk read the same rows at a time.
 constexpr long long ONE_GRID_MAX = 4096;      // workgroups
