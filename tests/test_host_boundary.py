@@ -150,7 +150,8 @@ def test_default_plan_properties(name):
 
 
 def test_backward_chunks_are_whole_rounds_of_256_tiles_when_a_group_needs_several():
-    # one workgroup per tile and 256 compute units: a chunk of a multiple of 256 tiles has no partly filled last round
+    # four tiles x 256 hidden columns per workgroup of the dz GEMM and 256 compute units: at H = 1024 a multiple of 256 tiles leaves no
+    # partly filled last round
     for name in ("C3", "C4"):
         wl, desc, T, U = _lens(name)
         st, info, groups = Bd.rnnt_joint_loss_plan(desc, T, U, 0)
