@@ -32,6 +32,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_FLOPS = 2.5e15     # MI355X dense bf16 MFMA
 PEAK_F32_FLOPS = 157.3e12    # MI355X fp32, vector and MFMA alike
+PEAK_F32_GEMM_FLOPS = PEAK_BF16_FLOPS / 6    # fp32 products out of six bf16 ones
 CPU_SAMPLE = {"C1": 2, "C2": 32, "C3": 12, "C4": 12, "C5": 8}  # samples the checker is timed on (10-30 s)
 COPY_BYTES = 256 << 20
 
@@ -185,7 +186,7 @@ def main():
     if args.config in ("P16", "P16F32"):
         # shaped like the paper's benchmark (Section 5.1): 16 samples of up to 500 x 100, joint size 1024,
         # 4096 word pieces; lengths drawn uniformly down to the paper's largest padding (9.3 % / 45.8 %)
-        # P16F32: the same in fp32 (the paper's own precision), on the fp32 MFMA GEMM form of the path
+        # P16F32: the same in fp32 (the paper's own precision), on the fp32 GEMM form of the path
         wl = synth.custom_workload(args.config, B=16, T_max=500, U_max=100, H=1024, V=4096,
                                    dtype="bf16" if args.config == "P16" else "f32", index=5,
                                    t_rule="uniform", t_lo=454, u_rule="uniform", u_lo=54)
@@ -366,7 +367,7 @@ def main():
     avg_s = kernels[dom]["avg_launch_us"] * 1e-6
     flops_per_launch = alg_flops_per_step[dom] / launches
     exec_per_launch = exec_flops_per_step[dom] / launches
-    peak = PEAK_BF16_FLOPS if wl.dtype == "bf16" else PEAK_F32_FLOPS
+    peak = PEAK_BF16_FLOPS if wl.dtype == "bf16" else PEAK_F32_GEMM_FLOPS if info["chunk_rows"] > 0 else PEAK_F32_FLOPS
     achieved = flops_per_launch / avg_s
     for name, k in kernels.items():
         if name in alg_flops_per_step:
@@ -375,7 +376,7 @@ def main():
     # HBM bytes per launch from the committed rocprofv3 counter summary of this workload, if any
     tname = f"hbm_traffic_{wl.name}" + ("_keep_scores" if args.keep_scores else "") + ".txt"
     traffic = read_traffic(os.path.join(ROOT, "profiles", tname)) if not args.batch else {}
-    # fp32: GEMMs on the fp32 MFMA instruction where the plan has chunk buffers (H, V multiples of 128; `kernel` is
+    # fp32: GEMMs (each operand as three bf16 parts) where the plan has chunk buffers (H, V multiples of 128; `kernel` is
     # then the group of launches of one chunk: three GEMMs and the row kernels between them), else plain FMA
     roofline = {"bound": "mfma" if (wl.dtype == "bf16" or info["chunk_rows"] > 0) else "alu", "kernel": dom,
                 "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s", "frac": achieved / peak,

@@ -49,7 +49,7 @@ typedef enum {
 
 typedef enum {
     RNNT_F32 = 0, /* enc, pred, W_out are float; everything is computed in fp32: the three      */
-                  /* GEMMs on fp32 MFMA where H, V are multiples of 4 from 64 on, else plain FMA */
+                  /* matrix GEMMs where H, V are multiples of 4 from 64 on, else plain FMA */
     RNNT_BF16 = 1 /* enc, pred, W_out are bfloat16; the three GEMMs run on bf16 MFMA with     */
                   /* fp32 accumulation, tanh/softmax/lattice in fp32                          */
 } rnnt_dtype;

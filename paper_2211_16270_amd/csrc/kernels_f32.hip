@@ -1,7 +1,7 @@
 // fp32 path.  Two forms:
 //  * plain FMA kernels, one wavefront per lattice node, for any H, V (the small fp32 workloads);
-//  * for H and V multiples of 4 from 64 on, the same steps over chunks of lattice nodes as fp32 MFMA GEMMs
-//    (v_mfma_f32_32x32x2_f32, full fp32 products and sums) with row kernels between them:
+//  * for H and V multiples of 4 from 64 on, the same steps over chunks of lattice nodes as matrix GEMMs of fp32
+//    precision (operands as three bf16 parts, k_gemm_f32) with row kernels between them:
 //      Z = tanh(enc_t + pred_u)              (Eq. 4)            k_rows_z_f32
 //      S = Z W + b                            (Eq. 6)            k_gemm_f32 <A k-contiguous, B k-slow>
 //      lse, lpb, lpy per row                  (f^W_1)            k_rows_stats_f32
@@ -11,6 +11,7 @@
 //      d_enc, d_pred += dZ (1 - Z^2)                             k_rows_dz_f32
 //    The chunk buffers S [rows, V], Z and dZ [rows, H] live in the workspace; rows beyond the chunk's
 //    last node (up to the next multiple of 128) are zero.  The throughput path is the bf16 one.
+#include <algorithm>
 #include <cstdint>
 
 #include "device_common.h"
@@ -149,134 +150,186 @@ hipError_t launch_bwd_f32(const Problem& pr, const SampleTable& st, const Lattic
     return hipGetLastError();
 }
 
-// ---- fp32 MFMA GEMM path ---------------------------------------------------------------------
+// ---- fp32 GEMM path ---------------------------------------------------------------------
 
 namespace {
 
-constexpr int FT = 128;       // output tile edge
-constexpr int FK = 16;        // K-step (32: 2.7 % slower at H = 1024, V = 4096)
-constexpr int FQ = FT * FK / 4 / 256;  // 16-byte pieces per thread, operand and step
-constexpr int FP = FT + 4;    // LDS row pitch (floats) of the [k][i] tile images
+constexpr int FT = 128;       // output tile: 128 rows x TN columns
+constexpr int FK = 16;        // K-step
 
-// One operand of the tile product.  KSLOW = false: element (i, k) at p[i*ld + k]; true: at p[k*ld + i].
-// i runs over the tile's 128 rows (m for A, n for B), k over one K-step; every extent is a multiple of the
-// tile sizes, so no access needs a guard.  In LDS both layouts become [k][i] (pitch FP): lane l of an MFMA
-// operand fragment is element (i_base + l%32, 2 kk + l/32).
-template <bool KSLOW>
+// C = A B in fp32 precision on the bf16 matrix instruction.  An fp32 value is the exact sum of three bf16 values, each the rounded rest
+// of the ones before: x = h + m + l with |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.  A product takes the six pairs h h, h m, m h, h l, m m, l h; what is
+// left out is below 2^-26 of it, a quarter of an fp32 rounding, and 16 products are added per rounding of the accumulator where the fp32
+// instruction adds two.  Against 64 bits (2-norm, normal operands, depth 64 ... 8800) the error is 0.75 ... 0.9 of that of v_mfma_f32_32x32x2_f32.
+// The accumulation rounds towards minus infinity, a mean of 5e-11 of the result's size per unit of depth, which would show from a depth of
+// about 30000 on: longer sums (the weight gradients) are split (k_splits_f32).  Values beyond the largest bf16, 3.39e38, infinities and NaN give NaN.
+// The bf16 instruction does sixteen times the work of the fp32 one, a sixth of it still 2.7 times.  What bounds it: power (1.7 GHz, matrix pipes busy
+// 64 to 67 % of the time; 200 TFLOP/s against 123 to 130 with the fp32 instruction).  H = 1024, V = 4096, 131 k nodes: a call 37.2 -> 23.3 ms.
+// The parts are formed on the way into LDS, so the operands stay as they are in memory.
+// One part of two values, which leave as what remains of them.
+__device__ __forceinline__ unsigned split_part(float& x0, float& x1) {
+    unsigned p;
+    // (as text: the compiler otherwise converts the first of the two once more by itself)
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(p) : "v"(x0), "v"(x1));
+    x0 -= __uint_as_float(p << 16);
+    x1 -= __uint_as_float(p & 0xffff0000u);
+    return p;
+}
+
+// One operand of the tile product, ROWS rows (m for A, n for B) x FK.  KSLOW = false: element (i, k) at p[i*ld + k]; true: at p[k*ld + i].
+// EDGE: elements with i >= n_i or k >= n_k, and those of a padded source row (the row index is i if !KSLOW, k if KSLOW; see RowMask), read as
+// zero.  The extent along the contiguous index is a multiple of 4, so a 16-byte piece is inside or outside as a whole.  Branch-free: a
+// piece outside is loaded from the operand's first element and cleared.
+// In LDS: blocks of 32 rows, each three MFMA fragments of 1 KiB (the three parts), in a fragment 64 granules of 16 bytes: 8 consecutive k (half kh) of
+// one row, the row's place r at granule 32 kh + (r ^ 12 kh) (the xor spreads a write of both halves over all banks).  The place of row
+// i is i for a k-contiguous operand; a k-slow one, whose threads hold four consecutive rows of two k, puts row i at i / 4 + 8 (i % 4), so that eight
+// threads write 128 bytes in one piece.
+template <bool KSLOW, bool EDGE, int ROWS>
 struct OperandF32 {
     const float* p;
     long long ld;
-    __device__ __forceinline__ void fetch(f32x4 (&v)[FQ], long long i0, long long k0, int tid) const {
-#pragma unroll
-        for (int q = 0; q < FQ; ++q) {
-            const int e = tid + 256 * q;
-            const long long off = !KSLOW ? (i0 + e / (FK / 4)) * ld + k0 + (e % (FK / 4)) * 4
-                                         : (k0 + (e >> 5)) * ld + i0 + (e & 31) * 4;
-            v[q] = *reinterpret_cast<const f32x4*>(p + off);
-        }
-    }
-    __device__ __forceinline__ void stage(const f32x4 (&v)[FQ], float* tile, int tid) const {
-#pragma unroll
-        for (int q = 0; q < FQ; ++q) {
-            const int e = tid + 256 * q;
-            if (!KSLOW) {
-                const int i = e / (FK / 4), k = (e % (FK / 4)) * 4;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) tile[(k + j) * FP + i] = v[q][j];
-            } else {
-                *reinterpret_cast<f32x4*>(tile + (e >> 5) * FP + (e & 31) * 4) = v[q];
-            }
-        }
-    }
-};
-
-// The same operand with edges: elements with i >= n_i or k >= n_k, and those of a padded source row (the
-// row index is i if !KSLOW, k if KSLOW; see RowMask), read as zero.  The extent along the contiguous index
-// is a multiple of 4, so a 16-byte piece is inside or outside as a whole.  Branch-free: a piece outside is
-// loaded from the operand's first element and cleared.
-template <bool KSLOW>
-struct OperandF32Edge : OperandF32<KSLOW> {
     long long n_i, n_k;
     RowMask mask;
-    __device__ __forceinline__ void fetch(f32x4 (&v)[FQ], long long i0, long long k0, int tid) const {
-        typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+    static constexpr int NQ = ROWS / 64;              // 16-byte pieces per thread and step
+    // 16-byte piece q of the step at k0 (i0, k0 uniform)
+    __device__ __forceinline__ f32x4 piece(long long i0, long long k0, int q, int tid) const {
+        const int lane = tid & 63, wave = tid >> 6;
+        const int di = KSLOW ? wave * 32 + (lane & 7) * 4 : tid >> 2, dk = KSLOW ? (lane >> 3) * 2 : (tid & 3) * 4;
+        i0 += KSLOW ? (q >> 1) * 128 : q * 64;
+        k0 += KSLOW ? q & 1 : 0;
+        if constexpr (!EDGE) {
+            const unsigned voff = (unsigned)(KSLOW ? dk * (int)ld + di : di * (int)ld + dk) * 4u;
+            const float* base = p + (KSLOW ? k0 * ld + i0 : i0 * ld + k0);
+            return *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(base) + voff);
+        }
+        const long long i = i0 + di, k = k0 + dk, off = !KSLOW ? i * ld + k : k * ld + i;
+        const bool ok = i < n_i && k < n_k;
+        bool keep = ok;
+        if (mask.len != nullptr) {
+            const long long src = ok ? (!KSLOW ? i : k) : 0, b = src / mask.period;
+            keep = ok && (int)(src - b * mask.period) < mask.len[b] + mask.extra;
+        }
+        u32x4 w = __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(p + (ok ? off : 0)));
+        w &= keep ? ~0u : 0u;
+        return __builtin_bit_cast(f32x4, w);
+    }
+    __device__ __forceinline__ void fetch(f32x4 (&v)[NQ], long long i0, long long k0, int tid) const {
 #pragma unroll
-        for (int q = 0; q < FQ; ++q) {
-            const int e = tid + 256 * q;
-            const long long i = !KSLOW ? i0 + e / (FK / 4) : i0 + (e & 31) * 4;
-            const long long k = !KSLOW ? k0 + (e % (FK / 4)) * 4 : k0 + (e >> 5);
-            const long long off = !KSLOW ? i * this->ld + k : k * this->ld + i;
-            const bool ok = i < n_i && k < n_k;
-            bool keep = ok;
-            if (mask.len != nullptr) {
-                const long long src = ok ? (!KSLOW ? i : k) : 0, b = src / mask.period;
-                keep = ok && (int)(src - b * mask.period) < mask.len[b] + mask.extra;
+        for (int q = 0; q < NQ; ++q) v[q] = piece(i0, k0, q, tid);
+    }
+    // The work of bringing a step's pieces into LDS, cut into units of about five vector instructions and one LDS write: part n / 3 ... of two values
+    // (k-contiguous operands: every second unit, with ten, of four).  The last unit of a piece loads that of the step at k2.
+    static constexpr int UNITS = 6 * NQ;
+    template <int U>
+    __device__ __forceinline__ void unit(f32x4 (&v)[NQ], unsigned char* tile, int tid, long long i0, long long k2) const {
+        if constexpr (!KSLOW) {
+            if constexpr (U % 2 == 0) {
+                constexpr int q = U / 6, part = U % 6 / 2;
+                const int r = (tid >> 2) & 31, kp = tid & 3, kh = kp >> 1;
+                float x[4] = {v[q][0], v[q][1], v[q][2], v[q][3]};
+                const unsigned a = split_part(x[0], x[1]), b = split_part(x[2], x[3]);
+                v[q] = f32x4{x[0], x[1], x[2], x[3]};
+                *reinterpret_cast<uint2*>(tile + (tid >> 7) * 3072 + q * 6144 + part * 1024 + kh * 512 + (r ^ (12 * kh)) * 16 + (kp & 1) * 8) =
+                    make_uint2(a, b);
+                if constexpr (part == 2) v[q] = piece(i0, k2, q, tid);
             }
-            u32x4_t w = __builtin_bit_cast(u32x4_t, *reinterpret_cast<const f32x4*>(this->p + (ok ? off : 0)));
-            w &= keep ? ~0u : 0u;
-            v[q] = __builtin_bit_cast(f32x4, w);
+        } else {
+            constexpr int q = U / 12 * 2, c = U % 12 / 3, part = U % 3;
+            const int lane = tid & 63, wave = tid >> 6, kp = lane >> 3, kh = kp >> 2;
+            float x0 = v[q][c], x1 = v[q + 1][c];
+            *reinterpret_cast<unsigned*>(tile + wave * 3072 + q * 6144 + part * 1024 + kh * 512 +
+                                         (((lane & 7) ^ (4 * kh)) + ((8 * c) ^ (8 * kh))) * 16 + (kp & 3) * 4) = split_part(x0, x1);
+            v[q][c] = x0;
+            v[q + 1][c] = x1;
+            if constexpr (U % 12 == 11) {
+                v[q] = piece(i0, k2, q, tid);
+                v[q + 1] = piece(i0, k2, q + 1, tid);
+            }
         }
     }
+    // row of a block that stands at place r
+    static __device__ __forceinline__ int row_at(int r) { return KSLOW ? (r & 7) * 4 + (r >> 3) : r; }
 };
 
-// C[m, n] (+)= sum_k A(m, k) B(k, n) (+ bias[n]) in fp32.  128x128 output tile per workgroup, 4 waves x
-// (64x64 = 2x2 MFMA 32x32x2 tiles), K-step 16, global loads one K-step ahead in registers.
-// grid (M/128, N/128, splits); a split covers k_per_split (a multiple of 16) of K.  atomic != 0: the tile
+// C[m, n] (+)= sum_k A(m, k) B(k, n) (+ bias[n]) in fp32.  128 x TN output tile per workgroup, 4 waves x (64 x TN/2) = 2 x TN/64 MFMA tiles of
+// 32 x 32, six MFMAs of depth 16 each per K-step; two LDS buffers, one barrier per K-step, global loads two K-steps ahead of their MFMAs in registers.
+// Two workgroups per compute unit (72 KiB of LDS and 256 registers each): one's splitting stands beside the other's MFMAs.
+// grid (M/128, N/TN, splits); a split covers k_per_split (a multiple of 16) of K.  atomic != 0: the tile
 // is added to C with float atomics (split over K, or C accumulates over calls).
-template <class OpA, class OpB>
-__global__ __launch_bounds__(256) void k_gemm_f32(OpA A, OpB B, float* __restrict__ C, long long ldc,
-                                                  const float* __restrict__ bias, int atomic, long long M,
-                                                  long long N, long long K, long long k_per_split) {
-    __shared__ __align__(16) float As[FK * FP];
-    __shared__ __align__(16) float Bs[FK * FP];
+template <int TN, class OpA, class OpB>
+__global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __restrict__ C, long long ldc,
+                                                     const float* __restrict__ bias, int atomic, long long M,
+                                                     long long N, long long K, long long k_per_split) {
+    constexpr int NT = TN / 64;                       // MFMA tiles of a wave along N
+    constexpr unsigned A_BYTES = FT / 32 * 3072, BUF = A_BYTES + TN / 32 * 3072;
+    __shared__ __align__(16) unsigned char smem[2 * BUF];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
-    const long long m0 = (long long)blockIdx.x * FT, n0 = (long long)blockIdx.y * FT;
+    const long long m0 = (long long)blockIdx.x * FT, n0 = (long long)blockIdx.y * TN;
     const long long ks = (long long)blockIdx.z * k_per_split;
     const long long ke = ks + k_per_split < K ? ks + k_per_split : K;
     if (ks >= ke) return;
-    f32x16 acc[2][2];
+    f32x16 acc[2][NT];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
-    f32x4 va[FQ], vb[FQ];
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x16{0};
+    f32x4 va[OpA::NQ], vb[OpB::NQ];
+    const unsigned frag = hb * 512u + (unsigned)(l32 ^ (12 * hb)) * 16u;
+    const unsigned char* fa0 = smem + wm * 2 * 3072 + frag;
+    const unsigned char* fb0 = smem + A_BYTES + wn * NT * 3072 + frag;
+    const long long last = ks + (ke - ks - 1) / FK * FK;
+    // unit w of a step: of B's, then of A's; into buffer `buf`; the loads that follow them take the step at k2
+    constexpr int UNITS = OpA::UNITS + OpB::UNITS;
+    auto unit = [&](auto w_tag, unsigned buf, long long k2) {
+        constexpr int w = decltype(w_tag)::value;
+        if constexpr (w < OpB::UNITS) B.template unit<w>(vb, smem + buf + A_BYTES, tid, n0, k2);
+        else A.template unit<w - OpB::UNITS>(va, smem + buf, tid, m0, k2);
+    };
     A.fetch(va, m0, ks, tid);
     B.fetch(vb, n0, ks, tid);
-    for (long long k0 = ks; k0 < ke; k0 += FK) {
-        __syncthreads();                     // the previous step's fragment reads are done
-        A.stage(va, As, tid);
-        B.stage(vb, Bs, tid);
+    static_for<0, UNITS>([&](auto w) { unit(w, 0u, ks + FK < last ? ks + FK : last); });
+    __syncthreads();
+    unsigned cur = 0;
+    for (long long k0 = ks; k0 < ke; k0 += FK, cur ^= BUF) {
+        // (past the end: the last step again, into a buffer nobody reads any more)
+        const long long k2 = k0 + 2 * FK < last ? k0 + 2 * FK : last;
+        bf16x8 fa[2][3], fb[2][3];
+        auto frag_b = [&](auto j_tag, int c) {
+            constexpr int j = decltype(j_tag)::value;
+            fb[j & 1][c] = *reinterpret_cast<const bf16x8*>(fb0 + cur + (j * 3 + c) * 1024);
+        };
+#pragma unroll
+        for (int c = 2; c >= 0; --c) {
+            fa[0][2 - c] = *reinterpret_cast<const bf16x8*>(fa0 + cur + (2 - c) * 1024);
+            frag_b(std::integral_constant<int, 0>{}, c);
+            fa[1][2 - c] = *reinterpret_cast<const bf16x8*>(fa0 + cur + (3 + 2 - c) * 1024);
+        }
+        // Behind each MFMA (it holds the matrix pipe for 32 clocks and the issue port for four) a share of the next step's staging: the buffer's last
+        // readers have passed the barrier that ended the step before.
+        static_for<0, 12 * NT>([&](auto g_tag) {
+            constexpr int g = decltype(g_tag)::value, j = g / 12, i = g & 1, pr = g % 12 / 2;
+            // the small products first: (part of A, part of B)
+            constexpr int pa[6] = {0, 1, 2, 0, 1, 0}, pb[6] = {2, 1, 0, 1, 0, 0};
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][pa[pr]], fb[j & 1][pb[pr]], acc[i][j], 0, 0, 0);
+            if constexpr (j + 1 < NT && g % 12 >= 3 && g % 12 < 6) frag_b(std::integral_constant<int, j + 1>{}, 5 - g % 12);
+            constexpr int w0 = g * UNITS / (12 * NT), w1 = (g + 1) * UNITS / (12 * NT);
+            static_for<w0, w1>([&](auto w) { unit(w, cur ^ BUF, k2); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
         __syncthreads();
-        if (k0 + FK < ke) {
-            A.fetch(va, m0, k0 + FK, tid);
-            B.fetch(vb, n0, k0 + FK, tid);
-        }
-#pragma unroll
-        for (int kk = 0; kk < FK / 2; ++kk) {
-            float fa[2], fb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) fa[i] = As[(2 * kk + hb) * FP + wm * 64 + i * 32 + l32];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = Bs[(2 * kk + hb) * FP + wn * 64 + j * 32 + l32];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
     }
-    // accumulator register 4q+r of tile (i,j): row 8q + 4hb + r, column l32
+    // accumulator register 4q+r of tile (i,j): place 8q + 4hb + r along M, l32 along N
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const long long n = n0 + wn * 64 + j * 32 + l32;
+        for (int j = 0; j < NT; ++j) {
+            const long long n = n0 + (wn * NT + j) * 32 + OpB::row_at(l32);
             if (n >= N) continue;
             const float bv = (bias != nullptr && blockIdx.z == 0) ? bias[n] : 0.0f;
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
-                const long long m = m0 + wm * 64 + i * 32 + 8 * (q >> 2) + 4 * hb + (q & 3);
+                const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(8 * (q >> 2) + 4 * hb + (q & 3));
                 if (m >= M) continue;
                 const float v = acc[i][j][q] + bv;
                 if (atomic) atomicAdd(C + m * ldc + n, v);
@@ -285,41 +338,65 @@ __global__ __launch_bounds__(256) void k_gemm_f32(OpA A, OpB B, float* __restric
         }
 }
 
-template <bool AK, bool BK>
-hipError_t launch_gemm_f32(const float* A, long long lda, const float* B, long long ldb, float* C, long long ldc,
-                           const float* bias, int atomic, long long M, long long N, long long K, int splits,
-                           hipStream_t stream) {
-    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-    if (M % FT != 0 || N % FT != 0 || K % FK != 0 || splits < 1 || (splits > 1 && !atomic)) return hipErrorInvalidValue;
-    long long per = (K + splits - 1) / splits;
+struct GemmF32 {
+    const float* A;
+    long long lda;
+    RowMask ma;
+    const float* B;
+    long long ldb;
+    RowMask mb;
+    float* C;
+    long long ldc;
+    const float* bias;
+    int atomic;
+    long long M, N, K;
+    int splits;
+};
+
+template <bool AK, bool BK, bool EDGE, int TN>
+hipError_t launch_gemm_f32_t(const GemmF32& g, hipStream_t stream) {
+    long long per = (g.K + g.splits - 1) / g.splits;
     per = (per + FK - 1) / FK * FK;
-    const long long nz = (K + per - 1) / per;
-    if (M / FT > 0x7fffffffLL || N / FT > 65535 || nz > 65535) return hipErrorInvalidValue;
-    k_gemm_f32<<<dim3((unsigned)(M / FT), (unsigned)(N / FT), (unsigned)nz), dim3(256), 0, stream>>>(
-        OperandF32<AK>{A, lda}, OperandF32<BK>{B, ldb}, C, ldc, bias, atomic, M, N, K, per);
+    const long long nz = (g.K + per - 1) / per, gm = (g.M + FT - 1) / FT, gn = (g.N + TN - 1) / TN;
+    if (gm > 0x7fffffffLL || gn > 65535 || nz > 65535) return hipErrorInvalidValue;
+    const OperandF32<AK, EDGE, FT> a{g.A, g.lda, g.M, g.K, g.ma};
+    const OperandF32<BK, EDGE, TN> b{g.B, g.ldb, g.N, g.K, g.mb};
+    k_gemm_f32<TN><<<dim3((unsigned)gm, (unsigned)gn, (unsigned)nz), dim3(256), 0, stream>>>(a, b, g.C, g.ldc, g.bias, g.atomic, g.M, g.N,
+                                                                                        g.K, per);
     return hipGetLastError();
 }
 
+// Splits of a sum over K rows: about 512 workgroups of 128 x 128 in all, at least 128 rows each; long sums (4096 rows and more per split) in as many as
+// 512 workgroups of 128 x 256 take (H = 1024, V = 4096, 33 k rows: 1323 -> 1190 us; with 4500 rows, H = 512, V = 1024, the atomics of so many splits
+// cost more: a call 245 -> 260 us); at most 16384 rows per split (the accumulation's bias, above).
+}  // namespace
+int k_splits_f32(long long M, long long N, long long K) {
+    const long long rows = (M + FT - 1) / FT, narrow = rows * ((N + 127) / 128), wide = rows * ((N + 255) / 256);
+    long long s = std::min((512 + narrow - 1) / narrow, (K + FT - 1) / FT);
+    if (K >= 4096 * s) s = std::max(s, (512 + wide - 1) / wide);
+    return (int)std::max({1LL, s, (K + 16383) / 16384});
+}
+namespace {
+
+// Tiles of 256 or 128 columns: the fewer rounds of the chip (two workgroups per compute unit), a narrow one costing 0.6 of a wide one.
+inline bool wide_tiles_pay(long long M, long long N, int splits) {
+    const long long rows = (M + FT - 1) / FT * splits;
+    const long long wide = (rows * ((N + 255) / 256) + 511) / 512, narrow = (rows * ((N + 127) / 128) + 511) / 512;
+    return 10 * wide <= 6 * narrow;
+}
+
+// Without edge handling where M, N, K are multiples of the tile and no row is masked, else with it.
 template <bool AK, bool BK>
-hipError_t launch_gemm_f32_edge(const float* A, long long lda, const RowMask& ma, const float* B, long long ldb,
-                                const RowMask& mb, float* C, long long ldc, const float* bias, int atomic,
-                                long long M, long long N, long long K, int splits, hipStream_t stream) {
-    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
+hipError_t launch_gemm_f32(const GemmF32& g, hipStream_t stream) {
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipSuccess;
     // 16-byte pieces along each operand's contiguous index
-    const bool fits = lda % 4 == 0 && ldb % 4 == 0 && (AK ? M : K) % 4 == 0 && (BK ? N : K) % 4 == 0 &&
-                      (uintptr_t)A % 16 == 0 && (uintptr_t)B % 16 == 0;
-    if (!fits || splits < 1 || (splits > 1 && !atomic)) return hipErrorInvalidValue;
-    long long per = (K + splits - 1) / splits;
-    per = (per + FK - 1) / FK * FK;
-    const long long nz = (K + per - 1) / per, gm = (M + FT - 1) / FT, gn = (N + FT - 1) / FT;
-    if (gm > 0x7fffffffLL || gn > 65535 || nz > 65535) return hipErrorInvalidValue;
-    OperandF32Edge<AK> a;
-    a.p = A; a.ld = lda; a.n_i = M; a.n_k = K; a.mask = ma;
-    OperandF32Edge<BK> b;
-    b.p = B; b.ld = ldb; b.n_i = N; b.n_k = K; b.mask = mb;
-    k_gemm_f32<<<dim3((unsigned)gm, (unsigned)gn, (unsigned)nz), dim3(256), 0, stream>>>(a, b, C, ldc, bias, atomic, M,
-                                                                                        N, K, per);
-    return hipGetLastError();
+    const bool fits = g.lda % 4 == 0 && g.ldb % 4 == 0 && (AK ? g.M : g.K) % 4 == 0 && (BK ? g.N : g.K) % 4 == 0 &&
+                      (uintptr_t)g.A % 16 == 0 && (uintptr_t)g.B % 16 == 0;
+    if (!fits || g.splits < 1 || (g.splits > 1 && !g.atomic)) return hipErrorInvalidValue;
+    const bool wide = wide_tiles_pay(g.M, g.N, g.splits);
+    const bool edge = g.ma.len != nullptr || g.mb.len != nullptr || g.M % FT != 0 || g.N % (wide ? 256 : 128) != 0 || g.K % FK != 0;
+    if (wide) return edge ? launch_gemm_f32_t<AK, BK, true, 256>(g, stream) : launch_gemm_f32_t<AK, BK, false, 256>(g, stream);
+    return edge ? launch_gemm_f32_t<AK, BK, true, 128>(g, stream) : launch_gemm_f32_t<AK, BK, false, 128>(g, stream);
 }
 
 // Row i of the chunk is lattice node r0 + i of the group (i < n), or padding (n <= i < gridDim.x).
@@ -428,25 +505,21 @@ hipError_t launch_gemm_f32_masked(int a_kslow, int b_kslow, const float* A, long
                                   const float* B, long long ldb, const RowMask& mb, float* C, long long ldc,
                                   const float* bias, int atomic, long long M, long long N, long long K, int splits,
                                   hipStream_t stream) {
-    if (!a_kslow && b_kslow)
-        return launch_gemm_f32_edge<false, true>(A, lda, ma, B, ldb, mb, C, ldc, bias, atomic, M, N, K, splits, stream);
-    if (!a_kslow && !b_kslow)
-        return launch_gemm_f32_edge<false, false>(A, lda, ma, B, ldb, mb, C, ldc, bias, atomic, M, N, K, splits, stream);
-    if (a_kslow && b_kslow)
-        return launch_gemm_f32_edge<true, true>(A, lda, ma, B, ldb, mb, C, ldc, bias, atomic, M, N, K, splits, stream);
+    const GemmF32 g{A, lda, ma, B, ldb, mb, C, ldc, bias, atomic, M, N, K, splits};
+    if (!a_kslow && b_kslow) return launch_gemm_f32<false, true>(g, stream);
+    if (!a_kslow && !b_kslow) return launch_gemm_f32<false, false>(g, stream);
+    if (a_kslow && b_kslow) return launch_gemm_f32<true, true>(g, stream);
     return hipErrorInvalidValue;
 }
 
 namespace {
-// The GEMM of the joint path: without edge handling where H and V are multiples of the tile, else with it.
+// The GEMM of the joint path (no padded source rows)
 template <bool AK, bool BK>
 hipError_t joint_gemm_f32(const float* A, long long lda, const float* B, long long ldb, float* C, long long ldc,
                           const float* bias, int atomic, long long M, long long N, long long K, int splits,
                           hipStream_t stream) {
-    if (M % FT == 0 && N % FT == 0 && K % FK == 0)
-        return launch_gemm_f32<AK, BK>(A, lda, B, ldb, C, ldc, bias, atomic, M, N, K, splits, stream);
     const RowMask none{nullptr, 1, 0};
-    return launch_gemm_f32_edge<AK, BK>(A, lda, none, B, ldb, none, C, ldc, bias, atomic, M, N, K, splits, stream);
+    return launch_gemm_f32<AK, BK>(GemmF32{A, lda, none, B, ldb, none, C, ldc, bias, atomic, M, N, K, splits}, stream);
 }
 }  // namespace
 
@@ -483,11 +556,8 @@ hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
     if (e != hipSuccess) return e;
     e = launch_col_sum(S, np, V, go.db, stream);
     if (e != hipSuccess) return e;
-    // dW += Z^T dh: about 512 workgroups in all, at least 128 rows per split
-    const long long tiles = (long long)((H + FT - 1) / FT) * ((V + FT - 1) / FT);
-    long long splits = (512 + tiles - 1) / tiles;
-    if (splits > np / FT) splits = np / FT;
-    e = joint_gemm_f32<true, true>(Z, H, S, V, go.dW, V, nullptr, 1, H, V, np, (int)splits, stream);
+    // dW += Z^T dh
+    e = joint_gemm_f32<true, true>(Z, H, S, V, go.dW, V, nullptr, 1, H, V, np, k_splits_f32(H, V, np), stream);
     if (e != hipSuccess) return e;
     // dZ = dh W^T   (B(k = v, n = h) = W[h, v]: k-contiguous)
     e = joint_gemm_f32<false, false>(S, V, W, V, dZ, H, nullptr, 0, np, H, V, 1, stream);

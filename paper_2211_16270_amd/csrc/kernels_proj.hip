@@ -13,7 +13,7 @@
 // A k-contiguous operand lies in LDS as [row][k] and gives fragments by plain 16-byte reads; a k-slow
 // operand lies there as in memory ([k][row], 16-byte chunks XOR-swizzled) and gives fragments by the
 // transposing LDS read.  Global loads run one K-step ahead in registers.  These GEMMs are about 1 % of the path's flops.
-// fp32 path: the fp32 MFMA tile GEMM of the fp32 joint path where rows are 16-byte aligned (D, H multiples of 4);
+// fp32 path: the tile GEMM of the fp32 joint path where rows are 16-byte aligned (D, H multiples of 4);
 // else one thread per output element.
 #include "device_common.h"
 #include "kernels.h"
@@ -320,14 +320,9 @@ hipError_t launch_proj_backward_weight(int bf16, const void* h, long long rows, 
         return launch_tile_gemm<bf16_t, true, float, true>(h, D, mask, d_out, H, mask, ep, D, H, rows, (int)splits, stream);
     }
     if (gemm_f32_edge_fits(h, D, d_out, H, D, H)) {
-        // split over the rows as on the bf16 path; dW is added to with float atomics
-        const long long tiles = (long long)((D + PT - 1) / PT) * ((H + PT - 1) / PT);
-        long long splits = (512 + tiles - 1) / tiles;
-        const long long max_splits = (rows + 255) / 256;
-        if (splits > max_splits) splits = max_splits;
-        if (splits < 1) splits = 1;
+        // dW is added to with float atomics
         return launch_gemm_f32_masked(1, 1, (const float*)h, D, mask, d_out, H, mask, dW, H, nullptr, 1, D, H, rows,
-                                      (int)splits, stream);
+                                      k_splits_f32(D, H, rows), stream);
     }
     const long long total = (long long)D * H;
     k_proj_gemm_f32<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(

@@ -38,7 +38,7 @@ struct Chunk {
 struct Plan {
     int B = 0;
     bool bf16 = false;
-    bool f32_gemm = false;              // fp32 only: H, V multiples of 4 from 64 on, the steps run as fp32 MFMA GEMMs over chunks
+    bool f32_gemm = false;              // fp32 only: H, V multiples of 4 from 64 on, the steps run as fp32 GEMMs over chunks
     bool keep = false;                  // bf16 only: forward keeps the scores, one backward chunk per group
     bool stage = false;                 // bf16 only: d_enc, d_pred leave as bf16; fp32 sums of one group in the workspace
     long long stage_samples = 0;        // samples a group may hold then

@@ -153,7 +153,7 @@ def main(argv):
                 if c:
                     print(f"    {k:24s} launches per step {c // 4:3d}   {ms / 4:8.3f} ms per step")
     elif which == "fp32":
-        print(f"H = {H}, V = {V}, fp32 inputs and arithmetic (fp32 MFMA GEMMs over chunks of lattice nodes), packed\n")
+        print(f"H = {H}, V = {V}, fp32 inputs and arithmetic (fp32 GEMMs over chunks of lattice nodes), packed\n")
         print("| B | T x U | ms per step | samples/s | executed TFLOP/s | workspace GB | peak GB (inputs + outputs + workspace) |")
         print("|---|---|---|---|---|---|---|")
         cases = [(16, T, U) for T, U in [(50, 10), (100, 20), (139, 27), (232, 46), (300, 60), (400, 80), (500, 100)]]

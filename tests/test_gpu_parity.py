@@ -108,6 +108,15 @@ def test_f32_gemm_form_edge_lattices(T_len, U_len, blank):
     assert_padding_zero(got, batch)
 
 
+def test_f32_gemm_form_wide_tiles_with_edges():
+    """Enough nodes for GEMM tiles of 256 columns, whose last one is partly filled (V = 300, H = 320)."""
+    wl = synth.custom_workload("g32w", B=2, T_max=230, U_max=90, H=320, V=300, dtype="f32", index=134)
+    batch = synth.make_batch(wl)
+    got, ref = run_gpu(batch), run_oracle(batch)
+    e, errs = assert_parity(got, ref, "f32", "fp32 GEMM form, wide tiles")
+    _say("fp32 GEMM form, wide tiles", e, errs)
+
+
 def test_f32_gemm_form_several_chunks_and_accumulate():
     import torch
     wl = synth.custom_workload("g32b", B=6, T_max=90, U_max=20, H=256, V=512, dtype="f32", index=133,
