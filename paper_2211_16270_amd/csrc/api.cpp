@@ -203,8 +203,7 @@ WsView view_workspace(const Plan& p, void* ws) {
     v.st.row_off = (const long long*)(w + p.off_row_off);
     v.st.tile_sample = (const int*)(w + p.off_tile_sample);
     v.ls.lse = (float*)(w + p.off_lse);
-    v.ls.lpb = (float*)(w + p.off_lpb);
-    v.ls.lpy = (float*)(w + p.off_lpy);
+    v.ls.em = (float2*)(w + p.off_em);
     v.ls.alpha = (float*)(w + p.off_alpha);
     v.ls.beta = (float*)(w + p.off_beta);
     v.ls.lnP = (float*)(w + p.off_lnP);
@@ -355,7 +354,7 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         const Group& g = plan.groups[gi];
         LatticeState ls = wv.ls;
         const size_t half = (plan.lat_buffers == 2 && (gi & 1)) ? (size_t)plan.group_rows_cap : 0;
-        ls.lse += half; ls.lpb += half; ls.lpy += half; ls.alpha += half; ls.beta += half;
+        ls.lse += half; ls.em += half; ls.alpha += half; ls.beta += half;
         ls.row_base = plan.row_off[g.s0];
         ls.weight = sample_weight ? (const float*)(w + plan.off_weight) : nullptr;
         return ls;
@@ -825,11 +824,12 @@ extern "C" rnnt_status rnnt_debug_read_lattice(const rnnt_desc* desc, const int3
     RNNT_HIP(hipMemcpy(alpha_host, w + plan.off_alpha + off, n * 4, hipMemcpyDeviceToHost));
     RNNT_HIP(hipMemcpy(beta_host, w + plan.off_beta + off, n * 4, hipMemcpyDeviceToHost));
     RNNT_HIP(hipMemcpy(&shift, w + plan.off_shift + (size_t)b * 4, 4, hipMemcpyDeviceToHost));
+    const std::vector<float> a(alpha_host, alpha_host + n), be(beta_host, beta_host + n);
     for (int t = 0; t < T; ++t)
         for (int u = 0; u <= U; ++u) {
-            const size_t i = (size_t)t * (U + 1) + u;
-            alpha_host[i] -= shift * (float)(t + u);
-            beta_host[i] -= shift * (float)((T - t) + (U - u));
+            const size_t i = (size_t)t * (U + 1) + u, at = (size_t)lattice_index(T, U + 1, t, u);
+            alpha_host[i] = a[at] - shift * (float)(t + u);
+            beta_host[i] = be[at] - shift * (float)((T - t) + (U - u));
         }
     return RNNT_OK;
 }

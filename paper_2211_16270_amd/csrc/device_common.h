@@ -66,6 +66,11 @@ __device__ __forceinline__ bf16x8 joint_tanh8(bf16x8 e, bf16x8 q) {
     return z;
 }
 
+__device__ __forceinline__ float2 emissions(float blank, float label) {
+    // (comparisons that keep NaN)
+    return make_float2(blank < EMISSION_FLOOR ? EMISSION_FLOOR : blank, label < EMISSION_FLOOR ? EMISSION_FLOOR : label);
+}
+
 // ln(e^a + e^b); either may be -inf.
 __device__ __forceinline__ float log_add_exp(float a, float b) {
     float m = fmaxf(a, b);
@@ -96,10 +101,12 @@ __device__ __forceinline__ RowPost row_posteriors(const LatticeState& ls, long l
     const float a = ls.alpha[idx], lnP = ls.lnP[s], c = ls.shift[s];
     RowPost r;
     r.log_gamma = a + ls.beta[idx] - lnP;
-    const float ab = a + ls.lpb[idx] + c - lnP;
-    if (t < T - 1) r.Bk = __expf(ab + ls.beta[idx + (U + 1)]);
+    const float2 em = ls.em[idx];
+    const float ab = a + em.x + c - lnP;
+    const float* __restrict__ next = ls.beta + idx + next_diagonal_step(T, U + 1, t + u);
+    if (t < T - 1) r.Bk = __expf(ab + next[0]);
     else r.Bk = (u == U) ? __expf(ab) : 0.0f;
-    r.Yk = (u < U) ? __expf(a + ls.lpy[idx] + c - lnP + ls.beta[idx + 1]) : 0.0f;
+    r.Yk = (u < U) ? __expf(a + em.y + c - lnP + next[1]) : 0.0f;
     if (ls.weight) {
         // gradients of sum_b w_b loss_b: every posterior weight of sample s is scaled by w_s >= 0
         const float w = ls.weight[s];
@@ -122,8 +129,8 @@ __device__ __forceinline__ RowDh row_score_gradient(const LatticeState& ls, long
     const float both = (label == blank) ? 1.0f : 0.0f;
     RowDh r;
     r.g = (rp.log_gamma - ls.lse[idx]) * LOG2E_F;
-    r.at_blank = __expf(rp.log_gamma + ls.lpb[idx]) - rp.Bk - both * rp.Yk;
-    r.at_label = (label >= 0) ? __expf(rp.log_gamma + ls.lpy[idx]) - rp.Yk - both * rp.Bk : 0.0f;
+    r.at_blank = __expf(rp.log_gamma + ls.em[idx].x) - rp.Bk - both * rp.Yk;
+    r.at_label = (label >= 0) ? __expf(rp.log_gamma + ls.em[idx].y) - rp.Yk - both * rp.Bk : 0.0f;
     return r;
 }
 

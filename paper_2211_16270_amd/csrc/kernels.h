@@ -17,16 +17,38 @@ struct SampleTable {
 };
 
 // Per-group lattice state; arrays are indexed by (row_off[s] - row_base) + t*(U_s+1) + u.
+// The nodes of a sample lie anti-diagonal after anti-diagonal (t + u = 0, 1, ...), on each by rising u: the lattice sweeps, which
+// take one anti-diagonal per step, then read and write memory in one piece.  W = U + 1 columns.
+__host__ __device__ inline int diagonal_offset(int T, int W, int k) {
+    const int a = T < W ? T : W, b = T < W ? W : T;
+    if (k <= a) return k * (k + 1) / 2;
+    if (k <= b) return a * (a + 1) / 2 + (k - a) * a;
+    const int r = T + W - 1 - k;
+    return T * W - r * (r + 1) / 2;
+}
+__host__ __device__ inline int lattice_index(int T, int W, int t, int u) {
+    const int k = t + u;
+    return diagonal_offset(T, W, k) + u - (k >= T ? k - T + 1 : 0);
+}
+// Distance from node (t, u) to (t + 1, u); (t, u + 1) is the one behind that.
+__host__ __device__ inline int next_diagonal_step(int T, int W, int k) {
+    const int a = T < W ? T : W, r = T + W - 1 - k;
+    int len = k + 1 < a ? k + 1 : a;
+    len = len < r ? len : r;
+    return len - (k + 1 >= T ? 1 : 0);
+}
+// Stands for ln 0 in the emissions: finite, so that the sums of two impossible ways are no NaN.
+constexpr float EMISSION_FLOOR = -1e30f;
+
 struct LatticeState {
     float* lse;    // ln of the softmax denominator (f^W_1)
-    float* lpb;    // blank log-probability
-    float* lpy;    // log-probability of label y_u (unused at u = U_s)
+    float2* em;    // log-probabilities of the blank (x) and of label y_u (y; EMISSION_FLOOR at u = U_s), not below EMISSION_FLOOR
     float* alpha;  // forward variable, offset by shift*(t+u)
     float* beta;   // backward variable, offset by shift*((T-t)+(U-u))
     float* lnP;    // [B] ln P(y|x) + shift*(T+U), per sample
     float* shift;  // [B] per-sample offset added to every emission log-probability
     const float* weight;  // [B] weight of loss[b] in the differentiated sum, or null (all ones)
-    float* tile_esum;     // [tiles of the call] sum over a tile's nodes of max(lpb, lpy) (lpb where there is no
+    float* tile_esum;     // [tiles of the call] sum over a tile's nodes of max(blank, label) (blank where there is no
                           // label), written by the bf16 forward kernels for the lattice kernels' offset; or null
     long long row_base;
 };
@@ -117,7 +139,7 @@ constexpr ActiveTiles EVERY_TILE{nullptr, nullptr, 0, 0, -1};
 
 // ---- bf16 MFMA path -------------------------------------------------------------------------
 // Wpack: W_out^T in fragments [V/32][H/16], Wq: W_out in fragments [V/16][H/32] (launch_prepare).
-// scores on MFMA -> online log-softmax -> lse, lpb, lpy   (tiles [tile0,tile1)).  part: scratch for partial statistics where
+// scores on MFMA -> online log-softmax -> lse, emissions   (tiles [tile0,tile1)).  part: scratch for partial statistics where
 // a small launch splits the vocabulary over workgroups; these count their arrivals in the emission sums of the tiles, which are
 // zero before the launch (launch_prepare)
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void k_kept_to_dh(KeptArgs a) {
     const int lab = (t < tp.T && u < tp.U) ? a.pr.labels[(size_t)b * a.pr.U_max + u] : -1;
     float g = RNNT_NEG_INF, vB = 0.0f, vY = 0.0f;
     if (t < tp.T && u <= tp.U) {
-        const long long idx = (a.st.row_off[b] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+        const long long idx = (a.st.row_off[b] - a.ls.row_base) + lattice_index(tp.T, tp.U + 1, t, u);
         const RowDh rd = row_score_gradient(a.ls, idx, t, u, tp.T, tp.U, b, lab, a.pr.blank);
         g = rd.g;
         vB = rd.at_blank;

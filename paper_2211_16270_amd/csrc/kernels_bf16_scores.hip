@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
             gexp[rb] = RNNT_NEG_INF;
             vB[rb] = vY[rb] = 0.0f;
             if (t < tp.T && u <= tp.U) {
-                const long long idx = (a.st.row_off[b] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+                const long long idx = (a.st.row_off[b] - a.ls.row_base) + lattice_index(tp.T, tp.U + 1, t, u);
                 const RowDh rd = row_score_gradient(a.ls, idx, t, u, tp.T, tp.U, b, lab[rb], a.pr.blank);
                 gexp[rb] = rd.g;
                 vB[rb] = rd.at_blank;
@@ -478,10 +478,9 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
         const float cb = both_halves_max(cap_b[rb]), cy = both_halves_max(cap_y[rb]);
         const float lse = m_tot[rb] + __logf(s_tot[rb]);
         if (present && t < tp.T && u <= tp.U && hb == 0) {
-            const long long idx = (a.st.row_off[b] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+            const long long idx = (a.st.row_off[b] - a.ls.row_base) + lattice_index(tp.T, tp.U + 1, t, u);
             a.ls.lse[idx] = lse;
-            a.ls.lpb[idx] = cb - lse;
-            a.ls.lpy[idx] = (lab[rb] >= 0) ? cy - lse : 0.0f;
+            a.ls.em[idx] = emissions(cb - lse, lab[rb] >= 0 ? cy - lse : EMISSION_FLOOR);
             // this node's share of the sum the lattice kernels take their per-sample offset from
             esum += (u < tp.U) ? fmaxf(cb, cy) - lse : cb - lse;
         }

@@ -4,7 +4,7 @@
 //    precision (operands as three bf16 parts, k_gemm_f32) with row kernels between them:
 //      Z = tanh(enc_t + pred_u)              (Eq. 4)            k_rows_z_f32
 //      S = Z W + b                            (Eq. 6)            k_gemm_f32 <A k-contiguous, B k-slow>
-//      lse, lpb, lpy per row                  (f^W_1)            k_rows_stats_f32
+//      lse, emissions per row                 (f^W_1)            k_rows_stats_f32
 //      dh = gamma softmax - posteriors        (f^W_4)            k_rows_dh_f32 (in place of S)
 //      db += column sums, dW += Z^T dh        (Alg. 1 line 8)    k_gemm_f32 <A k-slow, B k-slow>, split over the rows
 //      dZ = dh W^T                            (Alg. 1 l. 10-11)  k_gemm_f32 <A k-contiguous, B k-contiguous>
@@ -45,7 +45,7 @@ __device__ __forceinline__ NodePos locate_node(const SampleTable& st, long long 
     const int local = (int)(rg - st.row_off[p.s]);
     p.t = local / (p.U + 1);
     p.u = local - p.t * (p.U + 1);
-    p.idx = r;
+    p.idx = st.row_off[p.s] - row_base + lattice_index(p.T, p.U + 1, p.t, p.u);
     return p;
 }
 
@@ -82,8 +82,7 @@ __global__ __launch_bounds__(64) void k_fwd_f32(Problem pr, SampleTable st, Latt
     cap_y = wave_max(cap_y);
     if (lane == 0) {
         ls.lse[p.idx] = lse;
-        ls.lpb[p.idx] = cap_b - lse;
-        ls.lpy[p.idx] = (p.u < p.U) ? cap_y - lse : 0.0f;
+        ls.em[p.idx] = emissions(cap_b - lse, p.u < p.U ? cap_y - lse : EMISSION_FLOOR);
     }
 }
 
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(256) void k_rows_z_f32(Problem pr, SampleTable st, 
     for (int k = threadIdx.x; k < H; k += 256) z[k] = tanhf(enc[k] + prd[k]);
 }
 
-// f^W_1 for one row of scores per wavefront (4 rows per workgroup): lse, lpb, lpy of node r0 + i.
+// f^W_1 for one row of scores per wavefront (4 rows per workgroup): lse, emissions of node r0 + i.
 __global__ __launch_bounds__(256) void k_rows_stats_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1,
                                                         long long r0, long long n, const float* __restrict__ S) {
     const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -440,8 +439,7 @@ __global__ __launch_bounds__(256) void k_rows_stats_f32(Problem pr, SampleTable 
     const float lse = M + logf(wave_sum(ssum));
     if (lane == 0) {
         ls.lse[p.idx] = lse;
-        ls.lpb[p.idx] = row[pr.blank] - lse;
-        ls.lpy[p.idx] = (label >= 0) ? row[label] - lse : 0.0f;
+        ls.em[p.idx] = emissions(row[pr.blank] - lse, label >= 0 ? row[label] - lse : EMISSION_FLOOR);
     }
 }
 

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void k_tile_flags(SelectArgs a) {
     const int t = tp.t0 + (lane >> tp.us), u = tp.u0 + (lane & (tp.uw - 1));
     float lg = RNNT_NEG_INF;
     if (t < tp.T && u <= tp.U) {
-        const long long idx = (a.st.row_off[tp.s] - a.ls.row_base) + (long long)t * (tp.U + 1) + u;
+        const long long idx = (a.st.row_off[tp.s] - a.ls.row_base) + lattice_index(tp.T, tp.U + 1, t, u);
         lg = a.ls.alpha[idx] + a.ls.beta[idx] - a.ls.lnP[tp.s];
         if (a.ls.weight) lg += __logf(a.ls.weight[tp.s]);
     }

@@ -70,8 +70,7 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     // lattice sweep can run while its neighbour's state is still in use
     const size_t lat_elems = (size_t)lat_cap * (size_t)p.lat_buffers;
     p.off_lse = take(lat_elems * 4);
-    p.off_lpb = take(lat_elems * 4);
-    p.off_lpy = take(lat_elems * 4);
+    p.off_em = take(align_up(lat_elems * 4, WS_ALIGN) * 2);
     p.off_alpha = take(lat_elems * 4);
     p.off_beta = take(lat_elems * 4);
     p.lattice_bytes = o - lat0;

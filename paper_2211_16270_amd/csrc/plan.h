@@ -57,7 +57,7 @@ struct Plan {
     size_t off_n_active = 0;           // skip_log2 > 0: per group the number of tiles that stay (their list lies in the
                                        // tile_esum array, over the entries of the same tiles)
     size_t off_wpack = 0, off_wq = 0;
-    size_t off_lse = 0, off_lpb = 0, off_lpy = 0, off_alpha = 0, off_beta = 0;
+    size_t off_lse = 0, off_em = 0, off_alpha = 0, off_beta = 0;
     size_t off_dh = 0, off_z = 0, off_kept_max = 0;
     size_t off_dz32 = 0;                // fp32 GEMM form: dZ [chunk_rows, H]; off_dh, off_z hold S and Z as fp32
     size_t off_stage_enc = 0, off_stage_pred = 0;   // fp32 [stage_samples, T_max, H], [stage_samples, U_max+1, H]

@@ -63,6 +63,19 @@ def test_f32_moderate_shape_and_group_splitting():
     assert_parity(got2, ref, "f32", "mid32 min workspace")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("U", [62, 63, 64, 127, 130, 511, 512, 700])
+def test_lattice_columns_around_the_wavefronts_of_a_sweep(U, dtype):
+    """A sweep's wavefronts hold 64 label positions each (eight of them at most in one kernel, sixteen in the other)."""
+    H, V = (16, 12) if dtype == "f32" else (128, 256)
+    wl = synth.custom_workload("cols", B=3, T_max=19, U_max=U, H=H, V=V, dtype=dtype, index=135)
+    batch = synth.with_lengths(synth.make_batch(wl), [19, 1, 10], [U, U - 1, U // 2])
+    got, ref = run_gpu(batch), run_oracle(batch)
+    e, errs = assert_parity(got, ref, dtype, f"U {U} {dtype}")
+    _say("columns", U, dtype, e, errs)
+    assert_padding_zero(got, batch)
+
+
 # ------------------------------------------------------------------ fp32 MFMA GEMM form (H, V multiples of 4, >= 64)
 @pytest.mark.parametrize("H,V", [(128, 128), (256, 384), (384, 128), (64, 64), (68, 100), (320, 1000), (132, 72)])
 def test_f32_gemm_form_against_the_checker(H, V):
