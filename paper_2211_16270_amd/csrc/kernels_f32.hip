@@ -1,5 +1,5 @@
 // fp32 path.  Two forms:
-//  * plain FMA kernels, one wavefront per lattice node, for any H, V (the small fp32 workloads);
+//  * plain FMA kernels for any H, V (the small fp32 workloads);
 //  * for H and V multiples of 4 from 64 on, the same steps over chunks of lattice nodes as matrix GEMMs of fp32
 //    precision (operands as three bf16 parts, k_gemm_f32) with row kernels between them:
 //      Z = tanh(enc_t + pred_u)              (Eq. 4)            k_rows_z_f32
@@ -49,86 +49,155 @@ __device__ __forceinline__ NodePos locate_node(const SampleTable& st, long long 
     return p;
 }
 
-// Eq. (4), Eq. (6), f^W_1 for one lattice node per wavefront.
-__global__ __launch_bounds__(64) void k_fwd_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1,
-                                                long long rows) {
-    extern __shared__ float zs[];  // [H]
-    const long long r = blockIdx.x;
-    if (r >= rows) return;
-    const int lane = threadIdx.x;
-    const NodePos p = locate_node(st, ls.row_base, s0, s1, r);
-    const int H = pr.H, V = pr.V;
-    const float* enc = (const float*)pr.enc + ((size_t)p.s * pr.T_max + p.t) * H;
-    const float* prd = (const float*)pr.pred + ((size_t)p.s * (pr.U_max + 1) + p.u) * H;
-    for (int k = lane; k < H; k += 64) zs[k] = tanhf(enc[k] + prd[k]);
-    __syncthreads();
-    const float* W = (const float*)pr.W;
-    const int label = (p.u < p.U) ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
-    float m = RNNT_NEG_INF, ssum = 0.0f, cap_b = RNNT_NEG_INF, cap_y = RNNT_NEG_INF;
-    for (int v = lane; v < V; v += 64) {
-        float acc = 0.0f;
-        for (int k = 0; k < H; ++k) acc = fmaf(zs[k], W[(size_t)k * V + v], acc);
-        acc += pr.b_out[v];
-        if (v == pr.blank) cap_b = acc;
-        if (v == label) cap_y = acc;
-        const float mn = fmaxf(m, acc);
-        ssum = ssum * expf(m - mn) + expf(acc - mn);
-        m = mn;
+// ---- plain kernels, any H and V: a workgroup takes `nodes` lattice nodes, their joint rows and scores lie in LDS, and W_out too where it is small.
+// Threads stand in rows of G (a power of two, at most 64) over the vocabulary resp. the hidden columns.  What bounds them: latency; these are calls of
+// a few thousand nodes at most.  One node per wavefront before: every node added its H V products to dW_out with atomics of its own, here
+// a workgroup's nodes are summed first.  A call, H = 32, V = 16, 240 nodes 46.7 -> 25.0 us (43.4 with the present sweep and the old kernels); H = 63,
+// V = 99, 5 k nodes 510 -> 97; H = 301, V = 1001, 300 nodes 1328 -> 589.
+
+namespace {
+
+constexpr int PLAIN_NODES = 16;            // most nodes per workgroup
+constexpr size_t PLAIN_W = 24 * 1024;      // bytes of W_out that are kept in LDS
+constexpr size_t PLAIN_ROWS = 64 * 1024;   // bytes of rows, for more than one node
+
+struct PlainShape {
+    int nodes;                             // per workgroup
+    int w_pitch;                           // floats per row of W_out in LDS (odd: rows start in different banks), 0: W_out stays in memory
+    int gv, gh;                            // log2 of the thread rows over the vocabulary, the hidden columns
+    size_t smem;
+};
+// Few nodes: small workgroups, so that there are enough of them (240 nodes: 60).
+inline PlainShape plain_shape(int H, int V, long long rows) {
+    auto log2_up = [](int n) { int g = 0; while (g < 6 && (1 << g) < n) ++g; return g; };
+    PlainShape s{};
+    s.nodes = rows >= 4096 ? 16 : rows >= 1024 ? 8 : 4;
+    const size_t row = (size_t)(H + V) * 4;
+    while (s.nodes > 1 && s.nodes * row > PLAIN_ROWS) s.nodes /= 2;
+    s.w_pitch = (size_t)H * (V | 1) * 4 <= PLAIN_W ? V | 1 : 0;
+    s.gv = log2_up(V);
+    s.gh = log2_up(H);
+    s.smem = s.nodes * row + (size_t)H * s.w_pitch * 4;
+    return s;
+}
+
+// z[i][H] = tanh(enc_t + pred_u), h[i][V] = scores of the workgroup's n nodes; W: W_out as the caller reads it (LDS or memory, pitch ldw)
+struct PlainRows {
+    float* z;
+    float* h;
+    const float* W;
+    int ldw;
+};
+__device__ __forceinline__ PlainRows plain_scores(const Problem& pr, const PlainShape& sh, const NodePos* node, int n, float* smem) {
+    const int H = pr.H, V = pr.V, tid = threadIdx.x;
+    const float* Wg = (const float*)pr.W;
+    PlainRows r{smem, smem + (size_t)sh.nodes * H, Wg, V};
+    const int rv = tid >> sh.gv, cv = tid & ((1 << sh.gv) - 1), nv = 256 >> sh.gv;
+    if (sh.w_pitch) {
+        float* Wl = r.h + (size_t)sh.nodes * V;
+        for (int k = rv; k < H; k += nv)
+            for (int v = cv; v < V; v += 1 << sh.gv) Wl[k * sh.w_pitch + v] = Wg[(size_t)k * V + v];
+        r.W = Wl;
+        r.ldw = sh.w_pitch;
     }
-    const float M = wave_max(m);
-    const float S = wave_sum(m == RNNT_NEG_INF ? 0.0f : ssum * expf(m - M));
-    const float lse = M + logf(S);
-    cap_b = wave_max(cap_b);
-    cap_y = wave_max(cap_y);
-    if (lane == 0) {
-        ls.lse[p.idx] = lse;
-        ls.em[p.idx] = emissions(cap_b - lse, p.u < p.U ? cap_y - lse : EMISSION_FLOOR);
+    __syncthreads();                       // (the nodes, too)
+    for (int i = tid >> sh.gh; i < n; i += 256 >> sh.gh) {
+        const float* enc = (const float*)pr.enc + ((size_t)node[i].s * pr.T_max + node[i].t) * H;
+        const float* prd = (const float*)pr.pred + ((size_t)node[i].s * (pr.U_max + 1) + node[i].u) * H;
+        for (int k = tid & ((1 << sh.gh) - 1); k < H; k += 1 << sh.gh) r.z[i * H + k] = tanhf(enc[k] + prd[k]);
+    }
+    __syncthreads();
+    for (int i = rv; i < n; i += nv)
+        for (int v = cv; v < V; v += 1 << sh.gv) {
+            float acc = 0.0f;
+#pragma unroll 8
+            for (int k = 0; k < H; ++k) acc = fmaf(r.z[i * H + k], r.W[(size_t)k * r.ldw + v], acc);
+            r.h[i * V + v] = acc + pr.b_out[v];
+        }
+    return r;
+}
+__device__ __forceinline__ int node_label(const Problem& pr, const NodePos& p) {
+    return p.u < p.U ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
+}
+
+}  // namespace
+
+// Eq. (4), Eq. (6), f^W_1
+__global__ __launch_bounds__(256) void k_fwd_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1, long long rows,
+                                                 PlainShape sh) {
+    extern __shared__ float smem[];
+    __shared__ NodePos node[PLAIN_NODES];
+    const long long r0 = (long long)blockIdx.x * sh.nodes;
+    const int n = rows - r0 < sh.nodes ? (int)(rows - r0) : sh.nodes, V = pr.V;
+    if ((int)threadIdx.x < n) node[threadIdx.x] = locate_node(st, ls.row_base, s0, s1, r0 + threadIdx.x);
+    const PlainRows rw = plain_scores(pr, sh, node, n, smem);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x >> 6; i < n; i += 4) {
+        const float* h = rw.h + i * V;
+        float m = RNNT_NEG_INF;
+        for (int v = lane; v < V; v += 64) m = fmaxf(m, h[v]);
+        const float M = wave_max(m);
+        float ssum = 0.0f;
+        for (int v = lane; v < V; v += 64) ssum += expf(h[v] - M);
+        const float lse = M + logf(wave_sum(ssum));
+        if (lane == 0) {
+            const int label = node_label(pr, node[i]);
+            ls.lse[node[i].idx] = lse;
+            ls.em[node[i].idx] = emissions(h[pr.blank] - lse, label >= 0 ? h[label] - lse : EMISSION_FLOOR);
+        }
     }
 }
 
-// f^W_4 and Algorithm 1 lines 8, 10, 11 for one lattice node per wavefront.
-__global__ __launch_bounds__(64) void k_bwd_f32(Problem pr, SampleTable st, LatticeState ls, GradOut go, int s0,
-                                                int s1, long long rows) {
-    extern __shared__ float sm[];  // z[H], dh[V]
-    const long long r = blockIdx.x;
-    if (r >= rows) return;
-    const int lane = threadIdx.x;
-    const NodePos p = locate_node(st, ls.row_base, s0, s1, r);
-    const int H = pr.H, V = pr.V;
-    float* zs = sm;
-    float* dh = sm + H;
-    const float* enc = (const float*)pr.enc + ((size_t)p.s * pr.T_max + p.t) * H;
-    const float* prd = (const float*)pr.pred + ((size_t)p.s * (pr.U_max + 1) + p.u) * H;
-    for (int k = lane; k < H; k += 64) zs[k] = tanhf(enc[k] + prd[k]);
-    __syncthreads();
-    const float* W = (const float*)pr.W;
-    const int label = (p.u < p.U) ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
-    const RowPost rp = row_posteriors(ls, p.idx, p.t, p.u, p.T, p.U, p.s);
-    const float off = rp.log_gamma - ls.lse[p.idx];
-    for (int v = lane; v < V; v += 64) {
-        float acc = 0.0f;
-        for (int k = 0; k < H; ++k) acc = fmaf(zs[k], W[(size_t)k * V + v], acc);
-        acc += pr.b_out[v];
-        float d = expf(acc + off);
-        if (v == pr.blank) d -= rp.Bk;
-        if (v == label) d -= rp.Yk;
-        dh[v] = d;
-        atomicAdd(&go.db[v], d);
+// f^W_4 and Algorithm 1 lines 8, 10, 11
+__global__ __launch_bounds__(256) void k_bwd_f32(Problem pr, SampleTable st, LatticeState ls, GradOut go, int s0, int s1, long long rows,
+                                                 PlainShape sh) {
+    extern __shared__ float smem[];
+    __shared__ NodePos node[PLAIN_NODES];
+    __shared__ RowPost post[PLAIN_NODES];
+    __shared__ float lse[PLAIN_NODES];
+    __shared__ int label[PLAIN_NODES];
+    const long long r0 = (long long)blockIdx.x * sh.nodes;
+    const int n = rows - r0 < sh.nodes ? (int)(rows - r0) : sh.nodes, tid = threadIdx.x, H = pr.H, V = pr.V;
+    if (tid < n) {
+        const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + tid);
+        node[tid] = p;
+        post[tid] = row_posteriors(ls, p.idx, p.t, p.u, p.T, p.U, p.s);
+        lse[tid] = ls.lse[p.idx];
+        label[tid] = node_label(pr, p);
+    }
+    const PlainRows rw = plain_scores(pr, sh, node, n, smem);
+    const int rv = tid >> sh.gv, cv = tid & ((1 << sh.gv) - 1), nv = 256 >> sh.gv;
+    // (each thread the scores it has formed itself)
+    for (int i = rv; i < n; i += nv) {
+        const float off = post[i].log_gamma - lse[i];
+        for (int v = cv; v < V; v += 1 << sh.gv) {
+            float d = expf(rw.h[i * V + v] + off);
+            if (v == pr.blank) d -= post[i].Bk;
+            if (v == label[i]) d -= post[i].Yk;
+            rw.h[i * V + v] = d;
+        }
     }
     __syncthreads();
-    float* d_enc = go.d_enc + ((size_t)p.s * pr.T_max + p.t) * H;
-    float* d_prd = go.d_pred + ((size_t)p.s * (pr.U_max + 1) + p.u) * H;
-    for (int k = 0; k < H; ++k) {
-        const float zk = zs[k];
-        float part = 0.0f;
-        for (int v = lane; v < V; v += 64) {
-            const float d = dh[v];
-            part = fmaf(d, W[(size_t)k * V + v], part);
-            atomicAdd(&go.dW[(size_t)k * V + v], zk * d);
+    for (int v = tid; v < V; v += 256) {
+        float sum = 0.0f;
+        for (int i = 0; i < n; ++i) sum += rw.h[i * V + v];
+        atomicAdd(&go.db[v], sum);
+    }
+    for (int k = rv; k < H; k += nv)
+        for (int v = cv; v < V; v += 1 << sh.gv) {
+            float sum = 0.0f;
+            for (int i = 0; i < n; ++i) sum = fmaf(rw.z[i * H + k], rw.h[i * V + v], sum);
+            atomicAdd(&go.dW[(size_t)k * V + v], sum);
         }
-        part = wave_sum(part);
-        if (lane == 0) {
-            const float dx = part * (1.0f - zk * zk);
+    for (int i = tid >> sh.gh; i < n; i += 256 >> sh.gh) {
+        float* d_enc = go.d_enc + ((size_t)node[i].s * pr.T_max + node[i].t) * H;
+        float* d_prd = go.d_pred + ((size_t)node[i].s * (pr.U_max + 1) + node[i].u) * H;
+        for (int k = tid & ((1 << sh.gh) - 1); k < H; k += 1 << sh.gh) {
+            float dz = 0.0f;
+#pragma unroll 8
+            for (int v = 0; v < V; ++v) dz = fmaf(rw.h[i * V + v], rw.W[(size_t)k * rw.ldw + v], dz);
+            const float zk = rw.z[i * H + k], dx = dz * (1.0f - zk * zk);
             atomicAdd(&d_enc[k], dx);
             atomicAdd(&d_prd[k], dx);
         }
@@ -138,14 +207,16 @@ __global__ __launch_bounds__(64) void k_bwd_f32(Problem pr, SampleTable st, Latt
 hipError_t launch_fwd_f32(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0, int s1,
                           long long rows, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
-    k_fwd_f32<<<dim3((unsigned)rows), dim3(64), (size_t)pr.H * 4, stream>>>(pr, st, ls, s0, s1, rows);
+    const PlainShape sh = plain_shape(pr.H, pr.V, rows);
+    k_fwd_f32<<<dim3((unsigned)((rows + sh.nodes - 1) / sh.nodes)), dim3(256), sh.smem, stream>>>(pr, st, ls, s0, s1, rows, sh);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const Problem& pr, const SampleTable& st, const LatticeState& ls, const GradOut& go,
                           int s0, int s1, long long rows, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
-    k_bwd_f32<<<dim3((unsigned)rows), dim3(64), (size_t)(pr.H + pr.V) * 4, stream>>>(pr, st, ls, go, s0, s1, rows);
+    const PlainShape sh = plain_shape(pr.H, pr.V, rows);
+    k_bwd_f32<<<dim3((unsigned)((rows + sh.nodes - 1) / sh.nodes)), dim3(256), sh.smem, stream>>>(pr, st, ls, go, s0, s1, rows, sh);
     return hipGetLastError();
 }
 

@@ -186,11 +186,12 @@ __device__ __forceinline__ float lattice_sweep(const SampleTable& st, const Latt
     if (!BETA && v == U) {
         // alpha[T-1,U] and the final blank
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const float lnP_off = *(volatile const float*)(out + (n - 1)) + (em[n - 1].x + c);
-        const bool none = lnP_off < 0.1f * EMISSION_FLOOR;           // no alignment has a probability above 0
-        ls.lnP[s] = none ? RNNT_NEG_INF : lnP_off;
-        ls.shift[s] = c;
-        loss[s] = none ? -RNNT_NEG_INF : -(lnP_off - c * (float)(T + U));
+        const double lnP2 = *(volatile const float*)(out + (n - 1)) / (double)LN2_F + fma((double)em[n - 1].x, (double)LOG2E_F, (double)c2);
+        const bool none = lnP2 < 0.1 * EMISSION_FLOOR;               // no alignment has a probability above 0
+        ls.lnP[s] = none ? RNNT_NEG_INF : (float)(lnP2 * LN2_F);
+        ls.shift[s] = c2 * LN2_F;
+        // (the offset as it was added, T + U times, and the emissions as they were scaled: neither one's rounding stays in the loss)
+        loss[s] = none ? -RNNT_NEG_INF : (float)(((double)c2 * (T + U) - lnP2) / LOG2E_F);
     }
     return 0.0f;
 }

@@ -46,6 +46,25 @@ def test_f32_degenerate_and_ragged_lattices(T_len, U_len, blank):
     assert_padding_zero(got, batch)
 
 
+@pytest.mark.parametrize("H,V,B,T,U", [
+    (1, 2, 2, 7, 3),                # the least network
+    (63, 99, 3, 30, 8),             # W_out in LDS, 4 nodes per workgroup
+    (65, 63, 5, 40, 7),             # thread rows of 64 with a rest; 8 nodes
+    (13, 7, 8, 60, 15),             # 16 nodes, short thread rows
+    (301, 1001, 2, 20, 5),          # W_out stays in memory
+    (2047, 5001, 1, 4, 2),          # two nodes' rows fill the LDS
+    (4095, 16383, 1, 2, 1),         # one node's rows
+])
+def test_f32_plain_kernels(H, V, B, T, U):
+    wl = synth.custom_workload("plain32", B=B, T_max=T, U_max=U, H=H, V=V, dtype="f32", index=136,
+                               t_rule="uniform", t_lo=max(1, T // 2), u_rule="uniform", u_lo=0)
+    batch = synth.make_batch(wl)
+    got, ref = run_gpu(batch), run_oracle(batch)
+    e, errs = assert_parity(got, ref, "f32", f"plain fp32 {H} {V}")
+    _say("plain fp32", H, V, e, errs)
+    assert_padding_zero(got, batch)
+
+
 def test_f32_moderate_shape_and_group_splitting():
     wl = synth.custom_workload("mid32", B=5, T_max=33, U_max=12, H=48, V=70, dtype="f32", index=102,
                                t_rule="uniform", t_lo=5, u_rule="uniform", u_lo=0)
