@@ -10,8 +10,8 @@ constexpr int JT_ROWS = 64;       // rows of a lattice tile
 
 // ------------------------------------------------------------------------------------------------
 // dW += Z^T dH and db += column sums of dH (Alg. 1 line 8) as one split-K GEMM with 256x256 tiles.
-// 256 threads = 4 waves in 2 (hidden) x 2 (vocabulary), one per SIMD; each wave owns 128 x 128 = 4 x 4
-// accumulator tiles (256 accumulator registers), so that a k16-step reads 8 fragments from LDS for 16
+// 512 threads = 8 waves in 2 (hidden) x 4 (vocabulary), two per SIMD; each wave owns 128 x 64 = 4 x 2
+// accumulator tiles, so that a k16-step reads 6 fragments from LDS for 8
 // MFMAs and every byte of a stage feeds 128 flops.  Both operands, Z [rows,H] and dH [rows,V], lie in 1 KiB fragments of
 // 32 rows x 16 columns (device_common.h), eight columns of a row together, so the 256 columns of a tile are 16 KiB in one piece, and the
 // contraction index (the chunk's rows) is the slow one inside a fragment.  Stages of 32 rows travel global -> LDS asynchronously (global_load_lds, no registers), five stages deep, and lie
@@ -21,6 +21,9 @@ constexpr int JT_ROWS = 64;       // rows of a lattice tile
 // into different banks.
 // The workgroups of the first hidden-tile row also sum their B fragments over the rows (the bias
 // gradient) with packed bf16 dot products against ones.
+// What bounds it: of 7.45 ms (H = 512, V = 1024, 13 M nodes, 0.58 of the tiles) the MFMAs alone take 5.4 (1.6 PFLOP/s, power), the copies 1.2, the sums
+// of the chunks before 0.4, the LDS reads 0.4.  Four waves of 128 x 128 with a stage less in flight: 8.05; eight with a stage less 7.7; V = 8192, 3.7 M nodes 20.2 ms
+// against 18.6.
 // ------------------------------------------------------------------------------------------------
 constexpr int WT = 256;       // tile edge
 constexpr int WK = 32;        // rows per pipeline stage
@@ -54,15 +57,15 @@ __device__ __forceinline__ bf16x8 lds_read_tr_frag(const unsigned char* lo_p, co
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// HALF: the last hidden tile of 128 columns; the waves stand 2 (hidden) x 2 as for a whole tile, each 64 x 128
+// HALF: the last hidden tile of 128 columns; the waves stand 2 (hidden) x 4 as for a whole tile, each 64 x 64
 template <bool BY_TILE, bool HALF>
 __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem, int split, int tile) {
     constexpr int MT = HALF ? 2 : 4;                  // 32-column blocks of the hidden side per wave
-    constexpr int AF = HALF ? 2 : 4;                  // fragments of Z a wave copies per stage
-    constexpr int DMAS = AF + 4;                      // copies per wave and stage
+    constexpr int AF = HALF ? 1 : 2;                  // fragments of Z a wave copies per stage
+    constexpr int DMAS = AF + 2;                      // copies per wave and stage
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int ntile = g.mt * g.nt;
     const int bm = tile % g.mt, bn = tile / g.mt;
     const long long m0 = (long long)bm * WT, n0 = (long long)bn * WT;
@@ -83,14 +86,14 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
     constexpr unsigned OPER_BYTES = (unsigned)WK * WT * 2u;
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dw_smem;
 
-    // global -> LDS: one DMA instruction moves one fragment; wave w moves fragments 4 w .. 4 w + 3 of dH
+    // global -> LDS: one DMA instruction moves one fragment; wave w moves fragments 2 w, 2 w + 1 of dH
     // and AF w .. of Z.  Everything but
     // the lane's 16 bytes is wave-uniform and lives in scalar registers, so issuing a DMA costs no vector instruction.
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const size_t ZB = chunk_block_bytes(g.H), DB = chunk_block_bytes(g.V);   // bytes of a block of 32 rows
     const unsigned char* Zs = g.Z + (size_t)(ks / WK) * ZB + (size_t)(m0 / 16 + AF * wv) * 1024;
-    const unsigned char* Ds = g.dH + (size_t)(ks / WK) * DB + (size_t)(n0 / 16 + 4 * wv) * 1024;
-    const unsigned dst_a = smem_base + (unsigned)(AF * wv) * 1024u, dst_b = smem_base + OPER_BYTES + (unsigned)(4 * wv) * 1024u;
+    const unsigned char* Ds = g.dH + (size_t)(ks / WK) * DB + (size_t)(n0 / 16 + 2 * wv) * 1024;
+    const unsigned dst_a = smem_base + (unsigned)(AF * wv) * 1024u, dst_b = smem_base + OPER_BYTES + (unsigned)(2 * wv) * 1024u;
     const unsigned lane_b = (unsigned)lane * 16u;
     // Block of 32 rows of stage gstep of the split, relative to the split's first; `entry` is the list entry of the stage's slot
     // (BY_TILE only).
@@ -103,11 +106,12 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
         if (!BY_TILE) return gstep;
         return ((long long)(entry - g.at.slot_tile0) << 1) + (((ks + gstep * WK) >> 5) & 1) - ks / WK;
     };
-    // Copies 2 j, 2 j + 1 of the stage whose rows are block blk, into LDS buffer buf (in pairs: M0 and its wait state once)
+    // Copies of dH (j = 0) or Z (1) of the stage whose rows are block blk, into LDS buffer buf (in pairs: M0 and its wait state once)
     auto issue_pair = [&](long long blk, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
-        if constexpr (j < 2) lds_dma16_pair<j * 2048>(Ds + blk * (long long)DB, lane_b, dst_b + buf * STAGE_BYTES);
-        else lds_dma16_pair<(j - 2) * 2048>(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
+        if constexpr (j == 0) lds_dma16_pair<0>(Ds + blk * (long long)DB, lane_b, dst_b + buf * STAGE_BYTES);
+        else if constexpr (HALF) lds_dma16_s(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
+        else lds_dma16_pair<0>(Zs + blk * (long long)ZB, lane_b, dst_a + buf * STAGE_BYTES);
     };
     // fragment addresses: lane = 16 g + 4 j + c supplies row 8*(g/2) + j, columns 16*(g%2) + 4c .. +3 of a 32-column tile: granule
     // (row, c/2) of fragment 2 * tile + g % 2, at position 32 (c/2) + (row ^ 4 (2 (g % 2) + c/2))
@@ -117,48 +121,47 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
     const unsigned f_lo = fbase + (unsigned)(((8 * (fg >> 1)) ^ fswz) + fj) * 16u;
     const unsigned f_hi = fbase + (unsigned)(((8 * (fg >> 1) + 4) ^ fswz) + fj) * 16u;
     const unsigned a_lo = f_lo + (unsigned)(wm * MT) * 2048u, a_hi = f_hi + (unsigned)(wm * MT) * 2048u;
-    const unsigned b_lo = f_lo + OPER_BYTES + (unsigned)wn * 8192u, b_hi = f_hi + OPER_BYTES + (unsigned)wn * 8192u;
+    const unsigned b_lo = f_lo + OPER_BYTES + (unsigned)wn * 4096u, b_hi = f_hi + OPER_BYTES + (unsigned)wn * 4096u;
 
-    f32x16 acc[MT][4];
+    f32x16 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
-    float dbs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
+    float dbs[2] = {0.0f, 0.0f};
     const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
 
     const long long nsteps = ke > ks ? (ke - ks) / WK : 0;   // a split beyond the chunk still writes its slot
     if (nsteps == 0 && !g.first) return;                     // ... unless the slot already holds a sum: nothing to add
     static_assert(WK == 32, "the loop below is written for two k16-steps per stage");
-    bf16x8 fa[2][MT], fb[2][4];
+    bf16x8 fa[2][MT], fb[2][2];
     auto read_frags = [&](int set, unsigned buf, int kk) {
         const unsigned char* st = dw_smem + buf * STAGE_BYTES + kk * 256;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) fa[set][mt] = lds_read_tr_frag(st + a_lo + mt * 2048, st + a_hi + mt * 2048);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) fb[set][nt] = lds_read_tr_frag(st + b_lo + nt * 2048, st + b_hi + nt * 2048);
+        for (int nt = 0; nt < 2; ++nt) fb[set][nt] = lds_read_tr_frag(st + b_lo + nt * 2048, st + b_hi + nt * 2048);
     };
-    // The 4 MT MFMAs of one k16-step (register set `set`); behind each of the first MT + 4, one fragment of the
+    // The 2 MT MFMAs of one k16-step (register set `set`); behind each of the first MT + 2, one fragment of the
     // following k16-step is read into the other set.  An MFMA keeps the matrix pipe busy for 32 clocks but
-    // the issue port only briefly: the reads go out in its shadow, and the last of them is 8 MFMAs (HALF: 2) old when
-    // the step ends.
-    // Behind every second of the last DMAS of a stage's second step go two copies of a later stage.
+    // the issue port only briefly: the reads go out in its shadow.  Behind two of the last four of a stage's second step go the copies of a later
+    // stage.
     auto multiply = [&](auto set_tag, unsigned next_buf, int next_kk, long long dma_block, unsigned dma_buf) {
         constexpr int set = decltype(set_tag)::value;
         const unsigned char* st = dw_smem + next_buf * STAGE_BYTES + next_kk * 256;
-        static_for<0, 4 * MT>([&](auto idx_tag) {
-            constexpr int idx = decltype(idx_tag)::value, mt = idx >> 2, nt = idx & 3;
+        static_for<0, 2 * MT>([&](auto idx_tag) {
+            constexpr int idx = decltype(idx_tag)::value, mt = idx >> 1, nt = idx & 1;
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
             if constexpr (idx < MT) fa[set ^ 1][idx] = lds_read_tr_frag(st + a_lo + idx * 2048, st + a_hi + idx * 2048);
-            else if constexpr (idx < MT + 4)
+            else if constexpr (idx < MT + 2)
                 fb[set ^ 1][idx - MT] = lds_read_tr_frag(st + b_lo + (idx - MT) * 2048, st + b_hi + (idx - MT) * 2048);
-            if constexpr (set == 1 && idx >= 4 * MT - DMAS && (idx - (4 * MT - DMAS)) % 2 == 0)
-                issue_pair(dma_block, dma_buf, std::integral_constant<int, (idx - (4 * MT - DMAS)) / 2>{});
+            if constexpr (set == 1 && idx >= 2 * MT - 4 && idx % 2 == 0)
+                issue_pair(dma_block, dma_buf, std::integral_constant<int, (idx - (2 * MT - 4)) / 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
         if (do_db) {
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
+            for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                 for (int q2 = 0; q2 < 4; ++q2) {
                     const bf16x2 pr2 = {fb[set][nt][2 * q2], fb[set][nt][2 * q2 + 1]};
@@ -166,40 +169,37 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
                 }
         }
     };
-    // Four stages in flight before the first one is consumed (DMAS copies per wave and stage).
-    // One wave per SIMD: nothing else hides an LDS read or the issue of a DMA, so both are spread over the
-    // MFMAs (see multiply).  The hand-over to the next stage (wait for this wave's copies, then for
-    // everyone's) sits in the middle of a stage.  Beyond the last stage the pipeline keeps re-loading the
+    // Five stages in flight before the first one is consumed (DMAS copies per wave and stage).  The hand-over to the next stage (wait
+    // for this wave's copies, then for everyone's) sits in the middle of a stage; there every wave has read all its fragments of the
+    // present one, whose buffer may be refilled.  Beyond the last stage the pipeline keeps re-loading the
     // last one into buffers nobody reads any more, which keeps the loop free of branches and the number of
     // copies in flight constant.
     if (nsteps > 0) {
         const long long last = nsteps - 1;
 #pragma unroll
-        for (int s4 = 0; s4 < WST - 1; ++s4) {
-            const long long gs = s4 < last ? s4 : last;
+        for (int s5 = 0; s5 < WST; ++s5) {
+            const long long gs = s5 < last ? s5 : last;
             const long long blk = stage_block(gs, stage_entry(gs));
-            static_for<0, DMAS / 2>([&](auto j) { issue_pair(blk, (unsigned)s4, j); });
+            static_for<0, 2>([&](auto j) { issue_pair(blk, (unsigned)s5, j); });
         }
-        int entry_ahead = stage_entry(4 < last ? 4 : last);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * DMAS) : "memory");
+        int entry_ahead = stage_entry(WST < last ? WST : last);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WST - 1) * DMAS) : "memory");
         __syncthreads();
         read_frags(0, 0, 0);
-        unsigned buf = 0, refill = WST - 1;             // of stage it, of stage it + 4
+        unsigned buf = 0;                               // of stage it
         for (long long it = 0; it < nsteps; ++it) {
             const unsigned next = buf + 1 == WST ? 0 : buf + 1;
             __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);     // set 0 landed (read behind the first MFMAs of the step before)
             __builtin_amdgcn_sched_barrier(0);
-            const long long dma_block = stage_block(it + 4 < last ? it + 4 : last, entry_ahead);
-            entry_ahead = stage_entry(it + 5 < last ? it + 5 : last);      // arrives during this iteration
+            const long long dma_block = stage_block(it + WST < last ? it + WST : last, entry_ahead);
+            entry_ahead = stage_entry(it + WST + 1 < last ? it + WST + 1 : last);      // arrives during this iteration
             multiply(std::integral_constant<int, 0>{}, buf, 1, 0, 0);
             __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);     // set 1 landed
-            // stage it+1 landed (it+2 and it+3 stay in flight); every wave is past stage it-1, whose buffer
-            // takes stage it+4
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DMAS) : "memory");
+            // stage it + 1 landed; the later ones stay in flight
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WST - 2) * DMAS) : "memory");
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
-            multiply(std::integral_constant<int, 1>{}, next, 0, dma_block, refill);
-            refill = buf;
+            multiply(std::integral_constant<int, 1>{}, next, 0, dma_block, buf);
             buf = next;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no copy may land after the workgroup has ended
@@ -208,11 +208,11 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
     // and four accumulator rows): no atomics, and the same workgroup adds the next chunk's product.
     {
         f32x4* slot = reinterpret_cast<f32x4*>(g.slots) +
-                      (((size_t)split * ntile + tile) * 4 + wave) * (size_t)(4 * 4 * 4 * 64) + lane;
+                      (((size_t)split * ntile + tile) * 4 + (wm * 2 + (wn >> 1))) * (size_t)(4 * 4 * 4 * 64) + (wn & 1) * (2 * 4 * 64) + lane;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
+            for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     f32x4 v = {acc[mt][nt][4 * j], acc[mt][nt][4 * j + 1], acc[mt][nt][4 * j + 2],
@@ -224,9 +224,9 @@ __device__ __forceinline__ void dw_tile(const DwArgs& g, unsigned char* dw_smem,
     }
     if (do_db) {
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < 2; ++nt) {
             float v = dbs[nt] + __shfl_xor(dbs[nt], 32, 64);
-            if (hb == 0) atomicAdd(&g.db[n0 + wn * 128 + nt * 32 + l32], v);
+            if (hb == 0) atomicAdd(&g.db[n0 + wn * 64 + nt * 32 + l32], v);
         }
     }
 }

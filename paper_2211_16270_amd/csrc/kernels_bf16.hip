@@ -109,7 +109,7 @@ hipError_t launch_kept_to_dh_bf16(const Problem& pr, const SampleTable& st, cons
 }
 
 template <bool BY_TILE>
-__global__ __launch_bounds__(256) void k_gemm_dw256(DwArgs g) {
+__global__ __launch_bounds__(512) void k_gemm_dw256(DwArgs g) {
     extern __shared__ __align__(16) unsigned char dw_smem[];
     dw_workgroup<BY_TILE>(g, dw_smem, blockIdx.x);
 }
@@ -129,8 +129,8 @@ hipError_t launch_gemm_dw_bf16(int H, int V, long long rows, int splits, int fir
         configured = true;
     }
     const dim3 grid((unsigned)dw_grid(H, V, splits));
-    if (at.active && at.slot_tile0 >= 0) k_gemm_dw256<true><<<grid, dim3(256), DW_SMEM, stream>>>(g);
-    else k_gemm_dw256<false><<<grid, dim3(256), DW_SMEM, stream>>>(g);
+    if (at.active && at.slot_tile0 >= 0) k_gemm_dw256<true><<<grid, dim3(512), DW_SMEM, stream>>>(g);
+    else k_gemm_dw256<false><<<grid, dim3(512), DW_SMEM, stream>>>(g);
     return hipGetLastError();
 }
 

@@ -2,19 +2,22 @@
 //   dz = dH W_out^T   (dH [rows,V] from the chunk buffer, contraction over the vocabulary),
 //   dx = dz (1 - z^2),  d_enc[t] += sum_u dx,  d_pred[u] += sum_t dx  per lattice tile (64 rows: 8 frames x 8 labels or 16 x 4).
 //
-// 256x256 output tile (4 lattice tiles x 256 hidden) per workgroup; 256 threads = 4 waves in 2 x 2, one per
-// SIMD, each 128 x 128 = 4 x 4 accumulator tiles (256 accumulator registers), so that one k16-step is 8
-// LDS fragment reads for 16 MFMAs.  Where only 128 hidden columns are left (H not a multiple of 256) the waves stand 4 x 1, each 64 x 128.
+// 256x256 output tile (4 lattice tiles x 256 hidden) per workgroup; 512 threads = 8 waves in 2 x 4, two per SIMD, each 128 x 64 = 4 x 2
+// accumulator tiles, so that one k16-step is 6 LDS fragment reads for 8 MFMAs, and one wave's waits and epilogue stand beside the other's
+// work.  (Four waves of 128 x 128, one per SIMD, read a third less from LDS and were slower, see below.)  Where only 128 hidden columns are left
+// (H not a multiple of 256) the waves stand 4 x 2, each 64 x 64.
 // Both operands lie in memory as MFMA fragments of 1 KiB (dH: device_common.h; W_out: the packed copy
 // [V/16][H/32]), so stages of 32 vocabulary entries (16 fragments of each) travel global -> LDS
 // asynchronously in whole cache lines, five stages deep, and are read back without bank conflicts.  Fragments are read one
 // k16-step ahead of their MFMAs, also across the stage hand-over.
 //
-// The epilogue costs as much as 16 stages of the loop: 1 - z^2 = 4 r (1 - r) with r = 1 / (1 + e^{2 enc} e^{2 pred}), one reciprocal per
+// Epilogue: 1 - z^2 = 4 r (1 - r) with r = 1 / (1 + e^{2 enc} e^{2 pred}), one reciprocal per
 // element from per-row exponentials; the input rows they come from are loaded before the main loop.  Everything after the product
 // is linear in dz, so the vocabulary may be split over workgroups: a launch that leaves the chip partly idle, or its last
-// round partly filled, does that.  What bounds it: that epilogue and the wait for stages, not power (H = 512, V = 1024, 106 M nodes: 2.2 GHz,
-// matrix pipes busy 35 % of the time, 0.75 PFLOP/s).
+// round partly filled, does that.
+// What bounds it: of 9.6 ms (H = 512, V = 1024, 13 M nodes, 0.58 of the tiles) the MFMAs alone take 5.3 (1.6 PFLOP/s, power), the epilogue 2.7 (0.7 of it
+// its atomics, 0.3 the reciprocals), the copies 1.1 and the LDS reads 0.3.  Four waves instead of eight, four stages deep: 10.7; V = 8192, 3.7 M nodes 19.3 ms
+// against 18.6; H = 640, V = 1024, 32 k rows 654 us against 620.  No copies past the last stage, by a branch around them: 9.8 and 19.2.
 #include "device_common.h"
 #include "gemm_dw_tile.h"
 #include "plan.h"
@@ -50,56 +53,52 @@ struct DzArgs {
 template <bool HALF>
 __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem, int bx, int n0, int n_slots, int vs) {
     constexpr int MT = HALF ? 2 : 4;                  // 32-row blocks per wave
-    constexpr int DMAS = HALF ? 6 : 8;                // copies per wave and stage
+    constexpr int DMAS = HALF ? 3 : 4;                // copies per wave and stage
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = HALF ? wv : wv >> 1, wn = HALF ? 0 : wv & 1;
+    const int wm = HALF ? wv >> 1 : wv >> 2, wn = HALF ? wv & 1 : wv & 3;
     const int H = g.pr.H, V = g.pr.V;
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dz_smem;
 
     // global -> LDS: a stage is, per operand, blocks of 32 rows (lattice rows / hidden columns) x 2 fragments of 16 entries.
-    // LDS order: A [8 row blocks][entry half], B [entry half][8 hidden blocks].  Wave w moves the row blocks of lattice tile w and hidden
-    // blocks 2 w, 2 w + 1 (HALF: w).  Everything but the lane's 16 bytes is wave-uniform.  Slots past the list's end read the last
+    // LDS order: A [8 row blocks][entry half], B [entry half][8 hidden blocks].  Wave w moves row block w (lattice tile w / 2) and, of entry half w / 4,
+    // hidden blocks 2 (w % 4) and the next (HALF: w % 4).  Everything but the lane's 16 bytes is wave-uniform.  Slots past the list's end read the last
     // listed tile again; their products are never stored.
     const size_t DB = chunk_block_bytes(V);   // bytes of a block of 32 rows of dH
     const unsigned lane_b = (unsigned)lane * 16u;
-    const bool present = bx * 4 + wv < n_slots;
-    const int entry = present ? bx * 4 + wv : n_slots - 1;
+    const int wt = wv >> 1;                           // lattice tile whose copies and input rows are this wave's
+    const bool present = bx * 4 + wt < n_slots;
+    const int entry = present ? bx * 4 + wt : n_slots - 1;
     const int tile = __builtin_amdgcn_readfirstlane(g.at.active ? g.at.active[g.at.group_tile0 + g.at.cbase + entry] : g.tile0 + entry);
     // (kept scores: wherever the forward pass has put the listed tile)
     const int slot = (g.at.active && g.at.slot_tile0 >= 0) ? tile - g.at.slot_tile0 : entry;
     const int nsteps = V / ZK / g.v_splits, step0 = vs * nsteps;
-    const unsigned char* As = g.dH + (size_t)(2 * slot) * DB + (size_t)step0 * 2048;
+    const unsigned char* As = g.dH + (size_t)(2 * slot + (wv & 1)) * DB + (size_t)step0 * 2048;
     const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
-    const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(n0 / 32 + (HALF ? wv : 2 * wv)) * 1024;
-    // The copies of stage gstep into LDS buffer buf: both entry halves of row block j (0, 1), then of entry half j - 2 (2, 3) the hidden blocks.
+    const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(wv >> 2) * WB + (size_t)(n0 / 32 + (HALF ? wv & 3 : 2 * (wv & 3))) * 1024;
+    // The copies of stage gstep into LDS buffer buf: both entry halves of the row block (j = 0), the hidden blocks (1).
     // (In pairs: M0 and its wait state once.)
     auto issue = [&](int gstep, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
         const unsigned sb = smem_base + buf * Z_STAGE;
-        if constexpr (j < 2) {
-            lds_dma16_pair<0>(As + j * DB + (size_t)gstep * 2048, lane_b, sb + (unsigned)(2 * wv + j) * 2048u);
-        } else if constexpr (HALF) {
-            constexpr int eh = j - 2;
-            lds_dma16_s(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + wv) * 1024u);
-        } else {
-            constexpr int eh = j - 2;
-            lds_dma16_pair<0>(Bs + (size_t)(2 * gstep + eh) * WB, lane_b, sb + Z_OPER + (unsigned)(eh * 8 + 2 * wv) * 1024u);
-        }
+        if constexpr (j == 0) lds_dma16_pair<0>(As + (size_t)gstep * 2048, lane_b, sb + (unsigned)wv * 2048u);
+        else if constexpr (HALF)
+            lds_dma16_s(Bs + (size_t)gstep * 2 * WB, lane_b, sb + Z_OPER + (unsigned)((wv >> 2) * 8 + (wv & 3)) * 1024u);
+        else lds_dma16_pair<0>(Bs + (size_t)gstep * 2 * WB, lane_b, sb + Z_OPER + (unsigned)((wv >> 2) * 8 + 2 * (wv & 3)) * 1024u);
     };
     const int last = nsteps - 1;
 #pragma unroll
-    for (int s4 = 0; s4 < ZST - 1; ++s4)
-        static_for<0, 4>([&](auto j) { issue(s4 < last ? s4 : last, (unsigned)s4, j); });
+    for (int s5 = 0; s5 < ZST; ++s5)
+        static_for<0, 2>([&](auto j) { issue(s5 < last ? s5 : last, (unsigned)s5, j); });
 
-    // the epilogue's input rows, this wave's lattice tile: lane = 8 columns of rows (lane / 32) + 2 i (zero outside the sample)
+    // the epilogue's input rows, half of a lattice tile's per wave: lane = 8 columns of every second (HALF: fourth) row (zero outside the sample)
     const TilePos tp = locate_tile(g.st, tile);
-    constexpr int NC = HALF ? 16 : 32, RPS = 64 / NC, NR = Z_ROWS / RPS;      // 8-column pieces per row, rows per step, steps
+    constexpr int NC = HALF ? 16 : 32, RPS = 64 / NC, NR = (Z_ROWS / RPS + 1) / 2;      // 8-column pieces per row, rows per step, steps
     bf16x8 in[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        const int r = lane / NC + RPS * i, c = lane % NC, th = 64 >> tp.us, u = tp.u0 + r - th;
+        const int r = lane / NC + RPS * (NR * (wv & 1) + i), c = lane % NC, th = 64 >> tp.us, u = tp.u0 + r - th;
         const bool is_enc = r < th, ok = is_enc ? tp.t0 + r < tp.T : (r - th < tp.uw && u <= tp.U);
         const bf16_t* src = is_enc ? reinterpret_cast<const bf16_t*>(g.pr.enc) + ((size_t)tp.s * g.pr.T_max + tp.t0 + r) * H
                                    : reinterpret_cast<const bf16_t*>(g.pr.pred) + ((size_t)tp.s * (g.pr.U_max + 1) + u) * H;
@@ -109,71 +108,69 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
 
     // fragment of a row block, k16-step kk (= entry half): dH lies with its rows permuted (frag_granule), W_out in lane order
     const unsigned a_off[2] = {frag_granule(lane, 0), frag_granule(lane, 1)};
-    f32x16 acc[MT][4];
+    f32x16 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{0};
-    bf16x8 fa[2][MT], fb[2][4];
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
+    bf16x8 fa[2][MT], fb[2][2];
     auto frag_a = [&](unsigned buf, int kk, int mt) {
         return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + (wm * MT + mt) * 2048 + kk * 1024 + a_off[kk]);
     };
     auto frag_b = [&](unsigned buf, int kk, int nt) {
-        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + Z_OPER + kk * 8192 + (wn * 4 + nt) * 1024 + lane_b);
+        return *reinterpret_cast<const bf16x8*>(dz_smem + buf * Z_STAGE + Z_OPER + kk * 8192 + (wn * 2 + nt) * 1024 + lane_b);
     };
     // The MFMAs of one k16-step (register set `set`).  Behind each of the first ones, one fragment of the following k16-step is
-    // read into the other set; behind every second of the others of the second step go the copies of a later stage.  An MFMA keeps the matrix pipe
-    // busy for 32 clocks but the issue port only briefly: with one wave per SIMD nothing else would hide these instructions.
-    auto multiply = [&](auto set_tag, unsigned next_buf, auto next_kk_tag, int dma_g, unsigned dma_buf) {
+    // read into the other set; behind two of the last ones of the second step go the copies of a later stage.
+    auto multiply = [&](auto set_tag, unsigned next_buf, auto next_kk_tag, int it, unsigned buf) {
         constexpr int set = decltype(set_tag)::value, next_kk = decltype(next_kk_tag)::value;
-        static_for<0, 4 * MT>([&](auto idx_tag) {
-            constexpr int idx = decltype(idx_tag)::value, mt = idx >> 2, nt = idx & 3;
+        static_for<0, 2 * MT>([&](auto idx_tag) {
+            constexpr int idx = decltype(idx_tag)::value, mt = idx >> 1, nt = idx & 1;
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
             if constexpr (idx < MT) fa[set ^ 1][idx] = frag_a(next_buf, next_kk, idx);
-            else if constexpr (idx < MT + 4) fb[set ^ 1][idx - MT] = frag_b(next_buf, next_kk, idx - MT);
-            if constexpr (set == 1 && idx >= 4 * MT - 8 && idx % 2 == 0)
-                issue(dma_g, dma_buf, std::integral_constant<int, (idx - (4 * MT - 8)) / 2>{});
+            else if constexpr (idx < MT + 2) fb[set ^ 1][idx - MT] = frag_b(next_buf, next_kk, idx - MT);
+            if constexpr (set == 1 && idx >= 2 * MT - 4 && idx % 2 == 0)
+                issue(it + ZST < last ? it + ZST : last, buf, std::integral_constant<int, (idx - (2 * MT - 4)) / 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // Four stages in flight before the first one is consumed.  The hand-over to the next stage (wait for this wave's copies, then for
-    // everyone's) sits in the middle of a stage.  Beyond the last stage the pipeline re-loads the last one into buffers nobody reads
-    // any more, which keeps the loop free of branches and the number of copies in flight constant.  The waits for LDS reads are placed
-    // by hand (as the builtin the compiler's own counter tracking understands) before the reads of the following step are issued: the
-    // counter completes in order, so a wait placed after them would wait for them too.
+    // Five stages in flight before the first one is consumed.  The hand-over to the next stage (wait for this wave's copies, then for
+    // everyone's) sits in the middle of a stage; there every wave has read all its fragments of the present one, whose buffer may be
+    // refilled.  Beyond the last stage the pipeline re-loads the last one into buffers nobody reads
+    // any more, which keeps the loop free of branches and the number of copies in flight constant.  The waits for LDS reads are placed by hand (as the builtin the compiler's own counter tracking understands) before the
+    // reads of the following step are issued: the counter completes in order, so a wait placed after them would wait for them too.
     typedef std::integral_constant<int, 0> I0;
     typedef std::integral_constant<int, 1> I1;
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * DMAS) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ZST - 1) * DMAS) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < MT; ++i) fa[0][i] = frag_a(0, 0, i);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fb[0][i] = frag_b(0, 0, i);
-    unsigned buf = 0, refill = ZST - 1;               // of stage it, of stage it + 4
+    for (int i = 0; i < 2; ++i) fb[0][i] = frag_b(0, 0, i);
+    unsigned buf = 0;                                 // of stage it
     for (int it = 0; it < nsteps; ++it) {
         const unsigned next = buf + 1 == ZST ? 0 : buf + 1;
         __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
         __builtin_amdgcn_sched_barrier(0);
         multiply(I0{}, buf, I1{}, 0, 0u);
         __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        // stage it+1 landed (it+2 and it+3 stay in flight); every wave is past stage it-1, whose buffer takes stage it+4
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DMAS) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ZST - 2) * DMAS) : "memory");  // of stage it + 1; the later ones stay in flight
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        multiply(I1{}, next, I0{}, it + 4 < last ? it + 4 : last, refill);
-        refill = buf;
+        multiply(I1{}, next, I0{}, it, buf);
         buf = next;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy may land any more: the stages become the epilogue's scratch
-    __syncthreads();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                  // the stages become the epilogue's scratch
 
     // ---- epilogue.  Per lattice tile Z_ROWS rows of e^{2x}: the tile's frames, behind them its label positions; where an input lies beyond
     // +-40 (the product of two exponentials could overflow, or cancel as inf * 0) the tile's rows are the inputs themselves.
     float* ex = reinterpret_cast<float*>(dz_smem);                // [4 tiles][Z_ROWS][Z_EP]
     struct TileInfo {
-        int s, T, U, t0, u0, us, by_sum;
+        int s, T, U, t0, u0, us;
+        int far[2];                                   // an input of the first, second half of the rows lies beyond the limit
     };
     TileInfo* info = reinterpret_cast<TileInfo*>(dz_smem + 4 * Z_ROWS * Z_EP * sizeof(float));
     {
@@ -183,10 +180,15 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
         for (int i = 0; i < NR; ++i)
 #pragma unroll
             for (int k = 0; k < 8; ++k) big = fmaxf(big, fabsf((float)in[i][k]));
-        const bool by_sum = __any(!(big <= 115.0f / K2));
+        const bool far = __any(!(big <= 115.0f / K2));
+        if (lane == 0) info[wt].far[wv & 1] = far;
+        __syncthreads();
+        const bool by_sum = (info[wt].far[0] | info[wt].far[1]) != 0;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-            float* dst = ex + (wv * Z_ROWS + lane / NC + RPS * i) * Z_EP + (lane % NC) * 8;
+            const int r = lane / NC + RPS * (NR * (wv & 1) + i);
+            if (r >= Z_ROWS) continue;
+            float* dst = ex + (wt * Z_ROWS + r) * Z_EP + (lane % NC) * 8;
             f32x4 lo, hi;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -200,17 +202,21 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
             *reinterpret_cast<f32x4*>(dst) = lo;
             *reinterpret_cast<f32x4*>(dst + 4) = hi;
         }
-        if (lane == 0) info[wv] = TileInfo{present ? tp.s : -1, tp.T, tp.U, tp.t0, tp.u0, tp.us, by_sum};
+        if (lane == 0 && (wv & 1) == 0) {
+            TileInfo& ti = info[wt];
+            ti.s = present ? tp.s : -1;
+            ti.T = tp.T; ti.U = tp.U; ti.t0 = tp.t0; ti.u0 = tp.u0; ti.us = tp.us;
+        }
     }
     __syncthreads();
     // Accumulator register 4j+i of row block 2*lt + m2 is row r = 32 m2 + 8j + 4 hb + i of lattice tile lt, hidden column l32: in an 8 x 8
     // tile frame 4 m2 + j, label 4 hb + i; in a 16 x 4 tile frame 8 m2 + 2j + hb, label i.  One copy of the loop nest per shape.
     auto tile_epilogue = [&](auto lt_tag) {
         constexpr int lt = decltype(lt_tag)::value;
-        const int t4 = HALF ? wv : wm * 2 + lt;
+        const int t4 = HALF ? wm : wm * 2 + lt;
         const TileInfo ti = info[t4];
         const int s = __builtin_amdgcn_readfirstlane(ti.s), us = __builtin_amdgcn_readfirstlane(ti.us);
-        const bool by_sum = __builtin_amdgcn_readfirstlane(ti.by_sum) != 0;
+        const bool by_sum = __builtin_amdgcn_readfirstlane(ti.far[0] | ti.far[1]) != 0;
         if (s < 0) return;
         float* d_enc = g.d_enc + (size_t)s * g.pr.T_max * H;
         float* d_prd = g.d_pred + (size_t)s * (g.pr.U_max + 1) * H;
@@ -220,8 +226,8 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
             constexpr int TH = WIDE ? 8 : 16;
             const int ulb = WIDE ? 4 * hb : 0;              // first of this lane's four label positions
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int hc = wn * 128 + nt * 32 + l32, h = n0 + hc;        // column inside the tile, hidden column
+            for (int nt = 0; nt < 2; ++nt) {
+                const int hc = wn * 64 + nt * 32 + l32, h = n0 + hc;        // column inside the tile, hidden column
                 float qv[4], pu[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) qv[i] = er[(TH + ulb + i) * Z_EP + hc];
@@ -242,9 +248,9 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
                                 const float r = __builtin_amdgcn_rcpf(fmaf(ev, qv[i], 1.0f));
                                 w = fmaf(-r, r, r);
                             }
-                            const float dx = acc[2 * lt + m2][nt][4 * j + i] * w;
-                            se[j] += dx;
-                            pu[i] += dx;
+                            const float d = acc[2 * lt + m2][nt][4 * j + i];
+                            se[j] = fmaf(d, w, se[j]);
+                            pu[i] = fmaf(d, w, pu[i]);
                         }
                     }
                     if (WIDE) {
@@ -310,14 +316,14 @@ __device__ __forceinline__ void dz_workgroup(const DzArgs& g, unsigned char* dz_
     else dz_tile<false>(g, dz_smem, bx, n0, n_slots, vs);
 }
 
-__global__ __launch_bounds__(256) void k_gemm_dz256(DzArgs g) {
+__global__ __launch_bounds__(512) void k_gemm_dz256(DzArgs g) {
     extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A, B: 16 fragments each }
     dz_workgroup(g, dz_smem, blockIdx.x);
 }
 
 // Both GEMMs of a chunk: dW's workgroups, then dz's (they share nothing but what they read: dH).  The rule and what it gives: plan.h.
 template <bool BY_TILE>
-__global__ __launch_bounds__(256) void k_gemm_dz_dw(DzArgs z, DwArgs w, int nw) {
+__global__ __launch_bounds__(512) void k_gemm_dz_dw(DzArgs z, DwArgs w, int nw) {
     extern __shared__ __align__(16) unsigned char smem[];
     if ((int)blockIdx.x < nw) dw_workgroup<BY_TILE>(w, smem, blockIdx.x);
     else dz_workgroup(z, smem, blockIdx.x - nw);
@@ -347,7 +353,7 @@ hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTa
         if (e != hipSuccess) return e;
         configured = true;
     }
-    k_gemm_dz256<<<dim3((unsigned)(g.v_splits * g.per_part)), dim3(256), DZ_SMEM, stream>>>(g);
+    k_gemm_dz256<<<dim3((unsigned)(g.v_splits * g.per_part)), dim3(512), DZ_SMEM, stream>>>(g);
     return hipGetLastError();
 }
 
@@ -371,8 +377,8 @@ hipError_t launch_gemm_dz_dw_bf16(const Problem& pr, const void* Wq, const Sampl
     }
     const int nw = dw_grid(pr.H, pr.V, splits);
     const dim3 grid((unsigned)(nw + z.v_splits * z.per_part));
-    if (at.active && at.slot_tile0 >= 0) k_gemm_dz_dw<true><<<grid, dim3(256), smem, stream>>>(z, w, nw);
-    else k_gemm_dz_dw<false><<<grid, dim3(256), smem, stream>>>(z, w, nw);
+    if (at.active && at.slot_tile0 >= 0) k_gemm_dz_dw<true><<<grid, dim3(512), smem, stream>>>(z, w, nw);
+    else k_gemm_dz_dw<false><<<grid, dim3(512), smem, stream>>>(z, w, nw);
     return hipGetLastError();
 }
 

@@ -890,3 +890,17 @@ def test_bf16_both_backward_gemms_in_one_grid(H, V, keep):
         two = run_gpu(batch, keep_scores=keep, budget_bytes=nmin)
         assert_parity(two, ref, "bf16", f"{B} x {T} x {U}, smallest workspace")
         np.testing.assert_array_equal(two["loss"], got["loss"])
+
+
+@pytest.mark.parametrize("H", [128, 384, 512])
+@pytest.mark.parametrize("T,U,t,u", [(31, 23, 3, 9), (31, 23, 30, 16), (47, 3, 2, 1), (47, 3, 44, 3)])
+def test_bf16_single_inputs_beyond_the_exponentials(H, T, U, t, u):
+    # one frame and one label position of a sample hold inputs beyond +-40 that cancel in their node (tanh(0), not 0 * inf): the tile's derivatives come
+    # from the sums whichever of the waves that share its input rows has seen them; 8 x 8 and 16 x 4 tiles, whole and half hidden tiles
+    wl = synth.custom_workload("far", B=2, T_max=T, U_max=U, H=H, V=256, dtype="bf16", index=148)
+    batch = synth.with_lengths(synth.make_batch(wl), [T, T - 1], [U, U])
+    batch.enc[0, t, :] = 64.0
+    batch.pred[0, u, :] = -64.0
+    got, ref = run_gpu(batch), run_oracle(batch)
+    assert_parity(got, ref, "bf16", f"far {t} {u}")
+    assert_padding_zero(got, batch)
