@@ -8,7 +8,7 @@
 //           maximum m (t <= 0, so an entry's error exp(t) |t| 2^-11 in the softmax is at most 2^-11 / e whatever the size of
 //           the scores; m is the row's largest score so far in its quarter of the vocabulary, one float per row and 64 entries)
 //
-// A workgroup is 4 waves; a wave owns 32 RB rows (RB = 1: half a lattice tile, 2: a whole one) and keeps their joint
+// A workgroup is 4 waves (8: eight_waves_pay); a wave owns 32 RB rows (RB = 1: half a lattice tile, 2: a whole one) and keeps their joint
 // activations in registers for the whole pass (H/16 fragments of 4 registers per 32 rows: 128 registers at H = 512).
 // The scores are computed transposed (A = 32 vocabulary entries of W_out^T, B = 32 rows), so a lane owns one row (with its
 // partner lane in the other half) and the softmax reductions over the vocabulary stay in registers.
@@ -58,27 +58,27 @@ constexpr int SC_AGPR_FRAGS = 64;  // joint fragments kept in the 256 accumulati
 
 // LDS ring: stages of SF fragments (1 KiB each), a whole or half block of W_out^T, so many of them that a stage's copies are sent
 // at least one whole stage ahead of their use, inside the 160 KiB of a compute unit (half of it where two workgroups share one).
-constexpr int stage_frags(int KK, int WPS) { return KK <= 16 || (WPS == 1 && KK <= 32) ? KK : KK / 2; }
-constexpr int score_stages(int KK, int WPS) {
-    const int room = (WPS == 2 ? 76 : 152) / stage_frags(KK, WPS);
+constexpr int stage_frags(int KK, int WPS, int WAVES) { return KK <= 16 || (4 * WPS == WAVES && KK <= 32) ? KK : KK / 2; }
+constexpr int score_stages(int KK, int WPS, int WAVES) {
+    const int room = (4 * WPS == WAVES ? 152 : 76) / stage_frags(KK, WPS, WAVES);
     return room < 6 ? room : 6;
 }
-constexpr size_t score_smem_bytes(int KK, int WPS) {
-    return (size_t)score_stages(KK, WPS) * (stage_frags(KK, WPS) * 1024 + 256) + 256;
+constexpr size_t score_smem_bytes(int KK, int WPS, int WAVES) {
+    return (size_t)score_stages(KK, WPS, WAVES) * (stage_frags(KK, WPS, WAVES) * 1024 + 256) + 256;
 }
 
-template <int MODE, int KK, int RB, int WPS>
-__global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
+template <int MODE, int KK, int RB, int WPS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NST = score_stages(KK, WPS), SF = stage_frags(KK, WPS), SPB = KK / SF;
+    constexpr int NST = score_stages(KK, WPS, WAVES), SF = stage_frags(KK, WPS, WAVES), SPB = KK / SF;
     constexpr unsigned SB = SF * 1024;
-    constexpr int PER = SF / 4;                       // fragments a wave copies per stage
+    constexpr int PER = SF / WAVES;                       // fragments a wave copies per stage
     constexpr int RG = SC_RING;
-    constexpr int TW = 2 * RB;                        // lattice tiles per workgroup
+    constexpr int TW = WAVES / 2 * RB;                // lattice tiles per workgroup
     constexpr int NACC = MODE == 2 ? 4 : 2;           // score blocks alive: running, previous (MODE 2: two more until their pair is stored)
-    static_assert(KK % RG == 0 && KK % SF == 0 && SF % 4 == 0 && SF >= RG && NST >= 4, "ring geometry");
+    static_assert(KK % RG == 0 && KK % SF == 0 && SF % WAVES == 0 && SF >= RG && NST >= 4, "ring geometry");
     static_assert(6 * ((PER + 1) / 2 - 1) < SF, "a stage's copies go out before the next hand-over");
-    static_assert((NST - 1) * SB >= 4 * JR_SCRATCH, "the build scratch lies in the later stages");
+    static_assert((NST - 1) * SB >= WAVES * JR_SCRATCH, "the build scratch lies in the later stages");
     const int H = KK * 16, V = a.pr.V;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     if ((int)blockIdx.x * TW >= n_tiles) return;
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
     float* bias_lds = reinterpret_cast<float*>(smem + NST * SB);          // [NST][64], 32 values and their repetition
-    float* esum_lds = bias_lds + NST * 64;                               // [4], and the arrival order [1]
+    float* esum_lds = bias_lds + NST * 64;                               // [WAVES], and the arrival order [1]
     // this workgroup's part of the vocabulary: blocks [vb0, vb0 + nvb)
     const int nvb = V / SC_VB / (int)gridDim.y, vb0 = (int)blockIdx.y * nvb;
     const char* wpb = reinterpret_cast<const char*>(a.Wp) + (size_t)vb0 * (KK * 1024) + wave * (PER * 1024);
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
 
     if (gridDim.y > 1) {
         // the workgroup of this column that arrives last folds the segments of all of them, in order
-        int* order = reinterpret_cast<int*>(esum_lds + 4);
+        int* order = reinterpret_cast<int*>(esum_lds + WAVES);
         // (the segments leave as agent-scope stores, complete at the vmcnt(0) above, and are read by agent-scope loads: no cache
         // has to be written back or invalidated between them)
         __syncthreads();
@@ -495,27 +495,27 @@ __global__ __launch_bounds__(256, WPS) void k_scores(ScoreArgs a) {
     }
 }
 
-template <int MODE, int KK, int RB, int WPS>
+template <int MODE, int KK, int RB, int WPS, int WAVES = 4>
 hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
-    constexpr int TW = 2 * RB;
+    constexpr int TW = WAVES / 2 * RB, SLOTS = 256 * 4 * WPS / WAVES;
     const int n = (a.tile1 - a.tile0 + TW - 1) / TW;
-    constexpr size_t smem = score_smem_bytes(KK, WPS);
+    constexpr size_t smem = score_smem_bytes(KK, WPS, WAVES);
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scores<MODE, KK, RB, WPS>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scores<MODE, KK, RB, WPS, WAVES>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         configured = true;
     }
     int vs = 1;
     if (MODE == 1) {
-        vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
+        vs = vocabulary_split(n, SLOTS, a.pr.V / SC_VB);
     } else if (n <= SC_SPLIT_MAX_WG) {
-        vs = vocabulary_split(n, 256 * WPS, a.pr.V / SC_VB);
+        vs = vocabulary_split(n, SLOTS, a.pr.V / SC_VB);
         while (MODE == 2 && a.pr.V / SC_VB / vs % 4 != 0) vs /= 2;      // (kept scores leave in pairs of blocks, two pairs at a time)
         if ((size_t)SC_SEG * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
     }
-    k_scores<MODE, KK, RB, WPS><<<dim3((unsigned)n, (unsigned)vs), dim3(256), smem, stream>>>(a);
+    k_scores<MODE, KK, RB, WPS, WAVES><<<dim3((unsigned)n, (unsigned)vs), dim3(64 * WAVES), smem, stream>>>(a);
     return hipGetLastError();
 }
 
@@ -530,9 +530,21 @@ bool half_tiles_pay(int tiles, int V) {
     return c1 * 10 < c2 * 9;
 }
 
+// Joint sizes 384 and 512: one workgroup of eight waves per compute unit instead of two of four.  W_out^T crosses from the L2 once for all eight
+// waves and its stages are twice as long (half the hand-overs); on the other hand nothing stands beside the start and end of a workgroup,
+// which weigh less the longer the vocabulary.  Losses alone, 64 samples of 400 x 80: H = 384 V = 1024 951 -> 950 us, 2048 1703 -> 1657, 8192
+// 6253 -> 5922; H = 512 V = 1024 1156 -> 1169, 2048 2072 -> 2069, 4096 3944 -> 3888.  In the backward form the stores of dH push W_out^T out of the L2
+// where it comes near the 4 MiB of an XCD, so there the line lies at H V.  Calls with both kernels in eight waves, 64 samples of 400 x 80: H = 384
+// V = 2048 6874 -> 6975 us, 4096 13354 -> 13268 (the forward kernel alone gains 125), 8192 30.4 -> 29.8 ms; H = 512 V = 1024 4448 -> 4487 us, 2048 8189
+// -> 8298, 4096 15.54 -> 15.38 ms, 8192 30.7 -> 30.1 (256 samples of up to 800 x 240: 198.6 -> 191.1 ms).  Joint sizes 128 and 256, whose
+// stages are no longer with eight waves, lose 1 to 18 %.
+bool eight_waves_pay(int mode, const Problem& pr) {
+    return mode == 0 ? pr.V >= (pr.H == 384 ? 2048 : 4096) : (long long)pr.H * pr.V >= 1 << 21;
+}
+
 }  // namespace
 
-// Joint sizes up to 512: two workgroups per compute unit (one's joint rows are built beside the other's MFMAs); 640: whole
+// Joint sizes up to 512: two workgroups per compute unit (one's joint rows are built beside the other's MFMAs), or one of eight waves; 640: whole
 // tiles per wave (half the LDS reads per MFMA) where they fill the chip; above: 32 rows per wave fill the registers.
 hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTable& st, const LatticeState& ls, int tile0,
                            int tile1, void* part, size_t part_bytes, hipStream_t stream) {
@@ -541,8 +553,12 @@ hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTab
     switch (pr.H) {
         case 128: return launch_scores_t<0, 8, 1, 2>(a, part_bytes, stream);
         case 256: return launch_scores_t<0, 16, 1, 2>(a, part_bytes, stream);
-        case 384: return launch_scores_t<0, 24, 1, 2>(a, part_bytes, stream);
-        case 512: return launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
+        case 384:
+            return eight_waves_pay(0, pr) ? launch_scores_t<0, 24, 1, 2, 8>(a, part_bytes, stream)
+                                          : launch_scores_t<0, 24, 1, 2>(a, part_bytes, stream);
+        case 512:
+            return eight_waves_pay(0, pr) ? launch_scores_t<0, 32, 1, 2, 8>(a, part_bytes, stream)
+                                          : launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
         case 640:
             return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<0, 40, 1, 1>(a, part_bytes, stream)
                                                        : launch_scores_t<0, 40, 2, 1>(a, part_bytes, stream);
@@ -560,8 +576,10 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
     switch (pr.H) {
         case 128: return launch_scores_t<1, 8, 1, 2>(a, 0, stream);
         case 256: return launch_scores_t<1, 16, 1, 2>(a, 0, stream);
-        case 384: return launch_scores_t<1, 24, 1, 2>(a, 0, stream);
-        case 512: return launch_scores_t<1, 32, 1, 2>(a, 0, stream);
+        case 384:
+            return eight_waves_pay(1, pr) ? launch_scores_t<1, 24, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 24, 1, 2>(a, 0, stream);
+        case 512:
+            return eight_waves_pay(1, pr) ? launch_scores_t<1, 32, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 32, 1, 2>(a, 0, stream);
         case 640:
             return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<1, 40, 1, 1>(a, 0, stream)
                                                        : launch_scores_t<1, 40, 2, 1>(a, 0, stream);

@@ -291,6 +291,19 @@ def test_bf16_other_hidden_sizes(H, V):
     assert_padding_zero(got, batch)
 
 
+@pytest.mark.parametrize("H,V", [(384, 2048), (384, 5632), (512, 4096), (512, 8192)])
+@pytest.mark.parametrize("T_len,U_len", [([24, 1, 9], [9, 0, 3]), ([8, 8, 8], [7, 7, 7]), ([120, 90, 3], [40, 17, 2])])
+def test_bf16_score_kernels_of_eight_waves(H, V, T_len, U_len):
+    # four lattice tiles per workgroup, the last one partly filled; from V = 2048 (H = 384) and 4096 (H = 512) on in the forward pass, from
+    # H V = 2^21 on in the backward one
+    wl = synth.custom_workload("eight", B=3, T_max=max(T_len), U_max=max(U_len), H=H, V=V, dtype="bf16", index=149)
+    batch = synth.with_lengths(synth.make_batch(wl), T_len, U_len)
+    got, ref = run_gpu(batch), run_oracle(batch)
+    e, errs = assert_parity(got, ref, "bf16", f"eight waves {H} {V}")
+    _say("eight waves", H, V, e, errs)
+    assert_padding_zero(got, batch)
+
+
 @pytest.mark.parametrize("H,V,keep", [(128, 256, 0), (128, 1024, 1), (384, 512, 0), (384, 256, 1), (768, 256, 0), (896, 512, 1)])
 def test_bf16_weight_gradient_with_half_tiles_and_few_rows(H, V, keep):
     # last hidden tile of 128 columns (alone at H = 128), rows from less than one 32-row stage per split up; the smallest workspace cuts
