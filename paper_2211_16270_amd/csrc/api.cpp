@@ -272,18 +272,26 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
     const WsView wv = view_workspace(plan, workspace);
     unsigned char* w = (unsigned char*)workspace;
     const size_t B = (size_t)desc->B;
+    std::vector<unsigned char> tab;              // host tables that travel with k_prepare
     {
         const size_t tab_bytes = table_bytes(plan, B);
         if (ts.staged && ts.staged_pinned && !ts.no_copy_engine) {
             // pinned source owned by the plan handle: a truly asynchronous copy
             RNNT_HIP(hipMemcpyAsync(w + plan.off_T, ts.staged, tab_bytes, hipMemcpyHostToDevice, stream));
-        } else {
-            std::vector<unsigned char> tab;
-            const unsigned char* src = ts.staged;
-            if (!src) {
+        } else if (tab_bytes <= (size_t)PREP_TABLE_MAX * 4) {
+            if (ts.staged) tab.assign(ts.staged, ts.staged + tab_bytes);
+            else {
                 tab.resize(tab_bytes);
                 fill_tables(plan, B, T_len, U_len, tab.data());
-                src = tab.data();
+            }
+            if (sample_weight) std::memcpy(tab.data() + (plan.off_weight - plan.off_T), sample_weight, B * 4);
+        } else {
+            std::vector<unsigned char> large;
+            const unsigned char* src = ts.staged;
+            if (!src) {
+                large.resize(tab_bytes);
+                fill_tables(plan, B, T_len, U_len, large.data());
+                src = large.data();
             }
             // small tables travel as kernel arguments (a pageable host-to-device copy makes the host wait for
             // the stream; a few small launches do not); large ones by one copy, consumed before the call returns
@@ -292,7 +300,7 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
             else
                 RNNT_HIP(hipMemcpyAsync(w + plan.off_T, src, tab_bytes, hipMemcpyHostToDevice, stream));
         }
-        if (sample_weight)
+        if (sample_weight && tab.empty())
             RNNT_HIP(put_table(reinterpret_cast<const unsigned char*>(sample_weight), B * 4, w + plan.off_weight, stream));
     }
 
@@ -332,6 +340,10 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         }
         pa.H = desc->H;
         pa.V = desc->V;
+        pa.table = reinterpret_cast<const int*>(tab.data());
+        pa.table_n = (int)(tab.size() / 4);
+        pa.table_tile_off = (int)((plan.off_tile_off - plan.off_T) / 4);
+        pa.table_dst = (int*)(w + plan.off_T);
         RNNT_HIP(timed(KC_PREPARE, stream, [&] { return launch_prepare(pa, stream); }));
     }
 

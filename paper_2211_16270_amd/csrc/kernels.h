@@ -16,7 +16,7 @@ struct SampleTable {
     const long long* row_off;  // [B+1] cumulative lattice-node counts
 };
 
-// Per-group lattice state; arrays are indexed by (row_off[s] - row_base) + t*(U_s+1) + u.
+// Per-group lattice state; arrays are indexed by (row_off[s] - row_base) + lattice_index(T_s, U_s + 1, t, u).
 // The nodes of a sample lie anti-diagonal after anti-diagonal (t + u = 0, 1, ...), on each by rising u: the lattice sweeps, which
 // take one anti-diagonal per step, then read and write memory in one piece.  W = U + 1 columns.
 __host__ __device__ inline int diagonal_offset(int T, int W, int k) {
@@ -83,7 +83,13 @@ struct PrepArgs {
     void* Wp;
     void* Wq;
     int H, V;
+    // Host tables of at most PREP_TABLE_MAX ints that reach `table_dst` with this launch, as kernel arguments (table_n = 0: none;
+    // tile_off then holds its values already); tile_off lies table_tile_off ints behind table_dst.
+    const int* table;        // host
+    int table_n, table_tile_off;
+    int* table_dst;          // device
 };
+constexpr int PREP_TABLE_MAX = 800;
 hipError_t launch_prepare(const PrepArgs& a, hipStream_t stream);
 // dst[i] = bf16(src[i]), n a multiple of 8 (the gradients of a group, accumulated in fp32, on their way out)
 hipError_t launch_f32_to_bf16(const float* src, void* dst, size_t n, hipStream_t stream);

@@ -65,6 +65,19 @@ def test_f32_plain_kernels(H, V, B, T, U):
     assert_padding_zero(got, batch)
 
 
+@pytest.mark.parametrize("B", [1, 127, 128])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_tables_with_the_first_launch_or_ahead_of_it(B, weighted):
+    # the tables of up to 127 samples travel with the first launch, those of more in launches of their own
+    wl = synth.custom_workload("tables", B=B, T_max=6, U_max=3, H=16, V=12, dtype="f32", index=150,
+                               t_rule="uniform", t_lo=1, u_rule="uniform", u_lo=0)
+    batch = synth.make_batch(wl)
+    w = np.linspace(0.25, 2.0, B, dtype=np.float32) if weighted else None
+    got, ref = run_gpu(batch, sample_weight=w), run_oracle(batch, sample_weight=w)
+    assert_parity(got, ref, "f32", f"tables {B} {weighted}")
+    assert_padding_zero(got, batch)
+
+
 def test_f32_moderate_shape_and_group_splitting():
     wl = synth.custom_workload("mid32", B=5, T_max=33, U_max=12, H=48, V=70, dtype="f32", index=102,
                                t_rule="uniform", t_lo=5, u_rule="uniform", u_lo=0)
