@@ -537,8 +537,10 @@ bool half_tiles_pay(int tiles, int V) {
 // where it comes near the 4 MiB of an XCD, so there the line lies at H V.  Calls with both kernels in eight waves, 64 samples of 400 x 80: H = 384
 // V = 2048 6874 -> 6975 us, 4096 13354 -> 13268 (the forward kernel alone gains 125), 8192 30.4 -> 29.8 ms; H = 512 V = 1024 4448 -> 4487 us, 2048 8189
 // -> 8298, 4096 15.54 -> 15.38 ms, 8192 30.7 -> 30.1 (256 samples of up to 800 x 240: 198.6 -> 191.1 ms).  Joint sizes 128 and 256, whose
-// stages are no longer with eight waves, lose 1 to 18 %.
-bool eight_waves_pay(int mode, const Problem& pr) {
+// stages are no longer with eight waves, lose 1 to 18 %.  So do launches that leave most of the chip idle (a few workgroups per XCD, the vocabulary
+// split): H = 512, 12 tiles, V = 5376 134 -> 167 us a call, 100 tiles, V = 6144 219 -> 239; below half a round (512 tiles) it is four waves.
+bool eight_waves_pay(int mode, const Problem& pr, int tiles) {
+    if (tiles < 512) return false;
     return mode == 0 ? pr.V >= (pr.H == 384 ? 2048 : 4096) : (long long)pr.H * pr.V >= 1 << 21;
 }
 
@@ -554,10 +556,10 @@ hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTab
         case 128: return launch_scores_t<0, 8, 1, 2>(a, part_bytes, stream);
         case 256: return launch_scores_t<0, 16, 1, 2>(a, part_bytes, stream);
         case 384:
-            return eight_waves_pay(0, pr) ? launch_scores_t<0, 24, 1, 2, 8>(a, part_bytes, stream)
+            return eight_waves_pay(0, pr, tile1 - tile0) ? launch_scores_t<0, 24, 1, 2, 8>(a, part_bytes, stream)
                                           : launch_scores_t<0, 24, 1, 2>(a, part_bytes, stream);
         case 512:
-            return eight_waves_pay(0, pr) ? launch_scores_t<0, 32, 1, 2, 8>(a, part_bytes, stream)
+            return eight_waves_pay(0, pr, tile1 - tile0) ? launch_scores_t<0, 32, 1, 2, 8>(a, part_bytes, stream)
                                           : launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
         case 640:
             return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<0, 40, 1, 1>(a, part_bytes, stream)
@@ -577,9 +579,9 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
         case 128: return launch_scores_t<1, 8, 1, 2>(a, 0, stream);
         case 256: return launch_scores_t<1, 16, 1, 2>(a, 0, stream);
         case 384:
-            return eight_waves_pay(1, pr) ? launch_scores_t<1, 24, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 24, 1, 2>(a, 0, stream);
+            return eight_waves_pay(1, pr, tile1 - tile0) ? launch_scores_t<1, 24, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 24, 1, 2>(a, 0, stream);
         case 512:
-            return eight_waves_pay(1, pr) ? launch_scores_t<1, 32, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 32, 1, 2>(a, 0, stream);
+            return eight_waves_pay(1, pr, tile1 - tile0) ? launch_scores_t<1, 32, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 32, 1, 2>(a, 0, stream);
         case 640:
             return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<1, 40, 1, 1>(a, 0, stream)
                                                        : launch_scores_t<1, 40, 2, 1>(a, 0, stream);

@@ -304,11 +304,26 @@ def test_bf16_other_hidden_sizes(H, V):
     assert_padding_zero(got, batch)
 
 
+@pytest.mark.parametrize("H,V", [(384, 5632), (512, 4096)])
+def test_bf16_score_kernels_of_eight_waves_in_large_launches(H, V):
+    # 15 tiles a sample but the first, which has one: 496 tiles (four waves) and 526 (eight, the last workgroup partly filled), forward and backward; a
+    # sample's loss has the same bits either way
+    wl = synth.custom_workload("eight", B=36, T_max=40, U_max=20, H=H, V=V, dtype="bf16", index=151)
+    loss = []
+    for n in (34, 36):
+        batch = synth.with_lengths(synth.make_batch(wl, list(range(n))), [3] + [40] * (n - 1), [2] + [20] * (n - 1))
+        _say("eight waves, large", H, V, n)
+        got = run_gpu(batch)
+        assert_parity(got, run_oracle(batch), "bf16", f"eight waves {H} {V} {n}")
+        assert_padding_zero(got, batch)
+        loss.append(got["loss"])
+    np.testing.assert_array_equal(loss[0], loss[1][:34])
+
+
 @pytest.mark.parametrize("H,V", [(384, 2048), (384, 5632), (512, 4096), (512, 8192)])
 @pytest.mark.parametrize("T_len,U_len", [([24, 1, 9], [9, 0, 3]), ([8, 8, 8], [7, 7, 7]), ([120, 90, 3], [40, 17, 2])])
 def test_bf16_score_kernels_of_eight_waves(H, V, T_len, U_len):
-    # four lattice tiles per workgroup, the last one partly filled; from V = 2048 (H = 384) and 4096 (H = 512) on in the forward pass, from
-    # H V = 2^21 on in the backward one
+    # the sizes of the eight-wave kernels in launches of fewer than 512 tiles, which keep four waves
     wl = synth.custom_workload("eight", B=3, T_max=max(T_len), U_max=max(U_len), H=H, V=V, dtype="bf16", index=149)
     batch = synth.with_lengths(synth.make_batch(wl), T_len, U_len)
     got, ref = run_gpu(batch), run_oracle(batch)
