@@ -116,8 +116,10 @@ __device__ __forceinline__ PlainRows plain_scores(const Problem& pr, const Plain
         }
     return r;
 }
+// -1: no label here, or one outside the vocabulary, which can not be emitted (a label indexes a row of scores: never beyond its end)
 __device__ __forceinline__ int node_label(const Problem& pr, const NodePos& p) {
-    return p.u < p.U ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
+    const int y = p.u < p.U ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
+    return (unsigned)y < (unsigned)pr.V ? y : -1;
 }
 
 }  // namespace
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(256) void k_rows_stats_f32(Problem pr, SampleTable 
     const int lane = threadIdx.x & 63, V = pr.V;
     const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
     const float* row = S + i * V;
-    const int label = (p.u < p.U) ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
+    const int label = node_label(pr, p);
     const f32x4* row4 = reinterpret_cast<const f32x4*>(row);      // V is a multiple of 4, rows are 16-byte aligned
     float m = RNNT_NEG_INF;
     for (int v = lane; v < V / 4; v += 64) {
@@ -527,7 +529,7 @@ __global__ __launch_bounds__(256) void k_rows_dh_f32(Problem pr, SampleTable st,
         return;
     }
     const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
-    const int label = (p.u < p.U) ? pr.labels[(size_t)p.s * pr.U_max + p.u] : -1;
+    const int label = node_label(pr, p);
     const RowPost rp = row_posteriors(ls, p.idx, p.t, p.u, p.T, p.U, p.s);
     const float off = rp.log_gamma - ls.lse[p.idx];
     f32x4* row4 = reinterpret_cast<f32x4*>(row);

@@ -65,6 +65,29 @@ def test_f32_plain_kernels(H, V, B, T, U):
     assert_padding_zero(got, batch)
 
 
+@pytest.mark.parametrize("dtype,H,V", [("f32", 24, 11), ("f32", 301, 1001), ("f32", 64, 68), ("bf16", 128, 256)])
+@pytest.mark.parametrize("beyond", ["-1", "V", "V + 1", "2^31 - 1", "-2^31"])
+def test_label_outside_the_vocabulary(dtype, H, V, beyond):
+    # plain kernels with W_out in LDS and in memory, GEMM form, bf16: such a sample has loss +inf, whatever lies behind its rows of scores; the others
+    # are what they are without it
+    import torch
+    bad = {"-1": -1, "V": V, "V + 1": V + 1, "2^31 - 1": 2 ** 31 - 1, "-2^31": -2 ** 31}[beyond]
+    wl = synth.custom_workload("label", B=3, T_max=13, U_max=6, H=H, V=V, dtype=dtype, index=152)
+    batch = synth.with_lengths(synth.make_batch(wl), [13, 9, 5], [6, 4, 3])
+    ref = run_oracle(batch)
+    batch.labels[1, 2] = bad
+    _say("label outside", dtype, H, V, beyond)
+    got, others = run_gpu(batch), [0, 2]
+    assert got["loss"][1] == np.inf
+    assert rel_loss_err(got["loss"][others], ref["loss"][others]) <= TOL[dtype]["loss"]
+    for k in ("d_enc", "d_pred"):
+        assert rel_grad_err(got[k][others], ref[k][others]) <= TOL[dtype]["grad"], k
+    dev, loss = got["dev"], torch.empty(3, dtype=torch.float32, device="cuda")
+    assert Bd.rnnt_joint_loss_fwd(got["desc"], dev["enc"], dev["pred"], dev["W_out"], dev["b_out"], dev["labels"], batch.T_len, batch.U_len,
+                                  loss, got["workspace"].buf) == 0
+    np.testing.assert_array_equal(loss.cpu().numpy(), got["loss"])
+
+
 @pytest.mark.parametrize("B", [1, 127, 128])
 @pytest.mark.parametrize("weighted", [False, True])
 def test_tables_with_the_first_launch_or_ahead_of_it(B, weighted):
