@@ -37,8 +37,14 @@ __host__ __device__ inline int next_diagonal_step(int T, int W, int k) {
     len = len < r ? len : r;
     return len - (k + 1 >= T ? 1 : 0);
 }
-// Stands for ln 0 in the emissions: finite, so that the sums of two impossible ways are no NaN.
+// Stands for ln 0 in the emissions: finite, so that the sums of two impossible ways are no NaN.  A sample whose alignments all take one
+// has ln P below a tenth of it, however many they take and whatever else they do (no_alignment).
 constexpr float EMISSION_FLOOR = -1e30f;
+// A node's larger emission enters the sample's offset as at least this, so that an impossible one neither sets the offset nor is cancelled by
+// it: T + U (at most 2^30 + 1023) offsets stay far below EMISSION_FLOOR.
+constexpr float OFFSET_FLOOR = -1e9f;
+// lnP: without the offset
+__host__ __device__ inline bool no_alignment(double lnP) { return lnP < 0.1 * EMISSION_FLOOR; }
 
 struct LatticeState {
     float* lse;    // ln of the softmax denominator (f^W_1)
@@ -48,8 +54,8 @@ struct LatticeState {
     float* lnP;    // [B] ln P(y|x) + shift*(T+U), per sample
     float* shift;  // [B] per-sample offset added to every emission log-probability
     const float* weight;  // [B] weight of loss[b] in the differentiated sum, or null (all ones)
-    float* tile_esum;     // [tiles of the call] sum over a tile's nodes of max(blank, label) (blank where there is no
-                          // label), written by the bf16 forward kernels for the lattice kernels' offset; or null
+    float* tile_esum;     // [tiles of the call] sum over a tile's nodes of max(blank, label, OFFSET_FLOOR) (without label where there is
+                          // none), written by the bf16 forward kernels for the lattice kernels' offset; or null
     long long row_base;
 };
 

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
             a.ls.lse[idx] = lse;
             a.ls.em[idx] = emissions(cb - lse, lab[rb] >= 0 ? cy - lse : EMISSION_FLOOR);
             // this node's share of the sum the lattice kernels take their per-sample offset from
-            esum += (u < tp.U) ? fmaxf(cb, cy) - lse : cb - lse;
+            esum += fmaxf((u < tp.U ? fmaxf(cb, cy) : cb) - lse, OFFSET_FLOOR);
         }
     }
     esum = wave_sum(esum);

@@ -40,7 +40,7 @@ __device__ __forceinline__ float emission_sum_partial(const SampleTable& st, con
         const float* __restrict__ esum = ls.tile_esum + st.tile_off[s];
         add_all(st.tile_off[s + 1] - st.tile_off[s], [&](int i) { return esum[i]; });
     } else {
-        add_all(n, [&](int i) { const float2 e = em[i]; return fmaxf(e.x, e.y); });
+        add_all(n, [&](int i) { const float2 e = em[i]; return fmaxf(fmaxf(e.x, e.y), OFFSET_FLOOR); });
     }
     return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }
@@ -187,11 +187,12 @@ __device__ __forceinline__ float lattice_sweep(const SampleTable& st, const Latt
         // alpha[T-1,U] and the final blank
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const double lnP2 = *(volatile const float*)(out + (n - 1)) / (double)LN2_F + fma((double)em[n - 1].x, (double)LOG2E_F, (double)c2);
-        const bool none = lnP2 < 0.1 * EMISSION_FLOOR;               // no alignment has a probability above 0
+        // (the offset as it was added, T + U times, and the emissions as they were scaled: neither one's rounding stays in the loss)
+        const double lnP_true = (lnP2 - (double)c2 * (T + U)) / LOG2E_F;
+        const bool none = no_alignment(lnP_true);
         ls.lnP[s] = none ? RNNT_NEG_INF : (float)(lnP2 * LN2_F);
         ls.shift[s] = c2 * LN2_F;
-        // (the offset as it was added, T + U times, and the emissions as they were scaled: neither one's rounding stays in the loss)
-        loss[s] = none ? -RNNT_NEG_INF : (float)(((double)c2 * (T + U) - lnP2) / LOG2E_F);
+        loss[s] = none ? -RNNT_NEG_INF : (float)-lnP_true;
     }
     return 0.0f;
 }
@@ -255,8 +256,8 @@ __global__ __launch_bounds__(LAT_MAX_T) void k_lattice_f64(SampleTable st, Latti
         // scores, where the number of alignments adds hundreds to ln P, or peaked ones).  ln P is not known
         // beforehand: both workgroups of the sample first run the fp32 alpha sweep without storing anything (the same arithmetic in
         // both, hence the same c; any c near it would do), then the sweep proper.
-        const float lnP_off = lattice_sweep<false, true, false, 4>(st, ls, s, c_mean, nullptr, edge);
-        if (u == U) c_better = (float)((double)c_mean - (double)lnP_off / (double)(T + U));
+        const double lnP_off = lattice_sweep<false, true, false, 4>(st, ls, s, c_mean, nullptr, edge), steps = T + U;
+        if (u == U) c_better = no_alignment(lnP_off - c_mean * steps) ? c_mean : (float)(c_mean - lnP_off / steps);
         __syncthreads();
         c = c_better;
     }
@@ -310,9 +311,11 @@ __global__ __launch_bounds__(LAT_MAX_T) void k_lattice_f64(SampleTable st, Latti
         if (u == U) {
             // own = alpha[T-1,U]; ln P (offset) = alpha + final blank
             const double lnP_off = own + ((double)em[n - 1].x + (double)c);
-            ls.lnP[s] = (float)lnP_off;
+            const double lnP_true = lnP_off - (double)c * (double)(T + U);
+            const bool none = no_alignment(lnP_true);
+            ls.lnP[s] = none ? RNNT_NEG_INF : (float)lnP_off;
             ls.shift[s] = c;
-            loss[s] = (float)-(lnP_off - (double)c * (double)(T + U));
+            loss[s] = none ? -RNNT_NEG_INF : (float)-lnP_true;
         }
     } else {
         float* __restrict__ beta = ls.beta + base;

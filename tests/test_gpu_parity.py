@@ -88,6 +88,32 @@ def test_label_outside_the_vocabulary(dtype, H, V, beyond):
     np.testing.assert_array_equal(loss.cpu().numpy(), got["loss"])
 
 
+@pytest.mark.parametrize("dtype,H,V,keep", [("f32", 24, 11, 0), ("f32", 64, 68, 0), ("bf16", 128, 256, 0), ("bf16", 128, 256, 1)])
+@pytest.mark.parametrize("T,U", [(13, 6), (150, 10), (90, 80)])
+@pytest.mark.parametrize("mask", [-np.inf, float(np.finfo(np.float32).min)])
+def test_samples_without_a_possible_alignment(dtype, H, V, keep, T, U, mask):
+    # a label that only one sample needs is masked out: its loss is +inf in the short sweeps and in the long ones, the others' losses and
+    # gradients are what they are; with the blank masked every loss is +inf, also that of a sample without labels
+    wl = synth.custom_workload("impossible", B=4, T_max=T, U_max=U, H=H, V=V, dtype=dtype, index=153)
+    batch = synth.with_lengths(synth.make_batch(wl), [T, T - 3, 5, T - 1], [U, U - 2, 3, 0])
+    batch.labels[:] = 1 + batch.labels % (V - 2)
+    for what, entry in (("label", V - 1), ("blank", 0)):
+        batch.b_out[:] = np.where(np.arange(V) == entry, np.float32(mask), np.float32(0))
+        ref = run_oracle(batch) if what == "label" else None
+        with_label = synth.Batch(*(getattr(batch, f) for f in ("wl", "sample_ids", "enc", "pred", "W_out", "b_out")), batch.labels.copy(), batch.T_len, batch.U_len)
+        with_label.labels[1, U - 3] = V - 1
+        _say("impossible", dtype, H, V, keep, T, U, mask, what)
+        got = run_gpu(with_label, keep_scores=keep)
+        if what == "blank":
+            assert np.all(got["loss"] == np.inf)
+            continue
+        others = [0, 2, 3]
+        assert got["loss"][1] == np.inf
+        assert rel_loss_err(got["loss"][others], ref["loss"][others]) <= TOL[dtype]["loss"]
+        for k in ("d_enc", "d_pred"):
+            assert rel_grad_err(got[k][others], ref[k][others]) <= TOL[dtype]["grad"], k
+
+
 @pytest.mark.parametrize("B", [1, 127, 128])
 @pytest.mark.parametrize("weighted", [False, True])
 def test_tables_with_the_first_launch_or_ahead_of_it(B, weighted):
