@@ -228,15 +228,19 @@ namespace {
 
 constexpr int FT = 128;       // output tile: 128 rows x TN columns
 constexpr int FK = 16;        // K-step
+constexpr int FLIP = 256;     // depth after which the sum changes its sign
 
 // C = A B in fp32 precision on the bf16 matrix instruction.  An fp32 value is the exact sum of three bf16 values, each the rounded rest
 // of the ones before: x = h + m + l with |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.  A product takes the six pairs h h, h m, m h, h l, m m, l h; what is
 // left out is below 2^-26 of it, a quarter of an fp32 rounding, and 16 products are added per rounding of the accumulator where the fp32
-// instruction adds two.  Against 64 bits (2-norm, normal operands, depth 64 ... 8800) the error is 0.75 ... 0.9 of that of v_mfma_f32_32x32x2_f32.
-// The accumulation rounds towards minus infinity, a mean of 5e-11 of the result's size per unit of depth, which would show from a depth of
-// about 30000 on: longer sums (the weight gradients) are split (k_splits_f32).  Values beyond the largest bf16, 3.39e38, infinities and NaN give NaN.
+// instruction adds two.  The accumulation rounds towards minus infinity, a mean of 5e-11 of the result's size per unit of depth, alike for all results: sums over
+// many of them would show it (d_pred at V = 16384: a mean of -8e-7 of its size, twice the error of the fp32 instruction).  So every FLIP of depth the sum
+// changes its sign, and A enters with the other one: what is lost goes the other way (that mean then: 3e-8; 1.6 % of a call's time).  Error
+// against 64 bits over that of v_mfma_f32_32x32x2_f32, whole calls, 24 seeds each of seven shapes from H = 64, V = 2048 to H = 4096, V = 64: d_enc 0.69 to 0.97, d_pred
+// 0.67 to 1.06, dW_out 0.69 to 1.07.  Operands are exact from 2^-110 on; below, what lies under 2^-134 is lost.  Values beyond the largest bf16, 3.39e38, infinities
+// and NaN give NaN.
 // The bf16 instruction does sixteen times the work of the fp32 one, a sixth of it still 2.7 times.  What bounds it: power (1.7 GHz, matrix pipes busy
-// 64 to 67 % of the time; 200 TFLOP/s against 123 to 130 with the fp32 instruction).  H = 1024, V = 4096, 131 k nodes: a call 37.2 -> 23.3 ms.
+// 64 to 67 % of the time; 200 TFLOP/s against 123 to 130 with the fp32 instruction).  H = 1024, V = 4096, 131 k nodes: a call 37.2 -> 22.9 ms.
 // The parts are formed on the way into LDS, so the operands stay as they are in memory.
 // One part of two values, which leave as what remains of them.
 __device__ __forceinline__ unsigned split_part(float& x0, float& x1) {
@@ -291,14 +295,19 @@ struct OperandF32 {
     }
     // The work of bringing a step's pieces into LDS, cut into units of about five vector instructions and one LDS write: part n / 3 ... of two values
     // (k-contiguous operands: every second unit, with ten, of four).  The last unit of a piece loads that of the step at k2.
+    // The values enter with the sign bit of `sign` flipped.
     static constexpr int UNITS = 6 * NQ;
     template <int U>
-    __device__ __forceinline__ void unit(f32x4 (&v)[NQ], unsigned char* tile, int tid, long long i0, long long k2) const {
+    __device__ __forceinline__ void unit(f32x4 (&v)[NQ], unsigned char* tile, int tid, long long i0, long long k2, unsigned sign) const {
+        auto flip = [&](float x) { return __uint_as_float(__float_as_uint(x) ^ sign); };
         if constexpr (!KSLOW) {
             if constexpr (U % 2 == 0) {
                 constexpr int q = U / 6, part = U % 6 / 2;
                 const int r = (tid >> 2) & 31, kp = tid & 3, kh = kp >> 1;
                 float x[4] = {v[q][0], v[q][1], v[q][2], v[q][3]};
+                if constexpr (part == 0)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = flip(x[j]);
                 const unsigned a = split_part(x[0], x[1]), b = split_part(x[2], x[3]);
                 v[q] = f32x4{x[0], x[1], x[2], x[3]};
                 *reinterpret_cast<uint2*>(tile + (tid >> 7) * 3072 + q * 6144 + part * 1024 + kh * 512 + (r ^ (12 * kh)) * 16 + (kp & 1) * 8) =
@@ -309,6 +318,10 @@ struct OperandF32 {
             constexpr int q = U / 12 * 2, c = U % 12 / 3, part = U % 3;
             const int lane = tid & 63, wave = tid >> 6, kp = lane >> 3, kh = kp >> 2;
             float x0 = v[q][c], x1 = v[q + 1][c];
+            if constexpr (part == 0) {
+                x0 = flip(x0);
+                x1 = flip(x1);
+            }
             *reinterpret_cast<unsigned*>(tile + wave * 3072 + q * 6144 + part * 1024 + kh * 512 +
                                          (((lane & 7) ^ (4 * kh)) + ((8 * c) ^ (8 * kh))) * 16 + (kp & 3) * 4) = split_part(x0, x1);
             v[q][c] = x0;
@@ -351,21 +364,29 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __rest
     const unsigned char* fa0 = smem + wm * 2 * 3072 + frag;
     const unsigned char* fb0 = smem + A_BYTES + wn * NT * 3072 + frag;
     const long long last = ks + (ke - ks - 1) / FK * FK;
-    // unit w of a step: of B's, then of A's; into buffer `buf`; the loads that follow them take the step at k2
+    // unit w of a step: of B's, then of A's (with `sign`); into buffer `buf`; the loads that follow them take the step at k2
     constexpr int UNITS = OpA::UNITS + OpB::UNITS;
-    auto unit = [&](auto w_tag, unsigned buf, long long k2) {
+    auto unit = [&](auto w_tag, unsigned buf, long long k2, unsigned sign) {
         constexpr int w = decltype(w_tag)::value;
-        if constexpr (w < OpB::UNITS) B.template unit<w>(vb, smem + buf + A_BYTES, tid, n0, k2);
-        else A.template unit<w - OpB::UNITS>(va, smem + buf, tid, m0, k2);
+        if constexpr (w < OpB::UNITS) B.template unit<w>(vb, smem + buf + A_BYTES, tid, n0, k2, 0u);
+        else A.template unit<w - OpB::UNITS>(va, smem + buf, tid, m0, k2, sign);
+    };
+    auto negate = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = -acc[i][j];
     };
     A.fetch(va, m0, ks, tid);
     B.fetch(vb, n0, ks, tid);
-    static_for<0, UNITS>([&](auto w) { unit(w, 0u, ks + FK < last ? ks + FK : last); });
+    static_for<0, UNITS>([&](auto w) { unit(w, 0u, ks + FK < last ? ks + FK : last, 0u); });
     __syncthreads();
     unsigned cur = 0;
     for (long long k0 = ks; k0 < ke; k0 += FK, cur ^= BUF) {
         // (past the end: the last step again, into a buffer nobody reads any more)
         const long long k2 = k0 + 2 * FK < last ? k0 + 2 * FK : last;
+        if (k0 > ks && ((k0 - ks) & (FLIP - 1)) == 0) negate();
+        const unsigned sign = ((k0 - ks + FK) & FLIP) ? 0x80000000u : 0u;        // of the step being staged
         bf16x8 fa[2][3], fb[2][3];
         auto frag_b = [&](auto j_tag, int c) {
             constexpr int j = decltype(j_tag)::value;
@@ -386,11 +407,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __rest
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][pa[pr]], fb[j & 1][pb[pr]], acc[i][j], 0, 0, 0);
             if constexpr (j + 1 < NT && g % 12 >= 3 && g % 12 < 6) frag_b(std::integral_constant<int, j + 1>{}, 5 - g % 12);
             constexpr int w0 = g * UNITS / (12 * NT), w1 = (g + 1) * UNITS / (12 * NT);
-            static_for<w0, w1>([&](auto w) { unit(w, cur ^ BUF, k2); });
+            static_for<w0, w1>([&](auto w) { unit(w, cur ^ BUF, k2, sign); });
             __builtin_amdgcn_sched_barrier(0);
         });
         __syncthreads();
     }
+    if ((ke - ks - 1) & FLIP) negate();
     // accumulator register 4q+r of tile (i,j): place 8q + 4hb + r along M, l32 along N
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -440,7 +462,7 @@ hipError_t launch_gemm_f32_t(const GemmF32& g, hipStream_t stream) {
 
 // Splits of a sum over K rows: about 512 workgroups of 128 x 128 in all, at least 128 rows each; long sums (4096 rows and more per split) in as many as
 // 512 workgroups of 128 x 256 take (H = 1024, V = 4096, 33 k rows: 1323 -> 1190 us; with 4500 rows, H = 512, V = 1024, the atomics of so many splits
-// cost more: a call 245 -> 260 us); at most 16384 rows per split (the accumulation's bias, above).
+// cost more: a call 245 -> 260 us); at most 16384 rows per split, so that no sum's rounding grows beyond that of the longest one over the vocabulary.
 }  // namespace
 int k_splits_f32(long long M, long long N, long long K) {
     const long long rows = (M + FT - 1) / FT, narrow = rows * ((N + 127) / 128), wide = rows * ((N + 255) / 256);
