@@ -48,8 +48,10 @@ typedef enum {
 } rnnt_status;
 
 typedef enum {
-    RNNT_F32 = 0, /* enc, pred, W_out are float; everything is computed in fp32: the three      */
-                  /* matrix GEMMs where H, V are multiples of 4 from 64 on, else plain FMA */
+    RNNT_F32 = 0, /* enc, pred, W_out are float; everything is computed to fp32 precision: where  */
+                  /* H, V are multiples of 4 from 64 on as matrix products, each operand the exact */
+                  /* sum of three bfloat16 values (below 2^-110 it loses what lies under 2^-134),  */
+                  /* else by plain FMA                                                        */
     RNNT_BF16 = 1 /* enc, pred, W_out are bfloat16; the three GEMMs run on bf16 MFMA with     */
                   /* fp32 accumulation, tanh/softmax/lattice in fp32                          */
 } rnnt_dtype;

@@ -237,8 +237,8 @@ constexpr int FLIP = 256;     // depth after which the sum changes its sign
 // many of them would show it (d_pred at V = 16384: a mean of -8e-7 of its size, twice the error of the fp32 instruction).  So every FLIP of depth the sum
 // changes its sign, and A enters with the other one: what is lost goes the other way (that mean then: 3e-8; 1.6 % of a call's time).  Error
 // against 64 bits over that of v_mfma_f32_32x32x2_f32, whole calls, 24 seeds each of seven shapes from H = 64, V = 2048 to H = 4096, V = 64: d_enc 0.69 to 0.97, d_pred
-// 0.67 to 1.06, dW_out 0.69 to 1.07.  Operands are exact from 2^-110 on; below, what lies under 2^-134 is lost.  Values beyond the largest bf16, 3.39e38, infinities
-// and NaN give NaN.
+// 0.67 to 1.06, dW_out 0.69 to 1.07.  Operands are exact from 2^-110 on; below, what lies under 2^-134 is lost.  Values beyond the largest bf16, 3.39e38, and
+// infinities: see the end of the kernel.
 // The bf16 instruction does sixteen times the work of the fp32 one, a sixth of it still 2.7 times.  What bounds it: power (1.7 GHz, matrix pipes busy
 // 64 to 67 % of the time; 200 TFLOP/s against 123 to 130 with the fp32 instruction).  H = 1024, V = 4096, 131 k nodes: a call 37.2 -> 22.9 ms.
 // The parts are formed on the way into LDS, so the operands stay as they are in memory.
@@ -332,6 +332,16 @@ struct OperandF32 {
             }
         }
     }
+    // one value as it is
+    __device__ __forceinline__ float value(long long i, long long k) const {
+        bool keep = !EDGE || (i < n_i && k < n_k);
+        if (EDGE && mask.len != nullptr) {
+            const long long src = keep ? (!KSLOW ? i : k) : 0, b = src / mask.period;
+            keep = keep && (int)(src - b * mask.period) < mask.len[b] + mask.extra;
+        }
+        const float x = p[keep ? (!KSLOW ? i * ld + k : k * ld + i) : 0];
+        return keep ? x : 0.0f;
+    }
     // row of a block that stands at place r
     static __device__ __forceinline__ int row_at(int r) { return KSLOW ? (r & 7) * 4 + (r >> 3) : r; }
 };
@@ -414,22 +424,47 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __rest
     }
     if ((ke - ks - 1) & FLIP) negate();
     // accumulator register 4q+r of tile (i,j): place 8q + 4hb + r along M, l32 along N
+    auto store = [&](const f32x16& d, int i, int j) {
+        const long long n = n0 + (wn * NT + j) * 32 + OpB::row_at(l32);
+        if (n >= N) return;
+        const float bv = (bias != nullptr && blockIdx.z == 0) ? bias[n] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(8 * (q >> 2) + 4 * hb + (q & 3));
+            if (m >= M) continue;
+            const float v = d[q] + bv;
+            if (atomic) atomicAdd(C + m * ldc + n, v);
+            else C[m * ldc + n] = v;
+        }
+    };
+    // An operand that is infinite, or beyond the largest bf16, has no three parts: its rest is infinite or NaN, and so is every sum it enters.  A wave
+    // that holds such a sum (or one that is infinite or NaN for another reason) forms its sums again, of the values as they are, on the fp32
+    // instruction, tile after tile.  (H = 1024, V = 4096, 37 k nodes: 8.5 ms a call, the test included, 70 with a NaN in every sum)
+    float odd = 0.0f;                                 // NaN if one is
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const long long n = n0 + (wn * NT + j) * 32 + OpB::row_at(l32);
-            if (n >= N) continue;
-            const float bv = (bias != nullptr && blockIdx.z == 0) ? bias[n] : 0.0f;
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(8 * (q >> 2) + 4 * hb + (q & 3));
-                if (m >= M) continue;
-                const float v = acc[i][j][q] + bv;
-                if (atomic) atomicAdd(C + m * ldc + n, v);
-                else C[m * ldc + n] = v;
-            }
+            for (int q = 0; q < 16; ++q) odd = fmaf(acc[i][j][q], 0.0f, odd);
+    if (__any(odd != 0.0f)) {
+#pragma unroll 1
+        for (int t = 0; t < 2 * NT; ++t) {
+            const int i = t & 1, j = t >> 1;
+            const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(l32), n = n0 + (wn * NT + j) * 32 + OpB::row_at(l32);
+            f32x16 d = f32x16{0};
+            for (long long k0 = ks; k0 < ke; k0 += FK)
+#pragma unroll 2
+                for (int k = 0; k < FK; k += 2)       // (beyond the end of a sum: zeros of both operands)
+                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(A.value(m, k0 + k + hb), B.value(n, k0 + k + hb), d, 0, 0, 0);
+            store(d, i, j);
         }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) store(acc[i][j], i, j);
+    }
 }
 
 struct GemmF32 {

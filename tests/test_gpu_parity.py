@@ -224,6 +224,26 @@ def test_f32_gemm_form_rounds_to_neither_side():
         assert abs(mean) <= 2e-7, (k, mean)
 
 
+@pytest.mark.parametrize("H,V,T,U", [(64, 68, 37, 11), (128, 256, 37, 11), (256, 256, 130, 83)])
+@pytest.mark.parametrize("value", [3.4e38, np.inf])
+def test_f32_gemm_form_weights_beyond_the_largest_bf16(H, V, T, U, value):
+    """One weight that has no parts in bf16, on an activation of -1: its entry of the vocabulary is never emitted.  Narrow tiles with and without edges, wide
+    ones.  (An infinite weight has no finite gradient, in 64 bits neither.)"""
+    wl = synth.custom_workload("huge32", B=2, T_max=T, U_max=U, H=H, V=V, dtype="f32", index=155)
+    batch = synth.make_batch(wl)
+    k, v = H // 2 + 3, V - 7
+    batch.labels[:] = 1 + batch.labels % (V - 20)
+    batch.enc[:, :, k] = -20.0
+    batch.W_out[k, v] = value
+    with np.errstate(all="ignore"):
+        got, ref = run_gpu(batch), run_oracle(batch)
+    _say("huge weight", H, V, value, got["loss"], ref["loss"])
+    assert rel_loss_err(got["loss"].astype(np.float64), ref["loss"]) <= TOL["f32"]["loss"]
+    if np.isfinite(value):
+        assert_parity(got, ref, "f32", f"huge weight {H} {V}")
+        assert np.all(got["dW_out"][:, v] == 0.0)
+
+
 def test_f32_gemm_form_several_chunks_and_accumulate():
     import torch
     wl = synth.custom_workload("g32b", B=6, T_max=90, U_max=20, H=256, V=512, dtype="f32", index=133,

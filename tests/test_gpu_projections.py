@@ -68,6 +68,24 @@ def test_f32_projected_path_tile_gemms_with_edges_and_the_fallback(H, V, H_A, H_
     check(run_gpu_proj(batch, proj), run_oracle_proj(batch, proj), "f32", batch, f"f32 {H},{V},{H_A},{H_L}")
 
 
+@pytest.mark.parametrize("value", [np.inf, -np.inf, 3.4e38])
+def test_f32_projected_path_with_an_encoding_beyond_the_largest_bf16(value):
+    # the frame's activations are +-1; only the gradient of the weights that the infinite value meets has no value (inf times 0)
+    wl = synth.custom_workload("pinf32", B=4, T_max=37, U_max=11, H=256, V=128, dtype="f32", index=133,
+                               t_rule="uniform", t_lo=5, u_rule="uniform", u_lo=0)
+    batch = synth.make_batch(wl)
+    proj = synth.make_proj_inputs(batch, H_A=132, H_L=200)
+    proj.hA[1, 2, 5] = value
+    if np.isfinite(value):
+        proj.W_A[5] = np.copysign(0.9, proj.W_A[5])       # (no product overflows)
+    with np.errstate(all="ignore"):
+        got, ref = run_gpu_proj(batch, proj), run_oracle_proj(batch, proj)
+    if np.isinf(value):
+        assert np.all(np.isnan(got["dW_A"][5])) and np.all(np.isnan(ref["dW_A"][5]))
+        got["dW_A"][5] = ref["dW_A"][5] = 0.0
+    check(got, ref, "f32", batch, f"encoding {value}")
+
+
 def test_f32_identity_projection_equals_the_unprojected_entry_point():
     import torch
     batch = synth.make_batch("C1")
