@@ -348,11 +348,11 @@ struct OperandF32 {
 
 // C[m, n] (+)= sum_k A(m, k) B(k, n) (+ bias[n]) in fp32.  128 x TN output tile per workgroup, 4 waves x (64 x TN/2) = 2 x TN/64 MFMA tiles of
 // 32 x 32, six MFMAs of depth 16 each per K-step; two LDS buffers, one barrier per K-step, global loads two K-steps ahead of their MFMAs in registers.
-// Two workgroups per compute unit (72 KiB of LDS and 256 registers each): one's splitting stands beside the other's MFMAs.
+// Two workgroups per compute unit (72 KiB of LDS and 256 registers each; three of 128 x 128): one's splitting stands beside the other's MFMAs.
 // grid (M/128, N/TN, splits); a split covers k_per_split (a multiple of 16) of K.  atomic != 0: the tile
 // is added to C with float atomics (split over K, or C accumulates over calls).
 template <int TN, class OpA, class OpB>
-__global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __restrict__ C, long long ldc,
+__global__ __launch_bounds__(256, TN == 256 ? 2 : 3) void k_gemm_f32(OpA A, OpB B, float* __restrict__ C, long long ldc,
                                                      const float* __restrict__ bias, int atomic, long long M,
                                                      long long N, long long K, long long k_per_split) {
     constexpr int NT = TN / 64;                       // MFMA tiles of a wave along N
@@ -438,25 +438,71 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f32(OpA A, OpB B, float* __rest
         }
     };
     // An operand that is infinite, or beyond the largest bf16, has no three parts: its rest is infinite or NaN, and so is every sum it enters.  A wave
-    // that holds such a sum (or one that is infinite or NaN for another reason) forms its sums again, of the values as they are, on the fp32
-    // instruction, tile after tile.  (H = 1024, V = 4096, 37 k nodes: 8.5 ms a call, the test included, 70 with a NaN in every sum)
-    float odd = 0.0f;                                 // NaN if one is
+    // that holds such a sum forms its sums again, of the values as they are, on the fp32 instruction, tile after tile, unless NaN among its operands are
+    // the reason (padding, which may hold anything; a sample without an alignment): they give NaN either way.  (Projections of 400 frames, D = 512, whose
+    // padding is NaN: a call 390 -> 418 us; without the search for NaN 831.)
+    float odd = 0.0f;                                 // NaN if one is infinite or NaN
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int q = 0; q < 16; ++q) odd = fmaf(acc[i][j][q], 0.0f, odd);
-    if (__any(odd != 0.0f)) {
+    bool again = __any(odd != 0.0f);
+    int place = l32;
+    asm volatile("" : "+v"(place));                   // (nothing below is formed ahead of the main loop)
+    if (again) {
+        // a bit per place: the infinite and NaN sums of this lane's column (tile by tile), NaN found so far in the rows of A, the columns of B
+        unsigned sums[2][NT], nan_a[2] = {}, nan_b[NT] = {};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                unsigned m = 0;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) m |= fabsf(acc[i][j][q]) < -RNNT_NEG_INF ? 0u : 1u << (8 * (q >> 2) + (q & 3));
+                sums[i][j] = m << (4 * hb);
+            }
+        auto places = [](bool x) {
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(x);
+            return (unsigned)m | (unsigned)(m >> 32);
+        };
+        auto unexplained = [&] {
+            unsigned u = 0;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) u |= (nan_b[j] >> place) & 1u ? 0u : sums[i][j] & ~nan_a[i];
+            return (bool)__any(u != 0);
+        };
+        long long k0 = ks;
+        while (k0 < ke && (again = unexplained())) {
+            const long long k1 = k0 + 64 < ke ? k0 + 64 : ke;
+            bool na[2] = {}, nb[NT] = {};
+#pragma unroll 1
+            for (long long k = k0; k < k1; k += 2) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) na[i] |= __builtin_isnan(A.value(m0 + wm * 64 + i * 32 + OpA::row_at(place), k + hb));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) nb[j] |= __builtin_isnan(B.value(n0 + (wn * NT + j) * 32 + OpB::row_at(place), k + hb));
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) nan_a[i] |= places(na[i]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) nan_b[j] |= places(nb[j]);
+            k0 = k1;
+        }
+        if (again) again = unexplained();
+    }
+    if (again) {
 #pragma unroll 1
         for (int t = 0; t < 2 * NT; ++t) {
             const int i = t & 1, j = t >> 1;
-            const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(l32), n = n0 + (wn * NT + j) * 32 + OpB::row_at(l32);
+            const long long m = m0 + wm * 64 + i * 32 + OpA::row_at(place), n = n0 + (wn * NT + j) * 32 + OpB::row_at(place);
             f32x16 d = f32x16{0};
-            for (long long k0 = ks; k0 < ke; k0 += FK)
-#pragma unroll 2
-                for (int k = 0; k < FK; k += 2)       // (beyond the end of a sum: zeros of both operands)
-                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(A.value(m, k0 + k + hb), B.value(n, k0 + k + hb), d, 0, 0, 0);
+#pragma unroll 1
+            for (long long k = ks; k < ke; k += 2)    // (beyond the end of a sum: zeros of both operands)
+                d = __builtin_amdgcn_mfma_f32_32x32x2f32(A.value(m, k + hb), B.value(n, k + hb), d, 0, 0, 0);
             store(d, i, j);
         }
     } else {
