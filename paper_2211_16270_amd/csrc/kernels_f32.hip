@@ -53,13 +53,15 @@ __device__ __forceinline__ NodePos locate_node(const SampleTable& st, long long 
 // Threads stand in rows of G (a power of two, at most 64) over the vocabulary resp. the hidden columns.  What bounds them: latency; these are calls of
 // a few thousand nodes at most.  One node per wavefront before: every node added its H V products to dW_out with atomics of its own, here
 // a workgroup's nodes are summed first.  A call, H = 32, V = 16, 240 nodes 46.7 -> 25.0 us (43.4 with the present sweep and the old kernels); H = 63,
-// V = 99, 5 k nodes 510 -> 97; H = 301, V = 1001, 300 nodes 1328 -> 589.
+// V = 99, 8 k nodes 755 -> 108; H = 301, V = 1001, 240 nodes 1246 -> 508; H = 1023, V = 4097, 32 k nodes 585 -> 284 ms.
 
 namespace {
 
 constexpr int PLAIN_NODES = 16;            // most nodes per workgroup
 constexpr size_t PLAIN_W = 24 * 1024;      // bytes of W_out that are kept in LDS
 constexpr size_t PLAIN_ROWS = 64 * 1024;   // bytes of rows, for more than one node
+constexpr long long WIDE_WGS = 512;        // workgroups of k_fwd_f32_wide before a thread takes more than one node
+constexpr long long WIDE_LDS = 40 * 1024;
 
 struct PlainShape {
     int nodes;                             // per workgroup
@@ -151,6 +153,95 @@ __global__ __launch_bounds__(256) void k_fwd_f32(Problem pr, SampleTable st, Lat
     }
 }
 
+// The same where W_out stays in memory: a thread takes an entry of the vocabulary for NB nodes at once, so that W_out is read once for them, and keeps
+// running statistics instead of scores (a workgroup then needs 4 H bytes of LDS per node, and several share a compute unit).  Threads stand in rows of
+// 64, 128 or 256 over the vocabulary, a row has NB nodes of its own.
+// What bounds it: the loads of W_out from L1 and L2, one 256-byte line per wavefront for NB multiply-adds.  Losses alone, one node per wavefront, scores in LDS as
+// above, this kernel: H = 1023, V = 4097, 32 k nodes 23.2, 56.0, 7.0 ms; 2 k nodes 4.57, 5.28, 0.90 ms; H = 65, V = 16383, 2 k nodes 1257, 3124, 242 us; H = 30, V = 4097,
+// 32 k nodes 730, 1435, 304 us; H = 127, V = 255, 32 k nodes 194, 203, 118 us; H = 301, V = 1001, 240 nodes 180, 137, 48 us.
+struct WideShape {
+    int g;                                 // log2 of a thread row
+    int pitch;                             // floats per joint row in LDS
+    int nodes;                             // per workgroup
+};
+template <int NB>
+__global__ __launch_bounds__(256) void k_fwd_f32_wide(Problem pr, SampleTable st, LatticeState ls, int s0, int s1, long long rows, WideShape sh) {
+    extern __shared__ __align__(16) float zs[];      // [nodes][pitch]
+    __shared__ NodePos node[4 * NB];
+    __shared__ float4 part[4][NB];         // per wavefront: maximum, sum, blank, label
+    const long long r0 = (long long)blockIdx.x * sh.nodes;
+    const int n = rows - r0 < sh.nodes ? (int)(rows - r0) : sh.nodes, H = pr.H, V = pr.V, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < sh.nodes) node[tid] = locate_node(st, ls.row_base, s0, s1, r0 + (tid < n ? tid : n - 1));
+    __syncthreads();
+    for (int i = wave; i < sh.nodes; i += 4) {
+        const float* enc = (const float*)pr.enc + ((size_t)node[i].s * pr.T_max + node[i].t) * H;
+        const float* prd = (const float*)pr.pred + ((size_t)node[i].s * (pr.U_max + 1) + node[i].u) * H;
+        for (int k = lane; k < sh.pitch; k += 64) zs[i * sh.pitch + k] = k < H ? tanhf(enc[k] + prd[k]) : 0.0f;
+    }
+    __syncthreads();
+    const int row = tid >> sh.g, G = 1 << sh.g;
+    const float* z = zs + row * NB * sh.pitch;
+    float m[NB], sum[NB], cap_b[NB], cap_y[NB];
+    int label[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        m[i] = -3.402823466e38f;           // (finite: entries that are masked out add nothing to it)
+        sum[i] = 0.0f;
+        cap_b[i] = cap_y[i] = RNNT_NEG_INF;
+        label[i] = node_label(pr, node[row * NB + i]);
+    }
+    for (int v = tid & (G - 1); v < V; v += G) {
+        const float* w = (const float*)pr.W + v;
+        float acc[NB] = {};
+        int k = 0;
+#pragma unroll 2
+        for (; k + 4 <= H; k += 4, w += 4 * (size_t)V) {
+            float wk[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wk[j] = w[j * (size_t)V];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const f32x4 zk = *reinterpret_cast<const f32x4*>(z + i * sh.pitch + k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i] = fmaf(zk[j], wk[j], acc[i]);
+            }
+        }
+        for (; k < H; ++k, w += V)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) acc[i] = fmaf(z[i * sh.pitch + k], *w, acc[i]);
+        const float b = pr.b_out[v];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const float h = acc[i] + b, d = h - m[i], e = expf(-fabsf(d));
+            sum[i] = d > 0.0f ? fmaf(sum[i], e, 1.0f) : sum[i] + e;
+            m[i] = fmaxf(m[i], h);
+            if (v == pr.blank) cap_b[i] = h;
+            if (v == label[i]) cap_y[i] = h;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const float M = wave_max(m[i]), S = wave_sum(sum[i] * expf(m[i] - M));
+        cap_b[i] = wave_max(cap_b[i]);
+        cap_y[i] = wave_max(cap_y[i]);
+        if (lane == 0) part[wave][i] = make_float4(M, S, cap_b[i], cap_y[i]);
+    }
+    __syncthreads();
+    if (tid < n) {
+        // the wavefronts of the node's row
+        const int w0 = (tid / NB) << (sh.g - 6), nw = 1 << (sh.g - 6), i = tid % NB;
+        float4 p = part[w0][i];
+        for (int w = 1; w < nw; ++w) {
+            const float4 q = part[w0 + w][i];
+            const float M = fmaxf(p.x, q.x);
+            p = make_float4(M, p.y * expf(p.x - M) + q.y * expf(q.x - M), fmaxf(p.z, q.z), fmaxf(p.w, q.w));
+        }
+        const float lse = p.x + logf(p.y) + (p.x - p.x);                   // (an infinite score: NaN)
+        ls.lse[node[tid].idx] = lse;
+        ls.em[node[tid].idx] = emissions(p.z - lse, node_label(pr, node[tid]) >= 0 ? p.w - lse : EMISSION_FLOOR);
+    }
+}
+
 // f^W_4 and Algorithm 1 lines 8, 10, 11
 __global__ __launch_bounds__(256) void k_bwd_f32(Problem pr, SampleTable st, LatticeState ls, GradOut go, int s0, int s1, long long rows,
                                                  PlainShape sh) {
@@ -206,10 +297,32 @@ __global__ __launch_bounds__(256) void k_bwd_f32(Problem pr, SampleTable st, Lat
     }
 }
 
+namespace {
+template <int NB>
+hipError_t launch_fwd_f32_wide(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0, int s1, long long rows, WideShape sh,
+                               hipStream_t stream) {
+    sh.nodes = NB * (256 >> sh.g);
+    k_fwd_f32_wide<NB><<<dim3((unsigned)((rows + sh.nodes - 1) / sh.nodes)), dim3(256), (size_t)sh.nodes * sh.pitch * 4, stream>>>(pr, st, ls, s0, s1,
+                                                                                                                         rows, sh);
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_fwd_f32(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0, int s1,
                           long long rows, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
     const PlainShape sh = plain_shape(pr.H, pr.V, rows);
+    if (sh.w_pitch == 0) {
+        // as many nodes at once as leave WIDE_WGS workgroups, and at least four of them on a compute unit
+        WideShape w{pr.V <= 64 ? 6 : pr.V <= 128 ? 7 : 8, (pr.H + 3) & ~3, 0};
+        const long long rows_wg = 256 >> w.g;
+        int nb = 8;
+        while (nb > 1 && (rows < WIDE_WGS * rows_wg * nb || rows_wg * nb * w.pitch * 4 > WIDE_LDS)) nb /= 2;
+        if (nb == 8) return launch_fwd_f32_wide<8>(pr, st, ls, s0, s1, rows, w, stream);
+        if (nb == 4) return launch_fwd_f32_wide<4>(pr, st, ls, s0, s1, rows, w, stream);
+        if (nb == 2) return launch_fwd_f32_wide<2>(pr, st, ls, s0, s1, rows, w, stream);
+        return launch_fwd_f32_wide<1>(pr, st, ls, s0, s1, rows, w, stream);
+    }
     k_fwd_f32<<<dim3((unsigned)((rows + sh.nodes - 1) / sh.nodes)), dim3(256), sh.smem, stream>>>(pr, st, ls, s0, s1, rows, sh);
     return hipGetLastError();
 }

@@ -46,23 +46,78 @@ def test_f32_degenerate_and_ragged_lattices(T_len, U_len, blank):
     assert_padding_zero(got, batch)
 
 
-@pytest.mark.parametrize("H,V,B,T,U", [
-    (1, 2, 2, 7, 3),                # the least network
-    (63, 99, 3, 30, 8),             # W_out in LDS, 4 nodes per workgroup
-    (65, 63, 5, 40, 7),             # thread rows of 64 with a rest; 8 nodes
-    (13, 7, 8, 60, 15),             # 16 nodes, short thread rows
-    (301, 1001, 2, 20, 5),          # W_out stays in memory
-    (2047, 5001, 1, 4, 2),          # two nodes' rows fill the LDS
-    (4095, 16383, 1, 2, 1),         # one node's rows
+def _plain_nodes(H, V, rows):
+    """lattice nodes per workgroup of the plain fp32 kernels, and whether W_out lies in LDS"""
+    n = 16 if rows >= 4096 else 8 if rows >= 1024 else 4
+    while n > 1 and n * 4 * (H + V) > 64 * 1024:
+        n //= 2
+    return n, 4 * H * (V | 1) <= 24 * 1024
+
+
+def _wide_form(H, V, rows):
+    """threads per row over the vocabulary and nodes per thread of the plain forward kernel with W_out in memory"""
+    threads, nodes = 64 if V <= 64 else 128 if V <= 128 else 256, 8
+    while nodes > 1 and (rows < 512 * (256 // threads) * nodes or 256 // threads * nodes * 4 * ((H + 3) // 4 * 4) > 40 * 1024):
+        nodes //= 2
+    return threads, nodes
+
+
+@pytest.mark.parametrize("H,V,B,T,U,nodes,w_in_lds", [
+    (1, 2, 2, 7, 3, 4, True),                # the least network
+    (63, 95, 3, 30, 8, 4, True),
+    (63, 99, 3, 30, 8, 4, False),            # W_out just too large for LDS
+    (65, 63, 9, 40, 7, 8, True),             # thread rows of 64 with a rest
+    (13, 7, 14, 60, 15, 16, True),           # short thread rows
+    (301, 1001, 2, 20, 5, 4, False),
+    (2047, 5001, 1, 4, 2, 2, False),         # two nodes' rows fill the LDS
+    (4095, 16383, 1, 2, 1, 1, False),        # one node's rows
 ])
-def test_f32_plain_kernels(H, V, B, T, U):
+def test_f32_plain_kernels(H, V, B, T, U, nodes, w_in_lds):
     wl = synth.custom_workload("plain32", B=B, T_max=T, U_max=U, H=H, V=V, dtype="f32", index=136,
                                t_rule="uniform", t_lo=max(1, T // 2), u_rule="uniform", u_lo=0)
     batch = synth.make_batch(wl)
+    assert _plain_nodes(H, V, batch.rows) == (nodes, w_in_lds), batch.rows
     got, ref = run_gpu(batch), run_oracle(batch)
     e, errs = assert_parity(got, ref, "f32", f"plain fp32 {H} {V}")
     _say("plain fp32", H, V, e, errs)
     assert_padding_zero(got, batch)
+
+
+@pytest.mark.parametrize("H,V,B,T,U,threads,nodes", [
+    (103, 63, 2, 20, 5, 64, 1),
+    (103, 64, 8, 140, 15, 64, 8),            # several rounds, the last workgroup partly filled
+    (4095, 33, 2, 20, 5, 64, 1),             # the most LDS
+    (97, 65, 4, 90, 12, 128, 4),
+    (50, 128, 2, 60, 19, 128, 2),
+    (51, 129, 3, 50, 9, 256, 2),
+    (62, 257, 4, 64, 16, 256, 8),            # H not a multiple of 4, a second round over the vocabulary of one entry
+    (1281, 29, 4, 150, 15, 64, 1),
+    (1282, 301, 2, 150, 15, 256, 4),         # eight nodes would take more than a quarter of the LDS
+])
+def test_f32_plain_forward_kernel_with_the_weights_in_memory(H, V, B, T, U, threads, nodes):
+    wl = synth.custom_workload("wide32", B=B, T_max=T, U_max=U, H=H, V=V, dtype="f32", index=156)
+    batch = synth.with_lengths(synth.make_batch(wl), [T] * (B - 1) + [T - 3], [U] * (B - 1) + [U - 1])
+    assert _wide_form(H, V, batch.rows) == (threads, nodes) and not _plain_nodes(H, V, batch.rows)[1], batch.rows
+    got, ref = run_gpu(batch), run_oracle(batch)
+    e, errs = assert_parity(got, ref, "f32", f"plain fp32, wide {H} {V}")
+    _say("plain fp32, wide", H, V, e, errs)
+    assert_padding_zero(got, batch)
+
+
+@pytest.mark.parametrize("mask", [-np.inf, float(np.finfo(np.float32).min), -1e30])
+@pytest.mark.parametrize("H,V", [(24, 150), (51, 700), (64, 128)])
+def test_f32_masked_vocabulary_entries(H, V, mask):
+    # plain kernels with W_out in LDS and in memory, GEMM form: the first entries of every thread, and everything but blank and labels
+    blank = V - 5
+    wl = synth.custom_workload("masked32", B=2, T_max=17, U_max=5, H=H, V=V, dtype="f32", index=157, blank=blank)
+    batch = synth.make_batch(wl)
+    batch.labels[:] = V - 40 + 7 * np.arange(wl.U_max)
+    entry = np.arange(V)
+    for masked in (entry < V // 2, (entry != blank) & ~np.isin(entry, batch.labels)):
+        batch.b_out[:] = np.where(masked, np.float32(mask), np.linspace(-0.2, 0.2, V, dtype=np.float32))
+        got = run_gpu(batch)
+        assert_parity(got, run_oracle(batch), "f32", f"masked {H} {V}")
+        assert np.all(got["db_out"][masked] == 0.0) and np.all(got["dW_out"][:, masked] == 0.0)
 
 
 @pytest.mark.parametrize("dtype,H,V", [("f32", 24, 11), ("f32", 301, 1001), ("f32", 64, 68), ("bf16", 128, 256)])
