@@ -58,6 +58,7 @@ __device__ __forceinline__ NodePos locate_node(const SampleTable& st, long long 
 namespace {
 
 constexpr int PLAIN_NODES = 16;            // most nodes per workgroup
+constexpr int PLAIN_SUM = 64;              // entries of the vocabulary per partial sum of dz
 constexpr size_t PLAIN_W = 24 * 1024;      // bytes of W_out that are kept in LDS
 constexpr size_t PLAIN_ROWS = 64 * 1024;   // bytes of rows, for more than one node
 constexpr long long WIDE_WGS = 512;        // workgroups of k_fwd_f32_wide before a thread takes more than one node
@@ -287,9 +288,22 @@ __global__ __launch_bounds__(256) void k_bwd_f32(Problem pr, SampleTable st, Lat
         float* d_enc = go.d_enc + ((size_t)node[i].s * pr.T_max + node[i].t) * H;
         float* d_prd = go.d_pred + ((size_t)node[i].s * (pr.U_max + 1) + node[i].u) * H;
         for (int k = tid & ((1 << sh.gh) - 1); k < H; k += 1 << sh.gh) {
+            // (in blocks of four sums: one chain over the vocabulary would round at the full size of the sum all along; V = 16383: d_enc 2.9e-6 off,
+            // 5.2e-7 with a lane per entry before and 5.2e-7 now)
             float dz = 0.0f;
-#pragma unroll 8
-            for (int v = 0; v < V; ++v) dz = fmaf(rw.h[i * V + v], rw.W[(size_t)k * rw.ldw + v], dz);
+            for (int v0 = 0; v0 < V; v0 += PLAIN_SUM) {
+                const int v1 = v0 + PLAIN_SUM < V ? v0 + PLAIN_SUM : V;
+                const float* h = rw.h + i * V;
+                const float* w = rw.W + (size_t)k * rw.ldw;
+                float part[4] = {};
+                int v = v0;
+#pragma unroll 2
+                for (; v + 4 <= v1; v += 4)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) part[j] = fmaf(h[v + j], w[v + j], part[j]);
+                for (; v < v1; ++v) part[0] = fmaf(h[v], w[v], part[0]);
+                dz += (part[0] + part[1]) + (part[2] + part[3]);
+            }
             const float zk = rw.z[i * H + k], dx = dz * (1.0f - zk * zk);
             atomicAdd(&d_enc[k], dx);
             atomicAdd(&d_prd[k], dx);

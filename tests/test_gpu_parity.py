@@ -104,6 +104,18 @@ def test_f32_plain_forward_kernel_with_the_weights_in_memory(H, V, B, T, U, thre
     assert_padding_zero(got, batch)
 
 
+def test_f32_plain_kernels_sum_a_long_vocabulary():
+    """dz is a sum over 16383 entries.  One fp32 chain would leave a random error of about sqrt(16383) half roundings of its size, 2e-6 to 3e-6 (in d_enc,
+    which sums 20 of them); blocks of 64 leave about sqrt(256), and four sums side by side in a block less than that.  (110 frames: the sweep
+    accumulates in fp64 and adds nothing of that size.)"""
+    wl = synth.custom_workload("long32", B=1, T_max=110, U_max=19, H=65, V=16383, dtype="f32", index=158)
+    batch = synth.make_batch(wl)
+    got, ref = run_gpu(batch), run_oracle(batch)
+    err = float(np.linalg.norm(got["d_enc"] - ref["d_enc"]) / np.linalg.norm(ref["d_enc"]))
+    _say("long vocabulary", err)
+    assert err <= 1.2e-6, err
+
+
 @pytest.mark.parametrize("mask", [-np.inf, float(np.finfo(np.float32).min), -1e30])
 @pytest.mark.parametrize("H,V", [(24, 150), (51, 700), (64, 128)])
 def test_f32_masked_vocabulary_entries(H, V, mask):
