@@ -224,7 +224,7 @@ def test_lattice_columns_around_the_wavefronts_of_a_sweep(U, dtype):
     assert_padding_zero(got, batch)
 
 
-# ------------------------------------------------------------------ fp32 MFMA GEMM form (H, V multiples of 4, >= 64)
+# ------------------------------------------------------------------ fp32 GEMM form (H, V multiples of 4, >= 64)
 @pytest.mark.parametrize("H,V", [(128, 128), (256, 384), (384, 128), (64, 64), (68, 100), (320, 1000), (132, 72)])
 def test_f32_gemm_form_against_the_checker(H, V):
     wl = synth.custom_workload("g32", B=5, T_max=37, U_max=11, H=H, V=V, dtype="f32", index=131,
@@ -269,11 +269,24 @@ def test_f32_gemm_form_edge_lattices(T_len, U_len, blank):
     assert_padding_zero(got, batch)
 
 
-def test_f32_gemm_form_wide_tiles_with_edges():
-    """Enough nodes for GEMM tiles of 256 columns, whose last one is partly filled (V = 300, H = 320)."""
-    wl = synth.custom_workload("g32w", B=2, T_max=230, U_max=90, H=320, V=300, dtype="f32", index=134)
+def _wide_gemm_tiles(M, N, splits=1):
+    """Whether a GEMM of the fp32 form takes tiles of 256 columns instead of 128."""
+    rows = (M + 127) // 128 * splits
+    rounds = lambda edge: (rows * ((N + edge - 1) // edge) + 511) // 512
+    return 10 * rounds(256) <= 6 * rounds(128)
+
+
+@pytest.mark.parametrize("T,U,wide", [(150, 90, True), (230, 90, False)])
+def test_f32_gemm_form_wide_tiles_with_edges(T, U, wide):
+    """Tiles of 256 columns, the last one partly filled (V = 300, H = 320), in the scores, dZ and dW; with more nodes tiles of 128 in the first two."""
+    H, V = 320, 300
+    wl = synth.custom_workload("g32w", B=2, T_max=T, U_max=U, H=H, V=V, dtype="f32", index=134)
     batch = synth.make_batch(wl)
     got, ref = run_gpu(batch), run_oracle(batch)
+    st, info, _ = Bd.rnnt_joint_loss_plan(got["desc"], batch.T_len, batch.U_len, 0)
+    rows = (batch.rows + 127) // 128 * 128
+    assert st == 0 and info["chunk_rows"] == rows
+    assert _wide_gemm_tiles(rows, V) == wide and _wide_gemm_tiles(rows, H) == wide
     e, errs = assert_parity(got, ref, "f32", "fp32 GEMM form, wide tiles")
     _say("fp32 GEMM form, wide tiles", e, errs)
 
