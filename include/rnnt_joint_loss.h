@@ -173,7 +173,8 @@ rnnt_status rnnt_validate_labels_host(const rnnt_desc* desc, const int32_t* labe
  * T_len    HOST [B]                1..T_max
  * U_len    HOST [B]                0..U_max
  * loss     dev  [B]                float, out; +inf for a sample no alignment of which is possible (a needed score is -inf;
- *                                  a ln P below -1e29 counts as none), whose gradients are not finite then
+ *                                  a ln P below -1e29 counts as none), whose gradients are not finite then (a
+ *                                  sample_weight of 0 leaves it out, see below)
  * d_enc    dev  [B, T_max, H]      float (bfloat16 if desc->input_grads_bf16), out, fully overwritten
  *                                  (zeros in padded rows)
  * d_pred   dev  [B, U_max+1, H]    the same type, out, fully overwritten (zeros in padded rows)

@@ -108,11 +108,12 @@ __device__ __forceinline__ RowPost row_posteriors(const LatticeState& ls, long l
     else r.Bk = (u == U) ? __expf(ab) : 0.0f;
     r.Yk = (u < U) ? __expf(a + em.y + c - lnP + next[1]) : 0.0f;
     if (ls.weight) {
-        // gradients of sum_b w_b loss_b: every posterior weight of sample s is scaled by w_s >= 0
+        // gradients of sum_b w_b loss_b: every posterior weight of sample s is scaled by w_s >= 0; one of weight 0 contributes nothing, whatever its
+        // posteriors are (without a possible alignment they are infinite)
         const float w = ls.weight[s];
-        r.log_gamma += __logf(w);          // -inf for w = 0: the sample contributes nothing
-        r.Bk *= w;
-        r.Yk *= w;
+        r.log_gamma = w > 0.0f ? r.log_gamma + __logf(w) : RNNT_NEG_INF;
+        r.Bk = w > 0.0f ? r.Bk * w : 0.0f;
+        r.Yk = w > 0.0f ? r.Yk * w : 0.0f;
     }
     return r;
 }

@@ -179,6 +179,12 @@ def test_samples_without_a_possible_alignment(dtype, H, V, keep, T, U, mask):
         assert rel_loss_err(got["loss"][others], ref["loss"][others]) <= TOL[dtype]["loss"]
         for k in ("d_enc", "d_pred"):
             assert rel_grad_err(got[k][others], ref[k][others]) <= TOL[dtype]["grad"], k
+        # a weight of 0 leaves it out of every gradient
+        w = np.array([0.5, 0.0, 1.5, 1.0], dtype=np.float32)
+        got, ref = run_gpu(with_label, keep_scores=keep, sample_weight=w), run_oracle(batch, sample_weight=w)
+        assert got["loss"][1] == np.inf
+        for k in GRADS:
+            assert rel_grad_err(got[k].astype(np.float64), ref[k]) <= TOL[dtype]["grad"], k
 
 
 @pytest.mark.parametrize("B", [1, 127, 128])
