@@ -376,7 +376,7 @@ def main():
     # HBM bytes per launch from the committed rocprofv3 counter summary of this workload, if any
     tname = f"hbm_traffic_{wl.name}" + ("_keep_scores" if args.keep_scores else "") + ".txt"
     traffic = read_traffic(os.path.join(ROOT, "profiles", tname)) if not args.batch else {}
-    # fp32: GEMMs (each operand as three bf16 parts) where the plan has chunk buffers (H, V multiples of 128; `kernel` is
+    # fp32: GEMMs (each operand as three bf16 parts) where the plan has chunk buffers (H, V multiples of 4 from 64 on; `kernel` is
     # then the group of launches of one chunk: three GEMMs and the row kernels between them), else plain FMA
     roofline = {"bound": "mfma" if (wl.dtype == "bf16" or info["chunk_rows"] > 0) else "alu", "kernel": dom,
                 "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s", "frac": achieved / peak,

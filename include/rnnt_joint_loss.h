@@ -107,7 +107,7 @@ typedef struct {
     int64_t chunk_rows;       /* rows per backward chunk: tile-padded (bf16), lattice nodes    */
                               /* (fp32 GEMM form), 0 for the plain fp32 kernels                */
     size_t  workspace_bytes;  /* bytes the plan uses                                           */
-    size_t  lattice_bytes;    /* part of it: lse, lpb, lpy, alpha, beta of one group           */
+    size_t  lattice_bytes;    /* part of it: lse, emissions, alpha, beta of one group          */
     size_t  chunk_bytes;      /* part of it: bf16 score-gradient / joint chunk buffers         */
 } rnnt_plan_info;
 

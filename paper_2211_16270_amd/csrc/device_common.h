@@ -71,14 +71,6 @@ __device__ __forceinline__ float2 emissions(float blank, float label) {
     return make_float2(blank < EMISSION_FLOOR ? EMISSION_FLOOR : blank, label < EMISSION_FLOOR ? EMISSION_FLOOR : label);
 }
 
-// ln(e^a + e^b); either may be -inf.
-__device__ __forceinline__ float log_add_exp(float a, float b) {
-    float m = fmaxf(a, b);
-    if (m == RNNT_NEG_INF) return m;
-    float d = -fabsf(a - b);                      // -inf when exactly one is -inf
-    return m + __logf(1.0f + __expf(d));
-}
-
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -363,8 +363,8 @@ constexpr int FLIP = 1024;    // depth after which the sum changes its sign
 // instruction adds two.  The accumulation rounds towards minus infinity, a mean of 5e-11 of the result's size per unit of depth, alike for all results: sums over
 // many of them would show it (d_pred at V = 16384: a mean of -8e-7 of its size, twice the error of the fp32 instruction).  So every FLIP of depth the sum
 // changes its sign, and A enters with the other one: what is lost goes the other way (that mean then: 2e-8; 1.1 % of a call's time, 2 % with 256).  Error
-// against 64 bits over that of v_mfma_f32_32x32x2_f32, whole calls, 24 seeds each of seven shapes from H = 64, V = 2048 to H = 4096, V = 64: d_enc 0.69 to 0.97, d_pred
-// 0.67 to 1.06, dW_out 0.69 to 1.07.  Operands are exact from 2^-110 on; below, what lies under 2^-134 is lost.  Values beyond the largest bf16, 3.39e38, and
+// against 64 bits over that of v_mfma_f32_32x32x2_f32, whole calls, 24 seeds each of seven shapes from H = 64, V = 2048 to H = 4096, V = 64: d_enc 0.69 to 0.96, d_pred
+// 0.66 to 1.01, dW_out 0.62 to 1.00.  Operands are exact from 2^-110 on; below, what lies under 2^-134 is lost.  Values beyond the largest bf16, 3.39e38, and
 // infinities: see the end of the kernel.
 // The bf16 instruction does sixteen times the work of the fp32 one, a sixth of it still 2.7 times.  What bounds it: power (1.7 GHz, matrix pipes busy
 // 64 to 67 % of the time; 200 TFLOP/s against 123 to 130 with the fp32 instruction).  H = 1024, V = 4096, 131 k nodes: a call 37.2 -> 22.8 ms.

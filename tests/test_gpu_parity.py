@@ -828,7 +828,7 @@ def test_autograd_front_end_returns_the_library_gradients():
 
 
 def test_autograd_front_end_with_float32_leaves():
-    # fp32 tensors go through the fp32 path (here its MFMA GEMM form): gradients against the checker at the
+    # fp32 tensors go through the fp32 path (here its GEMM form): gradients against the checker at the
     # fp32 tolerance, for a plain sum and for a masked mean
     import torch
     from paper_2211_16270_amd.autograd import rnnt_joint_loss
