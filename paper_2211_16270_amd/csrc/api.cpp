@@ -757,11 +757,9 @@ extern "C" rnnt_status rnnt_joint_proj_loss_fwd_bwd(const rnnt_desc* desc, int32
     if (!workspace || ((uintptr_t)workspace % WS_ALIGN) != 0) return RNNT_ERR_WORKSPACE;
     const ProjLayout l = proj_layout(*desc);
     if (workspace_bytes <= l.bytes) return RNNT_ERR_WORKSPACE;
-    {
-        Plan p;
-        build_plan(*desc, T_len, U_len, workspace_bytes - l.bytes, p);
-        if (p.total_bytes > workspace_bytes - l.bytes) return RNNT_ERR_WORKSPACE;
-    }
+    Plan p;
+    build_plan(*desc, T_len, U_len, workspace_bytes - l.bytes, p);
+    if (p.total_bytes > workspace_bytes - l.bytes) return RNNT_ERR_WORKSPACE;
     hipStream_t stream = (hipStream_t)hip_stream;
     unsigned char* w = (unsigned char*)workspace;
     void* enc = w + l.off_enc;
@@ -772,37 +770,24 @@ extern "C" rnnt_status rnnt_joint_proj_loss_fwd_bwd(const rnnt_desc* desc, int32
     const long long rows_a = (long long)desc->B * desc->T_max, rows_l = (long long)desc->B * (desc->U_max + 1);
     const int H = desc->H;
 
+    // (the inner call's checks, ahead of the first launch)
+    stt = check_call(desc, enc, pred, W_out, b_out, labels, loss, d_enc, d_pred, dW_out, db_out, true, nullptr);
+    if (stt != RNNT_OK) return stt;
+    // the inner call puts T_len, U_len at the start of its workspace (plan offsets off_T, off_U)
+    const ProjSide sides[2] = {{hA, rows_a, H_A, RowMask{(const int*)(w + l.bytes + p.off_T), desc->T_max, 0}, W_A, b_Z, enc, d_enc, d_hA, dW_A, db_Z},
+                               {hL, rows_l, H_L, RowMask{(const int*)(w + l.bytes + p.off_U), desc->U_max + 1, 1}, W_L, nullptr, pred, d_pred,
+                                d_hL, dW_L, nullptr}};
+
     // Eq. 4, the two linear maps.  The length tables of the inner call are not on the device yet:
     // the projections run over all rows and the padded ones, whose input may be anything, are
     // skipped by the inner path (never read), so no mask is needed here.
-    const RowMask none{nullptr, 1, 0};
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_forward(bf16, hA, rows_a, H_A, none, W_A, b_Z, H, enc, stream); }));
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_forward(bf16, hL, rows_l, H_L, none, W_L, nullptr, H, pred, stream); }));
+    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_forward(bf16, sides, H, !desc->accumulate_params, stream); }));
 
     stt = run(desc, enc, pred, W_out, b_out, labels, T_len, U_len, loss, d_enc, d_pred, dW_out, db_out,
               w + l.bytes, workspace_bytes - l.bytes, hip_stream, true);
     if (stt != RNNT_OK) return stt;
 
-    // the inner call has put T_len, U_len at the start of its workspace (plan offsets off_T, off_U)
-    Plan p;
-    build_plan(*desc, T_len, U_len, workspace_bytes - l.bytes, p);
-    const RowMask mask_a{(const int*)(w + l.bytes + p.off_T), desc->T_max, 0};
-    const RowMask mask_l{(const int*)(w + l.bytes + p.off_U), desc->U_max + 1, 1};
-    if (!desc->accumulate_params) {
-        PrepArgs pa{};
-        pa.zero_ptr[0] = dW_A;
-        pa.zero_n[0] = (size_t)H_A * H;
-        pa.zero_ptr[1] = dW_L;
-        pa.zero_n[1] = (size_t)H_L * H;
-        pa.zero_ptr[2] = db_Z;
-        pa.zero_n[2] = (size_t)H;
-        RNNT_HIP(timed(KC_PREPARE, stream, [&] { return launch_prepare(pa, stream); }));
-    }
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_backward_input(bf16, d_enc, rows_a, H, W_A, H_A, d_hA, stream); }));
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_backward_input(bf16, d_pred, rows_l, H, W_L, H_L, d_hL, stream); }));
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_backward_weight(bf16, hA, rows_a, H_A, mask_a, d_enc, H, dW_A, stream); }));
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_backward_weight(bf16, hL, rows_l, H_L, mask_l, d_pred, H, dW_L, stream); }));
-    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_col_sum(d_enc, rows_a, H, db_Z, stream); }));
+    RNNT_HIP(timed(KC_PROJ, stream, [&] { return launch_proj_backward(bf16, sides, H, stream); }));
     return RNNT_OK;
 }
 

@@ -208,15 +208,25 @@ struct RowMask {
     int period;       // T_max, or U_max + 1
     int extra;        // 0 for frames (t < T_len), 1 for label positions (u <= U_len)
 };
-// out[r,:] = h[r,:] W + bias  (out in the input dtype; bias may be null)   h [rows,D], W [D,H]
-hipError_t launch_proj_forward(int bf16, const void* h, long long rows, int D, const RowMask& mask, const void* W,
-                               const float* bias, int H, void* out, hipStream_t stream);
-// d_in[r,:] = d_out[r,:] W^T   (d_out fp32 [rows,H], zero in padded rows; d_in fp32 [rows,D])
-hipError_t launch_proj_backward_input(int bf16, const float* d_out, long long rows, int H, const void* W, int D,
-                                      float* d_in, hipStream_t stream);
-// dW += h^T d_out over the real rows   (dW fp32 [D,H])
-hipError_t launch_proj_backward_weight(int bf16, const void* h, long long rows, int D, const RowMask& mask,
-                                       const float* d_out, int H, float* dW, hipStream_t stream);
+// One of the two maps, out = h W (+ bias), with what its backward pass reads and writes.  h [rows,D] and W [D,H] in the input dtype, padded rows of h
+// may hold anything; out [rows,H] in the input dtype; d_out fp32 [rows,H], zero in padded rows; d_in fp32 [rows,D].
+struct ProjSide {
+    const void* h;
+    long long rows;
+    int D;
+    RowMask mask;            // of the rows (length tables on the device: read by the backward launch only)
+    const void* W;
+    const float* bias;       // or null
+    void* out;
+    const float* d_out;
+    float* d_in;
+    float* dW;               // fp32 [D,H], added to
+    float* db;               // += column sums of d_out, or null
+};
+// out of both maps; with `clear` dW of both and db of the first are cleared besides
+hipError_t launch_proj_forward(int bf16, const ProjSide (&s)[2], int H, bool clear, hipStream_t stream);
+// d_in = d_out W^T, dW += h^T d_out over the real rows, db += column sums of d_out
+hipError_t launch_proj_backward(int bf16, const ProjSide (&s)[2], int H, hipStream_t stream);
 // C[m,n] (+)= sum_k A(m,k) B(k,n) (+ bias[n]) in fp32 precision (operands as three bf16 parts), any M, N, K.  An operand
 // is k-slow (element (i,k) at p[k*ld + i]) or k-contiguous (at p[i*ld + k]); combinations: A contiguous with
 // either B, or both slow.  Rows of an operand's source array outside its mask read as zero.  atomic: C is
