@@ -6,7 +6,7 @@
 //   MODE 1  dh = gamma softmax - posteriors as bf16, and z, into the chunk buffers (f^W_4, backward)
 //   MODE 2  MODE 0, and z and the scores themselves kept for the backward pass, as fp16 differences t = h - m to a running
 //           maximum m (t <= 0, so an entry's error exp(t) |t| 2^-11 in the softmax is at most 2^-11 / e whatever the size of
-//           the scores; m is the row's largest score so far in its quarter of the vocabulary, one float per row and 64 entries)
+//           the scores; m is the row's largest score so far in its segment of the vocabulary, one float per row and 64 entries)
 //
 // A workgroup is 4 waves (8: eight_waves_pay); a wave owns 32 RB rows (RB = 1: half a lattice tile, 2: a whole one) and keeps their joint
 // activations in registers for the whole pass (H/16 fragments of 4 registers per 32 rows: 128 registers at H = 512).
@@ -41,17 +41,15 @@ struct ScoreArgs {
     unsigned char* Z;
     float* kept_max;       // MODE 2: [tiles][V/64][64 rows]
     ActiveTiles at;        // MODE 1
-    f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0, 2): [4 segments][rows of the launch] {max, sum, blank, label score}
+    f32x4* part;           // vocabulary split over gridDim.y > 1 (MODE 0, 2): [segments][rows of the launch] {max, sum, blank, label score}
 };
 
 constexpr int SC_VB = 32;          // vocabulary entries per block
 constexpr int SC_RING = 8;         // W_out fragments a wave holds ahead of its MFMAs
-constexpr int SC_SEG = 4;          // statistics are formed per quarter of the vocabulary and folded in order, so that a
-                                   // result does not depend on how many workgroups share the vocabulary
 // Smallest running maximum, finite: entries that are masked out (bias -inf, or finite and below anything a network gives) then have the
-// exponential 0, and blocks or quarters of nothing else the sum 0, instead of -inf - -inf or the rounding error of -1e30 log2 e in the
+// exponential 0, and blocks or segments of nothing else the sum 0, instead of -inf - -inf or the rounding error of -1e30 log2 e in the
 // exponent.  At this size that error is at most 2^6, and 2^64 times as many entries as there may be is still finite in fp32: maxima
-// just above the floor lose to any other quarter's without an infinity.
+// just above the floor lose to any other segment's without an infinity.
 constexpr float SC_MAX_FLOOR = -1073741824.0f;
 constexpr int SC_SPLIT_MAX_WG = 512;  // launches of more workgroups fill the chip without sharing the vocabulary (forward)
 constexpr int SC_AGPR_FRAGS = 64;  // joint fragments kept in the 256 accumulation registers; the rest in vector registers
@@ -93,7 +91,8 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
     float* bias_lds = reinterpret_cast<float*>(smem + NST * SB);          // [NST][64], 32 values and their repetition
     float* esum_lds = bias_lds + NST * 64;                               // [WAVES], and the arrival order [1]
     // this workgroup's part of the vocabulary: blocks [vb0, vb0 + nvb)
-    const int nvb = V / SC_VB / (int)gridDim.y, vb0 = (int)blockIdx.y * nvb;
+    const int vb0 = score_part_begin((int)blockIdx.y, (int)gridDim.y, V, MODE != 1);
+    const int nvb = score_part_begin((int)blockIdx.y + 1, (int)gridDim.y, V, MODE != 1) - vb0;
     const char* wpb = reinterpret_cast<const char*>(a.Wp) + (size_t)vb0 * (KK * 1024) + wave * (PER * 1024);
     const float* bias_g = a.pr.b_out + vb0 * SC_VB;
     const unsigned lane_b = (unsigned)lane * 16u;
@@ -247,9 +246,10 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
         s_tot[rb] = s_tot[rb] * __builtin_amdgcn_exp2f((m_tot[rb] - mn) * LOG2E_F) + S * __builtin_amdgcn_exp2f((M - mn) * LOG2E_F);
         m_tot[rb] = mn;
     };
-    const int segs = SC_SEG / (int)gridDim.y, seg_blocks = nvb / segs;
+    const int seg_blocks = V / SC_VB / score_segments(V);
+    int seg = vb0 / seg_blocks, seg_next = seg_blocks;       // (MODE 0, 2) the segment, and the part's block behind its end
     const size_t part_rows = (size_t)gridDim.x * TW * 64, part_row = (size_t)ti * 64 + 32 * half0 + l32;
-    auto segment_end = [&](int seg) {
+    auto segment_end = [&](int segment) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const float S = both_halves_sum(s_run[rb]);
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
             } else {
                 const float cb = both_halves_max(cap_b[rb]), cy = both_halves_max(cap_y[rb]);
                 if (hb == 0) {
-                    float* q = reinterpret_cast<float*>(a.part + (size_t)((int)blockIdx.y * segs + seg) * part_rows + part_row + 32 * rb);
+                    float* q = reinterpret_cast<float*>(a.part + (size_t)segment * part_rows + part_row + 32 * rb);
                     __hip_atomic_store(q, m_run[rb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(q + 1, S, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(q + 2, cb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -369,7 +369,10 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
                             s_run[rb] += sum0[rb] + sum1[rb];
                             if (MODE == 2) m_pair[rb] = m_run[rb];
                         }
-                        if (vb % seg_blocks == 0) segment_end(vb / seg_blocks - 1);
+                        if (vb == seg_next) {
+                            segment_end(seg++);
+                            seg_next += seg_blocks;
+                        }
                     }
                     if constexpr (MODE == 2 && CUR % 2 == 1) {
                         // the pair (vb - 3, vb - 2): its running maximum was complete when block vb - 1 ended
@@ -438,7 +441,7 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
                     keep_max(rb, nvb - 2);
                 }
             }
-            segment_end(segs - 1);
+            segment_end(seg);
         }
     };
     tail(std::integral_constant<int, NACC - 1>{});
@@ -458,18 +461,22 @@ __global__ __launch_bounds__(64 * WAVES, WPS) void k_scores(ScoreArgs a) {
         }
         __syncthreads();
         if (*order != (int)gridDim.y - 1) return;
+        auto fold_all = [&](auto n_tag) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
+            for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-            for (int seg = 0; seg < SC_SEG; ++seg) {
-                const float* p = reinterpret_cast<const float*>(a.part + (size_t)seg * part_rows + part_row + 32 * rb);
-                const float M = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const float S = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                cap_b[rb] = fmaxf(cap_b[rb], __hip_atomic_load(p + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                cap_y[rb] = fmaxf(cap_y[rb], __hip_atomic_load(p + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                fold(rb, M, S);
+                for (int seg = 0; seg < decltype(n_tag)::value; ++seg) {
+                    const float* p = reinterpret_cast<const float*>(a.part + (size_t)seg * part_rows + part_row + 32 * rb);
+                    const float M = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const float S = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cap_b[rb] = fmaxf(cap_b[rb], __hip_atomic_load(p + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                    cap_y[rb] = fmaxf(cap_y[rb], __hip_atomic_load(p + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                    fold(rb, M, S);
+                }
             }
-        }
+        };
+        if (score_segments(V) == 8) fold_all(std::integral_constant<int, 8>{});
+        else fold_all(std::integral_constant<int, 4>{});
     }
     float esum = 0.0f;
 #pragma unroll
@@ -508,13 +515,9 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
         configured = true;
     }
     int vs = 1;
-    if (MODE == 1) {
-        vs = vocabulary_split(n, SLOTS, a.pr.V / SC_VB);
-    } else if (n <= SC_SPLIT_MAX_WG) {
-        vs = vocabulary_split(n, SLOTS, a.pr.V / SC_VB);
-        while (MODE == 2 && a.pr.V / SC_VB / vs % 4 != 0) vs /= 2;      // (kept scores leave in pairs of blocks, two pairs at a time)
-        if ((size_t)SC_SEG * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
-    }
+    // (kept scores leave in pairs of blocks, two pairs at a time)
+    if (MODE == 1 || n <= SC_SPLIT_MAX_WG) vs = score_split(n, SLOTS, a.pr.V, MODE != 1, MODE == 2 ? 4 : 2).parts;
+    if (MODE != 1 && (size_t)score_segments(a.pr.V) * n * TW * 64 * sizeof(f32x4) > part_bytes) vs = 1;
     k_scores<MODE, KK, RB, WPS, WAVES><<<dim3((unsigned)n, (unsigned)vs), dim3(64 * WAVES), smem, stream>>>(a);
     return hipGetLastError();
 }
@@ -523,10 +526,8 @@ hipError_t launch_scores_t(ScoreArgs a, size_t part_bytes, hipStream_t stream) {
 // as much from LDS per MFMA, but a small launch of them has to split the vocabulary to fill the chip, and then every part builds the
 // joint rows again, which costs as much as 8 blocks.  A call with V = 1024: one sample of 250 x 50 176 -> 147 us, two of 120 x 24 148 -> 116,
 // eight 195 -> 179, 32 619 -> 567; sixteen, where the rule leaves the whole tiles, 361 -> 362; V = 4096: one sample 319 -> 269 us.
-bool half_tiles_pay(int tiles, int V) {
-    const int nvb = V / SC_VB, n2 = (tiles + 3) / 4, n1 = (tiles + 1) / 2;
-    const long long c2 = 2 * split_cost(n2, vocabulary_split(n2, 256, nvb), 256, nvb, 8);
-    const long long c1 = split_cost(n1, vocabulary_split(n1, 256, nvb), 256, nvb, 8);
+bool half_tiles_pay(int tiles, int V, bool statistics) {
+    const long long c2 = 2 * score_split((tiles + 3) / 4, 256, V, statistics).cost, c1 = score_split((tiles + 1) / 2, 256, V, statistics).cost;
     return c1 * 10 < c2 * 9;
 }
 
@@ -562,7 +563,7 @@ hipError_t launch_fwd_bf16(const Problem& pr, const void* Wpack, const SampleTab
             return eight_waves_pay(0, pr, tile1 - tile0) ? launch_scores_t<0, 32, 1, 2, 8>(a, part_bytes, stream)
                                           : launch_scores_t<0, 32, 1, 2>(a, part_bytes, stream);
         case 640:
-            return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<0, 40, 1, 1>(a, part_bytes, stream)
+            return half_tiles_pay(tile1 - tile0, pr.V, true) ? launch_scores_t<0, 40, 1, 1>(a, part_bytes, stream)
                                                        : launch_scores_t<0, 40, 2, 1>(a, part_bytes, stream);
         case 768: return launch_scores_t<0, 48, 1, 1>(a, part_bytes, stream);
         case 896: return launch_scores_t<0, 56, 1, 1>(a, part_bytes, stream);
@@ -583,7 +584,7 @@ hipError_t launch_bwd_scores_bf16(const Problem& pr, const void* Wpack, const Sa
         case 512:
             return eight_waves_pay(1, pr, tile1 - tile0) ? launch_scores_t<1, 32, 1, 2, 8>(a, 0, stream) : launch_scores_t<1, 32, 1, 2>(a, 0, stream);
         case 640:
-            return half_tiles_pay(tile1 - tile0, pr.V) ? launch_scores_t<1, 40, 1, 1>(a, 0, stream)
+            return half_tiles_pay(tile1 - tile0, pr.V, false) ? launch_scores_t<1, 40, 1, 1>(a, 0, stream)
                                                        : launch_scores_t<1, 40, 2, 1>(a, 0, stream);
         case 768: return launch_scores_t<1, 48, 1, 1>(a, 0, stream);
         case 896: return launch_scores_t<1, 56, 1, 1>(a, 0, stream);

@@ -15,7 +15,8 @@
 // transposing LDS read.  Both maps of a direction are one launch (forward: k_proj_forward; backward: k_proj_backward, the four products and db_Z).
 // What bounds it: at the sizes of a training step (8000 + 1632 rows, D = H = 512: 15 GFLOP in all) the latency of a K-step's loads and the number of
 // launches; a large batch, the bytes.  So loads run two K-steps ahead in registers and are not touched before they go to LDS (masks and the rounding of
-// fp32 operands are applied there).  BEFORE_AFTER
+// fp32 operands are applied there).  32 samples of 250 x 50, D = H = 512: forward 18.6 us, backward 47,
+// where seven launches that waited for each step's loads took 55 and 172; a call 1161 -> 1012 us.
 // fp32 path: the tile GEMM of the fp32 joint path where rows are 16-byte aligned (D, H multiples of 4);
 // else one thread per output element.
 #include "device_common.h"
@@ -416,7 +417,8 @@ __global__ __launch_bounds__(256) void k_col_sum(const float* __restrict__ x, lo
     atomicAdd(&out[c], (s0 + s1) + (s2 + s3));
 }
 
-// Splits of a weight gradient's sum over the rows: about 256 workgroups, at least 256 rows each (every split adds its tile to dW with float atomics).
+// Splits of a weight gradient's sum over the rows: about 256 workgroups, at least 256 rows each (every split adds its tile to dW with float atomics:
+// with about 512 the call above takes 1012 us, with 256 or 128 1000 to 1004).
 int proj_weight_splits(int tiles, long long rows) {
     long long s = (256 + tiles - 1) / tiles;
     const long long most = (rows + 255) / 256;

@@ -16,6 +16,13 @@
 
 #include "../../include/rnnt_joint_loss.h"
 
+// (this header is also read by a host compiler)
+#ifdef __HIPCC__
+#define RNNT_HOST_DEVICE __host__ __device__
+#else
+#define RNNT_HOST_DEVICE
+#endif
+
 namespace rnnt {
 
 constexpr int TILE_ROWS = 64;    // lattice tile: 8 frames x 8 label positions or 16 x 4 (kernels.h: tile_label_width)
@@ -93,7 +100,7 @@ inline int dw_splits_max(int H, int V) {
     return (int)(dw_slot_bytes(H, V) / ((size_t)dw_tiles(H, V) * DW_TILE * DW_TILE * 4));
 }
 
-// How many workgroups share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
+// How many workgroups of the dz GEMM share the vocabulary of one set of rows (1, 2 or 4): the fewest rounds of the chip, a workgroup costing
 // its share of the blocks and `fixed` blocks' time for its start and end.
 inline long long split_cost(int workgroups, int vs, int slots, int nvb, int fixed) {
     return ((long long)workgroups * vs + slots - 1) / slots * (fixed + nvb / vs);
@@ -107,6 +114,42 @@ inline int vocabulary_split(int workgroups, int slots, int nvb, int fixed = 8) {
             best = vs;
             best_cost = cost;
         }
+    }
+    return best;
+}
+
+// Score kernels: how many workgroups share the vocabulary of one set of rows.  Statistics (forward pass) are formed per segment of the vocabulary and
+// folded in order, so that a result does not depend on the number of workgroups; a part is a run of whole segments, of up to one more than another's.
+// Eight segments from V = 2048 on, where a fold per 256 entries and more is nothing; else four.  The backward pass forms no statistics: its parts are
+// runs of whole pairs of blocks.
+// (A segment is a whole number of pairs of blocks: kept scores leave in pairs, as differences to one maximum.)
+RNNT_HOST_DEVICE inline int score_segments(int V) { return V >= 2048 && V % 512 == 0 ? 8 : 4; }
+// first block (of 32 entries) of part y of `parts`; statistics: parts of whole segments
+RNNT_HOST_DEVICE inline int score_part_begin(int y, int parts, int V, bool statistics) {
+    const int nvb = V / 32, units = statistics ? score_segments(V) : nvb / 2;
+    return units * y / parts * (nvb / units);
+}
+// The fewest rounds of the chip, a workgroup costing the blocks of the longest part and `fixed` blocks' time for its start and end; every part has a
+// multiple of `multiple` blocks.  Up to eight parts instead of 1, 2 or 4, a call: H = 640, V = 8192 one sample of 60 x 10 205 -> 152 us, of 250 x 50
+// 506 -> 454; H = 1024, V = 4096 one of 60 x 10 174 -> 139, 16 of up to 50 x 10 380 -> 346, eight of 100 x 20 623 -> 581; losses alone 16 of 50 x 10,
+// H = 640, V = 4096 90.5 -> 76.1 (H = 512, where the number of parts stays: 68.8 -> 69.5, eight segments to fold instead of four).
+struct ScoreSplit {
+    int parts;
+    long long cost;
+};
+inline ScoreSplit score_split(int workgroups, int slots, int V, bool statistics, int multiple = 2, int fixed = 8) {
+    ScoreSplit best{1, 0};
+    for (int p = 1; p <= 8; ++p) {
+        int longest = 0;
+        bool whole = true;
+        for (int y = 0; y < p; ++y) {
+            const int n = score_part_begin(y + 1, p, V, statistics) - score_part_begin(y, p, V, statistics);
+            longest = std::max(longest, n);
+            whole = whole && n > 0 && n % multiple == 0;
+        }
+        if (!whole) continue;
+        const long long cost = ((long long)workgroups * p + slots - 1) / slots * (fixed + longest);
+        if (p == 1 || cost * 10 < best.cost * 9) best = ScoreSplit{p, cost};
     }
     return best;
 }

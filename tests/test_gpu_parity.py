@@ -1113,3 +1113,24 @@ def test_bf16_single_inputs_beyond_the_exponentials(H, T, U, t, u):
     got, ref = run_gpu(batch), run_oracle(batch)
     assert_parity(got, ref, "bf16", f"far {t} {u}")
     assert_padding_zero(got, batch)
+
+
+@pytest.mark.parametrize("H,V,T", [
+    (1024, 2048, 576),      # 36 workgroups: seven parts, forward and backward
+    (1024, 2048, 800),      # 50: five
+    (1024, 4096, 1000),     # 63: four, and 1000 x 8 nodes in 16 x 4 or 8 x 8 tiles
+    (768, 2304, 1000),      # a vocabulary of four segments (V / 256 is odd), the backward pass in other parts than the forward pass
+    (640, 4096, 400),       # half a tile per wave, 25 workgroups
+    (512, 2048, 1000),      # two workgroups per compute unit, eight parts
+    (128, 8192, 90),
+])
+def test_bf16_vocabulary_in_any_number_of_parts(H, V, T):
+    wl = synth.custom_workload("vparts", B=1, T_max=T, U_max=7, H=H, V=V, dtype="bf16", index=160)
+    one = synth.make_batch(wl)
+    _say("vocabulary parts", H, V, T)
+    ref = run_oracle(one)
+    got = run_gpu(one, skip_below_log2=-1)
+    assert_parity(got, ref, "bf16", f"H={H} V={V} T={T}")
+    kept = run_gpu(one, keep_scores=1)
+    assert_parity(kept, ref, "bf16", f"H={H} V={V} T={T}, kept scores")
+    np.testing.assert_array_equal(got["loss"], kept["loss"])

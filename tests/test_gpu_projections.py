@@ -129,3 +129,17 @@ def test_bf16_projected_path_bench_workload_subbatch_and_accumulate():
     for k in ("dW_A", "db_Z", "dW_L", "dW_out", "db_out"):
         e = rel_grad_err(got2[k].astype(np.float64), 2.0 * ref[k])
         assert e <= TOL["bf16"]["grad"], (k, e)
+
+
+@pytest.mark.parametrize("B,T_max,U_max,H,H_A,H_L", [
+    (1, 1, 0, 128, 128, 128),       # one row a side
+    (2, 64, 127, 128, 128, 256),    # whole tiles and K-steps
+    (37, 29, 6, 384, 256, 640),     # several splits of the rows, padded rows (NaN) among them and at the end of a split
+    (3, 341, 2, 256, 128, 128),     # a split ends inside a K-step
+])
+def test_bf16_projections_at_the_edges_of_tiles_and_splits(B, T_max, U_max, H, H_A, H_L):
+    wl = synth.custom_workload("pedge", B=B, T_max=T_max, U_max=U_max, H=H, V=256, dtype="bf16", index=134,
+                               t_rule="uniform", t_lo=max(1, T_max // 2), u_rule="uniform", u_lo=U_max // 2)
+    batch = synth.make_batch(wl)
+    proj = synth.make_proj_inputs(batch, H_A=H_A, H_L=H_L)
+    check(run_gpu_proj(batch, proj), run_oracle_proj(batch, proj), "bf16", batch, f"bf16 {B}x{T_max}x{U_max} {H},{H_A},{H_L}")

@@ -484,3 +484,39 @@ def test_counter_summaries_name_kernels_the_library_has():
     for f in files:
         names = {line.split()[0] for line in open(f) if line.strip() and not line.startswith("#")}
         assert names and names <= have, (os.path.basename(f), names - have)
+
+
+def test_parts_of_the_vocabulary_are_runs_of_whole_segments(tmp_path):
+    # every vocabulary the score kernels take, every number of parts the rule may choose: the parts follow each other, cover the vocabulary, hold
+    # whole segments (statistics) or pairs of blocks, and where scores are kept a multiple of four blocks
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "parts.cpp"
+    src.write_text('#include "%s"\n' % os.path.join(ROOT, "paper_2211_16270_amd", "csrc", "plan.h") + """
+#include <cstdio>
+int main() {
+    int bad = 0, most = 0;
+    for (int V = 256; V <= 16384; V += 256)
+        for (int statistics = 0; statistics < 2; ++statistics)
+            for (int multiple = 2; multiple <= (statistics ? 4 : 2); multiple += 2)
+                for (int slots = 256; slots <= 512; slots += 256)
+                    for (int n = 1; n <= 520; ++n) {
+                        const int p = rnnt::score_split(n, slots, V, statistics, multiple).parts, seg = V / 32 / rnnt::score_segments(V);
+                        most = std::max(most, p);
+                        if (seg % 2) ++bad;
+                        if (rnnt::score_part_begin(0, p, V, statistics) != 0 || rnnt::score_part_begin(p, p, V, statistics) != V / 32) ++bad;
+                        for (int y = 0; y < p; ++y) {
+                            const int b = rnnt::score_part_begin(y, p, V, statistics), e = rnnt::score_part_begin(y + 1, p, V, statistics);
+                            if (e <= b || (e - b) % multiple || (statistics && b % seg)) ++bad;
+                        }
+                    }
+    std::printf("%d %d\\n", bad, most);
+}
+""")
+    exe = tmp_path / "parts"
+    subprocess.run([gxx, "-std=c++17", "-O1", "-o", str(exe), str(src)], check=True, capture_output=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+    assert out.split() == ["0", "8"]
