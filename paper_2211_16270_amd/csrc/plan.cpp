@@ -150,6 +150,10 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
         // kept scores: 8 GiB, so that a group still fills the GPU when a row takes 10 KB
         const unsigned long long budget = p.keep ? (8ULL << 30) : (832ULL << 20);
         long long by_bytes = (long long)(budget / crb) / GEMM_TILE * GEMM_TILE;
+        // fp32: up to 2 GiB where the longest sample needs them, so that its scores are computed once (H = 1024, V = 4096, four samples of up to 500 x 100, 45 k nodes
+        // each where 832 MiB hold 35 k: 30.9 -> 26.3 ms a call)
+        if (p.f32_gemm)
+            by_bytes = std::max(by_bytes, std::min((long long)align_up((size_t)max_rows, GEMM_TILE), (long long)((2ULL << 30) / crb) / GEMM_TILE * GEMM_TILE));
         chunk_default = std::min(all_tile_rows, std::max<long long>(chunk_floor, by_bytes));
     }
     // fp32 sums of d_enc, d_pred for the samples of a group: 256 MiB by default
@@ -256,14 +260,23 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
             }
         }
     } else if (p.f32_gemm) {
-        // fp32 GEMM form: ranges of lattice nodes that fit the chunk buffers
+        // fp32 GEMM form: ranges of lattice nodes that fit the chunk buffers.  Whole samples where they fit: their sweep and backward pass then follow their
+        // forward pass, and find its scores in the buffers.
         for (int gi = 0; gi < (int)p.groups.size(); ++gi) {
             const Group& g = p.groups[gi];
-            for (long long r0 = 0; r0 < g.rows; r0 += chunk_rows) {
-                Chunk c{gi, g.tile0, g.tile1};
-                c.row0 = r0;
-                c.rows = std::min(chunk_rows, g.rows - r0);
-                p.chunks.push_back(c);
+            for (int s0 = g.s0, s1; s0 < g.s1; s0 = s1) {
+                s1 = s0 + 1;
+                while (s1 < g.s1 && p.row_off[s1 + 1] - p.row_off[s0] <= chunk_rows) ++s1;
+                const long long rows = p.row_off[s1] - p.row_off[s0], nch = (rows + chunk_rows - 1) / chunk_rows;
+                const long long per = (long long)align_up((size_t)((rows + nch - 1) / nch), GEMM_TILE);
+                for (long long r0 = 0; r0 < rows; r0 += per) {
+                    Chunk c{gi, g.tile0, g.tile1};
+                    c.row0 = p.row_off[s0] - p.row_off[g.s0] + r0;
+                    c.rows = std::min(per, rows - r0);
+                    c.s0 = s0;
+                    c.s1 = s1;
+                    p.chunks.push_back(c);
+                }
             }
         }
     } else {

@@ -39,7 +39,10 @@ struct Group {
 struct Chunk {
     int group;
     int tile0, tile1;    // global tile range, inside the group's range
-    long long row0 = 0, rows = 0;   // fp32 GEMM form: lattice nodes [row0, row0 + rows) of the group instead
+    // fp32 GEMM form: lattice nodes [row0, row0 + rows) of the group instead, all of samples [s0, s1): as many whole samples as one chunk holds, or
+    // one that takes several chunks
+    long long row0 = 0, rows = 0;
+    int s0 = 0, s1 = 0;
 };
 
 struct Plan {

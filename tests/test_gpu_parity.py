@@ -1134,3 +1134,22 @@ def test_bf16_vocabulary_in_any_number_of_parts(H, V, T):
     kept = run_gpu(one, keep_scores=1)
     assert_parity(kept, ref, "bf16", f"H={H} V={V} T={T}, kept scores")
     np.testing.assert_array_equal(got["loss"], kept["loss"])
+
+
+@pytest.mark.parametrize("rows", [128, 256, 640, 1408])
+def test_f32_chunks_of_whole_samples_and_samples_of_several_chunks(rows):
+    # 276 to 451 nodes a sample: chunks of 128 and 256 nodes take one sample in several (of equal size, the last one a little shorter), of 640 one or two
+    # samples, of 1408 three to five
+    wl = synth.custom_workload("f32chunks", B=7, T_max=41, U_max=10, H=64, V=100, dtype="f32", index=161,
+                               t_rule="uniform", t_lo=33, u_rule="uniform", u_lo=8)
+    batch = synth.make_batch(wl)
+    ref = run_oracle(batch)
+    desc = Bd.make_desc(batch.B, wl.T_max, wl.U_max, wl.H, wl.V, wl.blank, Bd.RNNT_F32)
+    least = Bd.rnnt_joint_loss_workspace_bytes(desc, batch.T_len, batch.U_len, 1)
+    budget = least + (rows - 128) * 4 * (wl.V + 2 * wl.H)
+    while Bd.rnnt_joint_loss_plan(desc, batch.T_len, batch.U_len, budget)[1]["chunk_rows"] < rows:
+        budget += 1 << 14
+    st, info, _ = Bd.rnnt_joint_loss_plan(desc, batch.T_len, batch.U_len, budget)
+    _say("f32 chunks", rows, info, batch.T_len, batch.U_len)
+    assert st == 0 and info["chunk_rows"] >= rows
+    assert_parity(run_gpu(batch, budget_bytes=budget), ref, "f32", f"chunks of {rows}")
