@@ -213,153 +213,177 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void k_lattice_wave(SampleTable st,
 
 // ---- sweep in fp64 (fp32 path, 128 steps or more): the recursion accumulates in fp64 and alpha, beta are rounded to fp32 once, when stored (a
 // sweep of T+U dependent fp32 log-add-exps loses about sqrt(T+U) half-ulps of values of the order of 100, 2e-4 relative in
-// the posteriors of a 500 x 100 lattice).  One thread per label position, the neighbour's value through LDS.
-constexpr int LAT_PF = 8;       // prefetch distance in steps
-__device__ __forceinline__ double lattice_lae(double a, double b) {
-    const double m = fmax(a, b);
-    return m + log1p(exp(-fabs(a - b)));      // one of the two may be -inf
+// the posteriors of a 500 x 100 lattice).  The same wavefronts, blocks and loads as the fp32 sweep.  A value is m 2^k: a step multiplies the two ways
+// by their emissions, brings them to the larger k and adds, so the dependent chain holds no exponential and no logarithm; those of the emissions and of
+// what is stored stand beside it.  k is a whole number in fp64, so no emission is too small for it (EMISSION_FLOOR included).
+// What bounds it: issue, about 110 instructions a step.  One thread per label position, a barrier per step and the recursion in logarithms before: a call, two
+// samples of 120 x 24, H = V = 64, 220 -> 137 us; four of 500 x 100 1002 -> 714; 16 of up to 232 x 46 717 -> 573.  Errors against 64 bits as before (what is stored
+// differs by 1e-11 ahead of its rounding).
+struct Scaled {
+    double m, k;
+};
+constexpr double LW_NONE_K = -1e280;      // 0 = 2^LW_NONE_K (absorbs whatever is added)
+constexpr double LOG2E_D = 1.4426950408889634074, LN2_D = 0.69314718055994530942;
+
+// 2^x, |x| <= 1/2: Taylor series, relative error below 1e-11
+__device__ __forceinline__ double exp2_half(double x) {
+    constexpr double c[10] = {1.0, 0.69314718055994530942, 0.24022650695910071233, 0.055504108664821579953, 0.0096181291076284771620,
+                              0.0013333558146428443423, 1.5403530393381609954e-4, 1.5252733804059840280e-5, 1.3215486790144309488e-6,
+                              1.0178086009239699728e-7};
+    double r = c[9];
+#pragma unroll
+    for (int i = 8; i >= 0; --i) r = fma(r, x, c[i]);
+    return r;
+}
+// e^x
+__device__ __forceinline__ Scaled scaled_exp(double x) {
+#pragma clang fp contract(off)      // (y - k is at most 1/2, and 0 for an emission of EMISSION_FLOOR, only with y rounded)
+    const double y = x * LOG2E_D, k = rint(y);
+    return {exp2_half(y - k), k};
+}
+__device__ __forceinline__ Scaled times(const Scaled& a, const Scaled& b) { return {a.m * b.m, a.k + b.k}; }
+// 2^d, d <= 0 a whole number (far below the exponents of fp64: 0)
+__device__ __forceinline__ double scale_down(double m, double d) { return ldexp(m, (int)fmax(d, -4000.0)); }
+__device__ __forceinline__ Scaled plus(const Scaled& a, const Scaled& b) {
+    const double k = fmax(a.k, b.k);
+    return {scale_down(a.m, a.k - k) + scale_down(b.m, b.k - k), k};
+}
+// ln(m 2^k), m > 0: an fp32 logarithm, and what it leaves over: the logarithm of a number within 1e-6 of 1
+__device__ __forceinline__ double scaled_log(const Scaled& a) {
+    const int e = __builtin_amdgcn_frexp_exp(a.m);
+    const double f = __builtin_amdgcn_frexp_mant(a.m) * 1.41421356237309504880;      // [0.71, 1.42)
+    const double l = (double)__builtin_amdgcn_logf((float)f);
+    return fma(l + (a.k + (e - 0.5)), LN2_D, fma(f, exp2_half(-l), -1.0));
 }
 
-__global__ __launch_bounds__(LAT_MAX_T) void k_lattice_f64(SampleTable st, LatticeState ls, int s0, float* __restrict__ loss) {
-    __shared__ double xch[2][LAT_MAX_T + 2];
-    __shared__ float red[LAT_MAX_T / 64];
-    __shared__ __align__(16) float edge[LAT_MAX_T / 64][2][LW_B];
-    __shared__ float c_better;
-    if (threadIdx.x < LAT_MAX_T / 64 * LW_B) edge[threadIdx.x / LW_B][1][threadIdx.x % LW_B] = LW_NONE;
+__device__ __forceinline__ double from_words(int lo, int hi) { return __hiloint2double(hi, lo); }
+__device__ __forceinline__ double lane_from_below(double v, double first) {
+    return from_words(__builtin_amdgcn_update_dpp(__double2loint(first), __double2loint(v), 0x138, 0xf, 0xf, false),
+                      __builtin_amdgcn_update_dpp(__double2hiint(first), __double2hiint(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return from_words(__builtin_amdgcn_readlane(__double2loint(v), lane), __builtin_amdgcn_readlane(__double2hiint(v), lane));
+}
 
-    const int s = s0 + blockIdx.x;
-    const bool is_beta = (blockIdx.y != 0);
-    const int tid = threadIdx.x;
-    const int T = st.T[s], U = st.U[s], W1 = U + 1;
+template <bool BETA, bool MANY, int BLOCKS>
+__device__ __forceinline__ void lattice_sweep_f64(const SampleTable& st, const LatticeState& ls, int s, float c, float* __restrict__ loss,
+                                                  Scaled (*edge)[2][LW_B]) {
+    const int lane = threadIdx.x & 63, wave = MANY ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int waves = MANY ? (int)(blockDim.x >> 6) : 1;
+    const int T = st.T[s], U = st.U[s], W = U + 1, n = T * W;
     const long long base = st.row_off[s] - ls.row_base;
     const float2* __restrict__ em = ls.em + base;
-    const int n = T * W1;
-    auto at = [&](int t, int u) { return lattice_index(T, W1, t, u); };
+    float* __restrict__ out = (BETA ? ls.beta : ls.alpha) + base;
+    const double cd = (double)c;
+    const int nsteps = T + U;
+    const int v = 64 * wave + lane;               // column in sweep order: label position v (alpha), U - v (beta)
+    const unsigned T_act = v < W ? (unsigned)T : 0u;
+    const int v_off = BETA ? U - v : v;
 
-    const float c_mean = emission_offset(st, ls, s, em, n, red);
-    {
-        xch[0][tid + 1] = (double)RNNT_NEG_INF;
-        xch[1][tid + 1] = (double)RNNT_NEG_INF;
-        if (tid == 0) {
-            xch[0][0] = xch[1][0] = (double)RNNT_NEG_INF;
-            xch[0][blockDim.x + 1] = xch[1][blockDim.x + 1] = (double)RNNT_NEG_INF;
-        }
-        __syncthreads();
+    // (as in the fp32 sweep)
+    auto block_base = [&](int b) {
+        int k = LW_B * b + (lane & (LW_B - 1));
+        k = k < 0 ? 0 : k < nsteps ? k : nsteps - 1;
+        const int K = BETA ? nsteps - 1 - k : k;
+        return diagonal_offset(T, W, K) - (K >= T ? K - T + 1 : 0);
+    };
+    auto node = [&](int bases, int j) {
+        const unsigned i = (unsigned)(__builtin_amdgcn_readlane(bases, j) + v_off);
+        return i < (unsigned)(n - 1) ? i : (unsigned)(n - 1);
+    };
+    float2 e[BLOCKS][LW_B];
+    unsigned at[BLOCKS][LW_B];
+    auto load = [&](auto slot_tag, int bases, auto j_tag) {
+        constexpr int slot = decltype(slot_tag)::value, j = decltype(j_tag)::value;
+        at[slot][j] = node(bases, j);
+        e[slot][j] = em[at[slot][j]];
+    };
+    static_for<0, BLOCKS - 1>([&](auto q) {
+        const int bases = block_base(decltype(q)::value - wave);
+        static_for<0, LW_B>([&](auto j) { load(q, bases, j); });
+    });
+    const Scaled none{1.0, LW_NONE_K};
+    // What leaves a node for the next step, to this lane's column and to the next one's: alpha with the node's own emissions, beta without any (those of
+    // the node that is entered are taken there).
+    Scaled to_own = none, to_next = none, fin = none;
+    if (v == 0) to_own = Scaled{1.0, 0.0};
+    const int nblk = (nsteps + LW_B - 1) / LW_B, total = nblk + waves - 1;
+    Scaled carry = none;                          // last column of the wavefront below, at the step before the block
+    for (int i0 = 0; i0 < total; i0 += BLOCKS) {
+        static_for<0, BLOCKS>([&](auto q_tag) {
+            constexpr int q = decltype(q_tag)::value;
+            const int i = i0 + q, b = i - wave;
+            Scaled below = none;                              // lane j: the last column of the wavefront below at step j
+            if (MANY && wave > 0) below = edge[wave - 1][(q + 1) & 1][lane & (LW_B - 1)];
+            const int bases_ahead = block_base(b + BLOCKS - 1);
+            static_for<0, LW_B>([&](auto j_tag) {
+                constexpr int j = decltype(j_tag)::value;
+                const int k = LW_B * b + j;
+                Scaled first = none;
+                if (MANY) first = j == 0 ? carry : Scaled{lane_value(below.m, j - 1), lane_value(below.k, j - 1)};
+                Scaled x = to_own, y{lane_from_below(to_next.m, first.m), lane_from_below(to_next.k, first.k)};
+                const Scaled eb = scaled_exp((double)e[q][j].x + cd), ey = scaled_exp((double)e[q][j].y + cd);
+                if constexpr (BETA) {
+                    x = times(x, eb);
+                    y = times(y, ey);
+                }
+                Scaled val = plus(x, y);
+                if constexpr (j == LW_B - 1) {                // (the mantissa of a value stays within 2^(2 LW_B) of 1)
+                    const int up = __builtin_amdgcn_frexp_exp(val.m);
+                    val = Scaled{__builtin_amdgcn_frexp_mant(val.m), val.k + up};
+                }
+                to_own = BETA ? val : times(val, eb);
+                to_next = BETA ? val : times(val, ey);
+                if (!BETA) {
+                    const bool end = k == nsteps - 1;
+                    fin.m = end ? to_own.m : fin.m;
+                    fin.k = end ? to_own.k : fin.k;
+                }
+                if (MANY && wave + 1 < waves && lane == 63) edge[wave][q & 1][j] = to_next;
+                if ((unsigned)(k - v) < T_act) out[at[q][j]] = (float)scaled_log(val);
+                load(std::integral_constant<int, (q + BLOCKS - 1) % BLOCKS>{}, bases_ahead, j_tag);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if (MANY) {
+                if (wave > 0) carry = Scaled{lane_value(below.m, LW_B - 1), lane_value(below.k, LW_B - 1)};
+                __syncthreads();
+            }
+        });
     }
-    float c;
-    const int u = tid;
-    const bool col = (u <= U);
-    const int nsteps = T + U;   // anti-diagonals 0 .. T+U-1
-    {
-        // alpha and beta are still stored as fp32, so their magnitude where the posteriors
-        // are not negligible decides the accuracy.  With c = -ln P / (T+U) the offset ln P is zero and alpha, beta
-        // stay near zero along the alignments that carry the probability, whatever the emissions look like (flat
-        // scores, where the number of alignments adds hundreds to ln P, or peaked ones).  ln P is not known
-        // beforehand: both workgroups of the sample first run the fp32 alpha sweep without storing anything (the same arithmetic in
-        // both, hence the same c; any c near it would do), then the sweep proper.
-        const double lnP_off = lattice_sweep<false, true, false, 4>(st, ls, s, c_mean, nullptr, edge), steps = T + U;
-        if (u == U) c_better = no_alignment(lnP_off - c_mean * steps) ? c_mean : (float)(c_mean - lnP_off / steps);
-        __syncthreads();
-        c = c_better;
+    if (!BETA && v == U) {
+        const double lnP_off = scaled_log(fin), lnP_true = lnP_off - cd * (double)(T + U);
+        const bool none_possible = no_alignment(lnP_true);
+        ls.lnP[s] = none_possible ? RNNT_NEG_INF : (float)lnP_off;
+        ls.shift[s] = c;
+        loss[s] = none_possible ? -RNNT_NEG_INF : (float)-lnP_true;
     }
-    double own = RNNT_NEG_INF;
-    int par = 0;
-    float pb[LAT_PF], py[LAT_PF];
+}
 
-    if (!is_beta) {
-        float* __restrict__ alpha = ls.alpha + base;
-        // step k handles node (t = k - u, u): needs the blank's emission at (t-1,u), the label's at (t,u-1)
-        auto fetch = [&](int k, float& fb, float& fy) {
-            const int t = k - u;
-            fb = 0.0f;
-            fy = 0.0f;
-            if (col && t >= 0 && t < T) {
-                if (t > 0) fb = em[at(t - 1, u)].x;
-                if (u > 0) fy = em[at(t, u - 1)].y;
-            }
-        };
-#pragma unroll
-        for (int i = 0; i < LAT_PF; ++i) fetch(i, pb[i], py[i]);
-        for (int k0 = 0; k0 < nsteps; k0 += LAT_PF) {
-#pragma unroll
-            for (int i = 0; i < LAT_PF; ++i) {
-                const int k = k0 + i;
-                if (k < nsteps) {
-                    const int t = k - u;
-                    const bool act = col && t >= 0 && t < T;
-                    const double left = xch[par][u];          // column u-1, previous step
-                    double val = own;
-                    if (act) {
-                        if (k == 0) {
-                            val = (double)0;
-                        } else {
-                            // the offset and the boundary conditions go into the emission values, which do not
-                            // depend on the step before: the dependent chain is own -> add -> log-add-exp
-                            const double eb = (t > 0) ? (double)pb[i] + (double)c : (double)RNNT_NEG_INF;
-                            const double ey = (u > 0) ? (double)py[i] + (double)c : (double)RNNT_NEG_INF;
-                            val = lattice_lae(own + eb, left + ey);
-                        }
-                        alpha[at(t, u)] = (float)val;
-                        own = val;
-                    }
-                    xch[par ^ 1][u + 1] = val;
-                    fetch(k + LAT_PF, pb[i], py[i]);
-                    __syncthreads();
-                    par ^= 1;
-                }
-            }
-        }
-        if (u == U) {
-            // own = alpha[T-1,U]; ln P (offset) = alpha + final blank
-            const double lnP_off = own + ((double)em[n - 1].x + (double)c);
-            const double lnP_true = lnP_off - (double)c * (double)(T + U);
-            const bool none = no_alignment(lnP_true);
-            ls.lnP[s] = none ? RNNT_NEG_INF : (float)lnP_off;
-            ls.shift[s] = c;
-            loss[s] = none ? -RNNT_NEG_INF : (float)-lnP_true;
-        }
-    } else {
-        float* __restrict__ beta = ls.beta + base;
-        // step k handles node (t = T-1 - (k - (U-u)), u): needs both emissions of the node
-        auto fetch = [&](int k, float& fb, float& fy) {
-            const int t = T - 1 - (k - (U - u));
-            fb = 0.0f;
-            fy = 0.0f;
-            if (col && t >= 0 && t < T) {
-                fb = em[at(t, u)].x;
-                if (u < U) fy = em[at(t, u)].y;
-            }
-        };
-#pragma unroll
-        for (int i = 0; i < LAT_PF; ++i) fetch(i, pb[i], py[i]);
-        for (int k0 = 0; k0 < nsteps; k0 += LAT_PF) {
-#pragma unroll
-            for (int i = 0; i < LAT_PF; ++i) {
-                const int k = k0 + i;
-                if (k < nsteps) {
-                    const int t = T - 1 - (k - (U - u));
-                    const bool act = col && t >= 0 && t < T;
-                    const double right = xch[par][u + 2];     // column u+1, previous step
-                    double val = own;
-                    if (act) {
-                        if (k == 0) {
-                            val = (double)pb[i] + (double)c;           // beta[T-1,U] = final blank
-                        } else {
-                            const double eb = (t < T - 1) ? (double)pb[i] + (double)c : (double)RNNT_NEG_INF;
-                            const double ey = (u < U) ? (double)py[i] + (double)c : (double)RNNT_NEG_INF;
-                            val = lattice_lae(own + eb, right + ey);
-                        }
-                        beta[at(t, u)] = (float)val;
-                        own = val;
-                    }
-                    xch[par ^ 1][u + 1] = val;
-                    fetch(k + LAT_PF, pb[i], py[i]);
-                    __syncthreads();
-                    par ^= 1;
-                }
-            }
-        }
+template <int MAX_WAVES>
+__global__ __launch_bounds__(64 * MAX_WAVES) void k_lattice_f64(SampleTable st, LatticeState ls, int s0, float* __restrict__ loss) {
+    constexpr bool MANY = MAX_WAVES > 1;
+    constexpr int BLOCKS = 2;                         // (registers; a step takes long enough that eight ahead suffice)
+    __shared__ float red[MAX_WAVES];
+    __shared__ __align__(16) float edge32[MAX_WAVES][2][LW_B];
+    __shared__ __align__(16) Scaled edge[MAX_WAVES][2][LW_B];
+    __shared__ float c_better;
+    if (threadIdx.x < MAX_WAVES * LW_B) {
+        edge32[threadIdx.x / LW_B][1][threadIdx.x % LW_B] = LW_NONE;
+        edge[threadIdx.x / LW_B][1][threadIdx.x % LW_B] = Scaled{1.0, LW_NONE_K};
     }
+    const int s = s0 + blockIdx.x, T = st.T[s], U = st.U[s];
+    const float c_mean = emission_offset(st, ls, s, ls.em + (st.row_off[s] - ls.row_base), T * (U + 1), red);
+    // alpha and beta are still stored as fp32, so their magnitude where the posteriors
+    // are not negligible decides the accuracy.  With c = -ln P / (T+U) the offset ln P is zero and alpha, beta
+    // stay near zero along the alignments that carry the probability, whatever the emissions look like (flat
+    // scores, where the number of alignments adds hundreds to ln P, or peaked ones).  ln P is not known
+    // beforehand: both workgroups of the sample first run the fp32 alpha sweep without storing anything (the same arithmetic in
+    // both, hence the same c; any c near it would do), then the sweep proper.
+    const double lnP_off = lattice_sweep<false, MANY, false, BLOCKS>(st, ls, s, c_mean, nullptr, edge32), steps = T + U;
+    if ((int)threadIdx.x == U) c_better = no_alignment(lnP_off - c_mean * steps) ? c_mean : (float)(c_mean - lnP_off / steps);
+    __syncthreads();
+    if (blockIdx.y == 0) lattice_sweep_f64<false, MANY, BLOCKS>(st, ls, s, c_better, loss, edge);
+    else lattice_sweep_f64<true, MANY, BLOCKS>(st, ls, s, c_better, loss, edge);
 }
 
 hipError_t launch_lattice(const SampleTable& st, const LatticeState& ls, int s0, int s1, int u_max, int wide,
@@ -368,7 +392,9 @@ hipError_t launch_lattice(const SampleTable& st, const LatticeState& ls, int s0,
     const int waves = (u_max + 64) / 64;
     if (64 * waves > LAT_MAX_T) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(s1 - s0), 2), threads(64 * waves);
-    if (wide) k_lattice_f64<<<grid, threads, 0, stream>>>(st, ls, s0, loss);
+    if (wide && waves == 1) k_lattice_f64<1><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
+    else if (wide && waves <= 8) k_lattice_f64<8><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
+    else if (wide) k_lattice_f64<16><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
     else if (waves == 1) k_lattice_wave<1><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
     else if (waves <= 8) k_lattice_wave<8><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
     else k_lattice_wave<16><<<grid, threads, 0, stream>>>(st, ls, s0, loss);
