@@ -386,7 +386,8 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         const Group& g = plan.groups[gi];
         const LatticeState ls = group_state(gi);
         RNNT_HIP(timed(KC_BWD_F32, stream, [&] {
-            return launch_bwd_f32_gemm(pr, wv.st, ls, go, g.s0, g.s1, c.row0, c.rows, have_scores, (float*)wv.dH, (float*)wv.Z, wv.dZ32, stream);
+            return launch_bwd_f32_gemm(pr, wv.st, ls, go, g.s0, g.s1, c.tile0, c.tile1, c.row0, c.rows, have_scores, (float*)wv.dH, (float*)wv.Z,
+                                       wv.dZ32, stream);
         }));
         return RNNT_OK;
     };

@@ -119,11 +119,12 @@ hipError_t launch_bwd_f32(const Problem& pr, const SampleTable& st, const Lattic
 // fp32 GEMM form of the same two steps for H, V multiples of 4, over lattice nodes [r0, r0 + n) of the
 // group (node index relative to the group's first).  S [rows, V], Z and dZ [rows, H] are chunk buffers of
 // n rounded up to a multiple of 128 rows.  have_scores: S and Z already hold what launch_fwd_f32_gemm left for these nodes.
+// Lattice tiles [tile0, tile1) hold all of the nodes.
 hipError_t launch_fwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, int s0, int s1,
                                long long r0, long long n, float* S, float* Z, hipStream_t stream);
 hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, const GradOut& go,
-                               int s0, int s1, long long r0, long long n, bool have_scores, float* S, float* Z, float* dZ,
-                               hipStream_t stream);
+                               int s0, int s1, int tile0, int tile1, long long r0, long long n, bool have_scores, float* S, float* Z,
+                               float* dZ, hipStream_t stream);
 
 // ---- lattice (alpha, beta, loss) ------------------------------------------------------------
 // wide != 0: the sweep accumulates in fp64 (alpha, beta, ln P still stored as fp32); used by the fp32 path

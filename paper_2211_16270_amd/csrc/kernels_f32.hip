@@ -6,7 +6,8 @@
 //      S = Z W + b                            (Eq. 6)            k_gemm_f32 <A k-contiguous, B k-slow>
 //      lse, emissions per row                 (f^W_1)            k_rows_stats_f32
 //      dh = gamma softmax - posteriors        (f^W_4)            k_rows_dh_f32 (in place of S)
-//      db += column sums, dW += Z^T dh        (Alg. 1 line 8)    k_gemm_f32 <A k-slow, B k-slow>, split over the rows
+//        db += column sums of dh              (Alg. 1 line 8)
+//      dW += Z^T dh                           (Alg. 1 line 8)    k_gemm_f32 <A k-slow, B k-slow>, split over the rows
 //      dZ = dh W^T                            (Alg. 1 l. 10-11)  k_gemm_f32 <A k-contiguous, B k-contiguous>
 //      d_enc, d_pred += dZ (1 - Z^2)                             k_rows_dz_f32
 //    The chunk buffers S [rows, V], Z and dZ [rows, H] live in the workspace; rows beyond the chunk's
@@ -718,26 +719,41 @@ __global__ __launch_bounds__(256) void k_rows_z_f32(Problem pr, SampleTable st, 
     for (int k = threadIdx.x; k < H; k += 256) z[k] = tanhf(enc[k] + prd[k]);
 }
 
-// f^W_1 for one row of scores per wavefront (4 rows per workgroup): lse, emissions of node r0 + i.
+// f^W_1 for one row of scores per wavefront (4 rows per workgroup): lse, emissions of node r0 + i.  Bound by reading the scores: once, where a row fits
+// the registers of a wavefront (Q pieces of 16 bytes per lane; Q = 0: twice, whatever its length).  V = 4096, 31 k rows: 116 us (4.4 TB/s; two passes
+// took 165).
+template <int Q>
 __global__ __launch_bounds__(256) void k_rows_stats_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1,
                                                         long long r0, long long n, const float* __restrict__ S) {
     const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n) return;
     const int lane = threadIdx.x & 63, V = pr.V;
-    const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
     const float* row = S + i * V;
-    const int label = node_label(pr, p);
     const f32x4* row4 = reinterpret_cast<const f32x4*>(row);      // V is a multiple of 4, rows are 16-byte aligned
+    f32x4 x[Q ? Q : 1];
     float m = RNNT_NEG_INF;
-    for (int v = lane; v < V / 4; v += 64) {
-        const f32x4 x = row4[v];
-        m = fmaxf(fmaxf(m, fmaxf(x[0], x[1])), fmaxf(x[2], x[3]));
+    if constexpr (Q > 0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) x[q] = lane + 64 * q < V / 4 ? row4[lane + 64 * q] : f32x4{RNNT_NEG_INF, RNNT_NEG_INF, RNNT_NEG_INF, RNNT_NEG_INF};
+#pragma unroll
+        for (int q = 0; q < Q; ++q) m = fmaxf(fmaxf(m, fmaxf(x[q][0], x[q][1])), fmaxf(x[q][2], x[q][3]));
+    } else {
+        for (int v = lane; v < V / 4; v += 64) {
+            const f32x4 y = row4[v];
+            m = fmaxf(fmaxf(m, fmaxf(y[0], y[1])), fmaxf(y[2], y[3]));
+        }
     }
+    const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
+    const int label = node_label(pr, p);
     const float M = wave_max(m);
     float ssum = 0.0f;
-    for (int v = lane; v < V / 4; v += 64) {
-        const f32x4 x = row4[v];
-        ssum += (expf(x[0] - M) + expf(x[1] - M)) + (expf(x[2] - M) + expf(x[3] - M));
+    auto add = [&](const f32x4& y) { ssum += (expf(y[0] - M) + expf(y[1] - M)) + (expf(y[2] - M) + expf(y[3] - M)); };
+    if constexpr (Q > 0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lane + 64 * q < V / 4) add(x[q]);
+    } else {
+        for (int v = lane; v < V / 4; v += 64) add(row4[v]);
     }
     const float lse = M + logf(wave_sum(ssum));
     if (lane == 0) {
@@ -746,52 +762,146 @@ __global__ __launch_bounds__(256) void k_rows_stats_f32(Problem pr, SampleTable 
     }
 }
 
-// f^W_4 for one row per wavefront, in place of the scores: dh = gamma softmax - posteriors; zero in padding rows.
+// f^W_4 in place of the scores: dh = gamma softmax - posteriors, zero in padding rows; db += its column sums.  A workgroup takes 4 << lc columns and
+// `rows` rows (a multiple of four per thread; the threads stand in rows of 1 << lc), so that the sums cost no further pass (31 k rows, V = 4096: 180 us,
+// one pass for dh and one for the sums 178 and 133).
+constexpr int DH_PER_THREAD = 128, DH_ROWS_MAX = DH_PER_THREAD * 16;
+struct DhShape {
+    int lc;                                           // threads over the vocabulary: 16 to 64
+    int rows;                                         // per workgroup
+};
+// Rows: as many as leave about 128 workgroups down the chunk (additions to one address follow each other at about 0.1 us; with 1177 workgroups of 1024
+// columns a call of 14 k rows, H = 256, V = 1024 took 376 us, now 267), at most 128 per thread.
+inline DhShape dh_shape(int V, long long np) {
+    DhShape s{4, 0};
+    while (s.lc < 6 && (4 << s.lc) < V) ++s.lc;
+    const long long groups = 256 >> s.lc;
+    long long per = np / (128 * groups) / 4 * 4;
+    per = per < 4 ? 4 : per > DH_PER_THREAD ? DH_PER_THREAD : per;
+    s.rows = (int)(per * groups);
+    return s;
+}
 __global__ __launch_bounds__(256) void k_rows_dh_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1,
-                                                     long long r0, long long n, long long n_padded,
-                                                     float* __restrict__ S) {
-    const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n_padded) return;
-    const int lane = threadIdx.x & 63, V = pr.V;
-    float* row = S + i * V;
-    if (i >= n) {
-        for (int v = lane; v < V; v += 64) row[v] = 0.0f;
-        return;
-    }
-    const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
-    const int label = node_label(pr, p);
-    const RowPost rp = row_posteriors(ls, p.idx, p.t, p.u, p.T, p.U, p.s);
-    const float off = rp.log_gamma - ls.lse[p.idx];
-    f32x4* row4 = reinterpret_cast<f32x4*>(row);
-    for (int v = lane; v < V / 4; v += 64) {
-        f32x4 x = row4[v];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float d = expf(x[j] + off);
-            if (4 * v + j == pr.blank) d -= rp.Bk;
-            if (4 * v + j == label) d -= rp.Yk;
-            x[j] = d;
+                                                     long long r0, long long n, long long n_padded, DhShape sh,
+                                                     float* __restrict__ S, float* __restrict__ db) {
+    __shared__ __align__(16) float row_data[DH_ROWS_MAX][4];      // offset of the exponent, what is taken off at the blank and the label, the label
+    const long long i0 = (long long)blockIdx.x * sh.rows;
+    const int tid = threadIdx.x, V = pr.V, rows = n_padded - i0 < sh.rows ? (int)(n_padded - i0) : sh.rows;
+    for (int r = tid; r < rows; r += 256) {
+        f32x4 d = f32x4{RNNT_NEG_INF, 0.0f, 0.0f, __int_as_float(-1)};
+        if (i0 + r < n) {
+            const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i0 + r);
+            const RowPost rp = row_posteriors(ls, p.idx, p.t, p.u, p.T, p.U, p.s);
+            d = f32x4{rp.log_gamma - ls.lse[p.idx], rp.Bk, rp.Yk, __int_as_float(node_label(pr, p))};
         }
-        row4[v] = x;
+        *reinterpret_cast<f32x4*>(row_data[r]) = d;
     }
+    __syncthreads();
+    const int cols = 1 << sh.lc, groups = 256 >> sh.lc, c = tid & (cols - 1);
+    const int v = ((int)blockIdx.y << (sh.lc + 2)) + c * 4;
+    f32x4 sum = f32x4{0};
+    if (v < V) {
+        float* col = S + i0 * V + v;
+        for (int q = tid >> sh.lc; q < rows; q += 4 * groups) {
+            f32x4 x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = q + j * groups < rows ? q + j * groups : q;     // (loads without branches between them)
+                x[j] = *reinterpret_cast<const f32x4*>(col + (long long)r * V);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = q + j * groups;
+                if (r >= rows) continue;
+                const f32x4 rd = *reinterpret_cast<const f32x4*>(row_data[r]);
+                const int label = __float_as_int(rd[3]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float d = expf(x[j][k] + rd[0]);
+                    if (v + k == pr.blank) d -= rd[1];
+                    if (v + k == label) d -= rd[2];
+                    x[j][k] = d;
+                }
+                if (i0 + r >= n) x[j] = f32x4{0};
+                sum += x[j];
+                *reinterpret_cast<f32x4*>(col + (long long)r * V) = x[j];
+            }
+        }
+    }
+    __syncthreads();                                  // row_data becomes [groups][4 cols] partial sums
+    *reinterpret_cast<f32x4*>(row_data[tid]) = sum;
+    __syncthreads();
+    const float* part = &row_data[0][0];
+    const int vt = ((int)blockIdx.y << (sh.lc + 2)) + tid;
+    if (tid >= 4 * cols || vt >= V) return;
+    float t = 0.0f;
+    for (int g = 0; g < groups; ++g) t += part[g * 4 * cols + tid];
+    atomicAdd(db + vt, t);
 }
 
-// d_enc[s, t, :] += dZ (1 - Z^2), d_pred[s, u, :] += the same, for one node per workgroup.
-__global__ __launch_bounds__(256) void k_rows_dz_f32(Problem pr, SampleTable st, LatticeState ls, int s0, int s1,
-                                                     long long r0, const float* __restrict__ Z,
+// d_enc[s, t, :] += dZ (1 - Z^2), d_pred[s, u, :] += the same: a lattice tile and 256 columns per workgroup (a wavefront takes every fourth frame, a lane
+// four columns), summed over the tile's labels resp. frames before it leaves: 16 to 20 atomics a column and tile, where a node by itself takes 128
+// (31 k nodes, H = 1024: 240 -> 72 us).  Nodes [r0, r0 + n) of the group have a row in Z and dZ; a tile may have others besides.
+__global__ __launch_bounds__(256) void k_rows_dz_f32(Problem pr, SampleTable st, LatticeState ls, int tile0,
+                                                     long long r0, long long n, const float* __restrict__ Z,
                                                      const float* __restrict__ dZ, float* __restrict__ d_enc,
                                                      float* __restrict__ d_pred) {
-    const long long i = blockIdx.x;
-    const int H = pr.H;
-    const NodePos p = locate_node(st, ls.row_base, s0, s1, r0 + i);
-    float* de = d_enc + ((size_t)p.s * pr.T_max + p.t) * H;
-    float* dp = d_pred + ((size_t)p.s * (pr.U_max + 1) + p.u) * H;
-    for (int k = threadIdx.x; k < H; k += 256) {
-        const float z = Z[i * H + k];
-        const float dx = dZ[i * H + k] * (1.0f - z * z);
-        atomicAdd(&de[k], dx);
-        atomicAdd(&dp[k], dx);
+    __shared__ __align__(16) float part[4][8][256], frame[4][256];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, H = pr.H;
+    const TilePos p = locate_tile(st, tile0 + (int)blockIdx.x);
+    const int h = (int)blockIdx.y * 256 + lane * 4;
+    const bool col = h < H;
+    const long long first = st.row_off[p.s] - ls.row_base - r0;        // row of the sample's first node
+    f32x4 pu[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) pu[u] = f32x4{0};
+    const int frames = 64 >> p.us;
+    for (int tl = wave; tl < frames; tl += 4) {
+        const int t = p.t0 + tl;
+        if (t >= p.T) break;
+        const long long row = first + (long long)t * (p.U + 1) + p.u0;
+        f32x4 de = f32x4{0}, z[8], g[8];
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {                 // (loads without branches between them: what is not a row of the chunk reads another one)
+            long long i = row + u;
+            i = i < 0 ? 0 : i < n ? i : n - 1;
+            z[u] = *reinterpret_cast<const f32x4*>(Z + i * H + (col ? h : 0));
+            g[u] = *reinterpret_cast<const f32x4*>(dZ + i * H + (col ? h : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const long long i = row + u;
+            const bool ok = u < p.uw && p.u0 + u <= p.U && i >= 0 && i < n && col;
+            any = any || ok;
+            f32x4 dx = g[u] * (1.0f - z[u] * z[u]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dx[j] = ok ? dx[j] : 0.0f;
+            de += dx;
+            pu[u] += dx;
+        }
+        // (through LDS, so that the lanes of an atomic lie side by side)
+        *reinterpret_cast<f32x4*>(&frame[wave][lane * 4]) = de;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (__any(any)) {
+            float* out = d_enc + ((size_t)p.s * pr.T_max + t) * H + (int)blockIdx.y * 256;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((int)blockIdx.y * 256 + j * 64 + lane < H) atomicAdd(out + j * 64 + lane, frame[wave][j * 64 + lane]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) *reinterpret_cast<f32x4*>(&part[wave][u][lane * 4]) = pu[u];
+    __syncthreads();
+    const int c = threadIdx.x, hc = (int)blockIdx.y * 256 + c;
+    if (hc >= H) return;
+    for (int u = 0; u < p.uw && p.u0 + u <= p.U; ++u)
+        atomicAdd(d_pred + ((size_t)p.s * (pr.U_max + 1) + p.u0 + u) * H + hc, (part[0][u][c] + part[1][u][c]) + (part[2][u][c] + part[3][u][c]));
 }
 
 }  // namespace
@@ -833,13 +943,16 @@ hipError_t launch_fwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
     if (e != hipSuccess) return e;
     e = joint_gemm_f32<false, true>(Z, pr.H, (const float*)pr.W, pr.V, S, pr.V, pr.b_out, 0, np, pr.V, pr.H, 1, stream);
     if (e != hipSuccess) return e;
-    k_rows_stats_f32<<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, S);
+    const dim3 grid((unsigned)((n + 3) / 4));
+    if (pr.V <= 1024) k_rows_stats_f32<4><<<grid, dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, S);
+    else if (pr.V <= 4096) k_rows_stats_f32<16><<<grid, dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, S);
+    else k_rows_stats_f32<0><<<grid, dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, S);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const LatticeState& ls, const GradOut& go,
-                               int s0, int s1, long long r0, long long n, bool have_scores, float* S, float* Z, float* dZ,
-                               hipStream_t stream) {
+                               int s0, int s1, int tile0, int tile1, long long r0, long long n, bool have_scores, float* S, float* Z,
+                               float* dZ, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     const long long np = (n + FT - 1) / FT * FT;
     const int H = pr.H, V = pr.V;
@@ -852,10 +965,10 @@ hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
         e = joint_gemm_f32<false, true>(Z, H, W, V, S, V, pr.b_out, 0, np, V, H, 1, stream);
         if (e != hipSuccess) return e;
     }
-    k_rows_dh_f32<<<dim3((unsigned)(np / 4)), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, n, np, S);
+    const DhShape sh = dh_shape(V, np);
+    k_rows_dh_f32<<<dim3((unsigned)((np + sh.rows - 1) / sh.rows), (unsigned)((V + (4 << sh.lc) - 1) / (4 << sh.lc))), dim3(256), 0, stream>>>(
+        pr, st, ls, s0, s1, r0, n, np, sh, S, go.db);
     e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch_col_sum(S, np, V, go.db, stream);
     if (e != hipSuccess) return e;
     // dW += Z^T dh
     e = joint_gemm_f32<true, true>(Z, H, S, V, go.dW, V, nullptr, 1, H, V, np, k_splits_f32(H, V, np), stream);
@@ -863,7 +976,8 @@ hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
     // dZ = dh W^T   (B(k = v, n = h) = W[h, v]: k-contiguous)
     e = joint_gemm_f32<false, false>(S, V, W, V, dZ, H, nullptr, 0, np, H, V, 1, stream);
     if (e != hipSuccess) return e;
-    k_rows_dz_f32<<<dim3((unsigned)n), dim3(256), 0, stream>>>(pr, st, ls, s0, s1, r0, Z, dZ, go.d_enc, go.d_pred);
+    k_rows_dz_f32<<<dim3((unsigned)(tile1 - tile0), (unsigned)((H + 255) / 256)), dim3(256), 0, stream>>>(pr, st, ls, tile0, r0, n, Z, dZ,
+                                                                                                      go.d_enc, go.d_pred);
     return hipGetLastError();
 }
 

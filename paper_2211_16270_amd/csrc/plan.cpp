@@ -270,9 +270,14 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
                 const long long rows = p.row_off[s1] - p.row_off[s0], nch = (rows + chunk_rows - 1) / chunk_rows;
                 const long long per = (long long)align_up((size_t)((rows + nch - 1) / nch), GEMM_TILE);
                 for (long long r0 = 0; r0 < rows; r0 += per) {
-                    Chunk c{gi, g.tile0, g.tile1};
+                    Chunk c{gi, p.tile_off[s0], p.tile_off[s1]};
                     c.row0 = p.row_off[s0] - p.row_off[g.s0] + r0;
                     c.rows = std::min(per, rows - r0);
+                    if (nch > 1) {                    // (one sample: the blocks of frames the range touches)
+                        const int W = U_len[s0] + 1, uw = tile_label_width(T_len[s0], U_len[s0]), th = TILE_ROWS / uw, across = (W + uw - 1) / uw;
+                        c.tile0 = p.tile_off[s0] + (int)(r0 / W / th) * across;
+                        c.tile1 = p.tile_off[s0] + (int)((r0 + c.rows - 1) / W / th + 1) * across;
+                    }
                     c.s0 = s0;
                     c.s1 = s1;
                     p.chunks.push_back(c);

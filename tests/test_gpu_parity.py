@@ -1153,3 +1153,14 @@ def test_f32_chunks_of_whole_samples_and_samples_of_several_chunks(rows):
     _say("f32 chunks", rows, info, batch.T_len, batch.U_len)
     assert st == 0 and info["chunk_rows"] >= rows
     assert_parity(run_gpu(batch, budget_bytes=budget), ref, "f32", f"chunks of {rows}")
+
+
+@pytest.mark.parametrize("H,V", [(64, 1024), (64, 1028), (260, 4096), (64, 4100), (516, 260)])
+def test_f32_row_kernels_at_the_edges_of_their_rows(H, V):
+    # statistics with a row in 4 or 16 registers or read twice; score gradients in one or several pieces of 256 columns, the last one short; d_enc, d_pred in
+    # pieces of 256 hidden columns; samples with both tile shapes, one of a single node
+    wl = synth.custom_workload("f32rows", B=3, T_max=67, U_max=17, H=H, V=V, dtype="f32", index=162)
+    batch = synth.with_lengths(synth.make_batch(wl), [67, 1, 50], [17, 0, 3])
+    got, ref = run_gpu(batch), run_oracle(batch)
+    _say("f32 rows", H, V, assert_parity(got, ref, "f32", f"H {H} V {V}"))
+    assert_padding_zero(got, batch)
