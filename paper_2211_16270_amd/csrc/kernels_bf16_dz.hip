@@ -3,12 +3,12 @@
 //   dx = dz (1 - z^2),  d_enc[t] += sum_u dx,  d_pred[u] += sum_t dx  per lattice tile (64 rows: 8 frames x 8 labels or 16 x 4).
 //
 // 256x256 output tile (4 lattice tiles x 256 hidden) per workgroup; 512 threads = 8 waves in 2 x 4, two per SIMD, each 128 x 64 = 4 x 2
-// accumulator tiles, so that one k16-step is 6 LDS fragment reads for 8 MFMAs, and one wave's waits and epilogue stand beside the other's
+// accumulator tiles (short vocabularies, dz_waves: 128x256 and 4 waves, two workgroups per compute unit, three stages of 24 KiB each), so that one k16-step is 6 LDS fragment reads for 8 MFMAs, and one wave's waits and epilogue stand beside the other's
 // work.  (Four waves of 128 x 128, one per SIMD, read a third less from LDS and were slower, see below.)  Where only 128 hidden columns are left
 // (H not a multiple of 256) the waves stand 4 x 2, each 64 x 64.
 // Both operands lie in memory as MFMA fragments of 1 KiB (dH: device_common.h; W_out: the packed copy
 // [V/16][H/32]), so stages of 32 vocabulary entries (16 fragments of each) travel global -> LDS
-// asynchronously in whole cache lines, five stages deep, and are read back without bank conflicts.  Fragments are read one
+// asynchronously in whole cache lines, five (three) stages deep, and are read back without bank conflicts.  Fragments are read one
 // k16-step ahead of their MFMAs, also across the stage hand-over.
 //
 // Epilogue: 1 - z^2 = 4 r (1 - r) with r = 1 / (1 + e^{2 enc} e^{2 pred}), one reciprocal per
@@ -28,9 +28,9 @@ namespace {
 
 constexpr int ZT = 256;       // tile edge
 constexpr int ZK = 32;        // vocabulary entries per stage
-constexpr int ZST = 5;        // stages
-constexpr unsigned Z_OPER = 16u * 1024u;     // bytes of one operand of a stage
-constexpr unsigned Z_STAGE = 2u * Z_OPER;
+constexpr int z_stages(int WAVES) { return WAVES == 8 ? 5 : 3; }
+constexpr unsigned z_a_bytes(int WAVES) { return WAVES * 2048u; }                 // dH's part of a stage
+constexpr unsigned z_stage_bytes(int WAVES) { return z_a_bytes(WAVES) + 16u * 1024u; }
 constexpr int Z_EP = 264;     // pitch (floats) of the epilogue's rows in LDS
 constexpr int Z_ROWS = 20;    // input rows of a lattice tile: 8 + 8 or 16 + 4
 
@@ -50,10 +50,13 @@ struct DzArgs {
 };
 
 // HALF: the last hidden tile, 128 columns; vs: part of the vocabulary
-template <bool HALF>
+template <bool HALF, int WAVES>
 __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem, int bx, int n0, int n_slots, int vs) {
     constexpr int MT = HALF ? 2 : 4;                  // 32-row blocks per wave
-    constexpr int DMAS = HALF ? 3 : 4;                // copies per wave and stage
+    constexpr int DMAS = 2 + (HALF ? 8 : 16) / WAVES; // copies per wave and stage
+    constexpr int TILES = WAVES / 2, ZST = z_stages(WAVES), NB = 8 / WAVES * (HALF ? 1 : 2);      // NB: hidden blocks of an entry half a wave copies
+    constexpr int NI = HALF || WAVES == 8 ? 2 : 3;    // issues per stage
+    constexpr unsigned Z_OPER = z_a_bytes(WAVES), Z_STAGE = z_stage_bytes(WAVES);
     const int tid = threadIdx.x;
     const int lane = tid & 63, l32 = lane & 31, hb = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -68,29 +71,29 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const size_t DB = chunk_block_bytes(V);   // bytes of a block of 32 rows of dH
     const unsigned lane_b = (unsigned)lane * 16u;
     const int wt = wv >> 1;                           // lattice tile whose copies and input rows are this wave's
-    const bool present = bx * 4 + wt < n_slots;
-    const int entry = present ? bx * 4 + wt : n_slots - 1;
+    const bool present = bx * TILES + wt < n_slots;
+    const int entry = present ? bx * TILES + wt : n_slots - 1;
     const int tile = __builtin_amdgcn_readfirstlane(g.at.active ? g.at.active[g.at.group_tile0 + g.at.cbase + entry] : g.tile0 + entry);
     // (kept scores: wherever the forward pass has put the listed tile)
     const int slot = (g.at.active && g.at.slot_tile0 >= 0) ? tile - g.at.slot_tile0 : entry;
     const int nsteps = V / ZK / g.v_splits, step0 = vs * nsteps;
     const unsigned char* As = g.dH + (size_t)(2 * slot + (wv & 1)) * DB + (size_t)step0 * 2048;
     const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
-    const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(wv >> 2) * WB + (size_t)(n0 / 32 + (HALF ? wv & 3 : 2 * (wv & 3))) * 1024;
+    const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(wv / TILES) * WB + (size_t)(n0 / 32 + NB * (wv % TILES)) * 1024;
     // The copies of stage gstep into LDS buffer buf: both entry halves of the row block (j = 0), the hidden blocks (1).
     // (In pairs: M0 and its wait state once.)
     auto issue = [&](int gstep, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;
         const unsigned sb = smem_base + buf * Z_STAGE;
+        const unsigned bdst = sb + Z_OPER + (unsigned)((wv / TILES) * 8 + NB * (wv % TILES)) * 1024u;
         if constexpr (j == 0) lds_dma16_pair<0>(As + (size_t)gstep * 2048, lane_b, sb + (unsigned)wv * 2048u);
-        else if constexpr (HALF)
-            lds_dma16_s(Bs + (size_t)gstep * 2 * WB, lane_b, sb + Z_OPER + (unsigned)((wv >> 2) * 8 + (wv & 3)) * 1024u);
-        else lds_dma16_pair<0>(Bs + (size_t)gstep * 2 * WB, lane_b, sb + Z_OPER + (unsigned)((wv >> 2) * 8 + 2 * (wv & 3)) * 1024u);
+        else if constexpr (NB == 1) lds_dma16_s(Bs + (size_t)gstep * 2 * WB, lane_b, bdst);
+        else lds_dma16_pair<(j - 1) * 2048>(Bs + (size_t)gstep * 2 * WB, lane_b, bdst);
     };
     const int last = nsteps - 1;
 #pragma unroll
     for (int s5 = 0; s5 < ZST; ++s5)
-        static_for<0, 2>([&](auto j) { issue(s5 < last ? s5 : last, (unsigned)s5, j); });
+        static_for<0, NI>([&](auto j) { issue(s5 < last ? s5 : last, (unsigned)s5, j); });
 
     // the epilogue's input rows, half of a lattice tile's per wave: lane = 8 columns of every second (HALF: fourth) row (zero outside the sample)
     const TilePos tp = locate_tile(g.st, tile);
@@ -129,12 +132,12 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mt], fb[set][nt], acc[mt][nt], 0, 0, 0);
             if constexpr (idx < MT) fa[set ^ 1][idx] = frag_a(next_buf, next_kk, idx);
             else if constexpr (idx < MT + 2) fb[set ^ 1][idx - MT] = frag_b(next_buf, next_kk, idx - MT);
-            if constexpr (set == 1 && idx >= 2 * MT - 4 && idx % 2 == 0)
-                issue(it + ZST < last ? it + ZST : last, buf, std::integral_constant<int, (idx - (2 * MT - 4)) / 2>{});
+            if constexpr (set == 1 && idx >= 2 * MT - 2 * NI && idx % 2 == 0)
+                issue(it + ZST < last ? it + ZST : last, buf, std::integral_constant<int, (idx - (2 * MT - 2 * NI)) / 2>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // Five stages in flight before the first one is consumed.  The hand-over to the next stage (wait for this wave's copies, then for
+    // All stages in flight before the first one is consumed.  The hand-over to the next stage (wait for this wave's copies, then for
     // everyone's) sits in the middle of a stage; there every wave has read all its fragments of the present one, whose buffer may be
     // refilled.  Beyond the last stage the pipeline re-loads the last one into buffers nobody reads
     // any more, which keeps the loop free of branches and the number of copies in flight constant.  The waits for LDS reads are placed by hand (as the builtin the compiler's own counter tracking understands) before the
@@ -167,12 +170,12 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
 
     // ---- epilogue.  Per lattice tile Z_ROWS rows of e^{2x}: the tile's frames, behind them its label positions; where an input lies beyond
     // +-40 (the product of two exponentials could overflow, or cancel as inf * 0) the tile's rows are the inputs themselves.
-    float* ex = reinterpret_cast<float*>(dz_smem);                // [4 tiles][Z_ROWS][Z_EP]
+    float* ex = reinterpret_cast<float*>(dz_smem);                // [TILES][Z_ROWS][Z_EP]
     struct TileInfo {
         int s, T, U, t0, u0, us;
         int far[2];                                   // an input of the first, second half of the rows lies beyond the limit
     };
-    TileInfo* info = reinterpret_cast<TileInfo*>(dz_smem + 4 * Z_ROWS * Z_EP * sizeof(float));
+    TileInfo* info = reinterpret_cast<TileInfo*>(dz_smem + TILES * Z_ROWS * Z_EP * sizeof(float));
     {
         constexpr float K2 = 2.0f * LOG2E_F;
         float big = 0.0f;
@@ -297,6 +300,7 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
 }
 
 // L: workgroup of the v_splits * per_part
+template <int WAVES>
 __device__ __forceinline__ void dz_workgroup(const DzArgs& g, unsigned char* dz_smem, int L) {
     // XCD-aware order (ids that agree modulo 8 share an L2): the hidden tiles of one row tile are
     // neighbours on one XCD, so the rows of dH are fetched from HBM once.
@@ -310,15 +314,16 @@ __device__ __forceinline__ void dz_workgroup(const DzArgs& g, unsigned char* dz_
         const int left = *g.at.n_active - g.at.cbase;
         n_slots = left < n_slots ? left : n_slots;
     }
-    if (bx * 4 >= n_slots) return;          // (uniform per workgroup)
+    if (bx * (WAVES / 2) >= n_slots) return;          // (uniform per workgroup)
     const int n0 = by * g.edge;
-    if (g.edge < ZT || n0 + 128 >= g.pr.H) dz_tile<true>(g, dz_smem, bx, n0, n_slots, vs);
-    else dz_tile<false>(g, dz_smem, bx, n0, n_slots, vs);
+    if (g.edge < ZT || n0 + 128 >= g.pr.H) dz_tile<true, WAVES>(g, dz_smem, bx, n0, n_slots, vs);
+    else dz_tile<false, WAVES>(g, dz_smem, bx, n0, n_slots, vs);
 }
 
-__global__ __launch_bounds__(512) void k_gemm_dz256(DzArgs g) {
-    extern __shared__ __align__(16) unsigned char dz_smem[];   // [ZST] x { A, B: 16 fragments each }
-    dz_workgroup(g, dz_smem, blockIdx.x);
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void k_gemm_dz256(DzArgs g) {
+    extern __shared__ __align__(16) unsigned char dz_smem[];   // [stages] x { A, B }
+    dz_workgroup<WAVES>(g, dz_smem, blockIdx.x);
 }
 
 // Both GEMMs of a chunk: dW's workgroups, then dz's (they share nothing but what they read: dH).  The rule and what it gives: plan.h.
@@ -326,35 +331,42 @@ template <bool BY_TILE>
 __global__ __launch_bounds__(512) void k_gemm_dz_dw(DzArgs z, DwArgs w, int nw) {
     extern __shared__ __align__(16) unsigned char smem[];
     if ((int)blockIdx.x < nw) dw_workgroup<BY_TILE>(w, smem, blockIdx.x);
-    else dz_workgroup(z, smem, blockIdx.x - nw);
+    else dz_workgroup<8>(z, smem, blockIdx.x - nw);
 }
 
-constexpr size_t DZ_SMEM = (size_t)ZST * Z_STAGE;
+constexpr size_t dz_smem_bytes(int WAVES) { return (size_t)z_stages(WAVES) * z_stage_bytes(WAVES); }
 
 DzArgs dz_args(const DzForm& f, const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
-               float* d_enc, float* d_pred, const ActiveTiles& at) {
-    const int m_tiles = (tile1 - tile0 + 3) / 4, n_tiles = (pr.H + f.edge - 1) / f.edge;
+               float* d_enc, float* d_pred, const ActiveTiles& at, int waves) {
+    const int m_tiles = (tile1 - tile0 + waves / 2 - 1) / (waves / 2), n_tiles = (pr.H + f.edge - 1) / f.edge;
     return DzArgs{(const unsigned char*)dH, (const unsigned char*)Wq, pr, st, tile0, tile1, d_enc, d_pred, n_tiles, f.edge, f.vs,
                   (m_tiles + 7) / 8 * 8 * n_tiles, at};
 }
 
 }  // namespace
 
+template <int WAVES>
+static hipError_t launch_dz(const DzArgs& g, hipStream_t stream) {
+    constexpr size_t smem = dz_smem_bytes(WAVES);
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz256<WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    k_gemm_dz256<WAVES><<<dim3((unsigned)(g.v_splits * g.per_part)), dim3(64 * WAVES), smem, stream>>>(g);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm_dz_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* dH,
                                float* d_enc, float* d_pred, const ActiveTiles& at, hipStream_t stream) {
     const int n = tile1 - tile0;
     if (n <= 0) return hipSuccess;
     if (pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
-    const DzArgs g = dz_args(dz_alone(pr.H, pr.V, n), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at);
-    static bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz256),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)DZ_SMEM);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
-    k_gemm_dz256<<<dim3((unsigned)(g.v_splits * g.per_part)), dim3(512), DZ_SMEM, stream>>>(g);
-    return hipGetLastError();
+    const int waves = dz_waves(pr.H, pr.V);
+    const DzArgs g = dz_args(dz_alone(pr.H, pr.V, n), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at, waves);
+    return waves == 4 ? launch_dz<4>(g, stream) : launch_dz<8>(g, stream);
 }
 
 hipError_t launch_gemm_dz_dw_bf16(const Problem& pr, const void* Wq, const SampleTable& st, int tile0, int tile1, const void* Z,
@@ -362,9 +374,9 @@ hipError_t launch_gemm_dz_dw_bf16(const Problem& pr, const void* Wq, const Sampl
                                   const ActiveTiles& at, hipStream_t stream) {
     const long long rows = (long long)(tile1 - tile0) * JT_ROWS;
     if (rows <= 0 || splits <= 0 || pr.V % (4 * ZK) != 0) return hipErrorInvalidValue;
-    const DzArgs z = dz_args(dz_one_grid(pr.H, pr.V, tile1 - tile0, splits), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at);
+    const DzArgs z = dz_args(dz_one_grid(pr.H, pr.V, tile1 - tile0, splits), pr, Wq, st, tile0, tile1, dH, d_enc, d_pred, at, 8);
     const DwArgs w = dw_args(pr.H, pr.V, rows, splits, first, Z, dH, slots, db, at);
-    constexpr size_t smem = DZ_SMEM > DW_SMEM ? DZ_SMEM : DW_SMEM;
+    constexpr size_t smem = dz_smem_bytes(8) > DW_SMEM ? dz_smem_bytes(8) : DW_SMEM;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_dz_dw<false>),

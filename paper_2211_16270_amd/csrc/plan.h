@@ -190,6 +190,12 @@ inline int dw_split_choice(int H, int V, long long rows) {
 struct DzForm {
     int edge, vs;
 };
+// Waves of a dz workgroup of its own launch.  Four and two workgroups per compute unit: one's start and epilogue (a quarter of the time at V = 1024) stand beside
+// the other's MFMAs, for half as much again of W_out's way from the L2 to LDS; a long vocabulary has little of the one and much of the other.  A call with
+// eight -> four, 64 samples of 500 x 100: H = 256 V = 1024 5.70 -> 5.53 ms, H = 384 V = 768 6.46 -> 6.23, H = 512 V = 512 5.49 -> 5.26, V = 1024 9.45 -> 9.26,
+// V = 2048 (with the line further up) 16.42 -> 16.42, H = 1024 V = 1024 18.4 -> 18.15; 1024 of up to 1000 x 200, H = 512, V = 1024 314.6 -> 310.2; H = 128
+// V = 1024 2130 -> 2145 us, H = 1024 V = 4096 11.1 -> 11.6.
+inline int dz_waves(int H, int V) { return H >= 256 && V <= 1024 ? 4 : 8; }
 inline DzForm dz_alone(int H, int V, long long tiles) {
     const int m_tiles = (int)((tiles + 3) / 4), stages = V / 32;
     const int whole = (m_tiles * H + 255) / 256, halves = m_tiles * (H / 128);

@@ -1164,3 +1164,18 @@ def test_f32_row_kernels_at_the_edges_of_their_rows(H, V):
     got, ref = run_gpu(batch), run_oracle(batch)
     _say("f32 rows", H, V, assert_parity(got, ref, "f32", f"H {H} V {V}"))
     assert_padding_zero(got, batch)
+
+
+@pytest.mark.parametrize("H,V", [(128, 512), (256, 256), (384, 768), (512, 1024), (640, 1024), (256, 1280), (1024, 256)])
+@pytest.mark.parametrize("T", [8, 24, 40, 200])
+def test_bf16_dz_in_a_launch_of_its_own(H, V, T):
+    # workgroups of four waves and two lattice tiles, or of eight and four, the last one partly filled; whole and half hidden tiles, the vocabulary in parts.
+    # Two samples of one, three, five or more lattice tiles in the smallest workspace: several chunks, so dz and dW are launches of their own.
+    wl = synth.custom_workload("dzalone", B=2, T_max=T, U_max=7, H=H, V=V, dtype="bf16", index=163)
+    batch = synth.make_batch(wl)
+    desc = Bd.make_desc(2, T, 7, H, V, wl.blank, Bd.RNNT_BF16)
+    nmin = Bd.rnnt_joint_loss_workspace_bytes(desc, batch.T_len, batch.U_len, 1)
+    st, info, _ = Bd.rnnt_joint_loss_plan(desc, batch.T_len, batch.U_len, nmin)
+    assert st == 0 and info["n_chunks"] >= 2
+    _say("dz alone", H, V, T, info["n_chunks"])
+    assert_parity(run_gpu(batch, budget_bytes=nmin), run_oracle(batch), "bf16", f"H={H} V={V} T={T}")
