@@ -347,7 +347,12 @@ def main():
                           "joint_scores_fwd_keep": 2.0 * R * HV,
                           "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV, "gemm_dz_dw_db": 4.0 * R * HV,
                           "fwd_f32": 2.0 * R * HV, "bwd_f32": 4.0 * R * HV}
-    exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=6.0 * R * HV)
+    # fp32: the plain kernels compute every score twice, the GEMM form those of a sample that takes several chunks, but for its last one
+    again = R
+    if wl.dtype == "f32" and info["chunk_rows"] > 0:
+        again = sum(rows - -(-rows // -(-rows // info["chunk_rows"])) for rows in (batch.T_len.astype(int) * (batch.U_len.astype(int) + 1)).tolist()
+                    if rows > info["chunk_rows"])
+    exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=(4.0 * R + 2.0 * again) * HV)
     if bwd_share < 1.0:
         # tiles of negligible posterior are left out: both counts cover only the rows the kernels worked on
         for name in ("joint_scores_bwd", "gemm_dz", "gemm_dw_db", "gemm_dz_dw_db"):
@@ -390,7 +395,8 @@ def main():
                      for name, bits in pats if name in ("zeros", "random bf16")} if wl.dtype == "bf16" else None
     step_s = elapsed / steps
     util_alg = (2.0 + 4.0 * bwd_share) * R * HV / step_s / peak
-    util_exec = (2.0 + (4.0 if args.keep_scores else 6.0) * bwd_share) * R * HV / step_s / peak
+    util_exec = (6.0 * R + 2.0 * again) * HV / step_s / peak if wl.dtype == "f32" else \
+        (2.0 + (4.0 if args.keep_scores else 6.0) * bwd_share) * R * HV / step_s / peak
     lat = kernels.get("lattice")
     # lattice pass: bytes per launch from the committed FETCH_SIZE / WRITE_SIZE summary where there is one,
     # next to the figure from the 24 bytes per node the sweep has to move (emissions read twice, alpha, beta written)

@@ -373,8 +373,12 @@ __global__ __launch_bounds__(256, 2) void k_proj_backward(BackwardArgs a) {
 template <typename ARGS>
 hipError_t launch_proj(void (*kernel)(ARGS), const ARGS& a, long long workgroups, hipStream_t stream) {
     if (workgroups > 0x7fffffffLL) return hipErrorInvalidValue;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)P_SMEM);
-    if (e != hipSuccess) return e;
+    static bool configured = false;          // one flag per instantiation, i.e. kernel
+    if (!configured) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)P_SMEM);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
     kernel<<<dim3((unsigned)workgroups), dim3(256), P_SMEM, stream>>>(a);
     return hipGetLastError();
 }

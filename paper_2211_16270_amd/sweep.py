@@ -101,7 +101,8 @@ def run_case(B, T, U, H, V, mode, steps=3, warmup=1, seed=2211, dtype="bf16", re
         share = act / tot
     res = dict(ms=dt * 1e3, samples_per_s=B / dt, peak_gb=torch.cuda.max_memory_allocated() / 1e9,
                workspace_gb=nb / 1e9, rows=rows, tile_share=share,
-               pflops_exec=(2.0 + (4.0 if mode == "kept" else 6.0) * share) * rows * H * V / dt / 1e15,
+               # (fp32: every sample of these sweeps fits a chunk, whose scores the backward pass finds)
+               pflops_exec=(2.0 + (4.0 if mode == "kept" or dtype == "f32" else 6.0) * share) * rows * H * V / dt / 1e15,
                pflops_dense=6.0 * rows * H * V / dt / 1e15)
     if return_tensors:
         res["tensors"] = dict(enc=enc, pred=pred, W_out=W, b_out=b_out, labels=labels, T_len=T_len, U_len=U_len,
