@@ -382,7 +382,7 @@ def main():
     tname = f"hbm_traffic_{wl.name}" + ("_keep_scores" if args.keep_scores else "") + ".txt"
     traffic = read_traffic(os.path.join(ROOT, "profiles", tname)) if not args.batch else {}
     # fp32: GEMMs (each operand as three bf16 parts) where the plan has chunk buffers (H, V multiples of 4 from 64 on; `kernel` is
-    # then the group of launches of one chunk: three GEMMs and the row kernels between them), else plain FMA
+    # then the group of launches of one chunk: two GEMMs and the row kernels between them, and a third where its scores are computed again), else plain FMA
     roofline = {"bound": "mfma" if (wl.dtype == "bf16" or info["chunk_rows"] > 0) else "alu", "kernel": dom,
                 "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": traffic.get(dom), "traffic_source": ("profiles/" + tname) if traffic.get(dom) else None,
