@@ -673,7 +673,7 @@ hipError_t launch_gemm_f32_t(const GemmF32& g, hipStream_t stream) {
 // 512 workgroups of 128 x 256 take (H = 1024, V = 4096, 33 k rows: 1323 -> 1190 us; with 4500 rows, H = 512, V = 1024, the atomics of so many splits
 // cost more: a call 245 -> 260 us); at most 16384 rows per split, so that no sum's rounding grows beyond that of the longest one over the vocabulary
 // (and whole rounds of those workgroups: H = 1024, V = 4096, 73 k rows, five splits in three rounds of narrow tiles -> eight in two of wide ones: a call of 16 samples of up to
-// 500 x 100 79.9 -> 78.7 ms).
+// 500 x 100 in a workspace that holds such chunks 79.9 -> 78.7 ms).
 }  // namespace
 int k_splits_f32(long long M, long long N, long long K) {
     const long long rows = (M + FT - 1) / FT, narrow = rows * ((N + 127) / 128), wide = rows * ((N + 255) / 256);

@@ -148,11 +148,12 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
     if (chunked) {
         // 832 MiB: 768 MiB of rows at H = 512, V = 1024 plus the padding of their row pitch
         // kept scores: 8 GiB, so that a group still fills the GPU when a row takes 10 KB
-        // fp32: 2 GiB, so that few samples are longer than a chunk (their scores are computed once then) and few sweeps stand alone.  Against 832 MiB a call of
-        // four samples of 500 x 100, H = 256, V = 1024 2517 -> 2240 us, 64 of 200 x 40, H = 512, V = 1024 9.24 -> 8.82 ms, 16 of up to 232 x 46, H = 1024,
-        // V = 4096 17.0 -> 16.75; before, four of 500 x 100 at that size (45 k nodes each, where 832 MiB hold 35 k) 30.9 -> 26.3.  4 GiB give 2 % more at most.
-        const unsigned long long budget = p.keep ? (8ULL << 30) : p.f32_gemm ? (2ULL << 30) : (832ULL << 20);
-        const long long by_bytes = (long long)(budget / crb) / GEMM_TILE * GEMM_TILE;
+        const unsigned long long budget = p.keep ? (8ULL << 30) : (832ULL << 20);
+        long long by_bytes = (long long)(budget / crb) / GEMM_TILE * GEMM_TILE;
+        // fp32: up to 2 GiB where the longest sample needs them, so that its scores are computed once (H = 1024, V = 4096, four samples of up to 500 x 100,
+        // 45 k nodes each where 832 MiB hold 35 k: 30.9 -> 26.3 ms a call).  (2 GiB for every call would give 1 to 12 % more.)
+        if (p.f32_gemm)
+            by_bytes = std::max(by_bytes, std::min((long long)align_up((size_t)max_rows, GEMM_TILE), (long long)((2ULL << 30) / crb) / GEMM_TILE * GEMM_TILE));
         chunk_default = std::min(all_tile_rows, std::max<long long>(chunk_floor, by_bytes));
     }
     // fp32 sums of d_enc, d_pred for the samples of a group: 256 MiB by default
