@@ -403,8 +403,11 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
             }));
         else if (bf16)
             RNNT_HIP(timed(KC_FWD_SCORES, stream, [&] {
-                // (the chunk buffers are free until the group's backward pass: scratch)
-                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, wv.dH, plan.chunk_bytes, stream);
+                // scratch: the slots of the dW GEMM until the first backward pass (they hold what any launch needs), then the chunk buffers, which are free
+                // until the group's backward pass
+                const bool slots = gi == 0 || !grads;
+                return launch_fwd_bf16(pr, wv.wpack, wv.st, ls, g.tile0, g.tile1, slots ? (void*)wv.dw_slots : wv.dH,
+                                       slots ? dw_slot_bytes(desc->H, desc->V) : plan.chunk_bytes, stream);
             }));
         else if (plan.f32_gemm) {
             for (const Chunk& c : plan.chunks)
