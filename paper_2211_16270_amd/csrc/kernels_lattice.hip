@@ -11,6 +11,7 @@
 // resolution for the posteriors of long utterances.  The fp32 path's long sweeps (k_lattice_f64)
 // accumulate in fp64 and take c = -ln P / (T+U) from a first sweep.
 #include "device_common.h"
+#include "scaled.h"
 
 namespace rnnt {
 
@@ -216,45 +217,10 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void k_lattice_wave(SampleTable st,
 // the posteriors of a 500 x 100 lattice).  The same wavefronts, blocks and loads as the fp32 sweep.  A value is m 2^k: a step multiplies the two ways
 // by their emissions, brings them to the larger k and adds, so the dependent chain holds no exponential and no logarithm; those of the emissions and of
 // what is stored stand beside it.  k is a whole number in fp64, so no emission is too small for it (EMISSION_FLOOR included).
-// What bounds it: issue, about 110 instructions a step.  One thread per label position, a barrier per step and the recursion in logarithms before: a call, two
-// samples of 120 x 24, H = V = 64, 220 -> 137 us; four of 500 x 100 1002 -> 714; 16 of up to 232 x 46 717 -> 573.  Errors against 64 bits as before (what is stored
-// differs by 1e-11 ahead of its rounding).
-struct Scaled {
-    double m, k;
-};
+// What bounds it: issue, about 115 instructions a step.  One thread per label position, a barrier per step and the recursion in logarithms before: 16 samples
+// of 120 x 24 135 -> 49 us, four of 500 x 100 503 -> 219, one of 300 x 600 977 -> 712.  A step's functions are good to the last places of fp64 (scaled.h);
+// with exponentials good to 1e-11 the same three took 47, 212 and 686.
 constexpr double LW_NONE_K = -1e280;      // 0 = 2^LW_NONE_K (absorbs whatever is added)
-constexpr double LOG2E_D = 1.4426950408889634074, LN2_D = 0.69314718055994530942;
-
-// 2^x, |x| <= 1/2: Taylor series, relative error below 1e-11
-__device__ __forceinline__ double exp2_half(double x) {
-    constexpr double c[10] = {1.0, 0.69314718055994530942, 0.24022650695910071233, 0.055504108664821579953, 0.0096181291076284771620,
-                              0.0013333558146428443423, 1.5403530393381609954e-4, 1.5252733804059840280e-5, 1.3215486790144309488e-6,
-                              1.0178086009239699728e-7};
-    double r = c[9];
-#pragma unroll
-    for (int i = 8; i >= 0; --i) r = fma(r, x, c[i]);
-    return r;
-}
-// e^x
-__device__ __forceinline__ Scaled scaled_exp(double x) {
-#pragma clang fp contract(off)      // (y - k is at most 1/2, and 0 for an emission of EMISSION_FLOOR, only with y rounded)
-    const double y = x * LOG2E_D, k = rint(y);
-    return {exp2_half(y - k), k};
-}
-__device__ __forceinline__ Scaled times(const Scaled& a, const Scaled& b) { return {a.m * b.m, a.k + b.k}; }
-// 2^d, d <= 0 a whole number (far below the exponents of fp64: 0)
-__device__ __forceinline__ double scale_down(double m, double d) { return ldexp(m, (int)fmax(d, -4000.0)); }
-__device__ __forceinline__ Scaled plus(const Scaled& a, const Scaled& b) {
-    const double k = fmax(a.k, b.k);
-    return {scale_down(a.m, a.k - k) + scale_down(b.m, b.k - k), k};
-}
-// ln(m 2^k), m > 0: an fp32 logarithm, and what it leaves over: the logarithm of a number within 1e-6 of 1
-__device__ __forceinline__ double scaled_log(const Scaled& a) {
-    const int e = __builtin_amdgcn_frexp_exp(a.m);
-    const double f = __builtin_amdgcn_frexp_mant(a.m) * 1.41421356237309504880;      // [0.71, 1.42)
-    const double l = (double)__builtin_amdgcn_logf((float)f);
-    return fma(l + (a.k + (e - 0.5)), LN2_D, fma(f, exp2_half(-l), -1.0));
-}
 
 __device__ __forceinline__ double from_words(int lo, int hi) { return __hiloint2double(hi, lo); }
 __device__ __forceinline__ double lane_from_below(double v, double first) {
@@ -329,8 +295,9 @@ __device__ __forceinline__ void lattice_sweep_f64(const SampleTable& st, const L
                 }
                 Scaled val = plus(x, y);
                 if constexpr (j == LW_B - 1) {                // (the mantissa of a value stays within 2^(2 LW_B) of 1)
-                    const int up = __builtin_amdgcn_frexp_exp(val.m);
-                    val = Scaled{__builtin_amdgcn_frexp_mant(val.m), val.k + up};
+                    int up;
+                    const double m = mantissa(val.m, up);
+                    val = Scaled{m, val.k + up};
                 }
                 to_own = BETA ? val : times(val, eb);
                 to_next = BETA ? val : times(val, ey);

@@ -520,3 +520,51 @@ int main() {
     subprocess.run([gxx, "-std=c++17", "-O1", "-o", str(exe), str(src)], check=True, capture_output=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
     assert out.split() == ["0", "8"]
+
+
+def test_numbers_of_the_fp64_sweep_keep_64_bits(tmp_path):
+    # the sweep's exponentials and logarithm against 80-bit arithmetic, with h = 2^-53 (a rounding).  An emission: log2 e and the product with it, h |x| each;
+    # the polynomial, 2.8 h and 1.5 h for its last steps: h (2 |x| + 4.5).  The logarithm: a sum, ln 2 and the last step, h |x| each; sqrt 2 twice, the
+    # polynomial and a step, 7.5 h.  1200 equal emissions, whose errors all have one sign: an emission and a product each.
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "scaled.cpp"
+    src.write_text('#include "%s"\n' % os.path.join(ROOT, "paper_2211_16270_amd", "csrc", "scaled.h") + """
+#include <cstdio>
+using namespace rnnt;
+int main() {
+    const double eps = 1.1102230246251565e-16;
+    double one = 0, log_ = 0, chain = 0, sum = 0;
+    for (int i = -40000; i <= 4000; ++i) {
+        const double x = i * 1.0009765625e-3;
+        const Scaled e = scaled_exp(x);
+        one = std::max(one, (double)(std::abs(logl((long double)e.m) + (long double)e.k * logl(2.0L) - x) / (eps * (4.5 + 2 * std::abs(x)))));
+        const double v = scaled_log(e);
+        log_ = std::max(log_, (double)(std::abs(logl((long double)e.m) + (long double)e.k * logl(2.0L) - v) / (eps * (7.5 + 3 * std::abs(x)))));
+    }
+    for (int i = 0; i < 400; ++i) {
+        const double x = -8 + 0.0203125 * i;
+        Scaled v{1.0, 0.0};
+        const Scaled e = scaled_exp(x);
+        for (int n = 1; n <= 1200; ++n) {
+            v = times(v, e);
+            if (n % 8 == 0) { int up; const double m = mantissa(v.m, up); v = Scaled{m, v.k + up}; }
+        }
+        chain = std::max(chain, (double)(std::abs((long double)scaled_log(v) - 1200.0L * x) / (eps * (1200 * (5.5 + 2 * std::abs(x)) + 7.5 + 3 * 1200 * std::abs(x)))));
+        const Scaled a = scaled_exp(x), b = scaled_exp(-3.0 - 0.31 * x);
+        const long double want = logl(expl((long double)x) + expl((long double)(-3.0 - 0.31 * x)));
+        sum = std::max(sum, (double)(std::abs((long double)scaled_log(plus(a, b)) - want) / (eps * (4.5 + 2 * std::abs(x) + 7.5 + 3 * std::abs(x) + 4.5 + 2 * std::abs(-3.0 - 0.31 * x)))));
+    }
+    const Scaled floor_ = scaled_exp(-1e30), none{1.0, -1e280};
+    const bool edge = floor_.m == 1.0 && scaled_log(plus(floor_, none)) == scaled_log(floor_) && scaled_log(plus(scaled_exp(-700.0), floor_)) + 700 < 1e-12;
+    std::printf("%d %d %d %d %d\\n", one <= 1, log_ <= 1, chain <= 1, sum <= 1, edge);
+    std::fprintf(stderr, "%g %g %g %g\\n", one, log_, chain, sum);
+}
+""".replace("\\\\n", "\\n"))
+    exe = tmp_path / "scaled"
+    subprocess.run([gxx, "-std=c++17", "-O1", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(exe), str(src)], check=True, capture_output=True)
+    run = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60)
+    assert run.stdout.split() == ["1"] * 5, run.stderr
