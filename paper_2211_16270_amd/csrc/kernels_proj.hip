@@ -22,6 +22,9 @@
 #include "device_common.h"
 #include "kernels.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace rnnt {
 
 namespace {
@@ -421,12 +424,17 @@ __global__ __launch_bounds__(256) void k_col_sum(const float* __restrict__ x, lo
     atomicAdd(&out[c], (s0 + s1) + (s2 + s3));
 }
 
-// Splits of a weight gradient's sum over the rows: about 256 workgroups, at least 256 rows each (every split adds its tile to dW with float atomics:
-// with about 512 the call above takes 1012 us, with 256 or 128 1000 to 1004).
-int proj_weight_splits(int tiles, long long rows) {
-    long long s = (256 + tiles - 1) / tiles;
-    const long long most = (rows + 255) / 256;
-    return (int)(s > most ? most : s);
+// Rows per split of a weight gradient's sum: a multiple of 128, at least 256, for about 256 workgroups where that costs no accuracy, else as many as keep
+// the sum's error down.  A split of n rows is n / 16 additions of the matrix instruction, S splits are as many atomics.  Rounded additions of terms of
+// random sign leave u sqrt(n / 32 + S / 2) of the result, least at n = 4 sqrt(rows); of terms of one sign u sqrt(n / (48 S) + S / 3), least at
+// n = 2 rows^(2/3).  Between the two one grows as the other falls; there the splits are those of 512 workgroups.  Relative error of dW, inputs of either
+// sign (of one sign), 320 k rows, with 256 workgroups, with 512 of them and with this rule: D = H = 512 6.7e-7, 4.8e-7, 4.6e-7 (1.8e-7, 1.2e-7, 1.2e-7);
+// D = H = 1024 1.5e-6, 1.0e-6, 5.0e-7 (7.6e-7, 3.6e-7, 1.2e-7).  Time of a call with 256 workgroups and with this rule: that one 9300 -> 8215 us, D = H = 512
+// 3300 -> 3370, 64 samples of 1000 x 3, D = 1024, H = 640 1162 -> 1198; 8000 rows, D = H = 512 as before.
+long long proj_split_rows(int tiles, long long rows) {
+    const double n = (double)rows, fill = n * tiles / 256, low = 4.0 * std::sqrt(n), high = 2.0 * std::cbrt(n * n);
+    const double best = fill * fill <= 2.0 * low * low ? fill : std::max(low, std::min(0.5 * fill, high));      // (as far from low as half of it)
+    return std::max(256LL, ((long long)best + 64) / 128 * 128);
 }
 
 }  // namespace
@@ -522,8 +530,8 @@ hipError_t launch_proj_backward(int bf16, const ProjSide (&s)[2], int H, hipStre
         a.weight[i] = TileJob{x.h, x.d_out, x.D, H, x.dW, H, nullptr, x.db, x.mask, x.D, H, x.rows};
         a.input[i] = TileJob{x.d_out, x.W, H, H, x.d_in, x.D, nullptr, nullptr, RowMask{nullptr, 1, 0}, x.rows, x.D, H};
         a.tiles[i] = x.D / PT * a.n_tiles;
-        a.splits[i] = proj_weight_splits(a.tiles[i], x.rows);
-        a.per_split[i] = ((x.rows + a.splits[i] - 1) / a.splits[i] + 2 * PK - 1) / (2 * PK) * (2 * PK);
+        a.per_split[i] = proj_split_rows(a.tiles[i], x.rows);
+        a.splits[i] = (int)((x.rows + a.per_split[i] - 1) / a.per_split[i]);
         a.t[i] = RowTiles{(int)((x.rows + PT - 1) / PT), x.D / PT};
         wgs += (long long)(a.splits[i] + 7) / 8 * 8 * a.tiles[i] + a.t[i].workgroups();
     }

@@ -143,3 +143,44 @@ def test_bf16_projections_at_the_edges_of_tiles_and_splits(B, T_max, U_max, H, H
     batch = synth.make_batch(wl)
     proj = synth.make_proj_inputs(batch, H_A=H_A, H_L=H_L)
     check(run_gpu_proj(batch, proj), run_oracle_proj(batch, proj), "bf16", batch, f"bf16 {B}x{T_max}x{U_max} {H},{H_A},{H_L}")
+
+
+@pytest.mark.parametrize("one_sign", [False, True])
+@pytest.mark.parametrize("B,D", [(64, 1024), (128, 512), (16, 128)])
+def test_bf16_weight_gradients_of_many_rows_keep_their_precision(B, D, one_sign):
+    # Identity maps: d_hA is d_enc as it goes into dW_A's product, and the entry point without projections gives d_enc itself for db_Z, so what is left is
+    # the error of the sums alone.  n rows a split (the kernels' rule), S splits; a rounded addition is off by at most u = 2^-24 / sqrt(3) of the
+    # sum so far (root mean square), which over terms of random sign leaves u sqrt(n / 32 + S / 2) of the result (16 rows an addition: the matrix
+    # instruction's k, and the threads of a column of db_Z), over terms of one sign u sqrt(n / (48 S) + S / 3).
+    import torch
+    T, U, V, rows = 1000, 1, 256, B * 1000
+    g = torch.Generator(device="cuda").manual_seed(3)
+    normal = lambda *s, to=torch.bfloat16: torch.empty(*s, dtype=to, device="cuda").normal_(generator=g)
+    out = lambda *s: torch.empty(*s, device="cuda")
+    T_len, U_len = np.full(B, T, np.int32), np.full(B, U, np.int32)
+    desc = Bd.make_desc(B, T, U, D, V, 0, Bd.RNNT_BF16)
+    hA, hL, eye = normal(B, T, D), normal(B, U + 1, D), torch.eye(D, dtype=torch.bfloat16, device="cuda")
+    if one_sign:
+        hA = hA.abs()
+    W, b = normal(D, V) * D ** -0.5, normal(V, to=torch.float32) * 0.1
+    labels = torch.randint(1, V, (B, U), device="cuda", dtype=torch.int32, generator=g)
+    loss, d_hA, d_hL, dW_A, db_Z, dW_L, dW, db = out(B), out(B, T, D), out(B, U + 1, D), out(D, D), out(D), out(D, D), out(D, V), out(V)
+    _say("many rows", B, D, one_sign)
+    ws = Bd.Workspace(Bd.rnnt_joint_proj_workspace_bytes(desc, D, D, T_len, U_len))
+    assert Bd.rnnt_joint_proj_loss_fwd_bwd(desc, D, D, hA, hL, eye, torch.zeros(D, device="cuda"), eye, W, b, labels, T_len, U_len, loss,
+                                           d_hA, d_hL, dW_A, db_Z, dW_L, dW, db, ws.buf) == 0
+    d_enc, d_pred = out(B, T, D), out(B, U + 1, D)
+    ws = Bd.Workspace(Bd.rnnt_joint_loss_workspace_bytes(desc, T_len, U_len))
+    assert Bd.rnnt_joint_loss_fwd_bwd(desc, hA, hL, W, b, labels, T_len, U_len, loss, d_enc, d_pred, dW, db, ws.buf) == 0
+    ref_W, ref_b = torch.zeros(D, D, dtype=torch.float64, device="cuda"), torch.zeros(D, dtype=torch.float64, device="cuda")
+    for x, y, z in zip(hA.view(-1, D).split(16000), d_hA.view(-1, D).split(16000), d_enc.view(-1, D).split(16000)):
+        ref_W += x.double().t().contiguous() @ y.double()
+        ref_b += z.double().sum(0)
+    fill, low, high = rows * (D // 128) ** 2 / 256, 4 * rows ** 0.5, 2 * rows ** (2 / 3)
+    n = max(256, fill if fill ** 2 <= 2 * low ** 2 else max(low, min(fill / 2, high)))
+    u, S = 2.0 ** -24 / 3 ** 0.5, -(-rows // n)
+    err = lambda a, r: float((a.double() - r).norm() / r.norm())
+    either, one = u * (n / 32 + S / 2) ** 0.5, u * (n / (48 * S) + S / 3) ** 0.5
+    e_W, e_b = err(dW_A, ref_W), err(db_Z, ref_b)
+    _say("many rows", D, rows, "dW_A", e_W, "db_Z", e_b, "bounds", either, one)
+    assert e_W <= (one if one_sign else either) and e_b <= either
