@@ -504,10 +504,8 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
         return RNNT_OK;
     };
     if (plan.f32_gemm && grads && !overlap) {
-        // The samples of a chunk go through forward pass, sweep and backward pass before the next chunk's: their scores are computed once.  A sample that
-        // takes several chunks finds those of its last one, which comes first in its backward pass.  Against sweeps over
-        // all samples of a group, with every chunk's scores but the last's computed twice: H = 1024, V = 4096, 16 samples of up to 232 x 46 23.5 -> 19.8 ms
-        // a call, 64 of 200 x 40 79.3 -> 65.6; H = 512, V = 1024, 64 of 200 x 40 13.1 -> 12.0.
+        // The samples that are swept together go through forward pass, sweep and backward pass before the next ones.  Their last chunk, which comes first in
+        // the backward pass, finds its scores in the chunk buffers: whole samples in one chunk are computed once.  (Which samples: F32Chunks.)
         for (size_t c0 = 0, c1; c0 < plan.chunks.size(); c0 = c1) {
             const Chunk& first = plan.chunks[c0];
             const size_t gi = (size_t)first.group;
@@ -564,7 +562,7 @@ rnnt_status run(const rnnt_desc* desc, const void* enc, const void* pred, const 
     if (stt != RNNT_OK) return stt;
     if (!workspace || ((uintptr_t)workspace % WS_ALIGN) != 0 || workspace_bytes == 0) return RNNT_ERR_WORKSPACE;
     Plan plan;
-    build_plan(*desc, T_len, U_len, workspace_bytes, plan);
+    build_plan(*desc, T_len, U_len, workspace_bytes, plan, false, grads);
     if (plan.total_bytes > workspace_bytes) return RNNT_ERR_WORKSPACE;
     TableSource ts;
     ts.no_copy_engine = no_copy_engine;

@@ -97,10 +97,87 @@ size_t lay_out(const rnnt_desc& d, Plan& p, long long lat_cap, long long chunk_r
     return o;
 }
 
+// fp32 GEMM form: the chunks of a group, ranges of lattice nodes that fit the chunk buffers, in one of two orders.  Chunks of whole samples are swept as they
+// come, and their scores computed once; but a sweep takes as long for a few samples as for all of them, and the chunks are more.  Full chunks need one
+// sweep a group, and all their scores but the last chunk's twice.  64 samples of 500 x 100, one order -> the other: H = V = 64 in the default workspace 7.3 ms
+// -> 9.1, in a sixteenth of it 24.6 -> 14.4; H = V = 256 18.1 -> 21.8, 55.8 -> 41.9; 16 of them, H = 1024, V = 4096, 99.6 -> 127.1, and in a quarter
+// 134.3 -> 133.4.
+struct F32Chunks {
+    const rnnt_desc& d;
+    const int32_t *T_len, *U_len;
+    const Plan& p;
+    int gi;
+    long long chunk_rows;
+
+    // nodes [row0, row0 + rows) of the group, out of samples [s0, s1): the blocks of frames they touch
+    Chunk range(int s0, int s1, long long row0, long long rows) const {
+        const long long base = p.row_off[p.groups[gi].s0];
+        auto block = [&](long long row, int after) {
+            const int s = (int)(std::upper_bound(p.row_off.begin(), p.row_off.end(), base + row) - p.row_off.begin()) - 1;
+            const int W = U_len[s] + 1, uw = tile_label_width(T_len[s], U_len[s]), th = TILE_ROWS / uw, across = (W + uw - 1) / uw;
+            return p.tile_off[s] + (int)((base + row - p.row_off[s]) / W / th + after) * across;
+        };
+        Chunk c{gi, block(row0, 0), block(row0 + rows - 1, 1)};
+        c.row0 = row0;
+        c.rows = rows;
+        c.s0 = s0;
+        c.s1 = s1;
+        return c;
+    }
+    // samples [s0, s1) in chunks of `per` nodes
+    void cut(int s0, int s1, long long per, std::vector<Chunk>& out) const {
+        const long long base = p.row_off[p.groups[gi].s0], end = p.row_off[s1] - base;
+        for (long long r0 = p.row_off[s0] - base; r0 < end; r0 += per) out.push_back(range(s0, s1, r0, std::min(per, end - r0)));
+    }
+    // As many whole samples as a chunk holds, or one that takes several chunks (of equal size).
+    std::vector<Chunk> of_samples() const {
+        const Group& g = p.groups[gi];
+        std::vector<Chunk> out;
+        for (int s0 = g.s0, s1; s0 < g.s1; s0 = s1) {
+            s1 = s0 + 1;
+            while (s1 < g.s1 && p.row_off[s1 + 1] - p.row_off[s0] <= chunk_rows) ++s1;
+            const long long rows = p.row_off[s1] - p.row_off[s0], n = (rows + chunk_rows - 1) / chunk_rows;
+            cut(s0, s1, (long long)align_up((size_t)((rows + n - 1) / n), GEMM_TILE), out);
+        }
+        return out;
+    }
+    // Full chunks, wherever samples end.
+    std::vector<Chunk> of_nodes() const {
+        std::vector<Chunk> out;
+        cut(p.groups[gi].s0, p.groups[gi].s1, chunk_rows, out);
+        return out;
+    }
+    // What an order costs beyond the other, in microseconds.  Fitted to both orders of 91 calls, 16 to 200 samples of 40 x 8 to 1000 x 200, H x V from 64 x 64
+    // to 1024 x 4096, default workspaces to 1/24 of them: the order that is then chosen was the slower one in six of them, by at most 2.3 %.
+    double cost(const std::vector<Chunk>& chunks) const {
+        const double H = d.H, V = d.V;
+        // a chunk: its launches, and its GEMMs' last, partly empty round
+        double us = (double)chunks.size() * (75.0 + 0.04 * (H + V));
+        // a node's scores, computed again: Z (a workgroup a node), the GEMM, and the bytes of both
+        const double again = 0.5e-3 + 2.0 * H * std::max(V, 128.0) / 250e6 + (8.0 * H + 4.0 * V) / 2.4e6;
+        for (size_t i = 0; i < chunks.size(); ++i) {
+            const Chunk& c = chunks[i];
+            if (i + 1 < chunks.size() && chunks[i + 1].s0 == c.s0) {
+                us += 25.0 + (double)c.rows * again;
+                continue;
+            }
+            // the sweep of the chunk's samples: a step of the longest one's; more wavefronts than SIMDs take turns
+            int steps = 0, waves = 0;
+            for (int s = c.s0; s < c.s1; ++s) {
+                steps = std::max(steps, T_len[s] + U_len[s]);
+                waves = std::max(waves, (U_len[s] + 64) / 64);
+            }
+            const double step = d.T_max + d.U_max >= 128 ? 0.28 + 0.045 * waves : 0.075;
+            us += 7.0 + steps * step * std::max(1.0, 2.0 * (c.s1 - c.s0) * waves / 1024.0);
+        }
+        return us;
+    }
+};
+
 }  // namespace
 
 void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
-                size_t workspace_bytes, Plan& p, bool two_lattice_buffers) {
+                size_t workspace_bytes, Plan& p, bool two_lattice_buffers, bool grads) {
     const int B = d.B;
     p.B = B;
     p.lat_buffers = two_lattice_buffers ? 2 : 1;
@@ -260,29 +337,15 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
             }
         }
     } else if (p.f32_gemm) {
-        // fp32 GEMM form: ranges of lattice nodes that fit the chunk buffers.  Whole samples where they fit: their sweep and backward pass then follow their
-        // forward pass, and find its scores in the buffers.
         for (int gi = 0; gi < (int)p.groups.size(); ++gi) {
-            const Group& g = p.groups[gi];
-            for (int s0 = g.s0, s1; s0 < g.s1; s0 = s1) {
-                s1 = s0 + 1;
-                while (s1 < g.s1 && p.row_off[s1 + 1] - p.row_off[s0] <= chunk_rows) ++s1;
-                const long long rows = p.row_off[s1] - p.row_off[s0], nch = (rows + chunk_rows - 1) / chunk_rows;
-                const long long per = (long long)align_up((size_t)((rows + nch - 1) / nch), GEMM_TILE);
-                for (long long r0 = 0; r0 < rows; r0 += per) {
-                    Chunk c{gi, p.tile_off[s0], p.tile_off[s1]};
-                    c.row0 = p.row_off[s0] - p.row_off[g.s0] + r0;
-                    c.rows = std::min(per, rows - r0);
-                    if (nch > 1) {                    // (one sample: the blocks of frames the range touches)
-                        const int W = U_len[s0] + 1, uw = tile_label_width(T_len[s0], U_len[s0]), th = TILE_ROWS / uw, across = (W + uw - 1) / uw;
-                        c.tile0 = p.tile_off[s0] + (int)(r0 / W / th) * across;
-                        c.tile1 = p.tile_off[s0] + (int)((r0 + c.rows - 1) / W / th + 1) * across;
-                    }
-                    c.s0 = s0;
-                    c.s1 = s1;
-                    p.chunks.push_back(c);
-                }
+            const F32Chunks c{d, T_len, U_len, p, gi, chunk_rows};
+            // (losses alone: no score is needed again; sweeps on a stream of their own: a group each)
+            std::vector<Chunk> chunks = c.of_nodes();
+            if (grads && !(p.lat_buffers == 2 && p.groups.size() > 1)) {
+                std::vector<Chunk> samples = c.of_samples();
+                if (c.cost(samples) <= c.cost(chunks)) chunks.swap(samples);
             }
+            p.chunks.insert(p.chunks.end(), chunks.begin(), chunks.end());
         }
     } else {
         for (int gi = 0; gi < (int)p.groups.size(); ++gi)

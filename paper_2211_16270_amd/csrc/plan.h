@@ -39,8 +39,8 @@ struct Group {
 struct Chunk {
     int group;
     int tile0, tile1;    // global tile range, inside the group's range
-    // fp32 GEMM form: lattice nodes [row0, row0 + rows) of the group instead, all of samples [s0, s1): as many whole samples as one chunk holds, or
-    // one that takes several chunks
+    // fp32 GEMM form: lattice nodes [row0, row0 + rows) of the group instead, in tiles [tile0, tile1).  [s0, s1): the samples that are swept together, when all
+    // chunks with this s0 have their scores: whole samples that one chunk holds, one that takes several, or all of the group (plan.cpp: F32Chunks)
     long long row0 = 0, rows = 0;
     int s0 = 0, s1 = 0;
 };
@@ -275,8 +275,9 @@ rnnt_status check_lengths(const rnnt_desc* d, const int32_t* T_len, const int32_
 // is below the smallest workable one, plan.total_bytes = plan.min_bytes > workspace_bytes and
 // the group/chunk lists are those of the smallest plan.
 // two_lattice_buffers: room for the lattice state of two groups at a time (for calls that run a group's lattice
-// sweep on a second stream while the previous group's backward pass is still reading its own state).
+// sweep on a second stream while the previous group's backward pass is still reading its own state).  grads: false for calls that form
+// losses alone (the workspace is the same).
 void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
-                size_t workspace_bytes, Plan& plan, bool two_lattice_buffers = false);
+                size_t workspace_bytes, Plan& plan, bool two_lattice_buffers = false, bool grads = true);
 
 }  // namespace rnnt

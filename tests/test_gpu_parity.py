@@ -1138,8 +1138,8 @@ def test_bf16_vocabulary_in_any_number_of_parts(H, V, T):
 
 @pytest.mark.parametrize("rows", [128, 256, 640, 1408])
 def test_f32_chunks_of_whole_samples_and_samples_of_several_chunks(rows):
-    # 276 to 451 nodes a sample: chunks of 128 and 256 nodes take one sample in several (of equal size, the last one a little shorter), of 640 one or two
-    # samples, of 1408 three to five
+    # 330 to 429 nodes a sample: chunks of 128 nodes in groups of one sample, which takes several; full chunks of 256, 640 and 1408 nodes of a group of all
+    # samples, wherever those end
     wl = synth.custom_workload("f32chunks", B=7, T_max=41, U_max=10, H=64, V=100, dtype="f32", index=161,
                                t_rule="uniform", t_lo=33, u_rule="uniform", u_lo=8)
     batch = synth.make_batch(wl)
@@ -1153,6 +1153,30 @@ def test_f32_chunks_of_whole_samples_and_samples_of_several_chunks(rows):
     _say("f32 chunks", rows, info, batch.T_len, batch.U_len)
     assert st == 0 and info["chunk_rows"] >= rows
     assert_parity(run_gpu(batch, budget_bytes=budget), ref, "f32", f"chunks of {rows}")
+
+
+@pytest.mark.parametrize("rows", [128, 384, 768, 896])
+def test_f32_chunks_swept_as_they_come(rows):
+    # 384 nodes a sample, few steps: chunks of whole samples, a sweep each (the rule: a sweep costs less here than scores computed again), that hold one
+    # sample, two samples or two and some room, and three chunks a sample; losses alone take full chunks and one sweep, with the same losses
+    import torch
+    wl = synth.custom_workload("f32swept", B=5, T_max=32, U_max=11, H=64, V=100, dtype="f32", index=164)
+    batch = synth.make_batch(wl)
+    desc = Bd.make_desc(batch.B, wl.T_max, wl.U_max, wl.H, wl.V, wl.blank, Bd.RNNT_F32)
+    budget = Bd.rnnt_joint_loss_workspace_bytes(desc, batch.T_len, batch.U_len, 1) + 4 * 384 * 20 + (rows - 128) * 4 * (wl.V + 2 * wl.H)
+    plan = lambda: Bd.rnnt_joint_loss_plan(desc, batch.T_len, batch.U_len, budget)[1]
+    while plan()["chunk_rows"] < rows or plan()["n_groups"] > 1:
+        budget += 1 << 12
+    info = plan()
+    _say("f32 swept", rows, info)
+    assert info["chunk_rows"] == rows
+    got = run_gpu(batch, budget_bytes=budget)
+    assert_parity(got, run_oracle(batch), "f32", f"chunks of {rows}")
+    loss, dev = torch.empty(batch.B, device="cuda"), got["dev"]
+    ws = Bd.Workspace(budget)
+    assert Bd.rnnt_joint_loss_fwd(desc, dev["enc"], dev["pred"], dev["W_out"], dev["b_out"], dev["labels"], batch.T_len, batch.U_len, loss,
+                                  ws.buf) == 0
+    np.testing.assert_array_equal(loss.cpu().numpy(), got["loss"])
 
 
 @pytest.mark.parametrize("H,V", [(64, 1024), (64, 1028), (260, 4096), (64, 4100), (516, 260)])

@@ -568,3 +568,133 @@ int main() {
     subprocess.run([gxx, "-std=c++17", "-O1", "-ffp-contract=off", "-Wno-unknown-pragmas", "-o", str(exe), str(src)], check=True, capture_output=True)
     run = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60)
     assert run.stdout.split() == ["1"] * 5, run.stderr
+
+
+def _f32_chunk_counts(T_len, U_len, groups, chunk_rows):
+    """chunks of whole samples (one that takes several: of equal size), full chunks wherever samples end"""
+    rows = T_len.astype(np.int64) * (U_len + 1)
+    up = lambda x, k: -(-int(x) // k)
+    samples = nodes = 0
+    for g in np.unique(groups):
+        r = rows[groups == g]
+        nodes += up(r.sum(), chunk_rows)
+        s = 0
+        while s < len(r):
+            e = s + 1
+            while e < len(r) and r[s:e + 1].sum() <= chunk_rows:
+                e += 1
+            n = r[s:e].sum()
+            samples += up(n, up(up(n, up(n, chunk_rows)), 128) * 128)
+            s = e
+    return samples, nodes
+
+
+@pytest.mark.parametrize("B,T,U,H,V,parts", [
+    # (part of the default workspace, whole samples) where both orders were timed, ms: (1, 7.3 : 9.1), (4, 11.0 : 10.7), (16, 24.6 : 14.4)
+    (64, 500, 100, 64, 64, ((1, True), (4, False), (16, False))),
+    # (1, 18.1 : 21.8), (4, 34.5 : 26.0), (16, 55.8 : 41.9)
+    (64, 500, 100, 256, 256, ((1, True), (4, False), (16, False))),
+    # (1, 33.3 : 37.9), (4, 55.7 : 46.6), (16, 88.9 : 82.3)
+    (64, 500, 100, 128, 1024, ((1, True), (4, False), (16, False))),
+    # (1, 100.0 : 119.6), (4, 175.9 : 117.2)
+    (200, 1000, 200, 64, 64, ((1, True), (4, False))),
+    # (4, 13.6 : 15.4), (16, 31.3 : 24.5)
+    (64, 200, 40, 512, 1024, ((4, True), (16, False))),
+    # (1, 99.6 : 127.1)
+    (16, 500, 100, 1024, 4096, ((1, True),)),
+])
+def test_f32_samples_are_swept_with_their_chunk_only_where_that_is_faster(B, T, U, H, V, parts):
+    g = np.random.default_rng([2211, B, T, U])
+    T_len, U_len = g.integers(int(.9 * T), T + 1, size=B).astype(np.int32), g.integers(int(.9 * U), U + 1, size=B).astype(np.int32)
+    desc = Bd.make_desc(B, T, U, H, V, 0, Bd.RNNT_F32)
+    full = Bd.rnnt_joint_loss_workspace_bytes(desc, T_len, U_len)
+    for part, whole in parts:
+        n = Bd.rnnt_joint_loss_workspace_bytes(desc, T_len, U_len, full // part)
+        st, info, groups = Bd.rnnt_joint_loss_plan(desc, T_len, U_len, n)
+        samples, nodes = _f32_chunk_counts(T_len, U_len, groups, info["chunk_rows"])
+        assert st == 0 and info["n_chunks"] == (samples if whole else nodes), (part, info, samples, nodes)
+    # sweeps on a stream of their own take a group each
+    two = Bd.PlanHandle(desc, T_len, U_len, full // 4, overlap_lattice=True)
+    info = two.describe()
+    if info["n_groups"] > 1:
+        groups = np.zeros(B, np.int32)
+        rows, first = T_len.astype(np.int64) * (U_len + 1), 0
+        for s in range(1, B):
+            full_up = rows[first:s + 1].sum() > info["group_rows_cap"]
+            first = s if full_up else first
+            groups[s] = groups[s - 1] + full_up
+        assert info["n_groups"] == groups[-1] + 1
+        assert info["n_chunks"] == _f32_chunk_counts(T_len, U_len, groups, info["chunk_rows"])[1]
+
+
+def test_f32_chunks_cover_their_group_in_either_order(tmp_path):
+    # random batches and chunk sizes: every node of a group in one chunk, in order; what is swept together covers the group, too; the tiles of a chunk hold
+    # all of its nodes, and the first and the last of them some
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "chunks.cpp"
+    src.write_text('#include "%s"\n' % os.path.join(ROOT, "paper_2211_16270_amd", "csrc", "plan.cpp") + """
+#include <cstdio>
+#include <random>
+using namespace rnnt;
+int main() {
+    std::mt19937 g(11);
+    int bad = 0, several = 0, whole = 0, losses = 0;
+    for (int i = 0; i < 3000; ++i) {
+        const int B = 1 + g() % 9, T = 1 + g() % 90, U = g() % 40, H = 64 << (g() % 5), V = 64 << (g() % 7);
+        std::vector<int32_t> Tl(B), Ul(B);
+        for (int b = 0; b < B; ++b) { Tl[b] = 1 + g() % T; Ul[b] = g() % (U + 1); }
+        rnnt_desc d{};
+        d.B = B; d.T_max = T; d.U_max = U; d.H = H; d.V = V; d.dtype = RNNT_F32;
+        Plan p;
+        build_plan(d, Tl.data(), Ul.data(), 1, p);
+        const size_t given = p.min_bytes + g() % (1 << (14 + g() % 12));
+        build_plan(d, Tl.data(), Ul.data(), given, p);
+        Plan l;
+        build_plan(d, Tl.data(), Ul.data(), given, l, false, false);
+        for (int gi = 0; gi < (int)p.groups.size(); ++gi) {
+            const Group& gr = p.groups[gi];
+            const F32Chunks f{d, Tl.data(), Ul.data(), p, gi, p.chunk_rows};
+            std::vector<Chunk> taken, taken_l;
+            for (const Chunk& c : p.chunks) if (c.group == gi) taken.push_back(c);
+            for (const Chunk& c : l.chunks) if (c.group == gi) taken_l.push_back(c);
+            const std::vector<Chunk> samples = f.of_samples(), nodes = f.of_nodes();
+            const bool s = f.cost(samples) <= f.cost(nodes);
+            const std::vector<Chunk>& want = s ? samples : nodes;
+            if (taken.size() != want.size() || taken[0].s1 != want[0].s1) ++bad;
+            if (taken_l.size() != nodes.size()) ++losses;
+            if (samples.size() > 1) ++(s ? whole : several);
+            for (const std::vector<Chunk>& cs : {samples, nodes}) {
+                long long at = 0;
+                int swept = gr.s0;
+                for (size_t k = 0; k < cs.size(); ++k) {
+                    const Chunk& c = cs[k];
+                    if (c.row0 != at || c.rows < 1 || c.rows > p.chunk_rows || c.s0 != swept) ++bad;
+                    if (k + 1 < cs.size() ? cs[k + 1].s0 != c.s0 : true) swept = c.s1;
+                    at += c.rows;
+                    int lo = 1 << 30, hi = -1;
+                    for (int s2 = c.s0; s2 < c.s1; ++s2) {
+                        const int W = Ul[s2] + 1, uw = tile_label_width(Tl[s2], Ul[s2]), th = 64 / uw, across = (W + uw - 1) / uw;
+                        for (long long r = 0; r < (long long)Tl[s2] * W; ++r) {
+                            const long long n = p.row_off[s2] - p.row_off[gr.s0] + r;
+                            if (n < c.row0 || n >= c.row0 + c.rows) continue;
+                            const int tile = p.tile_off[s2] + (int)(r / W) / th * across + (int)(r % W) / uw;
+                            lo = std::min(lo, tile); hi = std::max(hi, tile);
+                        }
+                    }
+                    if (lo < c.tile0 || hi >= c.tile1 || c.tile0 < gr.tile0 || c.tile1 > gr.tile1) ++bad;
+                }
+                if (at != gr.rows || swept != gr.s1) ++bad;
+            }
+        }
+    }
+    std::printf("%d %d %d %d\\n", bad, losses, several > 100, whole > 100);
+}
+""")
+    exe = tmp_path / "chunks"
+    subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w", "-o", str(exe), str(src)], check=True,
+                   capture_output=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=100).stdout.split() == ["0", "0", "1", "1"]
