@@ -1115,19 +1115,45 @@ def test_bf16_single_inputs_beyond_the_exponentials(H, T, U, t, u):
     assert_padding_zero(got, batch)
 
 
-@pytest.mark.parametrize("H,V,T", [
-    (1024, 2048, 576),      # 36 workgroups: seven parts, forward and backward
-    (1024, 2048, 800),      # 50: five
-    (1024, 4096, 1000),     # 63: four, and 1000 x 8 nodes in 16 x 4 or 8 x 8 tiles
-    (768, 2304, 1000),      # a vocabulary of four segments (V / 256 is odd), the backward pass in other parts than the forward pass
-    (640, 4096, 400),       # half a tile per wave, 25 workgroups
-    (512, 2048, 1000),      # two workgroups per compute unit, eight parts
-    (128, 8192, 90),
+def _vocabulary_parts(V, tiles, statistics, multiple=2, slots=256):
+    """In how many parts the score kernels share the vocabulary: workgroups of two lattice tiles, `slots` of them at a time on the chip, parts of whole
+    segments (statistics) or pairs of blocks of 32 entries."""
+    blocks, n = V // 32, (tiles + 1) // 2
+    units = (8 if V >= 2048 and V % 512 == 0 else 4) if statistics else blocks // 2
+    best = None
+    for parts in range(1, 9):
+        ends = [units * y // parts * (blocks // units) for y in range(parts + 1)]
+        size = [e - s for s, e in zip(ends, ends[1:])]
+        if all(x > 0 and x % multiple == 0 for x in size):
+            cost = -(-n * parts // slots) * (8 + max(size))
+            if best is None or cost * 10 < best[1] * 9:
+                best = parts, cost
+    return best[0]
+
+
+@pytest.mark.parametrize("H,V,T,parts", [                 # parts of the forward pass, of the backward pass, of the forward pass that keeps scores
+    (1024, 2048, 576, (4, 6, 4)),       # 36 workgroups
+    (1024, 2048, 800, (4, 4, 4)),       # 50
+    (1024, 2048, 1100, (3, 3, 3)),      # 69: eight segments as 2, 3 and 3
+    (1024, 4096, 1160, (3, 3, 3)),      # 73
+    (1024, 4096, 750, (4, 5, 4)),       # 47
+    (1024, 4096, 1000, (4, 4, 4)),      # 63
+    (768, 2304, 1000, (4, 4, 2)),       # a vocabulary of four segments (V / 256 is odd)
+    (640, 4096, 400, (8, 8, 8)),        # half a tile per wave, 25 workgroups
+    (512, 2048, 1000, (8, 8, 4)),       # two workgroups per compute unit where no scores are kept
+    (512, 2048, 2300, (3, 3, 3)),       # 144
+    (128, 8192, 90, (8, 8, 8)),
 ])
-def test_bf16_vocabulary_in_any_number_of_parts(H, V, T):
+def test_bf16_vocabulary_in_any_number_of_parts(H, V, T, parts):
     wl = synth.custom_workload("vparts", B=1, T_max=T, U_max=7, H=H, V=V, dtype="bf16", index=160)
     one = synth.make_batch(wl)
-    _say("vocabulary parts", H, V, T)
+    _say("vocabulary parts", H, V, T, parts)
+    desc = Bd.make_desc(1, T, 7, H, V, wl.blank, Bd.RNNT_BF16)
+    st, info, _ = Bd.rnnt_joint_loss_plan(desc, one.T_len, one.U_len)
+    tiles = info["tiles_total"]
+    assert st == 0 and info["n_chunks"] == 1
+    assert parts == (_vocabulary_parts(V, tiles, True, slots=512 if H <= 512 else 256), _vocabulary_parts(V, tiles, False, slots=512 if H <= 512 else 256),
+                     _vocabulary_parts(V, tiles, True, multiple=4, slots=512 if H <= 384 else 256))
     ref = run_oracle(one)
     got = run_gpu(one, skip_below_log2=-1)
     assert_parity(got, ref, "bf16", f"H={H} V={V} T={T}")
@@ -1203,3 +1229,24 @@ def test_bf16_dz_in_a_launch_of_its_own(H, V, T):
     assert st == 0 and info["n_chunks"] >= 2
     _say("dz alone", H, V, T, info["n_chunks"])
     assert_parity(run_gpu(batch, budget_bytes=nmin), run_oracle(batch), "bf16", f"H={H} V={V} T={T}")
+
+
+@pytest.mark.parametrize("H,V", [(256, 256), (384, 512), (512, 1024)])
+@pytest.mark.parametrize("T,U,t,u", [(31, 23, 3, 9), (31, 23, 30, 16), (47, 3, 2, 1), (47, 3, 44, 3)])
+def test_bf16_single_inputs_beyond_the_exponentials_in_dz_of_four_waves(H, V, T, U, t, u):
+    # inputs beyond +-40 as above, where dz is a launch of its own and its workgroups have four waves and two lattice tiles: the smallest workspace, and one with
+    # chunks of more than a workgroup
+    wl = synth.custom_workload("far4", B=2, T_max=T, U_max=U, H=H, V=V, dtype="bf16", index=165)
+    batch = synth.with_lengths(synth.make_batch(wl), [T, T - 1], [U, U])
+    batch.enc[0, t, :] = 64.0
+    batch.pred[0, u, :] = -64.0
+    ref = run_oracle(batch)
+    desc = Bd.make_desc(2, T, U, H, V, wl.blank, Bd.RNNT_BF16)
+    nmin = Bd.rnnt_joint_loss_workspace_bytes(desc, batch.T_len, batch.U_len, 1)
+    for extra in (0, 4 * 64 * 2 * (V + H + 128) + 4096):
+        st, info, _ = Bd.rnnt_joint_loss_plan(desc, batch.T_len, batch.U_len, nmin + extra)
+        assert st == 0 and info["n_chunks"] >= 2
+        _say("far, four waves", H, V, T, U, t, u, info["n_chunks"], info["chunk_rows"])
+        got = run_gpu(batch, budget_bytes=nmin + extra)
+        assert_parity(got, ref, "bf16", f"far {t} {u} {extra}")
+        assert_padding_zero(got, batch)

@@ -698,3 +698,30 @@ int main() {
     subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w", "-o", str(exe), str(src)], check=True,
                    capture_output=True)
     assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=100).stdout.split() == ["0", "0", "1", "1"]
+
+
+def test_vocabulary_parts_as_the_gpu_tests_expect_them(tmp_path):
+    # the rule as the tests of the score kernels repeat it, to name the parts they run
+    import shutil
+    import subprocess
+    from tests.test_gpu_parity import _vocabulary_parts
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "rule.cpp"
+    src.write_text('#include "%s"\n' % os.path.join(ROOT, "paper_2211_16270_amd", "csrc", "plan.h") + """
+#include <cstdio>
+int main() {
+    for (int V : {256, 768, 2048, 2304, 4096, 8192})
+        for (int n = 1; n <= 300; ++n)
+            for (int slots : {256, 512})
+                std::printf("%d %d %d\\n", rnnt::score_split(n, slots, V, true).parts, rnnt::score_split(n, slots, V, false).parts,
+                            rnnt::score_split(n, slots, V, true, 4).parts);
+}
+""")
+    exe = tmp_path / "rule"
+    subprocess.run([gxx, "-std=c++17", "-O1", "-o", str(exe), str(src)], check=True, capture_output=True)
+    out = [tuple(map(int, l.split())) for l in subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout.splitlines()]
+    assert out == [(_vocabulary_parts(V, 2 * n, True, slots=slots), _vocabulary_parts(V, 2 * n, False, slots=slots),
+                    _vocabulary_parts(V, 2 * n, True, 4, slots)) for V in (256, 768, 2048, 2304, 4096, 8192) for n in range(1, 301)
+                   for slots in (256, 512)]
