@@ -843,69 +843,88 @@ __global__ __launch_bounds__(256) void k_rows_dh_f32(Problem pr, SampleTable st,
     atomicAdd(db + vt, t);
 }
 
-// d_enc[s, t, :] += dZ (1 - Z^2), d_pred[s, u, :] += the same: a lattice tile and 256 columns per workgroup (a wavefront takes every fourth frame, a lane
+// d_enc[s, t, :] += dZ (1 - Z^2), d_pred[s, u, :] += the same: a lattice tile and 256 columns per workgroup (a wavefront takes every eighth frame, a lane
 // four columns), summed over the tile's labels resp. frames before it leaves: 16 to 20 atomics a column and tile, where a node by itself takes 128
-// (31 k nodes, H = 1024: 240 -> 72 us).  Nodes [r0, r0 + n) of the group have a row in Z and dZ; a tile may have others besides.
-__global__ __launch_bounds__(256) void k_rows_dz_f32(Problem pr, SampleTable st, LatticeState ls, int tile0,
-                                                     long long r0, long long n, const float* __restrict__ Z,
-                                                     const float* __restrict__ dZ, float* __restrict__ d_enc,
-                                                     float* __restrict__ d_pred) {
-    __shared__ __align__(16) float part[4][8][256], frame[4][256];
+// (31 k nodes, H = 1024: 240 -> 60 us).  Nodes [r0, r0 + n) of the group have a row in Z and dZ; a tile may have others besides.  A wavefront's 8 nodes are
+// loaded ahead of the first sum, so that a small call waits for memory once: with four wavefronts that took a frame at a time four samples of 30 x 8,
+// H = 64, took 6.9 us, now 4.2, eight of 100 x 20, H = 512, 19.8, now 16.5.
+// UW: the tile's label positions.
+template <int UW>
+__device__ __forceinline__ void rows_dz_tile(const Problem& pr, const TilePos& p, long long first, long long n, const float* __restrict__ Z,
+                                             const float* __restrict__ dZ, float* __restrict__ d_enc, float* __restrict__ d_pred,
+                                             float (&part)[8][8][256]) {
+    constexpr int FRAMES = 8 / UW;                    // of a wavefront
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, H = pr.H;
-    const TilePos p = locate_tile(st, tile0 + (int)blockIdx.x);
-    const int h = (int)blockIdx.y * 256 + lane * 4;
+    const int h0 = (int)blockIdx.y * 256, h = h0 + lane * 4;
     const bool col = h < H;
-    const long long first = st.row_off[p.s] - ls.row_base - r0;        // row of the sample's first node
-    f32x4 pu[8];
+    f32x4 z[FRAMES][UW], g[FRAMES][UW];
+    auto row = [&](int f) { return first + (long long)(p.t0 + wave + 8 * f) * (p.U + 1) + p.u0; };
 #pragma unroll
-    for (int u = 0; u < 8; ++u) pu[u] = f32x4{0};
-    const int frames = 64 >> p.us;
-    for (int tl = wave; tl < frames; tl += 4) {
-        const int t = p.t0 + tl;
-        if (t >= p.T) break;
-        const long long row = first + (long long)t * (p.U + 1) + p.u0;
-        f32x4 de = f32x4{0}, z[8], g[8];
+    for (int f = 0; f < FRAMES; ++f)
+#pragma unroll
+        for (int u = 0; u < UW; ++u) {                // (loads without branches between them: what is not a row of the chunk reads another one)
+            long long i = row(f) + u;
+            i = i < 0 ? 0 : i < n ? i : n - 1;
+            z[f][u] = *reinterpret_cast<const f32x4*>(Z + i * H + (col ? h : 0));
+            g[f][u] = *reinterpret_cast<const f32x4*>(dZ + i * H + (col ? h : 0));
+        }
+    f32x4 pu[UW];
+#pragma unroll
+    for (int u = 0; u < UW; ++u) pu[u] = f32x4{0};
+#pragma unroll
+    for (int f = 0; f < FRAMES; ++f) {
+        const int t = p.t0 + wave + 8 * f;
+        f32x4 de = f32x4{0};
         bool any = false;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {                 // (loads without branches between them: what is not a row of the chunk reads another one)
-            long long i = row + u;
-            i = i < 0 ? 0 : i < n ? i : n - 1;
-            z[u] = *reinterpret_cast<const f32x4*>(Z + i * H + (col ? h : 0));
-            g[u] = *reinterpret_cast<const f32x4*>(dZ + i * H + (col ? h : 0));
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const long long i = row + u;
-            const bool ok = u < p.uw && p.u0 + u <= p.U && i >= 0 && i < n && col;
+        for (int u = 0; u < UW; ++u) {
+            const long long i = row(f) + u;
+            const bool ok = t < p.T && p.u0 + u <= p.U && i >= 0 && i < n && col;
             any = any || ok;
-            f32x4 dx = g[u] * (1.0f - z[u] * z[u]);
+            f32x4 dx = g[f][u] * (1.0f - z[f][u] * z[f][u]);
 #pragma unroll
             for (int j = 0; j < 4; ++j) dx[j] = ok ? dx[j] : 0.0f;
             de += dx;
             pu[u] += dx;
         }
         // (through LDS, so that the lanes of an atomic lie side by side)
-        *reinterpret_cast<f32x4*>(&frame[wave][lane * 4]) = de;
+        *reinterpret_cast<f32x4*>(&part[wave][0][lane * 4]) = de;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (__any(any)) {
-            float* out = d_enc + ((size_t)p.s * pr.T_max + t) * H + (int)blockIdx.y * 256;
+            float* out = d_enc + ((size_t)p.s * pr.T_max + t) * H + h0;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if ((int)blockIdx.y * 256 + j * 64 + lane < H) atomicAdd(out + j * 64 + lane, frame[wave][j * 64 + lane]);
+                if (h0 + j * 64 + lane < H) atomicAdd(out + j * 64 + lane, part[wave][0][j * 64 + lane]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) *reinterpret_cast<f32x4*>(&part[wave][u][lane * 4]) = pu[u];
+    for (int u = 0; u < UW; ++u) *reinterpret_cast<f32x4*>(&part[wave][u][lane * 4]) = pu[u];
     __syncthreads();
-    const int c = threadIdx.x, hc = (int)blockIdx.y * 256 + c;
+    const int c = threadIdx.x & 255, hc = h0 + c;
     if (hc >= H) return;
-    for (int u = 0; u < p.uw && p.u0 + u <= p.U; ++u)
-        atomicAdd(d_pred + ((size_t)p.s * (pr.U_max + 1) + p.u0 + u) * H + hc, (part[0][u][c] + part[1][u][c]) + (part[2][u][c] + part[3][u][c]));
+#pragma unroll
+    for (int i = 0; i < UW / 2; ++i) {
+        const int u = 2 * i + (int)(threadIdx.x >> 8);
+        if (p.u0 + u <= p.U)
+            atomicAdd(d_pred + ((size_t)p.s * (pr.U_max + 1) + p.u0 + u) * H + hc,
+                      ((part[0][u][c] + part[1][u][c]) + (part[2][u][c] + part[3][u][c])) +
+                          ((part[4][u][c] + part[5][u][c]) + (part[6][u][c] + part[7][u][c])));
+    }
+}
+__global__ __launch_bounds__(512, 4) void k_rows_dz_f32(Problem pr, SampleTable st, LatticeState ls, int tile0,
+                                                        long long r0, long long n, const float* __restrict__ Z,
+                                                        const float* __restrict__ dZ, float* __restrict__ d_enc,
+                                                        float* __restrict__ d_pred) {
+    __shared__ __align__(16) float part[8][8][256];
+    const TilePos p = locate_tile(st, tile0 + (int)blockIdx.x);
+    const long long first = st.row_off[p.s] - ls.row_base - r0;        // row of the sample's first node
+    if (p.uw == 8) rows_dz_tile<8>(pr, p, first, n, Z, dZ, d_enc, d_pred, part);
+    else rows_dz_tile<4>(pr, p, first, n, Z, dZ, d_enc, d_pred, part);
 }
 
 }  // namespace
@@ -980,7 +999,7 @@ hipError_t launch_bwd_f32_gemm(const Problem& pr, const SampleTable& st, const L
     // dZ = dh W^T   (B(k = v, n = h) = W[h, v]: k-contiguous)
     e = joint_gemm_f32<false, false>(S, V, W, V, dZ, H, nullptr, 0, np, H, V, 1, stream);
     if (e != hipSuccess) return e;
-    k_rows_dz_f32<<<dim3((unsigned)(tile1 - tile0), (unsigned)((H + 255) / 256)), dim3(256), 0, stream>>>(pr, st, ls, tile0, r0, n, Z, dZ,
+    k_rows_dz_f32<<<dim3((unsigned)(tile1 - tile0), (unsigned)((H + 255) / 256)), dim3(512), 0, stream>>>(pr, st, ls, tile0, r0, n, Z, dZ,
                                                                                                       go.d_enc, go.d_pred);
     return hipGetLastError();
 }
