@@ -65,9 +65,9 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)dz_smem;
 
     // global -> LDS: a stage is, per operand, blocks of 32 rows (lattice rows / hidden columns) x 2 fragments of 16 entries.
-    // LDS order: A [8 row blocks][entry half], B [entry half][8 hidden blocks].  Wave w moves row block w (lattice tile w / 2) and, of entry half w / 4,
-    // hidden blocks 2 (w % 4) and the next (HALF: w % 4).  Everything but the lane's 16 bytes is wave-uniform.  Slots past the list's end read the last
-    // listed tile again; their products are never stored.
+    // LDS order: A [WAVES row blocks][entry half], B [entry half][8 hidden blocks].  Wave w moves row block w (lattice tile w / 2) and, of entry half
+    // w / TILES, NB hidden blocks from NB (w % TILES) on: 2 with eight waves, 4 with four (HALF: 1 and 2).  Everything but the lane's 16 bytes is
+    // wave-uniform.  Slots past the list's end read the last listed tile again; their products are never stored.
     const size_t DB = chunk_block_bytes(V);   // bytes of a block of 32 rows of dH
     const unsigned lane_b = (unsigned)lane * 16u;
     const int wt = wv >> 1;                           // lattice tile whose copies and input rows are this wave's
@@ -80,7 +80,7 @@ __device__ __forceinline__ void dz_tile(const DzArgs& g, unsigned char* dz_smem,
     const unsigned char* As = g.dH + (size_t)(2 * slot + (wv & 1)) * DB + (size_t)step0 * 2048;
     const size_t WB = (size_t)(H / 32) * 1024;        // bytes of 16 entries of Wq
     const unsigned char* Bs = g.Wq + (size_t)step0 * 2 * WB + (size_t)(wv / TILES) * WB + (size_t)(n0 / 32 + NB * (wv % TILES)) * 1024;
-    // The copies of stage gstep into LDS buffer buf: both entry halves of the row block (j = 0), the hidden blocks (1).
+    // The copies of stage gstep into LDS buffer buf, NI issues: both entry halves of the row block (j = 0), the hidden blocks (1; four of them: 1 and 2).
     // (In pairs: M0 and its wait state once.)
     auto issue = [&](int gstep, unsigned buf, auto j_tag) {
         constexpr int j = decltype(j_tag)::value;

@@ -329,7 +329,9 @@ __device__ __forceinline__ void lattice_sweep_f64(const SampleTable& st, const L
 template <int MAX_WAVES>
 __global__ __launch_bounds__(64 * MAX_WAVES) void k_lattice_f64(SampleTable st, LatticeState ls, int s0, float* __restrict__ loss) {
     constexpr bool MANY = MAX_WAVES > 1;
-    constexpr int BLOCKS = 2;                         // (registers; a step takes long enough that eight ahead suffice)
+    // A step takes long enough that loads eight steps ahead suffice, in the first sweep, too (four blocks there: four samples of 500 x 100 606 -> 610 us a
+    // call).  Sixteen wavefronts leave 128 registers each; 25 of them are spilled, and the sweep still takes less time than the one it replaces.
+    constexpr int BLOCKS = 2;
     __shared__ float red[MAX_WAVES];
     __shared__ __align__(16) float edge32[MAX_WAVES][2][LW_B];
     __shared__ __align__(16) Scaled edge[MAX_WAVES][2][LW_B];

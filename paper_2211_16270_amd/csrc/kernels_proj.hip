@@ -387,20 +387,18 @@ hipError_t launch_proj(void (*kernel)(ARGS), const ARGS& a, long long workgroups
 }
 
 // ---- fp32: one thread per output element ---------------------------------------------------
-// A(m,k) at a[m*sam + k*sak], B(k,n) at b[k*sbk + n*sbn]; mask_on: 0 none, 1 rows m of A, 2 rows k (both operands)
+// A(m,k) at a[m*sam + k*sak], B(k,n) at b[k*sbk + n*sbn]; masked: rows k of both operands
 __global__ void k_proj_gemm_f32(const float* __restrict__ a, long long sam, long long sak, const float* __restrict__ b,
                                 long long sbk, long long sbn, float* __restrict__ c, long long ldc,
                                 const float* __restrict__ bias, long long M, long long N, long long K, RowMask mask,
-                                int mask_on, int accumulate) {
+                                int accumulate) {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= M * N) return;
     const long long m = idx / N, n = idx - m * N;
     float s = bias ? bias[n] : 0.0f;
-    if (mask_on != 1 || row_is_data(mask, m)) {
-        for (long long k = 0; k < K; ++k) {
-            if (mask_on == 2 && !row_is_data(mask, k)) continue;
-            s = fmaf(a[m * sam + k * sak], b[k * sbk + n * sbn], s);
-        }
+    for (long long k = 0; k < K; ++k) {
+        if (!row_is_data(mask, k)) continue;
+        s = fmaf(a[m * sam + k * sak], b[k * sbk + n * sbn], s);
     }
     c[m * ldc + n] = accumulate ? c[m * ldc + n] + s : s;
 }
@@ -446,7 +444,7 @@ static hipError_t proj_forward_f32(const ProjSide& s, int H, hipStream_t stream)
                                       stream);
     const long long total = s.rows * H;
     k_proj_gemm_f32<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(
-        (const float*)s.h, s.D, 1, (const float*)s.W, H, 1, (float*)s.out, H, s.bias, s.rows, H, s.D, none, 1, 0);
+        (const float*)s.h, s.D, 1, (const float*)s.W, H, 1, (float*)s.out, H, s.bias, s.rows, H, s.D, none, 0);
     return hipGetLastError();
 }
 
@@ -460,7 +458,7 @@ static hipError_t proj_backward_f32(const ProjSide& s, int H, hipStream_t stream
     } else {
         const long long total = s.rows * s.D;
         k_proj_gemm_f32<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(
-            s.d_out, H, 1, W, 1, H, s.d_in, s.D, nullptr, s.rows, s.D, H, none, 0, 0);
+            s.d_out, H, 1, W, 1, H, s.d_in, s.D, nullptr, s.rows, s.D, H, none, 0);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
@@ -470,7 +468,7 @@ static hipError_t proj_backward_f32(const ProjSide& s, int H, hipStream_t stream
     } else {
         const long long total = (long long)s.D * H;
         k_proj_gemm_f32<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(
-            h, 1, s.D, s.d_out, H, 1, s.dW, H, nullptr, s.D, H, s.rows, s.mask, 2, 1);
+            h, 1, s.D, s.d_out, H, 1, s.dW, H, nullptr, s.D, H, s.rows, s.mask, 1);
         e = hipGetLastError();
     }
     if (e != hipSuccess || s.db == nullptr) return e;

@@ -256,8 +256,9 @@ def test_lattice_sweeps_on_a_second_stream_against_the_checker(name, n, frac):
 
 @pytest.mark.parametrize("extra", [0, 1 << 20, 64 << 20])
 def test_f32_scores_left_by_the_forward_pass_on_one_and_two_streams(extra):
-    # fp32 GEMM form: the first backward chunk of a group takes the scores of the last forward chunk out of the chunk buffers.  Groups of
-    # several chunks, of one, and a second stream, where the next group's forward pass overwrites them first
+    # fp32 GEMM form: the first backward chunk of the samples that are swept together (all of a group, or those of a chunk) takes the scores of their last
+    # forward chunk out of the chunk buffers.  Groups of several chunks, of one, and a second stream, where the next group's forward pass overwrites
+    # them first
     import torch
     wl = synth.custom_workload("left32", B=6, T_max=45, U_max=12, H=128, V=260, dtype="f32", index=143,
                                t_rule="uniform", t_lo=20, u_rule="uniform", u_lo=3)
