@@ -347,11 +347,18 @@ def main():
                           "joint_scores_fwd_keep": 2.0 * R * HV,
                           "gemm_dz": 2.0 * R * HV, "gemm_dw_db": 2.0 * R * HV, "gemm_dz_dw_db": 4.0 * R * HV,
                           "fwd_f32": 2.0 * R * HV, "bwd_f32": 4.0 * R * HV}
-    # fp32: the plain kernels compute every score twice, the GEMM form those of a sample that takes several chunks, but for its last one
+    # fp32: the plain kernels compute every score twice.  The GEMM form: chunks of whole samples, and the scores of one that takes several chunks twice, but for
+    # its last one; or, recognised by being fewer, full chunks, and all scores of a group twice but the last chunk's (an average one).
     again = R
     if wl.dtype == "f32" and info["chunk_rows"] > 0:
-        again = sum(rows - -(-rows // -(-rows // info["chunk_rows"])) for rows in (batch.T_len.astype(int) * (batch.U_len.astype(int) + 1)).tolist()
-                    if rows > info["chunk_rows"])
+        rows, cap = (batch.T_len.astype(int) * (batch.U_len.astype(int) + 1)).tolist(), info["chunk_rows"]
+        whole = filled = 0
+        for n in rows:
+            filled = filled + n if filled + n <= cap and filled else n
+            whole += 0 if filled > n else -(-n // cap)
+        again = sum(n - -(-n // -(-n // cap)) for n in rows if n > cap)
+        if info["n_chunks"] < whole:
+            again = R * (1.0 - info["n_groups"] / info["n_chunks"])
     exec_flops_per_step = dict(alg_flops_per_step, joint_scores_bwd=2.0 * R * HV, bwd_f32=(4.0 * R + 2.0 * again) * HV)
     if bwd_share < 1.0:
         # tiles of negligible posterior are left out: both counts cover only the rows the kernels worked on
