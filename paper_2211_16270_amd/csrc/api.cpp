@@ -361,6 +361,7 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
     // the backward pass of group g, whose lattice state lies in the other half of the lattice arrays.  Kept scores
     // occupy the chunk buffers from a group's forward to its backward pass, so that mode stays on one stream.
     const bool overlap = ov.lattice_stream && plan.lat_buffers == 2 && !keep && ng > 1;
+    const std::vector<Chunk>& chunks = overlap && plan.f32_gemm ? plan.group_chunks : plan.chunks;
     // lattice state of group gi: with two buffers consecutive groups alternate between the halves of each array
     auto group_state = [&](size_t gi) {
         const Group& g = plan.groups[gi];
@@ -410,7 +411,7 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
                                        slots ? dw_slot_bytes(desc->H, desc->V) : plan.chunk_bytes, stream);
             }));
         else if (plan.f32_gemm) {
-            for (const Chunk& c : plan.chunks)
+            for (const Chunk& c : chunks)
                 if (c.group == (int)gi && (stt = forward_chunk(gi, c)) != RNNT_OK) return stt;
         } else
             RNNT_HIP(timed(KC_FWD_F32, stream,
@@ -448,10 +449,10 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
             d_pred = (float*)((uintptr_t)wv.stage_pred - (uintptr_t)g.s0 * pred_per_sample * 4);
         }
         const size_t c0 = ci;
-        while (ci < plan.chunks.size() && plan.chunks[ci].group == (int)gi) ++ci;
+        while (ci < chunks.size() && chunks[ci].group == (int)gi) ++ci;
         for (size_t cj = c0; cj < ci; ++cj) {
             if (!grads) break;
-            const Chunk& c = plan.chunks[cj];
+            const Chunk& c = chunks[cj];
             if (bf16) {
                 const long long rows = (long long)(c.tile1 - c.tile0) * TILE_ROWS;
                 // with a tile list the chunk takes entries [c.tile0 - g.tile0, c.tile1 - g.tile0) of the group's list
@@ -506,14 +507,14 @@ rnnt_status execute(const rnnt_desc* desc, const Plan& plan, const int32_t* T_le
     if (plan.f32_gemm && grads && !overlap) {
         // The samples that are swept together go through forward pass, sweep and backward pass before the next ones.  Their last chunk, which comes first in
         // the backward pass, finds its scores in the chunk buffers: whole samples in one chunk are computed once.  (Which samples: F32Chunks.)
-        for (size_t c0 = 0, c1; c0 < plan.chunks.size(); c0 = c1) {
-            const Chunk& first = plan.chunks[c0];
+        for (size_t c0 = 0, c1; c0 < chunks.size(); c0 = c1) {
+            const Chunk& first = chunks[c0];
             const size_t gi = (size_t)first.group;
-            for (c1 = c0; c1 < plan.chunks.size() && plan.chunks[c1].s0 == first.s0; ++c1)
-                if ((stt = forward_chunk(gi, plan.chunks[c1])) != RNNT_OK) return stt;
+            for (c1 = c0; c1 < chunks.size() && chunks[c1].s0 == first.s0; ++c1)
+                if ((stt = forward_chunk(gi, chunks[c1])) != RNNT_OK) return stt;
             if ((stt = lattice(gi, first.s0, first.s1, stream)) != RNNT_OK) return stt;
             for (size_t cj = c1; cj-- > c0;)
-                if ((stt = backward_chunk(gi, plan.chunks[cj], cj == c1 - 1)) != RNNT_OK) return stt;
+                if ((stt = backward_chunk(gi, chunks[cj], cj == c1 - 1)) != RNNT_OK) return stt;
         }
     } else if (!overlap) {
         for (size_t gi = 0; gi < ng; ++gi) {

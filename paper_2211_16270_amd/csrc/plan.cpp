@@ -293,6 +293,7 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
     // groups: consecutive samples while the lattice state fits
     p.groups.clear();
     p.chunks.clear();
+    p.group_chunks.clear();
     int s = 0;
     while (s < B) {
         Group g{};
@@ -339,9 +340,9 @@ void build_plan(const rnnt_desc& d, const int32_t* T_len, const int32_t* U_len,
     } else if (p.f32_gemm) {
         for (int gi = 0; gi < (int)p.groups.size(); ++gi) {
             const F32Chunks c{d, T_len, U_len, p, gi, chunk_rows};
-            // (losses alone: no score is needed again; sweeps on a stream of their own: a group each)
             std::vector<Chunk> chunks = c.of_nodes();
-            if (grads && !(p.lat_buffers == 2 && p.groups.size() > 1)) {
+            if (p.lat_buffers == 2) p.group_chunks.insert(p.group_chunks.end(), chunks.begin(), chunks.end());
+            if (grads) {                              // (losses alone: no score is needed again)
                 std::vector<Chunk> samples = c.of_samples();
                 if (c.cost(samples) <= c.cost(chunks)) chunks.swap(samples);
             }

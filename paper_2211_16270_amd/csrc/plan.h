@@ -56,6 +56,7 @@ struct Plan {
     std::vector<long long> row_off;     // [B+1] cumulative lattice nodes
     std::vector<Group> groups;
     std::vector<Chunk> chunks;
+    std::vector<Chunk> group_chunks;    // fp32 GEMM form, lat_buffers = 2: full chunks, for calls whose sweeps run on a stream of their own
     long long rows_total = 0, tiles_total = 0;
     long long group_rows_cap = 0;       // lattice nodes a group may hold
     int lat_buffers = 1;                // 2: the lattice arrays hold two groups (group g uses half g % 2)

@@ -613,18 +613,6 @@ def test_f32_samples_are_swept_with_their_chunk_only_where_that_is_faster(B, T, 
         st, info, groups = Bd.rnnt_joint_loss_plan(desc, T_len, U_len, n)
         samples, nodes = _f32_chunk_counts(T_len, U_len, groups, info["chunk_rows"])
         assert st == 0 and info["n_chunks"] == (samples if whole else nodes), (part, info, samples, nodes)
-    # sweeps on a stream of their own take a group each
-    two = Bd.PlanHandle(desc, T_len, U_len, full // 4, overlap_lattice=True)
-    info = two.describe()
-    if info["n_groups"] > 1:
-        groups = np.zeros(B, np.int32)
-        rows, first = T_len.astype(np.int64) * (U_len + 1), 0
-        for s in range(1, B):
-            full_up = rows[first:s + 1].sum() > info["group_rows_cap"]
-            first = s if full_up else first
-            groups[s] = groups[s - 1] + full_up
-        assert info["n_groups"] == groups[-1] + 1
-        assert info["n_chunks"] == _f32_chunk_counts(T_len, U_len, groups, info["chunk_rows"])[1]
 
 
 def test_f32_chunks_cover_their_group_in_either_order(tmp_path):
@@ -655,6 +643,15 @@ int main() {
         build_plan(d, Tl.data(), Ul.data(), given, p);
         Plan l;
         build_plan(d, Tl.data(), Ul.data(), given, l, false, false);
+        Plan two;                                     // sweeps on a stream of their own: full chunks
+        build_plan(d, Tl.data(), Ul.data(), given + (1 << 20), two, true);
+        size_t full = 0;
+        for (int gi = 0; gi < (int)two.groups.size(); ++gi) {
+            const std::vector<Chunk> nodes = F32Chunks{d, Tl.data(), Ul.data(), two, gi, two.chunk_rows}.of_nodes();
+            for (size_t k = 0; k < nodes.size(); ++k, ++full)
+                if (full >= two.group_chunks.size() || two.group_chunks[full].row0 != nodes[k].row0 || two.group_chunks[full].group != gi) ++bad;
+        }
+        if (full != two.group_chunks.size() || !p.group_chunks.empty()) ++bad;
         for (int gi = 0; gi < (int)p.groups.size(); ++gi) {
             const Group& gr = p.groups[gi];
             const F32Chunks f{d, Tl.data(), Ul.data(), p, gi, p.chunk_rows};
